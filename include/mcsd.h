@@ -118,7 +118,8 @@ int32_t mcsd_tree_validate(const int32_t *parent_host, int32_t n_nodes);
  *   out[b][i][h][:] = softmax_over_keys(scale * <q[b][i][h], K>) . V
  * Inputs are expected to be position-encoded already (each candidate keeps the
  * position it has in its own sequence, i.e. prefix_len + depth - 1).
- * fp32 accumulation; bf16 inputs use the matrix cores when d == 128.
+ * fp32 accumulation on the matrix cores.  The softmax weights enter PV as bf16 for bf16 storage
+ * with d == 128 and at fp32 accuracy otherwise.
  */
 typedef struct {
     uint32_t struct_size;
@@ -147,7 +148,9 @@ typedef struct {
     size_t workspace_bytes;
 } mcsd_attn_bufs;
 
-/* Bytes of scratch mcsd_tree_attn needs for this descriptor (0 on a bad descriptor). */
+/* Bytes of scratch mcsd_tree_attn needs for this descriptor (0 on a bad descriptor).  For bf16 with
+ * d != 128 a workspace of this size is only used to split long prefixes over more workgroups: the
+ * call also runs with less, or with none. */
 size_t mcsd_attn_workspace_bytes(const mcsd_attn_desc *desc);
 int32_t mcsd_tree_attn(const mcsd_attn_desc *desc, const mcsd_attn_bufs *bufs, void *stream);
 
@@ -181,8 +184,8 @@ int32_t mcsd_attn_plan_override(int32_t variant, int32_t chunk_tiles, int32_t ta
  * sequence b is row r % page_size of page block_table[b][r / page_size].  page_size is a
  * multiple of 32; desc->L_stride is the logical capacity, <= max_pages_per_seq * page_size;
  * only the pages that hold rows below prefix_len[b] are read.  A table entry outside
- * [0, n_pages) is a data error: its keys read as zeros (bf16 matrix-core path) or as page 0 /
- * n_pages-1 (other paths); memory outside the pool is never touched.  Everything else (tree
+ * [0, n_pages) is a data error: its keys read as zeros (bf16, d == 128) or as page 0 /
+ * n_pages-1 (fp32 storage, d != 128); memory outside the pool is never touched.  Everything else (tree
  * block, outputs, workspace) is as for mcsd_tree_attn.
  */
 typedef struct {

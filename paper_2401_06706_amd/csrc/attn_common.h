@@ -1,0 +1,141 @@
+// Shared by the tree-attention kernels: parameters, buffer resources, small arithmetic helpers,
+// the split of a sequence's key tiles into segments and the ancestor masks.
+#pragma once
+
+#include <math.h>
+
+#include "mcsd_internal.h"
+
+namespace mcsd {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr float LOG2E_F = 1.44269504088896340736f;
+constexpr float M_INIT = -1.0e30f;     // "no key seen yet" running max (finite so that differences stay finite)
+constexpr float RESCALE_GAP = 8.0f;    // running max is only raised when a score exceeds it by 2^8
+constexpr int KT = 32;                 // keys per tile
+
+struct AttnParams {
+    const void *q, *k_prefix, *v_prefix, *k_tree, *v_tree;
+    const int32_t *prefix_len, *parent;
+    void *out;
+    float *part_m, *part_l, *part_o;
+    int B, N, H_q, H_kv, G, d, L_stride, M;
+    int n_row_tiles, chunk_tiles, n_chunks_max, tiles_tree, parent_per_seq, dtype;
+    int root_row;         // 1: row 0 of the tree block is the root, N counts it
+    int R;                // rows per (b, g) in the partial buffers
+    int split_bias;       // see split_tiles
+    float scale_log2;     // scale * log2(e)
+    // paged prefix cache (block_table != nullptr): k_prefix / v_prefix are pools
+    // [n_pages][H_kv][page_size][d]; logical row r of sequence b lives in page
+    // block_table[b][r / page_size], slot r % page_size
+    const int32_t *block_table;
+    int page_size, n_pages, max_pages;
+};
+
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    bf16x2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// Raw buffer resource over [ptr, ptr + bytes): reads past the end return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(ptr), 0, bytes, 0x00020000);
+}
+
+// max(a, b, c) as the one hardware instruction: fmaxf() on values the compiler knows nothing
+// about (matrix-instruction results) costs an extra NaN-quieting v_max_f32 x, x per operand.
+__device__ __forceinline__ float max3_raw(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// A vector instruction that reads the result of a matrix instruction has to keep a distance
+// from it (seven wait states for v_mfma_f32_16x16x32_bf16) which the hardware does not enforce.
+// The compiler keeps it for the instructions it selects itself, but not for the text of an asm
+// statement: the four score accumulators pass through this statement before max3_raw reads
+// them, so every matrix instruction that writes them has been issued before its wait states
+// and every reader stands behind them.
+__device__ __forceinline__ void settle_scores(f32x4 &a, f32x4 &b, f32x4 &c, f32x4 &d)
+{
+    asm volatile("s_nop 7\n\ts_nop 1" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+
+__device__ __forceinline__ void settle_scores(f32x4 &a, f32x4 &b)
+{
+    asm volatile("s_nop 7\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
+// the largest of the eight scores a lane holds for one row (two accumulators of four)
+__device__ __forceinline__ float max_of_scores(const f32x4 &s0, const f32x4 &s1)
+{
+    const float m0 = max3_raw(s0[0], s0[1], s0[2]);
+    const float m1 = max3_raw(s0[3], s1[0], s1[1]);
+    return max3_raw(max3_raw(m0, m1, s1[2]), s1[3], s1[3]);
+}
+
+__device__ __forceinline__ float fast_exp2(float x)
+{
+    return __builtin_amdgcn_exp2f(x);      // v_exp_f32; results below the normal range flush to 0
+}
+
+__device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16)
+{
+    return __uint_as_float(bits16 << 16);
+}
+
+// The T key tiles of a sequence are cut into n segments of seg tiles (the last one possibly
+// shorter): n = (T + bias) / chunk_tiles, at least 1.  With bias = chunk_tiles / 2 that is
+// T / chunk_tiles rounded to nearest, so a sequence a little longer than a multiple of
+// chunk_tiles does not pay a partial for a sliver; seg < 1.5 chunk_tiles.
+__device__ __forceinline__ void split_tiles(int T, int chunk_tiles, int bias, int *n, int *seg)
+{
+    const int nn = max(1, (T + bias) / chunk_tiles);
+    *n = nn;
+    *seg = (T + nn - 1) / nn;
+}
+
+// anc[i] = {i} U anc[parent[i]]: one 128-bit mask per node, built by walking up.  The parent
+// array is copied to LDS with one coalesced load first, so that the walk (one dependent read
+// per level) does not pay a global-memory latency per step.  With a root row the tree block has
+// N rows of which row 0 is the root and row 1 + i candidate i: the root is every candidate's
+// ancestor, and the caller's array (N - 1 entries, -1 = child of the root) is shifted by one.
+// Contains a workgroup barrier; the caller adds the one that publishes the masks.
+__device__ __forceinline__ void build_ancestor_masks(const int32_t *parent, int N, int root_row, uint32_t (*s_anc)[4], int *s_parent)
+{
+    for (int i = threadIdx.x; i < MCSD_MAX_NODES; i += blockDim.x) {
+        int pa = -1;
+        if (i < N) {
+            if (!root_row) pa = parent[i];
+            else if (i > 0) pa = max(parent[i - 1], -1) + 1;
+        }
+        s_parent[i] = pa;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < MCSD_MAX_NODES; i += blockDim.x) {
+        uint32_t m[4] = {0u, 0u, 0u, 0u};
+        if (i < N) {
+            int a = i;
+            for (int step = 0; step < MCSD_MAX_NODES && a >= 0; ++step) {
+                m[a >> 5] |= 1u << (a & 31);
+                const int pa = s_parent[a];
+                a = (pa < a) ? pa : -1;      // a malformed array can not loop or index out of range
+            }
+        }
+        s_anc[i][0] = m[0]; s_anc[i][1] = m[1]; s_anc[i][2] = m[2]; s_anc[i][3] = m[3];
+    }
+}
+
+// fp32 storage and head dimensions other than 128 (tree_attn_any.hip): the attention, and the merge if it is split
+int32_t launch_attn_any(const AttnParams &p, const AttnPlan &plan, hipStream_t stream);
+
+}  // namespace mcsd

@@ -23,139 +23,16 @@
 //   The prefix cache is either one contiguous slab per (sequence, KV head) or a pool of
 //   pages addressed through a block table (PAGED instantiation); the tiles are the same.
 //
-// Everything else (fp32 storage, other head dims) runs tree_attn_generic_kernel on
-// the vector ALUs.
+// Everything else (fp32 storage, other head dims) runs the kernels of tree_attn_any.hip.
 #include <math.h>
 
 #include <atomic>
 #include <type_traits>
 
-#include "mcsd_internal.h"
+#include "attn_common.h"
 
 namespace mcsd {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr float LOG2E_F = 1.44269504088896340736f;
-constexpr float M_INIT = -1.0e30f;     // "no key seen yet" running max (finite so that differences stay finite)
-constexpr float RESCALE_GAP = 8.0f;    // running max is only raised when a score exceeds it by 2^8
-constexpr int KT = 32;                 // keys per tile
-
-struct AttnParams {
-    const void *q, *k_prefix, *v_prefix, *k_tree, *v_tree;
-    const int32_t *prefix_len, *parent;
-    void *out;
-    float *part_m, *part_l, *part_o;
-    int B, N, H_q, H_kv, G, d, L_stride, M;
-    int n_row_tiles, chunk_tiles, n_chunks_max, tiles_tree, parent_per_seq, dtype;
-    int root_row;         // 1: row 0 of the tree block is the root, N counts it
-    int R;                // rows per (b, g) in the partial buffers
-    int split_bias;       // see split_tiles
-    float scale_log2;     // scale * log2(e)
-    // paged prefix cache (block_table != nullptr): k_prefix / v_prefix are pools
-    // [n_pages][H_kv][page_size][d]; logical row r of sequence b lives in page
-    // block_table[b][r / page_size], slot r % page_size
-    const int32_t *block_table;
-    int page_size, n_pages, max_pages;
-};
-
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    bf16x2 v = {(__bf16)lo, (__bf16)hi};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// Raw buffer resource over [ptr, ptr + bytes): reads past the end return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(ptr), 0, bytes, 0x00020000);
-}
-
-// max(a, b, c) as the one hardware instruction: fmaxf() on values the compiler knows nothing
-// about (matrix-instruction results) costs an extra NaN-quieting v_max_f32 x, x per operand.
-__device__ __forceinline__ float max3_raw(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// A vector instruction that reads the result of a matrix instruction has to keep a distance
-// from it (seven wait states for v_mfma_f32_16x16x32_bf16) which the hardware does not enforce.
-// The compiler keeps it for the instructions it selects itself, but not for the text of an asm
-// statement: the four score accumulators pass through this statement before max3_raw reads
-// them, so every matrix instruction that writes them has been issued before its wait states
-// and every reader stands behind them.
-__device__ __forceinline__ void settle_scores(f32x4 &a, f32x4 &b, f32x4 &c, f32x4 &d)
-{
-    asm volatile("s_nop 7\n\ts_nop 1" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-}
-
-// the largest of the eight scores a lane holds for one row (two accumulators of four)
-__device__ __forceinline__ float max_of_scores(const f32x4 &s0, const f32x4 &s1)
-{
-    const float m0 = max3_raw(s0[0], s0[1], s0[2]);
-    const float m1 = max3_raw(s0[3], s1[0], s1[1]);
-    return max3_raw(max3_raw(m0, m1, s1[2]), s1[3], s1[3]);
-}
-
-__device__ __forceinline__ float fast_exp2(float x)
-{
-    return __builtin_amdgcn_exp2f(x);      // v_exp_f32; results below the normal range flush to 0
-}
-
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16)
-{
-    return __uint_as_float(bits16 << 16);
-}
-
-// The T key tiles of a sequence are cut into n segments of seg tiles (the last one possibly
-// shorter): n = (T + bias) / chunk_tiles, at least 1.  With bias = chunk_tiles / 2 that is
-// T / chunk_tiles rounded to nearest, so a sequence a little longer than a multiple of
-// chunk_tiles does not pay a partial for a sliver; seg < 1.5 chunk_tiles.
-__device__ __forceinline__ void split_tiles(int T, int chunk_tiles, int bias, int *n, int *seg)
-{
-    const int nn = max(1, (T + bias) / chunk_tiles);
-    *n = nn;
-    *seg = (T + nn - 1) / nn;
-}
-
-// anc[i] = {i} U anc[parent[i]]: one 128-bit mask per node, built by walking up.  The parent
-// array is copied to LDS with one coalesced load first, so that the walk (one dependent read
-// per level) does not pay a global-memory latency per step.  With a root row the tree block has
-// N rows of which row 0 is the root and row 1 + i candidate i: the root is every candidate's
-// ancestor, and the caller's array (N - 1 entries, -1 = child of the root) is shifted by one.
-// Contains a workgroup barrier; the caller adds the one that publishes the masks.
-__device__ __forceinline__ void build_ancestor_masks(const int32_t *parent, int N, int root_row, uint32_t (*s_anc)[4], int *s_parent)
-{
-    for (int i = threadIdx.x; i < MCSD_MAX_NODES; i += blockDim.x) {
-        int pa = -1;
-        if (i < N) {
-            if (!root_row) pa = parent[i];
-            else if (i > 0) pa = max(parent[i - 1], -1) + 1;
-        }
-        s_parent[i] = pa;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < MCSD_MAX_NODES; i += blockDim.x) {
-        uint32_t m[4] = {0u, 0u, 0u, 0u};
-        if (i < N) {
-            int a = i;
-            for (int step = 0; step < MCSD_MAX_NODES && a >= 0; ++step) {
-                m[a >> 5] |= 1u << (a & 31);
-                const int pa = s_parent[a];
-                a = (pa < a) ? pa : -1;      // a malformed array can not loop or index out of range
-            }
-        }
-        s_anc[i][0] = m[0]; s_anc[i][1] = m[1]; s_anc[i][2] = m[2]; s_anc[i][3] = m[3];
-    }
-}
 
 // --------------------------------------------------------------------- MFMA path
 // RH = row groups per workgroup, KS = key streams per workgroup.  Wave (rh, ks) owns query rows
@@ -926,118 +803,52 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnParams p, in
     __builtin_nontemporal_store((u32x2){pk.x, pk.y}, reinterpret_cast<u32x2 *>(ob + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * D + 4 * d4));
 }
 
-// ------------------------------------------------------------------ generic path
-// One 256-thread workgroup per (sequence, node, query head).  Keys are taken 256 at
-// a time: thread t scores key t (dot product over d on the vector ALU), the running
-// max is a wavefront-shuffle + LDS reduction, the weights go to LDS, and thread t
-// (t < d) accumulates output column t over the 256 keys.
-template <typename T>
-__device__ __forceinline__ float load_as_float(const T *p, size_t i);
-template <>
-__device__ __forceinline__ float load_as_float<float>(const float *p, size_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t *p, size_t i) { return bf16_bits_to_float(p[i]); }
-
-template <typename T>
-__device__ __forceinline__ void store_from_float(T *p, size_t i, float v);
-template <>
-__device__ __forceinline__ void store_from_float<float>(float *p, size_t i, float v) { p[i] = v; }
-template <>
-__device__ __forceinline__ void store_from_float<uint16_t>(uint16_t *p, size_t i, float v)
-{
-    p[i] = (uint16_t)(pack_bf16(v, 0.f) & 0xffffu);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void tree_attn_generic_kernel(AttnParams p)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = blockIdx.x, node = blockIdx.y, b = blockIdx.z;
-    const int g = h / p.G, d = p.d;
-    __shared__ float s_q[MCSD_MAX_HEAD_DIM];
-    __shared__ float s_p[256];
-    __shared__ float s_red[4];
-    __shared__ uint32_t s_anc[MCSD_MAX_NODES][4];
-    __shared__ int s_parent[MCSD_MAX_NODES];
-
-    build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
-    const T *qp = static_cast<const T *>(p.q) + (((size_t)b * p.N + node) * p.H_q + h) * (size_t)d;
-    for (int c = tid; c < d; c += 256) s_q[c] = load_as_float<T>(qp, c);
-    __syncthreads();
-
-    int L = p.prefix_len[b];
-    L = max(0, min(L, p.L_stride));
-    const size_t kv_head = (size_t)b * p.H_kv + g;
-    const bool paged = p.block_table != nullptr;
-    const T *kpre = static_cast<const T *>(p.k_prefix) + (paged ? 0 : kv_head * (size_t)p.L_stride * d);
-    const T *vpre = static_cast<const T *>(p.v_prefix) + (paged ? 0 : kv_head * (size_t)p.L_stride * d);
-    // row index (in units of d elements) of logical prefix row r inside kpre / vpre
-    auto prefix_row = [&](int r) -> size_t {
-        if (!paged) return (size_t)r;
-        int blk = p.block_table[(size_t)b * p.max_pages + r / p.page_size];
-        blk = min(max(blk, 0), p.n_pages - 1);      // an entry outside the pool never leaves it
-        return ((size_t)blk * p.H_kv + g) * (size_t)p.page_size + (size_t)(r % p.page_size);
-    };
-    const T *ktre = static_cast<const T *>(p.k_tree) + kv_head * (size_t)p.N * d;
-    const T *vtre = static_cast<const T *>(p.v_tree) + kv_head * (size_t)p.N * d;
-    const int n_keys = L + p.N;
-
-    float m_run = M_INIT, l_run = 0.f, o_acc = 0.f;      // o_acc: output column tid (tid < d)
-    for (int k0 = 0; k0 < n_keys; k0 += 256) {
-        const int key = k0 + tid;
-        float s = -INFINITY;
-        if (key < n_keys) {
-            bool on = true;
-            const T *kr;
-            if (key < L) kr = kpre + prefix_row(key) * d;
-            else {
-                const int a = key - L;
-                on = (s_anc[node][a >> 5] >> (a & 31)) & 1u;
-                kr = ktre + (size_t)a * d;
-            }
-            if (on) {
-                float acc = 0.f;
-                for (int c = 0; c < d; ++c) acc += s_q[c] * load_as_float<T>(kr, c);
-                s = acc * p.scale_log2;
-            }
-        }
-        float cm = s;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cm = fmaxf(cm, __shfl_xor(cm, o));
-        if (lane == 0) s_red[wave] = cm;
-        __syncthreads();
-        cm = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
-        const float m_new = fmaxf(m_run, cm);
-        const float alpha = exp2f(m_run - m_new);
-        const float pw = exp2f(s - m_new);          // 0 for masked / out-of-range keys
-        s_p[tid] = pw;
-        __syncthreads();
-        float ps = 0.f;
-        const int cnt = min(256, n_keys - k0);
-        if (tid < d) {
-            float acc = 0.f;
-            for (int j = 0; j < cnt; ++j) {
-                const int kj = k0 + j;
-                const T *vr = (kj < L) ? vpre + prefix_row(kj) * d : vtre + (size_t)(kj - L) * d;
-                acc += s_p[j] * load_as_float<T>(vr, tid);
-            }
-            o_acc = o_acc * alpha + acc;
-        }
-        for (int j = 0; j < cnt; ++j) ps += s_p[j];
-        l_run = l_run * alpha + ps;
-        m_run = m_new;
-        __syncthreads();
-    }
-    if (tid < d) {
-        T *op = static_cast<T *>(p.out) + (((size_t)b * p.N + node) * p.H_q + h) * (size_t)d;
-        store_from_float<T>(op, tid, o_acc / l_run);
-    }
-}
-
 // Launch-plan overrides of mcsd_attn_plan_override (0 = automatic), process-wide.
 std::atomic<int> g_force_variant{0}, g_force_chunk_tiles{0}, g_force_target_wgs{0};
 
 }  // namespace
+
+// bf16 with d != 128: rows per workgroup by the rows that share a KV head, segments as for d = 128.
+// 512 workgroups aimed at (two per CU) and at least 8 tiles (two steps) per segment: at d 64, GQA
+// 32/8, 8 sequences of 200..2000 tokens, targets of 256 / 512 / 1024 / 2048 with segments down to 2
+// tiles took 25.1 / 22.0 / 22.0 / 28.9 us with the merge; one sequence of 2000 tokens 16.7 us with 8
+// tiles per segment and 17.9 us with 2, where the merge costs as much as the attention.
+// The partials are kept within MCSD_STATIC_SCRATCH_BYTES, so that every shape also goes through the
+// entry point that brings no workspace.
+static void plan_bf16_any(const mcsd_attn_desc &d, AttnPlan *pl)
+{
+    const int n_rows_tree = d.N + (d.root_row ? 1 : 0);
+    const bool wide = d.d > 128;
+    pl->variant = pl->rows_per_kv <= 32 ? (wide ? 1 : 0) : (pl->rows_per_kv <= 64 && !wide ? 1 : 2);
+    pl->row_tile = (wide ? 16 : 32) << pl->variant;
+    const int key_streams = 4 >> pl->variant;
+    pl->n_row_tiles = (pl->rows_per_kv + pl->row_tile - 1) / pl->row_tile;
+    pl->tiles_prefix_max = (d.L_stride + KT - 1) / KT;
+    pl->tiles_tree = (n_rows_tree + KT - 1) / KT;
+    pl->partial_stride_rows = (size_t)pl->n_row_tiles * pl->row_tile;
+    const long total_max = pl->tiles_prefix_max + pl->tiles_tree;
+    const long units = (long)d.B * d.H_kv * pl->n_row_tiles;
+    const int forced_target = g_force_target_wgs.load(), forced_chunk = g_force_chunk_tiles.load();
+    const long target_wgs = forced_target > 0 ? forced_target : 512;
+    long chunk = (total_max * units + target_wgs - 1) / target_wgs;
+    chunk = (chunk + key_streams - 1) / key_streams * key_streams;
+    if (chunk < 8) chunk = 8;
+    if (forced_chunk > 0) chunk = forced_chunk;
+    const size_t bytes_per_chunk = (size_t)d.B * d.H_kv * pl->partial_stride_rows * (size_t)(d.d + 2) * sizeof(float);
+    const long n_fit = (long)((MCSD_STATIC_SCRATCH_BYTES - 255) / bytes_per_chunk);
+    if (chunk > total_max || n_fit < 2) chunk = total_max;
+    else if ((total_max + chunk - 1) / chunk > n_fit) chunk = (total_max + n_fit - 1) / n_fit;
+    pl->chunk_tiles = (int)chunk;
+    pl->n_chunks_max = (int)((total_max + chunk - 1) / chunk);
+    pl->ws_bytes = pl->n_chunks_max > 1 ? (bytes_per_chunk * pl->n_chunks_max + 255) & ~(size_t)255 : 0;
+}
+
+void unsplit_attn_plan(AttnPlan *pl)
+{
+    pl->chunk_tiles = pl->tiles_prefix_max + pl->tiles_tree;
+    pl->n_chunks_max = 1;
+    pl->ws_bytes = 0;
+}
 
 bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
 {
@@ -1048,7 +859,7 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     pl.use_mfma = (d.dtype == MCSD_DTYPE_BF16 && d.d == 128);
     if (!pl.use_mfma) {
         if (d.d > MCSD_MAX_HEAD_DIM) return false;
-        pl.ws_bytes = 0;
+        if (d.dtype == MCSD_DTYPE_BF16) plan_bf16_any(d, &pl);
         *plan = pl;
         return true;
     }
@@ -1124,18 +935,6 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
     p.B = d.B; p.N = d.N + p.root_row; p.H_q = d.H_q; p.H_kv = d.H_kv; p.G = d.H_q / d.H_kv; p.d = d.d;
     p.L_stride = d.L_stride; p.M = plan.rows_per_kv; p.parent_per_seq = d.parent_per_seq; p.dtype = d.dtype;
     p.scale_log2 = d.scale * LOG2E_F;
-    hipError_t e;
-    if (!plan.use_mfma) {
-        if (d.H_q > 2147483647 || d.B > 65535) { set_error("attn: grid too large"); return MCSD_E_UNSUPPORTED; }
-        dim3 grid(d.H_q, p.N, d.B), block(256);
-        if (d.dtype == MCSD_DTYPE_FP32)
-            launch_kernel(K_ATTN_GENERIC, tree_attn_generic_kernel<float>, grid, block, stream, p);
-        else
-            launch_kernel(K_ATTN_GENERIC, tree_attn_generic_kernel<uint16_t>, grid, block, stream, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) { set_error("tree_attn_generic launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
-        return MCSD_OK;
-    }
     p.n_row_tiles = plan.n_row_tiles; p.chunk_tiles = plan.chunk_tiles; p.n_chunks_max = plan.n_chunks_max;
     p.tiles_tree = plan.tiles_tree; p.R = (int)plan.partial_stride_rows;
     p.split_bias = plan.chunk_tiles / 2;
@@ -1146,6 +945,8 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         p.part_m = ws + rows * d.d;
         p.part_l = p.part_m + rows;
     }
+    if (!plan.use_mfma) return launch_attn_any(p, plan, stream);
+    hipError_t e;
     if (phases & ATTN_PHASE_MAIN) {
         // an unsplit attention has no merge launch to carry the walk: it rides on this one
         WalkParams mw = {};

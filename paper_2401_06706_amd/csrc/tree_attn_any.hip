@@ -1,0 +1,641 @@
+// Tree attention (Sec. 3.3 of the paper) for the storage types and head dimensions that the
+// d = 128 bf16 kernel does not take, on the matrix cores of gfx950.
+//
+//   tree_attn_bf16_kernel  bf16 storage, d a multiple of 8 up to 256 (padded to 64, 128 or 256)
+//   tree_attn_f32_kernel   fp32 storage, d a multiple of 4 up to 256 (same paddings)
+//
+// In both, a lane of S^T = K Q^T holds scores of one query row, which is the B operand layout of
+// O^T += V^T P^T: the weights never leave their lane.  Both keep the weights at fp32 accuracy:
+// the fp32 kernel multiplies in fp32 (v_mfma_f32_16x16x4_f32), the bf16 kernel feeds PV with two
+// bf16 terms per weight (see split_weight).
+#include <type_traits>
+
+#include "attn_common.h"
+
+namespace mcsd {
+namespace {
+
+// Where a tile of keys lies: K and V rows back to back from kb / vb, `bytes` of them valid (rows
+// past the end read as zero through the buffer resource, 0 = nothing is read).
+struct TileSrc {
+    const char *kb, *vb;
+    uint32_t bytes;
+};
+
+// The keys of a sequence: ceil(L / KW) prefix tiles, then ceil(N / KW) tree tiles.  All arguments
+// are wave-uniform.  Tiles at or past t_end are empty, which keeps every request unconditional.
+template <int KW>
+__device__ __forceinline__ TileSrc tile_source(const AttnParams &p, int b, int g, int L, int tiles_prefix, int t, int t_end, uint32_t row_bytes)
+{
+    TileSrc s;
+    const size_t kv_head = (size_t)b * p.H_kv + g;
+    s.kb = static_cast<const char *>(p.k_tree);
+    s.vb = static_cast<const char *>(p.v_tree);
+    s.bytes = 0u;
+    if (t >= t_end) return s;
+    size_t row;
+    if (t < tiles_prefix) {
+        const int key = t * KW;
+        if (p.block_table) {
+            // an entry outside the pool never leaves it
+            int blk = p.block_table[(size_t)b * p.max_pages + key / p.page_size];
+            blk = __builtin_amdgcn_readfirstlane(min(max(blk, 0), p.n_pages - 1));
+            row = ((size_t)blk * p.H_kv + g) * (size_t)p.page_size + (size_t)(key % p.page_size);
+        } else {
+            row = kv_head * (size_t)p.L_stride + (size_t)key;
+        }
+        s.kb = static_cast<const char *>(p.k_prefix);
+        s.vb = static_cast<const char *>(p.v_prefix);
+        s.bytes = (uint32_t)min(KW, L - key) * row_bytes;
+    } else {
+        const int node = (t - tiles_prefix) * KW;
+        row = kv_head * (size_t)p.N + (size_t)node;
+        s.bytes = (uint32_t)min(KW, p.N - node) * row_bytes;
+    }
+    s.kb += row * row_bytes;
+    s.vb += row * row_bytes;
+    return s;
+}
+
+constexpr uint32_t OFF_NOWHERE = 0x7fffffffu;       // beyond every tile's extent: reads as zero
+
+// ------------------------------------------------------------------------------ bf16
+// A weight p >= 0 as hi + lo, both bf16: hi is p cut to bf16, taken one step lower where that cut
+// would be exact, lo the rest rounded to bf16.  |hi + lo - p| <= 2^-17 p (hi alone: 2^-8), so
+// that PV rounds far below the bf16 output; and lo > 0 whenever p > 0, so that a weight times an
+// infinite value stays infinite instead of meeting 0 x inf in the second term.
+__device__ __forceinline__ uint32_t weight_hi_bits(float p)
+{
+    return __builtin_elementwise_sub_sat(__float_as_uint(p), 1u) & 0xffff0000u;
+}
+
+// Workgroup of 4 waves, one unit (sequence, KV head, row tile) and one segment of its key tiles.
+// Wave (rh, ks) owns 16 MT query rows and every KS-th tile; the TS tiles of a step are loaded by
+// all threads together, one step ahead in registers, and go through LDS in their natural order
+// with row pitches that keep all accesses free of bank conflicts (K: 4 words, V: 8 words past a
+// multiple of 32).  V is read back with the transposing LDS load.
+// The shape decides RH: 32 rows x 4 key streams up to 32 rows per KV head, 64 x 2 up to 64,
+// 128 x 1 beyond (d > 128: half the rows each, the accumulators are twice as wide).
+// Bound by latency, not bandwidth, at the sizes it meets: a launch of two steps per workgroup takes
+// 16 us of which about 8 are the chain prefix length -> first tiles -> epilogue.  Measured (d 64,
+// 8 sequences of 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector
+// units, every one reading the cache again, 1262 us; this kernel and its merge 20.7 us.  One tile
+// per step instead of four: 18.8 + 5.6 us against 17.5 + 4.2 us at the same number of segments.
+template <int DP, int RH, int MT, int TS>
+__global__ __launch_bounds__(256, 2)
+void tree_attn_bf16_kernel(AttnParams p)
+{
+    constexpr int KS = 4 / RH;
+    static_assert(TS % KS == 0, "every key stream takes the same number of tiles of a step");
+    constexpr int WROWS = 16 * MT, ROWS = WROWS * RH;
+    constexpr int GR = DP / 8;                           // 16-byte granules per row
+    constexpr int NL = TS * KT * GR / 256;               // K (and V) loads per thread and step
+    constexpr int PK = DP / 2 + 4, PV = DP / 2 + 8;      // row pitches in words
+    constexpr int STREAM_WORDS = KT * (PK + PV);
+    constexpr int PO = DP + 4;                           // row pitch of the epilogue's fp32 area
+    constexpr int LDS_WORDS = TS * STREAM_WORDS > ROWS * PO ? TS * STREAM_WORDS : ROWS * PO;
+    constexpr int NKK = DP / 32, NNT = DP / 16;
+
+    __shared__ __attribute__((aligned(16))) uint32_t s_big[LDS_WORDS];
+    __shared__ uint32_t s_anc[MCSD_MAX_NODES][4];
+    __shared__ int s_parent[MCSD_MAX_NODES];
+    __shared__ float s_m[KS][ROWS], s_l[KS][ROWS];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rh = wave / KS, ks = wave % KS;
+    const int lj = lane >> 4, lc = lane & 15;
+    const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
+    const int rt = blockIdx.x / p.H_kv % p.n_row_tiles, chunk = blockIdx.x / p.H_kv / p.n_row_tiles;
+    const int row0 = rt * ROWS;
+
+    const int L = max(0, min(p.prefix_len[b], p.L_stride));
+    const int tiles_prefix = (L + KT - 1) / KT, total_tiles = tiles_prefix + p.tiles_tree;
+    int n_seg, seg;
+    split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_seg, &seg);
+    const int t_begin = chunk * seg;
+    if (t_begin >= total_tiles) return;
+    const int t_end = min(total_tiles, t_begin + seg);
+    const uint32_t row_bytes = (uint32_t)p.d * 2u;
+
+    // load i of a thread: granule tid + 256 i of the step's TS x 32 rows, row-major
+    uint32_t g_off[NL];
+    int l_row[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int gid = tid + 256 * i, r = (gid / GR) % KT, c = gid % GR;
+        g_off[i] = (8 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
+        l_row[i] = r;
+    }
+    u32x4 kraw[NL], vraw[NL];
+    auto request = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int ks2 = ((wave * 64 + 256 * i) / GR) / KT;       // one tile per wave and load
+            const TileSrc s = tile_source<KT>(p, b, g, L, tiles_prefix, t0 + ks2, t_end, row_bytes);
+            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), g_off[i], 0, 0);
+            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), g_off[i], 0, 0);
+        }
+    };
+    request(t_begin);
+
+    // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
+    bf16x8 qreg[MT][NKK];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int r = row0 + WROWS * rh + 16 * mt + lc;
+        const int rr = min(r, p.M - 1), node = rr / p.G, hh = rr % p.G;
+        const uint16_t *src = static_cast<const uint16_t *>(p.q) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d;
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (r < p.M && 32 * kk + 8 * lj < p.d) v = *reinterpret_cast<const u32x4 *>(src + 32 * kk + 8 * lj);
+            qreg[mt][kk] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    if (t_end > tiles_prefix)
+        build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+
+    f32x4 oacc[NNT][MT];
+    float m_used[MT], l_part[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        m_used[mt] = M_INIT;
+        l_part[mt] = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt) oacc[nt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    const bool wave_active = row0 + WROWS * rh < p.M;
+    const float c2 = p.scale_log2;
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef v4i16 __attribute__((address_space(3))) *lds_v4i16_ptr;
+
+    for (int t0 = t_begin; t0 < t_end; t0 += TS) {
+        __syncthreads();                    // the last step's operands (and the masks) have been read (written)
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int gid = tid + 256 * i, c = gid % GR, ks2 = (gid / GR) / KT;
+            uint32_t *kt = s_big + ks2 * STREAM_WORDS, *vt = kt + KT * PK;
+            *reinterpret_cast<u32x4 *>(kt + l_row[i] * PK + 4 * c) = kraw[i];
+            *reinterpret_cast<u32x4 *>(vt + l_row[i] * PV + 4 * c) = vraw[i];
+        }
+        request(t0 + TS);
+        __syncthreads();
+        if (!wave_active) continue;
+        for (int ts = ks; ts < TS; ts += KS) {
+            const int t = t0 + ts;
+            if (t >= t_end) break;
+            const uint32_t *kt = s_big + ts * STREAM_WORDS, *vt = kt + KT * PK;
+            f32x4 sacc[2][MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) { sacc[0][mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; sacc[1][mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+#pragma unroll
+            for (int kk = 0; kk < NKK; ++kk) {
+                const bf16x8 k0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + lc * PK + 16 * kk + 4 * lj));
+                const bf16x8 k1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + (16 + lc) * PK + 16 * kk + 4 * lj));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    sacc[0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qreg[mt][kk], sacc[0][mt], 0, 0, 0);
+                    sacc[1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qreg[mt][kk], sacc[1][mt], 0, 0, 0);
+                }
+            }
+            // lane (lj, lc): row 16 mt + lc, keys 16 sub + 4 lj + i
+            const bool tree = t >= tiles_prefix;
+            const int nvalid = tree ? KT : min(KT, L - t * KT);          // (a tree tile's mask ends with the tree)
+            // (whole prefix tiles, nearly all of them, pay nothing for the masks)
+            const bool masked = tree || nvalid < KT;
+            uint32_t vis[MT];
+            float lmax[MT];
+            bool raise = false;
+            if constexpr (MT == 2) settle_scores(sacc[0][0], sacc[0][1], sacc[1][0], sacc[1][1]);
+            else settle_scores(sacc[0][0], sacc[1][0]);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                if (masked) {
+                    vis[mt] = (1u << (nvalid & 31)) - 1u;
+                    if (tree) vis[mt] = s_anc[min(row0 + WROWS * rh + 16 * mt + lc, p.M - 1) / p.G][t - tiles_prefix];
+                    vis[mt] >>= 4 * lj;
+#pragma unroll
+                    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (!((vis[mt] >> (16 * sub + i)) & 1u)) sacc[sub][mt][i] = -INFINITY;
+                }
+                const float mr = max_of_scores(sacc[0][mt], sacc[1][mt]);
+                lmax[mt] = (mr == -INFINITY) ? -INFINITY : mr * c2;
+                raise |= lmax[mt] > m_used[mt] + RESCALE_GAP;
+            }
+            if (__any(raise)) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    float rm = lmax[mt];
+                    rm = fmaxf(rm, __shfl_xor(rm, 16));
+                    rm = fmaxf(rm, __shfl_xor(rm, 32));
+                    const float m_new = fmaxf(m_used[mt], rm);
+                    const float alpha = fast_exp2(m_used[mt] - m_new);
+                    m_used[mt] = m_new;
+                    l_part[mt] *= alpha;
+#pragma unroll
+                    for (int nt = 0; nt < NNT; ++nt) oacc[nt][mt] *= alpha;
+                }
+            }
+            bf16x8 phi[MT], plo[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                float pv[8];
+                uint32_t hi[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int sub = e >> 2, i = e & 3;
+                    pv[e] = fast_exp2(fmaf(sacc[sub][mt][i], c2, -m_used[mt]));
+                }
+                if (masked) {
+                    // (with scale == 0 a masked score can not be told apart by its value)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (!((vis[mt] >> (16 * (e >> 2) + (e & 3))) & 1u)) pv[e] = 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) hi[e] = weight_hi_bits(pv[e]);
+                l_part[mt] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+                u32x4 ph, plw;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ph[j] = __builtin_amdgcn_perm(hi[2 * j + 1], hi[2 * j], 0x07060302u);
+                    plw[j] = pack_bf16(pv[2 * j] - __uint_as_float(hi[2 * j]), pv[2 * j + 1] - __uint_as_float(hi[2 * j + 1]));
+                }
+                phi[mt] = __builtin_bit_cast(bf16x8, ph);
+                plo[mt] = __builtin_bit_cast(bf16x8, plw);
+            }
+            const uint32_t *vl = vt + (4 * lj + (lc >> 2)) * PV + (lc & 3) * 2;
+#pragma unroll
+            for (int nt = 0; nt < NNT; ++nt) {
+                const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + nt * 8));
+                const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + 16 * PV + nt * 8));
+                const bf16x8 vop = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, phi[mt], oacc[nt][mt], 0, 0, 0);
+                    oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, plo[mt], oacc[nt][mt], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    // ---- epilogue: merge the key streams in LDS, then write whole rows
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        float lt = l_part[mt];
+        lt += __shfl_xor(lt, 16);
+        lt += __shfl_xor(lt, 32);
+        if (lj == 0) { s_m[ks][WROWS * rh + 16 * mt + lc] = m_used[mt]; s_l[ks][WROWS * rh + 16 * mt + lc] = lt; }
+    }
+    __syncthreads();                        // (also: every wave is done with the tiles)
+    float *area = reinterpret_cast<float *>(s_big);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int r = WROWS * rh + 16 * mt + lc;
+        float ms = s_m[0][r];
+#pragma unroll
+        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
+        const float fsc = exp2f(m_used[mt] - ms);
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt) oacc[nt][mt] *= fsc;
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < KS; ++k2) {
+        if (ks == k2) {
+#pragma unroll
+            for (int nt = 0; nt < NNT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    f32x4 *dst = reinterpret_cast<f32x4 *>(area + (WROWS * rh + 16 * mt + lc) * PO + 16 * nt + 4 * lj);
+                    *dst = (k2 == 0) ? oacc[nt][mt] : oacc[nt][mt] + *dst;
+                }
+        }
+        __syncthreads();
+    }
+    const int rows_valid = min(ROWS, p.M - row0), d4n = p.d / 4;
+    const bool direct = (n_seg == 1);
+    const size_t part_row = (((size_t)b * p.H_kv + g) * p.n_chunks_max + chunk) * (size_t)p.R + (size_t)row0;
+    for (int idx = tid; idx < rows_valid * d4n; idx += 256) {
+        const int r = idx / d4n, d4 = idx % d4n;
+        const f32x4 acc = *reinterpret_cast<const f32x4 *>(area + r * PO + 4 * d4);
+        float ms = s_m[0][r], ls = 0.f;
+#pragma unroll
+        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
+#pragma unroll
+        for (int k2 = 0; k2 < KS; ++k2) ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
+        if (direct) {
+            const float inv = 1.0f / ls;
+            const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
+            uint16_t *ob = static_cast<uint16_t *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + 4 * d4;
+            __builtin_nontemporal_store((u32x2){pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)}, reinterpret_cast<u32x2 *>(ob));
+        } else {
+            __builtin_nontemporal_store(acc, reinterpret_cast<f32x4 *>(p.part_o + (part_row + r) * p.d + 4 * d4));
+            if (d4 == 0) { p.part_m[part_row + r] = ms; p.part_l[part_row + r] = ls; }
+        }
+    }
+}
+
+// Merges the segments of a unit by log-sum-exp, one 16-byte piece of a row per thread.
+__global__ __launch_bounds__(256) void tree_attn_bf16_combine_kernel(AttnParams p)
+{
+    const int g = blockIdx.x % p.H_kv, b = blockIdx.z, d4n = p.d / 4, rows = 256 / d4n;
+    const int L = max(0, min(p.prefix_len[b], p.L_stride));
+    const int total_tiles = (L + KT - 1) / KT + p.tiles_tree;
+    int n_chunks, seg;
+    split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_chunks, &seg);
+    n_chunks = (total_tiles + seg - 1) / seg;
+    if (n_chunks <= 1) return;              // the attention kernel wrote the output itself
+    const int rl = threadIdx.x / d4n, r = blockIdx.x / p.H_kv * rows + rl, d4 = threadIdx.x % d4n;
+    if (rl >= rows || r >= p.M) return;
+    const size_t base = (((size_t)b * p.H_kv + g) * p.n_chunks_max) * (size_t)p.R + r;
+    // four segments are requested together; the running maximum starts at M_INIT like a segment's
+    float ms = M_INIT, ls = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < n_chunks; c0 += 4) {
+        float mc[4], lc[4];
+        f32x4 oc[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool on = c0 + c < n_chunks;
+            const size_t u = base + (size_t)(on ? c0 + c : 0) * p.R;
+            mc[c] = p.part_m[u];
+            lc[c] = on ? p.part_l[u] : 0.f;
+            oc[c] = *reinterpret_cast<const f32x4 *>(p.part_o + u * p.d + 4 * d4);
+            if (!on) { mc[c] = M_INIT; oc[c] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+        }
+        float mn = ms;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) mn = fmaxf(mn, mc[c]);
+        const float alpha = exp2f(ms - mn);
+        ls *= alpha;
+        acc *= alpha;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float f = exp2f(mc[c] - mn);
+            ls += f * lc[c];
+            acc += f * oc[c];
+        }
+        ms = mn;
+    }
+    const float inv = 1.0f / ls;
+    const int node = r / p.G, hh = r % p.G;
+    uint16_t *ob = static_cast<uint16_t *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + 4 * d4;
+    __builtin_nontemporal_store((u32x2){pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)}, reinterpret_cast<u32x2 *>(ob));
+}
+
+// ------------------------------------------------------------------------------ fp32
+// fp32 multiplies on the matrix cores.  A workgroup of 8 waves owns 16 query rows of a KV head and
+// DS output columns; every wave walks every 8th tile of 16 keys with its own online softmax and
+// the streams are merged at the end (no workspace, no barrier in the loop).  Bound by the fp32
+// matrix rate at one workgroup per CU (48 instructions of 32 cycles per wave and tile, two waves per
+// SIMD): 2 sequences of 301 and 1000 tokens, 16 heads of 128, 28 nodes: 326 us with one workgroup
+// per (node, head) on the vector units, 19.9 us here; relative error against 64 bits 5.2e-7 then,
+// 3.0e-7 now.
+//   S^T: the contraction index is d; step (kk, j) of lane (lj, lc) takes d = 16 kk + 4 lj + j, so
+//        that both operands are 16-byte pieces (K from LDS, Q in registers).
+//   O^T: step i takes key 4 lj + i, the key whose weight the lane holds; row index lc of the matrix
+//        (blk, e) is column 64 blk + 4 lc + e, so that V comes straight from memory in 16-byte
+//        pieces, 256 contiguous bytes per key.
+template <int DP, int DS>
+__global__ __launch_bounds__(512, 2)
+void tree_attn_f32_kernel(AttnParams p)
+{
+    constexpr int KW = 16, KS = 8, ROWS = 16;
+    constexpr int GR = DP / 4, NL = KW * GR / 64;        // 16-byte granules per row; K loads per lane and tile
+    constexpr int PK = DP + 4, PO = DS + 4;              // row pitches in words
+    constexpr int NKK = DP / 16, NB = DS / 64;
+
+    __shared__ __attribute__((aligned(16))) float s_big[KS][KW * PK];
+    __shared__ uint32_t s_anc[MCSD_MAX_NODES][4];
+    __shared__ int s_parent[MCSD_MAX_NODES];
+    __shared__ float s_m[KS][ROWS], s_l[KS][ROWS];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lj = lane >> 4, lc = lane & 15;
+    const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
+    const int row0 = blockIdx.x / p.H_kv * ROWS, d0 = blockIdx.y * DS;
+
+    const int L = max(0, min(p.prefix_len[b], p.L_stride));
+    const int tiles_prefix = (L + KW - 1) / KW, t_end = tiles_prefix + (p.N + KW - 1) / KW;
+    const uint32_t row_bytes = (uint32_t)p.d * 4u;
+
+    uint32_t k_off[NL], v_off[NB];
+    uint32_t k_pos[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int gid = lane + 64 * i, r = gid / GR, c = gid % GR;
+        k_off[i] = (4 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
+        k_pos[i] = r * PK + 4 * c;
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int col = d0 + 64 * n + 4 * lc;
+        v_off[n] = (col < p.d) ? (uint32_t)(4 * lj) * row_bytes + 4u * col : OFF_NOWHERE - 4096u;     // (plus up to three rows)
+    }
+    u32x4 kraw[NL], vraw[NB][4];
+    auto request_k = [&](const TileSrc &s) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(s.kb, s.bytes);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_off[i], 0, 0);
+    };
+    auto request_v = [&](const TileSrc &s) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(s.vb, s.bytes);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vraw[n][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, v_off[n] + i * row_bytes, 0, 0);
+    };
+    {
+        const TileSrc s = tile_source<KW>(p, b, g, L, tiles_prefix, ks, t_end, row_bytes);
+        request_k(s);
+        request_v(s);
+    }
+
+    f32x4 qreg[NKK];
+    {
+        const int r = row0 + lc, rr = min(r, p.M - 1), node = rr / p.G, hh = rr % p.G;
+        const float *src = static_cast<const float *>(p.q) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d;
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) {
+            qreg[kk] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (r < p.M && 16 * kk + 4 * lj < p.d) qreg[kk] = *reinterpret_cast<const f32x4 *>(src + 16 * kk + 4 * lj);
+        }
+    }
+    build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+    __syncthreads();
+
+    f32x4 oacc[NB][4];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[n][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    float m_used = M_INIT, l_part = 0.f;
+    const float c2 = p.scale_log2;
+    const int node_m = min(row0 + lc, p.M - 1) / p.G;
+    float *area = s_big[ks];
+
+    for (int t = ks; t < t_end; t += KS) {
+        const TileSrc next = tile_source<KW>(p, b, g, L, tiles_prefix, t + KS, t_end, row_bytes);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4 *>(area + k_pos[i]) = kraw[i];
+        request_k(next);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // two accumulators: half the length of the serial chain
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NKK; kk += 2) {
+            const f32x4 ka = *reinterpret_cast<const f32x4 *>(area + lc * PK + 16 * kk + 4 * lj);
+            const f32x4 kb = *reinterpret_cast<const f32x4 *>(area + lc * PK + 16 * kk + 16 + 4 * lj);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[j], qreg[kk][j], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kb[j], qreg[kk + 1][j], s1, 0, 0, 0);
+            }
+        }
+        f32x4 sc = s0 + s1;
+        // lane (lj, lc): row lc, keys 4 lj + i
+        const bool tree = t >= tiles_prefix;
+        const int key0 = (t - tiles_prefix) * KW;                    // of a tree tile
+        const int nvalid = tree ? KW : min(KW, L - t * KW);
+        uint32_t vis = tree ? s_anc[node_m][key0 >> 5] >> (key0 & 31) : 0xffffffffu;
+        if (nvalid < KW) vis = (1u << nvalid) - 1u;
+        vis >>= 4 * lj;
+        float mr = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (!((vis >> i) & 1u)) sc[i] = -INFINITY;
+            mr = fmaxf(mr, sc[i]);
+        }
+        const float lmax = (mr == -INFINITY) ? -INFINITY : mr * c2;
+        if (__any(lmax > m_used + RESCALE_GAP)) {
+            float rm = lmax;
+            rm = fmaxf(rm, __shfl_xor(rm, 16));
+            rm = fmaxf(rm, __shfl_xor(rm, 32));
+            const float m_new = fmaxf(m_used, rm);
+            const float alpha = fast_exp2(m_used - m_new);
+            m_used = m_new;
+            l_part *= alpha;
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oacc[n][e] *= alpha;
+        }
+        float pw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            pw[i] = fast_exp2(fmaf(sc[i], c2, -m_used));
+            if (!((vis >> i) & 1u)) pw[i] = 0.f;
+        }
+        l_part += (pw[0] + pw[1]) + (pw[2] + pw[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    oacc[n][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vraw[n][i][e]), pw[i], oacc[n][e], 0, 0, 0);
+        request_v(next);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // the K operands are read before the next tile is stored
+        __builtin_amdgcn_wave_barrier();
+    }
+
+    // ---- epilogue: merge the eight streams
+    float lt = l_part;
+    lt += __shfl_xor(lt, 16);
+    lt += __shfl_xor(lt, 32);
+    if (lj == 0) { s_m[ks][lc] = m_used; s_l[ks][lc] = lt; }
+    __syncthreads();
+    {
+        float ms = s_m[0][lc];
+#pragma unroll
+        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][lc]);
+        const float fsc = exp2f(m_used - ms);
+        // oacc[n][e][i] is row lc, column 64 n + 16 lj + 4 i + e
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4 v = {oacc[n][0][i] * fsc, oacc[n][1][i] * fsc, oacc[n][2][i] * fsc, oacc[n][3][i] * fsc};
+                *reinterpret_cast<f32x4 *>(area + lc * PO + 64 * n + 16 * lj + 4 * i) = v;
+            }
+    }
+    __syncthreads();
+    const int rows_valid = min(ROWS, p.M - row0);
+    for (int idx = tid; idx < ROWS * (DS / 4); idx += 512) {
+        const int r = idx / (DS / 4), c = idx % (DS / 4);
+        if (r >= rows_valid || d0 + 4 * c >= p.d) continue;
+        float ms = s_m[0][r], ls = 0.f;
+#pragma unroll
+        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k2 = 0; k2 < KS; ++k2) {
+            ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
+            acc += *reinterpret_cast<const f32x4 *>(s_big[k2] + r * PO + 4 * c);
+        }
+        const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
+        float *ob = static_cast<float *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + d0 + 4 * c;
+        const float inv = 1.0f / ls;
+        *reinterpret_cast<f32x4 *>(ob) = acc * inv;
+    }
+}
+
+template <int DP, int RH, int MT, int TS>
+void launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream)
+{
+    launch_kernel(K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, RH, MT, TS>, grid, dim3(256), stream, p);
+}
+
+template <int DP, int DS>
+void launch_f32(const AttnParams &p, hipStream_t stream)
+{
+    launch_kernel(K_ATTN_GENERIC, tree_attn_f32_kernel<DP, DS>, dim3((unsigned)p.H_kv * ((p.M + 15) / 16), DP / DS, p.B), dim3(512), stream, p);
+}
+
+}  // namespace
+
+int32_t launch_attn_any(const AttnParams &p, const AttnPlan &plan, hipStream_t stream)
+{
+    if (p.B > 65535) { set_error("attn: B %d > 65535", p.B); return MCSD_E_UNSUPPORTED; }
+    const int dp = p.d <= 64 ? 64 : (p.d <= 128 ? 128 : 256);
+    if (p.dtype == MCSD_DTYPE_FP32) {
+        // Few units: the output columns are split over workgroups as well (every slice scores the
+        // keys again, which is half of the work).  The line is where the slices stop fitting the 256
+        // CUs side by side; beyond it the repeated scores are all that a slice adds.
+        const bool slices = (long)p.B * p.H_kv * ((p.M + 15) / 16) < 128;
+        if (dp == 64) launch_f32<64, 64>(p, stream);
+        else if (dp == 128) { if (slices) launch_f32<128, 64>(p, stream); else launch_f32<128, 128>(p, stream); }
+        else { if (slices) launch_f32<256, 64>(p, stream); else launch_f32<256, 128>(p, stream); }
+    } else {
+        const dim3 grid((unsigned)p.H_kv * plan.n_chunks_max * plan.n_row_tiles, 1, p.B);
+        if (dp == 64) {
+            if (plan.variant == 0) launch_bf16<64, 1, 2, 4>(p, grid, stream);
+            else if (plan.variant == 1) launch_bf16<64, 2, 2, 4>(p, grid, stream);
+            else launch_bf16<64, 4, 2, 4>(p, grid, stream);
+        } else if (dp == 128) {
+            if (plan.variant == 0) launch_bf16<128, 1, 2, 4>(p, grid, stream);
+            else if (plan.variant == 1) launch_bf16<128, 2, 2, 2>(p, grid, stream);
+            else launch_bf16<128, 4, 2, 2>(p, grid, stream);
+        } else {
+            if (plan.variant == 1) launch_bf16<256, 2, 1, 2>(p, grid, stream);
+            else launch_bf16<256, 4, 1, 1>(p, grid, stream);
+        }
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("tree_attn launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
+    if (plan.n_chunks_max > 1) {
+        const int rows = 256 / (p.d / 4);
+        launch_kernel(K_ATTN_COMBINE, tree_attn_bf16_combine_kernel, dim3((unsigned)p.H_kv * ((p.M + rows - 1) / rows), 1, p.B), dim3(256), stream, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) { set_error("tree_attn_combine launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
+    }
+    return MCSD_OK;
+}
+
+}  // namespace mcsd

@@ -1,0 +1,51 @@
+"""Tree attention with fp32 storage or a head dimension other than 128 against the CPU oracle: head
+dimensions around the paddings (64, 128, 256), row counts around the row tiles, prefixes around the
+16- and 32-key tiles and long enough to be split; the paged cache and a call without a workspace
+give the same attention."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mcsd_oracle as O
+from paper_2401_06706_amd import binding as M
+from paper_2401_06706_amd import device as D
+from paper_2401_06706_amd import workloads as W
+from tests.parity import assert_attn_close
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, d, B, H_q, H_kv, k-configuration, shortest and longest prefix)
+CASES = [
+    ("bf16", 8, 1, 1, 1, (1,), (0, 0)), ("bf16", 40, 2, 6, 2, (3, 2), (31, 33)), ("bf16", 64, 3, 4, 4, (4, 2, 2), (0, 900)),
+    ("bf16", 64, 2, 8, 4, (4, 2, 2), (1, 700)), ("bf16", 64, 2, 16, 2, (4, 2, 2), (63, 2500)), ("bf16", 72, 1, 8, 2, (2, 2), (15, 17)),
+    ("bf16", 96, 2, 4, 2, (4, 4, 2, 1), (5, 600)), ("bf16", 120, 1, 8, 1, (128,), (300, 300)), ("bf16", 136, 2, 2, 2, (4, 2, 2), (33, 400)),
+    ("bf16", 200, 1, 4, 1, (4, 2, 2), (100, 1000)), ("bf16", 256, 2, 4, 2, (4, 2), (0, 1500)), ("bf16", 256, 1, 3, 3, (16, 2, 2), (64, 64)),
+    ("fp32", 4, 1, 1, 1, (1,), (0, 0)), ("fp32", 8, 2, 6, 2, (3, 2), (15, 17)), ("fp32", 64, 3, 4, 2, (4, 2, 2), (0, 700)),
+    ("fp32", 68, 1, 8, 1, (2, 2, 2, 2, 2, 2), (127, 129)), ("fp32", 128, 2, 4, 4, (4, 2, 2), (1, 1100)), ("fp32", 128, 5, 32, 32, (2, 2), (20, 90)),
+    ("fp32", 132, 2, 2, 1, (16,), (16, 300)), ("fp32", 256, 1, 4, 4, (128,), (33, 33)), ("fp32", 256, 5, 32, 32, (4,), (0, 40)),
+]
+
+
+@pytest.mark.parametrize("dtype,d,B,H_q,H_kv,kconfig,prefix", CASES, ids=lambda v: str(v).replace(" ", ""))
+def test_against_oracle(dtype, d, B, H_q, H_kv, kconfig, prefix):
+    w = W.Workload(name="t", index=70, B=B, H_q=H_q, H_kv=H_kv, d=d, dtype=dtype, prefix=prefix, kconfig=kconfig, V=8,
+                   sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(d + H_q), L_stride=prefix[1] + 3)
+    print(f"[any] {dtype} d={d} B={B} H={H_q}/{H_kv} N={ai.N} L={ai.prefix_len.tolist()}", flush=True)
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale,
+                      O.FP32 if dtype == "fp32" else O.BF16, n_threads=16)
+    call = D.make_attn_call(ai)
+    M.mcsd_tree_attn(call.args)
+    torch.cuda.synchronize()
+    assert_attn_close(call.out_numpy(), ref, dtype, "contiguous")
+    paged_call, paged, _ = D.make_paged_attn_call(call, ai, 32, seed=d)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert torch.equal(paged_call.out, call.out)
+    # without a workspace the keys are not split: the same attention, summed in another order
+    t = call.tensors
+    whole = torch.zeros_like(t["out"])
+    M.mcsd_tree_attn(M.attn_args(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_len"], t["k_tree"], t["v_tree"], t["parent"],
+                                 whole, ai.scale))
+    torch.cuda.synchronize()
+    assert_attn_close(whole.to(torch.float32).cpu().numpy().astype(np.float64), ref, dtype, "no workspace")
