@@ -436,5 +436,205 @@ __device__ __forceinline__ int inverse_cdf(const float4 (&a)[ITEMS], double A, d
     return cdf_search<ITEMS, VT>(a, A, u, eps, s_red, s_tot, s_int, flag_bits);
 }
 
+// ------------------------------------------------------------------ rows in pieces
+// The same search with fewer synchronisations.  A piece is what one wavefront holds of one item:
+// 256 consecutive tokens; piece number j = item * waves + wave is their order in the row.  Every
+// wavefront keeps all piece totals itself (PPL = pieces per lane, in order), so that it finds the
+// piece of a crossing with one scan over its lanes; the wavefront that owns that piece then finds
+// the token with a second scan and publishes it: one workgroup barrier per search.
+
+// Loads of a logit row, four tokens per thread and item, -inf past V.  The first FULL items lie
+// inside every row of this configuration.  A row whose length is no multiple of four starts at any
+// 4-byte address, which 128-bit buffer loads allow; its last tokens (fewer than four) come by
+// single loads, so that no load straddles the end of the resource.
+template <int ITEMS, int VT, int FULL, bool ALIGNED>
+__device__ __forceinline__ void load_pieces(const float *row, int V, int tid, float4 (&r)[ITEMS])
+{
+    constexpr int NT = 2;                   // non-temporal: a logit row is read once
+    const float ninf = -INFINITY;
+    const int V4 = V & ~3;
+    const __amdgpu_buffer_rsrc_t rs = row_resource(row, ALIGNED ? V : V4);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, i * (VT * 16), NT);
+        r[i] = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+    }
+    float4 tail = make_float4(ninf, ninf, ninf, ninf);
+    if (!ALIGNED) {
+        const __amdgpu_buffer_rsrc_t rt = row_resource(row, V);
+        tail.x = (V4 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 0, V4 * 4, NT)) : ninf;
+        tail.y = (V4 + 1 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 4, V4 * 4, NT)) : ninf;
+        tail.z = (V4 + 2 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 8, V4 * 4, NT)) : ninf;
+    }
+#pragma unroll
+    for (int i = FULL; i < ITEMS; ++i) {
+        if (4 * VT * (i + 1) > V4) {        // uniform
+            const int e = 4 * (tid + VT * i);
+            const bool past = e > V4 || (ALIGNED && e == V4), at = !ALIGNED && e == V4;
+            r[i] = make_float4(past ? ninf : (at ? tail.x : r[i].x), past ? ninf : (at ? tail.y : r[i].y),
+                               past ? ninf : (at ? tail.z : r[i].z), past ? ninf : (at ? ninf : r[i].w));
+        }
+    }
+}
+
+template <int ITEMS, int VT>
+struct Pieces {
+    static constexpr int NW = VT / 64, NP = ITEMS * NW, PPL = NP <= 64 ? 1 : NP / 64;
+    double tot[PPL];                        // totals of pieces lane * PPL ...
+
+    // s_piece holds 4 NP doubles: the totals per row of 16 lanes
+    static __device__ __forceinline__ void store4(const double (&x)[4], int i0, int lane, int wave, double *s_piece)
+    {
+        double y[4] = {x[0], x[1], x[2], x[3]};
+        int which;
+        const double w = row_totals_scattered<4>(y, lane, which);
+        s_piece[((i0 + which) * NW + wave) * 4 + (lane >> 4)] = w;
+    }
+    static __device__ __forceinline__ void store(const float4 (&a)[ITEMS], int lane, int wave, double *s_piece)
+    {
+#pragma unroll
+        for (int i0 = 0; i0 < ITEMS; i0 += 4) {
+            double x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = (i0 + i < ITEMS) ? sum4(a[i0 + i < ITEMS ? i0 + i : 0]) : 0.0;
+            store4(x, i0, lane, wave, s_piece);
+        }
+    }
+    __device__ __forceinline__ void read(const double *s_piece, int lane)
+    {
+#pragma unroll
+        for (int q = 0; q < PPL; ++q) {
+            const int j = lane * PPL + q;
+            const double *s = s_piece + 4 * (j < NP ? j : 0);
+            const double t = (s[0] + s[1]) + (s[2] + s[3]);
+            tot[q] = j < NP ? t : 0.0;
+        }
+    }
+    __device__ __forceinline__ double scan() const      // inclusive, over the lanes
+    {
+        double v = tot[0];
+#pragma unroll
+        for (int q = 1; q < PPL; ++q) v += tot[q];
+        return wave_scan_inclusive(v);
+    }
+    // the token's weight leaves its piece
+    __device__ __forceinline__ void remove(int token, float weight, int lane)
+    {
+        const int j = token >> 8;
+#pragma unroll
+        for (int q = 0; q < PPL; ++q)
+            if (j == lane * PPL + q) tot[q] -= (double)weight;
+    }
+};
+
+__device__ __forceinline__ double readlane_d(double v, int lane)
+{
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)x, lane), hi = __builtin_amdgcn_readlane((int)(x >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The smallest token whose cumulative weight exceeds tau = u A, or the last one that carries weight
+// where rounding leaves none.  `incl` = P.scan().  Every wavefront calls it; the one that owns the
+// token writes it, its weight and whether tau lies within tol of an edge of its interval to *out
+// (-1 if nothing carries weight: then wavefront 0 does); the caller publishes with one barrier.
+// The tokens of taken[0 .. n_taken) have left the row: their weights count as zero.
+struct Drawn {
+    int token;
+    float weight;
+    int near;
+};
+
+template <int ITEMS, int VT>
+__device__ __forceinline__ void draw_token(const float4 (&a)[ITEMS], const Pieces<ITEMS, VT> &P, double incl, double tau, double tol,
+                                           int lane, int wave, Drawn *out, const Drawn *taken = nullptr, int n_taken = 0)
+{
+    constexpr int PPL = Pieces<ITEMS, VT>::PPL, NW = Pieces<ITEMS, VT>::NW;
+    // piece of the crossing; without one, the last piece that carries weight
+    double mine_tot = P.tot[0];
+#pragma unroll
+    for (int q = 1; q < PPL; ++q) mine_tot += P.tot[q];
+    const unsigned long long cross = __ballot(incl > tau), weight = __ballot(mine_tot > 0.0);
+    if (!cross && !weight) {
+        if (wave == 0 && lane == 0) *out = {-1, 0.f, 1};
+        return;
+    }
+    const int ls = cross ? __ffsll((long long)cross) - 1 : 63 - __clzll((long long)weight);
+    double base = readlane_d(incl, ls > 0 ? ls - 1 : 0);
+    if (ls == 0) base = 0.0;
+    int qs = -1, q_last = 0;
+    double run = base, run_last = base;
+#pragma unroll
+    for (int q = 0; q < PPL; ++q) {
+        const double tq = readlane_d(P.tot[q], ls);
+        if (qs < 0) {
+            if (tq > 0.0) { q_last = q; run_last = run; }
+            if (cross && run + tq > tau) { qs = q; base = run; }
+            else run += tq;
+        }
+    }
+    const bool exact = qs >= 0;
+    if (!exact) { qs = q_last; base = run_last; }
+    const int j = __builtin_amdgcn_readfirstlane(ls * PPL + qs);
+    if (j % NW != wave) return;
+    const int is = j / NW;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (i == is) v = a[i];
+    for (int n0 = 0; n0 < n_taken; n0 += 64) {
+        const int x_lane = n0 + lane < n_taken ? taken[n0 + lane].token : -1;
+        for (unsigned long long m = __ballot((x_lane >> 8) == j); m; m &= m - 1) {      // those of this piece
+            const int x = __builtin_amdgcn_readlane(x_lane, __ffsll((long long)m) - 1);
+            if ((x >> 2) == 64 * j + lane) {
+                if ((x & 3) == 0) v.x = 0.f;
+                if ((x & 3) == 1) v.y = 0.f;
+                if ((x & 3) == 2) v.z = 0.f;
+                if ((x & 3) == 3) v.w = 0.f;
+            }
+        }
+    }
+    const double part = sum4(v);
+    const double hi_lane = base + wave_scan_inclusive(part);
+    const unsigned long long c2 = __ballot(hi_lane > tau), w2 = __ballot(part > 0.0);
+    if (!c2 && !w2) {                       // (a piece whose total is rounding residue)
+        if (lane == 0) *out = {4 * (64 * j + 63) + 3, 0.f, 1};
+        return;
+    }
+    const bool found = exact && c2 != 0ull;
+    const int l2 = found ? __ffsll((long long)c2) - 1 : 63 - __clzll((long long)(w2 ? w2 : c2));
+    double lo = readlane_d(hi_lane, l2 > 0 ? l2 - 1 : 0);
+    if (l2 == 0) lo = base;
+    if (lane == l2) {
+        const float w[4] = {v.x, v.y, v.z, v.w};
+        double cum = lo, hi = hi_lane;
+        int pick = -1, last_pos = -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double nxt = cum + (double)w[e];
+            if (w[e] > 0.f) last_pos = e;
+            if (found && pick < 0 && nxt > tau) { pick = e; lo = cum; hi = nxt; }
+            cum = nxt;
+        }
+        int near = 1;
+        if (pick >= 0) near = (fabs(tau - lo) < tol || fabs(hi - tau) < tol) ? 1 : 0;
+        else pick = last_pos < 0 ? 3 : last_pos;
+        float wt = w[0];
+        if (pick == 1) wt = w[1];
+        if (pick == 2) wt = w[2];
+        if (pick == 3) wt = w[3];
+        *out = {4 * (64 * j + lane) + pick, wt, near};
+    }
+}
+
+// Index of the n-th set bit (n from 0) of a 128-bit mask, the masks of the children of a row.
+struct Kids {
+    unsigned long long m0, m1;
+    __device__ __forceinline__ int count() const { return __popcll(m0) + __popcll(m1); }
+    // rank of node `lane` / `64 + lane` among the children
+    __device__ __forceinline__ int rank0(int lane) const { return __popcll(m0 & ((1ull << lane) - 1ull)); }
+    __device__ __forceinline__ int rank1(int lane) const { return __popcll(m0) + __popcll(m1 & ((1ull << lane) - 1ull)); }
+};
+
 }  // namespace vocab
 }  // namespace mcsd

@@ -201,3 +201,22 @@ def test_one_tree_per_sequence(variant):
     for b, vi in enumerate(vis):
         rt, rm = O.draft_sample(vi.draft_logits, vi.tree.q_row, vi.tree.parent, us[b], vi.temperature, variant, n_threads=2)
         compare(vi, {"cand_tok": tok[b:b + 1], "flags": fl[b:b + 1]}, rt, rm, f"per-seq tree {kconfigs[b]}")
+
+
+@pytest.mark.parametrize("V", [300, 5001, 9002, 20003, 32000, 50001, 65535])
+def test_draws_that_meet_in_one_piece_and_in_the_last_tokens(V):
+    """Nearly all mass on neighbouring tokens (one wavefront's piece of 256, each draw after the
+    first without the ones before it) and on the last tokens of a row whose length is no multiple of
+    four; one sequence greedy, one with ties."""
+    w = W.WORKLOADS["c2"].with_(B=4, V=V, kconfig=(14,), variant=W.WITHOUT_REPLACEMENT)
+    vi = W.gen_verify_inputs(w, np.random.default_rng(V), temperature=[1.0, 0.0, 0.7, 0.0], draw_candidates_on_host=False)
+    vi.draft_logits[:] -= 60.0
+    start = (V // 2) & ~255
+    rng = np.random.default_rng(V + 1)
+    vi.draft_logits[:, 0, start:start + 12] = rng.permutation(12).astype(np.float32) / 4
+    vi.draft_logits[:, 0, V - 5:] = np.arange(5, dtype=np.float32) / 3
+    vi.draft_logits[3, 0, start:start + 12] = 1.0
+    u = W.open_uniform(rng, (vi.B, vi.N))
+    got, rt, rm = run(vi, u)
+    compare(vi, got, rt, rm, f"V={V}")
+    np.testing.assert_array_equal(got["cand_tok"][[1, 3]], rt[[1, 3]])
