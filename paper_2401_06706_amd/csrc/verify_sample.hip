@@ -1,20 +1,14 @@
 // Multi-candidate speculative sampling on gfx950: Algorithm 1 (with replacement),
 // Algorithm 2 (without replacement), the endpoint draws and the root-to-leaf walk.
 //
-// One workgroup owns one row of the tree (the root or a node).
+// One workgroup owns one row of the tree (the root or a node).  Both logit rows of the node are read
+// from HBM exactly once with 128-bit loads and stay on the compute unit, in registers and (the larger
+// vocabularies) partly in LDS, for all k sequential accept/reject rounds; every round is one
+// elementwise pass over the resident data plus one block reduction.
 //
-// verify_rows_kernel (vocabularies up to 32768): both logit rows of the node are read from HBM
-// exactly once with 128-bit buffer loads and stay in registers for all k sequential
-// accept/reject rounds; every round is one elementwise pass over the resident data plus one
-// block reduction.  1024 threads up to 16384 tokens, 512 threads (twice the registers) beyond.
-//
-// verify_rows_stream_kernel (up to 65536): only the target row stays in registers, as the
-// unnormalised residual a(x).  The draft row is streamed: once from HBM for its maximum, again
-// (from the caches) for the exponentials and their sum, and once more for every rejection,
-// where the update a := max(0, a - beta e_q) needs e_q(x) = exp((z_q(x) - max) / T),
-// recomputed on the fly.  Algorithm 2's removal of a rejected token from q needs no pass
-// there: that token's residual is already 0 and stays 0 whatever is subtracted from it later,
-// so only Z_q changes, by exactly the fp32 weight of the token.
+// Algorithm 2's removal of a rejected token from q needs no pass: that token's residual is already
+// 0 and stays 0 whatever is subtracted from it later, so only Z_q changes, by exactly the fp32 weight
+// of the token.
 //
 // Instead of renormalising after each rejection the kernels carry an
 // unnormalised residual a(x) and its sum A (p-hat = a / A), and the unnormalised
@@ -78,20 +72,6 @@ __device__ __forceinline__ double exp2_neg(double x)
 }
 
 
-// The arguments of the kernel, read again from the kernel-argument segment through a pointer the
-// compiler can not see through.  Used where an argument is needed late in the kernel: kept in
-// scalar registers from the start it would be spilled around the vocabulary passes.
-__device__ __forceinline__ VerifyParams reload_params()
-{
-    typedef const uint32_t __attribute__((address_space(4))) *kernarg_words;
-    kernarg_words pk = (kernarg_words)__builtin_amdgcn_kernarg_segment_ptr();      // the only argument
-    asm volatile("" : "+s"(pk));
-    union { VerifyParams params; uint32_t words[sizeof(VerifyParams) / 4]; } copy;
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(VerifyParams) / 4); ++i) copy.words[i] = pk[i];
-    return copy.params;
-}
-
 // The residual row scaled by s, stored through a buffer resource (stores past the end of the row
 // are dropped).  The offset of a piece goes into the per-thread offset, not into the scalar
 // offset field: with a scalar register there, the compiler inserts no wait between a 128-bit
@@ -116,35 +96,6 @@ __device__ __forceinline__ void store_residual(float *dst, int V, const float4 (
     }
 }
 
-// One pass over a logit row that is not held in registers: thread t meets the same elements
-// as in a resident row (float4 number t + VT i for i = 0 .. ITEMS-1, -inf past V), in chunks of
-// CH pieces; f(i, values) is called in ascending i.  DOUBLE: two chunks are in flight, the next
-// one is requested before the current one is used; otherwise a chunk is requested when the
-// previous one has been used.  In both cases the scheduler may not move requests further ahead
-// than that (it would, at the price of spills).
-template <int ITEMS, int VT, bool ALIGNED, bool NONTEMPORAL, int CHUNK, bool DOUBLE, typename F>
-__device__ __forceinline__ void stream_row(__amdgpu_buffer_rsrc_t rs, int V, F &&f)
-{
-    constexpr int CH = ITEMS < CHUNK ? ITEMS : CHUNK;
-    float4 cur[CH], nxt[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) cur[c] = load_row_piece<VT, ALIGNED, NONTEMPORAL>(rs, c, V, threadIdx.x);
-#pragma unroll
-    for (int i0 = 0; i0 < ITEMS; i0 += CH) {
-        if (DOUBLE && i0 + CH < ITEMS) {
-#pragma unroll
-            for (int c = 0; c < CH; ++c) nxt[c] = load_row_piece<VT, ALIGNED, NONTEMPORAL>(rs, i0 + CH + c, V, threadIdx.x);
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) f(i0 + c, cur[c]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i0 + CH < ITEMS) {
-#pragma unroll
-            for (int c = 0; c < CH; ++c) cur[c] = DOUBLE ? nxt[c] : load_row_piece<VT, ALIGNED, NONTEMPORAL>(rs, i0 + CH + c, V, threadIdx.x);
-        }
-    }
-}
-
 // e_q of four logits, bit for bit what every pass (and the thread that tracks a candidate
 // token) computes: subtraction first, then the scale, then v_exp_f32.
 __device__ __forceinline__ float4 exp_weights(const float4 &z, float m, float c)
@@ -153,702 +104,469 @@ __device__ __forceinline__ float4 exp_weights(const float4 &z, float m, float c)
                        __builtin_amdgcn_exp2f((z.z - m) * c), __builtin_amdgcn_exp2f((z.w - m) * c));
 }
 
-template <int ITEMS, int VT, bool ALIGNED>
-__global__ __launch_bounds__(VT) __attribute__((amdgpu_waves_per_eu(ITEMS <= 16 ? 4 : 2, ITEMS <= 16 ? 4 : 2)))
-void verify_rows_stream_kernel(VerifyParams p)
+// A condition that is the same in all lanes though the compiler can not know it: as a scalar, so that
+// the branch on it is one.
+__device__ __forceinline__ bool uniform(bool c) { return __builtin_amdgcn_readfirstlane(c ? 1 : 0) != 0; }
+__device__ __forceinline__ double uniform(double v) { return readlane_d(v, 0); }
+
+// The sequence of rank y when the sampled sequences come before the argmax ones (each group in its
+// own order), and its temperature.  Workgroups start in the order y, x, and a sampled sequence costs
+// a workgroup about three times what an argmax sequence costs (two rows, exponentials, k dependent
+// rounds against one row and an argmax): handed out first, the cheap ones fill the end of the launch.
+// Every wavefront finds it by itself, without a barrier.  Batches above 512 keep their order.
+__device__ __forceinline__ void ranked_sequence(const float *temperature, int B, int y, int lane, int *seq, float *T)
 {
-    constexpr int NWAVES = VT / 64;
-    constexpr int PASS_CHUNK = 4;           // pieces of the draft row requested together while the target row is resident
-    constexpr bool PASS_DOUBLE = true;
-    const int row = blockIdx.x;
-    int b = blockIdx.y;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int N = p.N, V = p.V;
-
-    __shared__ double s_red[NWAVES];
-    __shared__ double s_red2[NWAVES];
-    __shared__ double s_seg[4 * NWAVES * ITEMS + ITEMS];
-    __shared__ float s_redf[NWAVES];
-    __shared__ float s_redf2[NWAVES];
-    __shared__ unsigned long long s_mask[2];
-    __shared__ int s_kids[MCSD_MAX_NODES];
-    __shared__ int s_k;
-    __shared__ int s_int[4];
-    __shared__ uint32_t s_flags;
-    __shared__ int s_accept;       // decision of the current round
-    __shared__ int s_xrem;         // token removed from q after a rejection (-1: none)
-    __shared__ float s_qrem;       // its weight e_q as the vector passes compute it
-    __shared__ float s_bestv[NWAVES];
-    __shared__ int s_besti[NWAVES];
-
-    // Workgroups start in the order y, x.  A sampled sequence costs a workgroup about three
-    // times what an argmax sequence costs (two rows, exponentials, k dependent rounds against
-    // one row and an argmax), so the sampled sequences are handed out first and the cheap ones
-    // fill the end of the launch: sequence number y in dispatch order is the y-th sampled
-    // sequence, then the argmax ones in their own order.  Done when B fits the workgroup.
-    __shared__ int s_cnt[NWAVES];
-    __shared__ int s_seq_of_rank[VT];
-    __shared__ float s_T_of_rank[VT];
-    // requested now, used after the ranking: the draft-row address needs it (with one tree per
-    // sequence the map is that sequence's and can only be read once the sequence is known)
-    int qr = p.per_seq ? -1 : p.q_row[row];
-    float T = 1.f;
-    const bool ranked = p.B > 1 && p.B <= VT;
-    if (p.B > 1 && p.B <= 64) {
-        // one wavefront ranks up to 64 sequences by itself: one load, one ballot, one barrier
-        if (wave == 0) {
-            const float Tt = (lane < p.B) ? p.temperature[lane] : 1.f;
-            const bool sampled = (lane < p.B) && (Tt != 0.f);
-            const unsigned long long m = __ballot(sampled);
-            const int total = __popcll(m);
-            const int idx_s = __popcll(m & ((1ull << lane) - 1ull));    // sampled sequences before this one
-            if (lane < p.B) {
-                const int r = sampled ? idx_s : total + (lane - idx_s);
-                s_seq_of_rank[r] = lane;
-                s_T_of_rank[r] = Tt;
-            }
-        }
-        __syncthreads();
-    } else if (ranked) {
-        const float Tt = (t < p.B) ? p.temperature[t] : 1.f;
-        const bool sampled = (t < p.B) && (Tt != 0.f);
-        const unsigned long long m = __ballot(sampled);
-        if (lane == 0) s_cnt[wave] = __popcll(m);
-        __syncthreads();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) {
-            const int c = s_cnt[w];
-            before += (w < wave) ? c : 0;
-            total += c;
-        }
-        const int idx_s = before + __popcll(m & ((1ull << lane) - 1ull));   // sampled sequences before this one
-        if (t < p.B) {
-            const int r = sampled ? idx_s : total + (t - idx_s);
-            s_seq_of_rank[r] = t;
-            s_T_of_rank[r] = Tt;
-        }
-        __syncthreads();
-    }
-    if (ranked) {
-        // back to wave-uniform values (they come out of LDS): addresses and branches stay scalar,
-        // and the temperature does not take a second trip to memory
-        b = __builtin_amdgcn_readfirstlane(s_seq_of_rank[blockIdx.y]);
-        T = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_T_of_rank[blockIdx.y])));
-    } else {
-        T = p.temperature[b];
-    }
-    const int32_t *parent = p.parent;
-    if (p.per_seq) {
-        qr = p.q_row[(size_t)b * (1 + N) + row];
-        parent += (size_t)b * N;
-    }
-
-    // The two logit rows are requested first; the bookkeeping below (children list, flags)
-    // runs while they are in flight.  A row has a draft row iff q_row says so; whether it
-    // also has children is checked afterwards (a mismatch is flagged, the row then counts
-    // as a leaf and the extra row that was fetched is ignored).
-    const size_t rix = (size_t)b * (1 + N) + row;
-    const float *zp_row = p.target_logits + rix * (size_t)V;
-    const float NaN = __int_as_float(0x7fc00000);
-    const bool naive = (p.variant == MCSD_NAIVE);      // the draft row is not needed: candidates are only compared
-    const bool have_q = (qr >= 0 && qr < p.P) && (T != 0.f) && !naive;
-    const float *zq_row = have_q ? p.draft_logits + ((size_t)b * p.P + qr) * (size_t)V : zp_row;
-
-    // children of this row, ascending node id = sampling order
-    if (t < 128) {
-        bool f = (t < N) && (parent[t] == row - 1);
-        unsigned long long m = __ballot(f);
-        if (lane == 0) s_mask[wave] = m;
-    }
-    if (t == 0) s_flags = 0u;
-    __syncthreads();
-    if (t == 0) {
-        int k = 0;
-        for (int w = 0; w < 2; ++w) {
-            unsigned long long m = s_mask[w];
-            while (m) {
-                s_kids[k++] = w * 64 + (__ffsll((long long)m) - 1);
-                m &= m - 1;
-            }
-        }
-        s_k = k;
-    }
-    __syncthreads();
-    int k = s_k;
-    if (k > 0 && (qr < 0 || qr >= p.P)) {
-        // a row with children needs a draft row; a bad map is reported, never dereferenced
-        k = 0;
-        if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_BAD_TREE);
-    }
-
-    if (T == 0.f) {
-        // argmax sampling: lowest id on ties; the row is streamed, nothing is kept.  Thread c
-        // fetches the token of child c first, so that the comparison after the scan does not
-        // wait for memory.
-        const int my_tok = (t < k) ? p.cand_tok[(size_t)b * N + s_kids[t]] : -1;
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-        stream_row<ITEMS, VT, ALIGNED, true, 16, false>(row_resource(zp_row, V), V, [&](int i, const float4 &z) {
-            // A thread meets its elements in ascending token order and the row is padded with
-            // -inf past V: a strict comparison keeps the first of equal values, and no bounds
-            // check is needed.
-            const int e = 4 * (t + VT * i);
-            const float v[4] = {z.x, z.y, z.z, z.w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (v[c] > bv) { bv = v[c]; bi = e + c; }
-        });
-        wave_argmax(bv, bi);
-        if (lane == 0) { s_bestv[wave] = bv; s_besti[wave] = bi; }
-        if (t == 0) s_int[0] = 0x7fffffff;
-        __syncthreads();
-        bv = s_bestv[0]; bi = s_besti[0];
-        for (int w = 1; w < NWAVES; ++w)
-            if (s_bestv[w] > bv || (s_bestv[w] == bv && s_besti[w] < bi)) { bv = s_bestv[w]; bi = s_besti[w]; }
-        if (bi == 0x7fffffff) bi = 0;
-        // the first child (ascending node id) that proposed the argmax is accepted
-        if (t < k && my_tok == bi) atomicMin(&s_int[0], t);
-        if (t < k && (my_tok < 0 || my_tok >= V)) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_BAD_TOKEN);
-        __syncthreads();
-        if (t == 0) {
-            const int c = s_int[0];
-            const int acc = (c < k) ? s_kids[c] : -1;
-            p.acc_child[rix] = acc;
-            p.endpoint[rix] = acc < 0 ? bi : -1;
-            p.flags[rix] = s_flags;
-        }
-        if (p.ratio && t < k) p.ratio[(size_t)b * N + s_kids[t]] = NaN;
-        if (p.residual_out) {
-            float *dst = p.residual_out + rix * (size_t)V;
-            for (int e = t; e < V; e += VT) dst[e] = (e == bi) ? 1.f : 0.f;
-        }
+    if (B == 1 || B > 512) {
+        *seq = y;
+        *T = temperature[y];
         return;
     }
-
-    // first trip over the draft row (from HBM): its maximum
-    float mq = -INFINITY;
-    const __amdgpu_buffer_rsrc_t rs_q = row_resource(zq_row, V);
-    if (have_q)
-        stream_row<ITEMS, VT, ALIGNED, false, 16, false>(rs_q, V, [&](int, const float4 &z) { mq = max3_raw(max3_raw(mq, z.x, z.y), z.z, z.w); });
-    // the target row: read exactly once by this workgroup (non-temporal: it does not displace
-    // anything in L2), resident from here on.  Requested behind the draft row's first trip, so
-    // that its registers are not tied up while that trip runs; it arrives during the bookkeeping
-    // below, and the other workgroup of the compute unit computes meanwhile.
-    float4 a[ITEMS];
-    {
-        const __amdgpu_buffer_rsrc_t rs_p = row_resource(zp_row, V);
+    auto pick = [&](unsigned long long m, int n, float t, int base) {      // n-th set bit of m
+        const bool here = ((m >> lane) & 1ull) && __popcll(m & ((1ull << lane) - 1ull)) == n;
+        const int l = __ffsll((long long)__ballot(here)) - 1;
+        *seq = base + l;
+        *T = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), l));
+    };
+    if (B <= 64) {
+        const float t = (lane < B) ? temperature[lane] : 0.f;
+        const unsigned long long in = B < 64 ? (1ull << B) - 1ull : ~0ull, sampled = __ballot(t != 0.f) & in;
+        const int total = __popcll(sampled);
+        if (y < total) pick(sampled, y, t, 0);
+        else pick(in & ~sampled, y - total, t, 0);
+        return;
+    }
+    float t[8];
+    int total = 0;
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) a[i] = load_row_piece<VT, ALIGNED, true>(rs_p, i, V, t);
-    }
-
-    // Thread c follows candidate c: its token, its uniform and the two logits of that token are
-    // requested now, so that the first accept decision does not wait for three dependent trips
-    // to memory after the exponentials.
-    int my_tok = -1;
-    float my_u = 0.f, my_zp = 0.f, my_zq = 0.f;
-    if (k > 0 && !naive && t < k) {
-        const int node = s_kids[t];
-        my_tok = p.cand_tok[(size_t)b * N + node];
-        my_u = p.u_accept[(size_t)b * N + node];
-        if (my_tok >= 0 && my_tok < V) {
-            my_zp = zp_row[my_tok];
-            my_zq = zq_row[my_tok];
-        }
-    }
-    const float invT = 1.0f / T;
-    const float c2 = invT * LOG2E_F;
-    float mp = row_max<ITEMS>(a);
-    block_max2<NWAVES>(mp, mq, s_redf, s_redf2);
-    double A = row_exp<ITEMS>(a, mp, c2);                 // a = e_p, A = Z_p
-    double Zq0 = 0.0;
-    if (k > 0 && !naive)                                   // second trip over the draft row: sum of e_q
-        stream_row<ITEMS, VT, ALIGNED, false, PASS_CHUNK, PASS_DOUBLE>(rs_q, V, [&](int, const float4 &z) { Zq0 += sum4(exp_weights(z, mq, c2)); });
-    block_sum2<NWAVES>(A, Zq0, s_red, s_red2);
-    if (!(A > 0.0) || !isfinite(A) || (k > 0 && !naive && (!(Zq0 > 0.0) || !isfinite(Zq0)))) {
-        if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_NONFINITE);
-    }
-
-    int accepted = -1;
-    if (k > 0 && !naive) {
-        // fp64 track of the candidate tokens: thread c follows candidate c
-        double my_a = 0.0, my_q = 0.0;
-        float my_q32 = 0.f;                 // e_q of the token with the rounding of the vector passes
-        if (t < k && my_tok >= 0 && my_tok < V) {
-            // same constants as the vector pass (float c2), evaluated exactly
-            my_a = exp2_neg(((double)my_zp - (double)mp) * (double)c2);
-            my_q = exp2_neg(((double)my_zq - (double)mq) * (double)c2);
-            my_q32 = __builtin_amdgcn_exp2f((my_zq - mq) * c2);
-        }
-        // Z_q: mass of the draft tokens not yet removed.  A removal takes away exactly the fp32
-        // weight that the sum over the row contained for that token (the same instructions on
-        // the same logit give the same bits), so the difference keeps its relative accuracy
-        // even when most of the mass has been removed.
-        double Zq = Zq0;
-
-        for (int i = 0; i < k; ++i) {
-            if (t == i) {
-                const VerifyParams pl = reload_params();
-                double ratio;
-                uint32_t fl = 0u;
-                const bool valid = (my_tok >= 0 && my_tok < V);
-                if (!valid) {
-                    ratio = 0.0;
-                    fl |= MCSD_FLAG_BAD_TOKEN;
-                } else if (my_q > 0.0) {
-                    ratio = (my_a * Zq) / (A * my_q);
-                    if (!(ratio < 1.0)) ratio = 1.0;
-                } else {
-                    ratio = my_a > 0.0 ? 1.0 : 0.0;
-                    fl |= MCSD_FLAG_ZERO_DRAFT_PROB;
-                }
-                const double u = (double)my_u;
-                // (a token of probability zero - a duplicate of a rejected one, Sec. 3.2 - is never
-                // accepted, also not by a uniform of exactly 0 from outside the open interval)
-                const bool acc = (ratio > 0.0) && (u <= ratio);
-                if (fabs(u - ratio) < (double)pl.eps) fl |= MCSD_FLAG_NEAR_TIE_ACCEPT;
-                if (fl) atomicOr(&s_flags, fl);
-                if (pl.ratio) pl.ratio[(size_t)b * N + s_kids[i]] = (float)ratio;
-                s_accept = acc ? 1 : 0;
-                const bool remove = (!acc) && valid && (pl.variant == MCSD_WITHOUT_REPLACEMENT);
-                s_xrem = remove ? my_tok : -1;
-                s_qrem = remove ? my_q32 : 0.f;
-            }
-            __syncthreads();
-            if (s_accept) {
-                accepted = i;
-                break;
-            }
-            // rejected: a := max(0, a - beta e_q) with beta = A / Z_q in fp64, applied as a
-            // two-term float product so that no common rounding of beta biases the sum
-            const double beta = (Zq > 0.0) ? A / Zq : 0.0;   // nothing left in q: the residual is p itself
-            const int xrem = s_xrem;
-            const double Zq_new = Zq - (double)s_qrem;
-            const float bh = (float)beta;
-            const float bl = (float)(beta - (double)bh);
-            double part = 0.0;
-            // one more trip over the draft row for e_q
-            stream_row<ITEMS, VT, ALIGNED, false, PASS_CHUNK, PASS_DOUBLE>(rs_q, V, [&](int j, const float4 &z) {
-                const float4 e = exp_weights(z, mq, c2);
-                a[j].x = fmaxf(0.f, fmaf(-bl, e.x, fmaf(-bh, e.x, a[j].x)));
-                a[j].y = fmaxf(0.f, fmaf(-bl, e.y, fmaf(-bh, e.y, a[j].y)));
-                a[j].z = fmaxf(0.f, fmaf(-bl, e.z, fmaf(-bh, e.z, a[j].z)));
-                a[j].w = fmaxf(0.f, fmaf(-bl, e.w, fmaf(-bh, e.w, a[j].w)));
-                part += sum4(a[j]);
-            });
-            const double my_a_new = fmax(0.0, my_a - beta * my_q);
-            if (t < k && xrem >= 0 && my_tok == xrem) { my_q = 0.0; my_q32 = 0.f; }
-            const double A_new = block_sum<NWAVES>(part, s_red);     // barriers inside also order the reuse of s_accept / s_xrem / s_qrem
-            Zq = Zq_new;
-            if (A_new > 0.0) {
-                A = A_new;
-                my_a = my_a_new;
-            } else {
-                // max(0, p - q) vanished everywhere, which a rejection excludes in exact arithmetic
-                // (it needs p = q) and rounding or a bad candidate can produce: p stays as it
-                // was.  With every a(x) <= beta e_q(x) and equal sums, the old a is beta e_q.
-                if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_ZERO_RESIDUAL);
-                stream_row<ITEMS, VT, ALIGNED, false, PASS_CHUNK, PASS_DOUBLE>(rs_q, V, [&](int j, const float4 &z) {
-                    const float4 e = exp_weights(z, mq, c2);
-                    a[j] = make_float4(fmaf(bl, e.x, bh * e.x), fmaf(bl, e.y, bh * e.y), fmaf(bl, e.z, bh * e.z), fmaf(bl, e.w, bh * e.w));
-                });
-            }
-        }
-        // candidates after the accepted one were never tested
-        const VerifyParams pl = reload_params();
-        if (pl.ratio && accepted >= 0 && t > accepted && t < k) pl.ratio[(size_t)b * N + s_kids[t]] = NaN;
-    }
-
-    const VerifyParams pe = reload_params();
-    int endpoint = -1;
-    if (accepted < 0) {
-        const double u = (double)pe.u_endpoint[rix];
-        endpoint = inverse_cdf<ITEMS, VT>(a, A, u, (double)pe.eps, s_red, s_seg, s_int, &s_flags);
-        if (endpoint < 0 || endpoint >= V) endpoint = V - 1;
-    }
-    if (naive && k > 0) {
-        // multi-candidate naive sampling (the comparison rule of the ablation, Sec. 4.5): the
-        // token just drawn from p is kept; a candidate equal to it is accepted, the first such
-        if (t == 0) {
-            int acc = -1;
-            uint32_t fl = 0u;
-            for (int i = 0; i < k; ++i) {
-                const int tok = pe.cand_tok[(size_t)b * N + s_kids[i]];
-                if (tok < 0 || tok >= V) fl |= MCSD_FLAG_BAD_TOKEN;
-                else if (acc < 0 && tok == endpoint) acc = i;
-            }
-            if (fl) atomicOr(&s_flags, fl);
-            s_accept = acc;
-        }
-        if (pe.ratio && t < k) pe.ratio[(size_t)b * N + s_kids[t]] = NaN;
-        __syncthreads();
-        accepted = s_accept;
-        if (accepted >= 0) endpoint = -1;
-    }
-    if (pe.residual_out) {
-        const float inv = (A > 0.0) ? (float)(1.0 / A) : 0.f;
-        store_residual<ITEMS, VT, ALIGNED>(pe.residual_out + rix * (size_t)V, V, a, inv);
-    }
-    __syncthreads();
-    if (t == 0) {
-        pe.acc_child[rix] = accepted >= 0 ? s_kids[accepted] : -1;
-        pe.endpoint[rix] = endpoint;
-        pe.flags[rix] = s_flags;
+    for (int c = 0; c < 8; ++c) t[c] = (64 * c + lane < B) ? temperature[64 * c + lane] : 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) total += __popcll(__ballot(t[c] != 0.f));
+    const bool want_sampled = y < total;
+    int n = want_sampled ? y : y - total;
+    *seq = 0;
+    *T = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const int left = B - 64 * c;
+        const unsigned long long in = left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
+        const unsigned long long sampled = __ballot(t[c] != 0.f), m = want_sampled ? sampled : (in & ~sampled);
+        const int have = __popcll(m);
+        if (n >= 0 && n < have) pick(m, n, t[c], 64 * c);
+        n -= have;
     }
 }
 
-// ---------------------------------------------------------------- both rows resident
-// Vocabularies up to 32768: one workgroup per tree row, both logit rows of the row in registers
-// for all rounds (1024 threads up to 16384 tokens, 512 threads with twice the registers beyond).
-template <int ITEMS, int VT, bool ALIGNED>
-__global__ __launch_bounds__(VT) void verify_rows_kernel(VerifyParams p)
+// One workgroup per tree row.  Both logit rows are read from HBM once and stay on the compute unit
+// for all rounds: the target row in registers (as the unnormalised residual a), the draft row (as
+// e_q) in registers up to item ITEMS - LQ and in LDS beyond.  LQ is chosen so that two workgroups
+// share a compute unit (256 registers per thread, 80 KB of LDS each), one loading while the other
+// computes: the two row pairs of 32000 tokens are 512 KB, as much as all registers of the unit.
+//
+// Bound: HBM in a batch (16 sequences of 61 rows, 8 of them argmax: 171 MB in 33.5 us = 5.1 TB/s;
+// 42.5 us with one workgroup per unit), the vector units of one CU for a single sequence (four
+// rejections: 4 us until the rows are there, 3.7 us maxima, exponentials and sums, 1.9 us per
+// rejection, of which fp64 conversions and additions are half, 2.3 us endpoint).
+// 50001 tokens, 6 sequences of 29 rows: 30.5 us; 90 us when the draft row was streamed again for every
+// pass.
+template <int ITEMS, int VT, int LQ, int FULL, int WGS, bool ALIGNED>
+__global__ __launch_bounds__(VT) __attribute__((amdgpu_waves_per_eu(WGS * VT / 256)))
+void verify_rows_kernel(VerifyParams p)
 {
-    constexpr int NWAVES = VT / 64;
+    constexpr int NWAVES = VT / 64, RQ = ITEMS - LQ;
+    using Row = Pieces<ITEMS, VT>;
     const int row = blockIdx.x;
-    int b = blockIdx.y;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int N = p.N, V = p.V;
 
-    __shared__ double s_red[NWAVES];
-    __shared__ double s_red2[NWAVES];
-    __shared__ double s_seg[4 * NWAVES * ITEMS + ITEMS];
-    __shared__ float s_redf[NWAVES];
-    __shared__ float s_redf2[NWAVES];
-    __shared__ unsigned long long s_mask[2];
-    __shared__ int s_kids[MCSD_MAX_NODES];
-    __shared__ int s_k;
-    __shared__ int s_int[4];
-    __shared__ uint32_t s_flags;
-    __shared__ int s_accept;       // decision of the current round
-    __shared__ int s_xrem;         // token removed from q after a rejection (-1: none)
-    __shared__ float s_bestv[NWAVES];
+    __shared__ float4 s_q[LQ ? LQ * VT : 1];            // [item - RQ][thread]: every thread reads only what is its own
+    __shared__ double s_piece[4 * (ITEMS < 4 ? 4 : ITEMS) * NWAVES];
+    __shared__ double s_sum[2][2][NWAVES];
+    __shared__ float s_max[2][NWAVES];
     __shared__ int s_besti[NWAVES];
+    __shared__ int s_tok[MCSD_MAX_NODES];
+    __shared__ uint8_t s_kid[MCSD_MAX_NODES];
+    __shared__ float s_u[MCSD_MAX_NODES], s_q32[MCSD_MAX_NODES];
+    __shared__ double s_pa[MCSD_MAX_NODES], s_qa[MCSD_MAX_NODES];       // the logits of the candidates, then e_p and e_q in fp64
+    double *s_beta = s_piece;                           // of the first 64 rejections (the pieces come last)
+    __shared__ Drawn s_drawn;
 
-    // Workgroups start in the order y, x.  A sampled sequence costs a workgroup about three
-    // times what an argmax sequence costs (two rows, exponentials, k dependent rounds against
-    // one row and an argmax), so the sampled sequences are handed out first and the cheap ones
-    // fill the end of the launch: sequence number y in dispatch order is the y-th sampled
-    // sequence, then the argmax ones in their own order.  Done when B fits the workgroup.
-    __shared__ int s_cnt[NWAVES];
-    __shared__ int s_seq_of_rank[VT];
-    __shared__ float s_T_of_rank[VT];
-    // requested now, used after the ranking: the draft-row address needs it (with one tree per
-    // sequence the map is that sequence's and can only be read once the sequence is known)
-    int qr = p.per_seq ? -1 : p.q_row[row];
-    float T = 1.f;
-    const bool ranked = p.B > 1 && p.B <= VT;
-    if (p.B > 1 && p.B <= 64) {
-        // one wavefront ranks up to 64 sequences by itself: one load, one ballot, one barrier
-        if (wave == 0) {
-            const float Tt = (lane < p.B) ? p.temperature[lane] : 1.f;
-            const bool sampled = (lane < p.B) && (Tt != 0.f);
-            const unsigned long long m = __ballot(sampled);
-            const int total = __popcll(m);
-            const int idx_s = __popcll(m & ((1ull << lane) - 1ull));    // sampled sequences before this one
-            if (lane < p.B) {
-                const int r = sampled ? idx_s : total + (lane - idx_s);
-                s_seq_of_rank[r] = lane;
-                s_T_of_rank[r] = Tt;
-            }
-        }
-        __syncthreads();
-    } else if (ranked) {
-        const float Tt = (t < p.B) ? p.temperature[t] : 1.f;
-        const bool sampled = (t < p.B) && (Tt != 0.f);
-        const unsigned long long m = __ballot(sampled);
-        if (lane == 0) s_cnt[wave] = __popcll(m);
-        __syncthreads();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) {
-            const int c = s_cnt[w];
-            before += (w < wave) ? c : 0;
-            total += c;
-        }
-        const int idx_s = before + __popcll(m & ((1ull << lane) - 1ull));   // sampled sequences before this one
-        if (t < p.B) {
-            const int r = sampled ? idx_s : total + (t - idx_s);
-            s_seq_of_rank[r] = t;
-            s_T_of_rank[r] = Tt;
-        }
-        __syncthreads();
-    }
-    if (ranked) {
-        // back to wave-uniform values (they come out of LDS): addresses and branches stay scalar,
-        // and the temperature does not take a second trip to memory
-        b = __builtin_amdgcn_readfirstlane(s_seq_of_rank[blockIdx.y]);
-        T = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_T_of_rank[blockIdx.y])));
-    } else {
-        T = p.temperature[b];
-    }
-    const int32_t *parent = p.parent;
-    if (p.per_seq) {
-        qr = p.q_row[(size_t)b * (1 + N) + row];
-        parent += (size_t)b * N;
-    }
-
-    // The two logit rows are requested first; the bookkeeping below (children list, flags)
-    // runs while they are in flight.  A row has a draft row iff q_row says so; whether it
-    // also has children is checked afterwards (a mismatch is flagged, the row then counts
-    // as a leaf and the extra row that was fetched is ignored).
+    int b;
+    float T_of_b;
+    ranked_sequence(p.temperature, p.B, blockIdx.y, lane, &b, &T_of_b);
+    const int qr_of_row = p.q_row[(p.per_seq ? (size_t)b * (1 + N) : 0) + row];
+    const int32_t *parent = p.parent + (p.per_seq ? (size_t)b * N : 0);
     const size_t rix = (size_t)b * (1 + N) + row;
     const float *zp_row = p.target_logits + rix * (size_t)V;
-    const float NaN = __int_as_float(0x7fc00000);
-    float4 a[ITEMS];
-    {
-        const __amdgpu_buffer_rsrc_t rs_p = row_resource(zp_row, V);
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) a[i] = load_row_piece<VT, ALIGNED, true>(rs_p, i, V, t);
-    }
     const bool naive = (p.variant == MCSD_NAIVE);      // the draft row is not needed: candidates are only compared
+    const float NaN = __int_as_float(0x7fc00000);
+
+    // Requested ahead of the rows (memory answers in order): the parent array, by every wavefront for
+    // itself, and by wavefront 0 the candidates; lane = node here.
+    const int pa0 = lane < N ? parent[lane] : -2, pa1 = 64 + lane < N ? parent[64 + lane] : -2;
+    int tok0 = -1, tok1 = -1;
+    if (wave == 0) {
+        if (lane < N) tok0 = p.cand_tok[(size_t)b * N + lane];
+        if (64 + lane < N) tok1 = p.cand_tok[(size_t)b * N + 64 + lane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // A row has a draft row iff q_row says so; whether it also has children is known a little later
+    // (a mismatch is flagged, the row then counts as a leaf and the extra row is ignored).
+    const int V4 = V & ~3;
+    float4 a[ITEMS], eq[RQ];
+    float4 tail_p, tail_q;
+    request_pieces<ITEMS, VT, ALIGNED>(zp_row, V, t, a, tail_p);
+    // (as scalars: the branches on them below are then scalar too)
+    const float T = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(T_of_b)));
+    const int qr = __builtin_amdgcn_readfirstlane(qr_of_row);
     const bool have_q = (qr >= 0 && qr < p.P) && (T != 0.f) && !naive;
     const float *zq_row = have_q ? p.draft_logits + ((size_t)b * p.P + qr) * (size_t)V : zp_row;
-    float4 eq[ITEMS];
     if (have_q) {
-        const __amdgpu_buffer_rsrc_t rs_q = row_resource(zq_row, V);
+        request_pieces<RQ, VT, ALIGNED>(zq_row, V, t, eq, tail_q);
+        if (LQ) {
+            // straight into LDS (16 bytes per lane, consecutive): no registers while in flight
+            const __amdgpu_buffer_rsrc_t rs = row_resource(zq_row, ALIGNED ? V : V4);
+            typedef __attribute__((address_space(3))) void *lds_ptr;
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) eq[i] = load_row_piece<VT, ALIGNED, true>(rs_q, i, V, t);
-    } else {
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) eq[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            for (int i = 0; i < LQ; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(s_q + i * VT + 64 * wave), 16, t * 16, (RQ + i) * (VT * 16), 0, 2);
+        }
     }
 
-    // children of this row, ascending node id = sampling order
-    if (t < 128) {
-        bool f = (t < N) && (parent[t] == row - 1);
-        unsigned long long m = __ballot(f);
-        if (lane == 0) s_mask[wave] = m;
-    }
-    if (t == 0) s_flags = 0u;
-    __syncthreads();
-    if (t == 0) {
-        int k = 0;
-        for (int w = 0; w < 2; ++w) {
-            unsigned long long m = s_mask[w];
-            while (m) {
-                s_kids[k++] = w * 64 + (__ffsll((long long)m) - 1);
-                m &= m - 1;
-            }
-        }
-        s_k = k;
-    }
-    __syncthreads();
-    int k = s_k;
+    const bool f0 = pa0 == row - 1, f1 = pa1 == row - 1;
+    const Kids kids = {__ballot(f0), __ballot(f1)};
+    uint32_t fl = 0u;
+    int k = kids.count();
     if (k > 0 && (qr < 0 || qr >= p.P)) {
         // a row with children needs a draft row; a bad map is reported, never dereferenced
         k = 0;
-        if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_BAD_TREE);
+        fl = (uint32_t)MCSD_FLAG_BAD_TREE;
     }
+    if (wave == 0 && k > 0 && T != 0.f) {
+        // candidate c (rank among the children) of the row: node, token, uniform and the two logits
+        // (naive sampling reads neither draft logits nor u_accept)
+        const bool v0 = f0 && tok0 >= 0 && tok0 < V && !naive, v1 = f1 && tok1 >= 0 && tok1 < V && !naive;
+        const float u0 = (f0 && !naive) ? p.u_accept[(size_t)b * N + lane] : 0.f;
+        const float u1 = (f1 && !naive) ? p.u_accept[(size_t)b * N + 64 + lane] : 0.f;
+        const float p0 = v0 ? zp_row[tok0] : 0.f, q0 = v0 ? zq_row[tok0] : 0.f;
+        const float p1 = v1 ? zp_row[tok1] : 0.f, q1 = v1 ? zq_row[tok1] : 0.f;
+        if (f0) { const int c = kids.rank0(lane); s_kid[c] = lane; s_tok[c] = tok0; s_u[c] = u0; s_pa[c] = p0; s_qa[c] = q0; }
+        if (f1) { const int c = kids.rank1(lane); s_kid[c] = 64 + lane; s_tok[c] = tok1; s_u[c] = u1; s_pa[c] = p1; s_qa[c] = q1; }
+    }
+    settle_pieces<ITEMS, VT, FULL, ALIGNED>(V, t, a, tail_p);
 
     if (T == 0.f) {
-        // argmax sampling: lowest id on ties.  Thread c fetches the token of child c now, so that
-        // the comparison after the scan does not wait for memory.
-        const int my_tok = (t < k) ? p.cand_tok[(size_t)b * N + s_kids[t]] : -1;
+        // argmax sampling: lowest id on ties.  Ascending token order: a strict comparison keeps the
+        // first of equal values; elements are named by their number in the thread (an inline constant).
         float bv = -INFINITY;
-        int bi = 0x7fffffff;
+        int bc = -1;
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            // A thread meets its elements in ascending token order and the row was padded with
-            // -inf past V when it was loaded: a strict comparison keeps the first of equal
-            // values, and no bounds check is needed.
-            const int e = 4 * (t + VT * i);
-            const float v[4] = {a[i].x, a[i].y, a[i].z, a[i].w};
+        for (int j = 0; j < ITEMS; ++j) {
+            const float v[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (v[c] > bv) { bv = v[c]; bi = e + c; }
+                if (v[c] > bv) { bv = v[c]; bc = 4 * j + c; }
         }
+        int bi = bc >= 0 ? 4 * (t + VT * (bc >> 2)) + (bc & 3) : 0x7fffffff;
         wave_argmax(bv, bi);
-        if (lane == 0) { s_bestv[wave] = bv; s_besti[wave] = bi; }
-        if (t == 0) s_int[0] = 0x7fffffff;
+        if (lane == 0) { s_max[0][wave] = bv; s_besti[wave] = bi; }
         __syncthreads();
-        bv = s_bestv[0]; bi = s_besti[0];
-        for (int w = 1; w < NWAVES; ++w)
-            if (s_bestv[w] > bv || (s_bestv[w] == bv && s_besti[w] < bi)) { bv = s_bestv[w]; bi = s_besti[w]; }
-        if (bi == 0x7fffffff) bi = 0;
-        // the first child (ascending node id) that proposed the argmax is accepted
-        if (t < k && my_tok == bi) atomicMin(&s_int[0], t);
-        if (t < k && (my_tok < 0 || my_tok >= V)) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_BAD_TOKEN);
-        __syncthreads();
-        if (t == 0) {
-            const int c = s_int[0];
-            const int acc = (c < k) ? s_kids[c] : -1;
-            p.acc_child[rix] = acc;
-            p.endpoint[rix] = acc < 0 ? bi : -1;
-            p.flags[rix] = s_flags;
+        bv = s_max[0][0]; bi = s_besti[0];
+#pragma unroll
+        for (int w = 1; w < NWAVES; ++w) {
+            const float ov = s_max[0][w];
+            const int oi = s_besti[w];
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
         }
-        if (p.ratio && t < k) p.ratio[(size_t)b * N + s_kids[t]] = NaN;
+        if (bi == 0x7fffffff) bi = 0;
+        if (wave == 0) {
+            // the first child (ascending node id) that proposed the argmax is accepted
+            const bool c0 = k > 0 && f0, c1 = k > 0 && f1;
+            const unsigned long long m0 = __ballot(c0 && tok0 == bi), m1 = __ballot(c1 && tok1 == bi);
+            if (__ballot((c0 && (tok0 < 0 || tok0 >= V)) || (c1 && (tok1 < 0 || tok1 >= V)))) fl |= (uint32_t)MCSD_FLAG_BAD_TOKEN;
+            const int acc = m0 ? __ffsll((long long)m0) - 1 : (m1 ? 63 + __ffsll((long long)m1) : -1);
+            if (lane == 0) {
+                p.acc_child[rix] = acc;
+                p.endpoint[rix] = acc < 0 ? bi : -1;
+                p.flags[rix] = fl;
+            }
+            if (p.ratio) {
+                if (c0) p.ratio[(size_t)b * N + lane] = NaN;
+                if (c1) p.ratio[(size_t)b * N + 64 + lane] = NaN;
+            }
+        }
         if (p.residual_out) {
             float *dst = p.residual_out + rix * (size_t)V;
             for (int e = t; e < V; e += VT) dst[e] = (e == bi) ? 1.f : 0.f;
         }
-        return;
     }
-
-    // Thread c follows candidate c: its token, its uniform and the two logits of that token are
-    // requested now, so that the first accept decision does not wait for three dependent trips
-    // to memory after the exponentials.
-    int my_tok = -1;
-    float my_u = 0.f, my_zp = 0.f, my_zq = 0.f;
-    if (k > 0 && !naive && t < k) {
-        const int node = s_kids[t];
-        my_tok = p.cand_tok[(size_t)b * N + node];
-        my_u = p.u_accept[(size_t)b * N + node];
-        if (my_tok >= 0 && my_tok < V) {
-            my_zp = zp_row[my_tok];
-            my_zq = zq_row[my_tok];
-        }
-    }
-    const float invT = 1.0f / T;
-    const float c2 = invT * LOG2E_F;
-    float mp = row_max<ITEMS>(a), mq = row_max<ITEMS>(eq);
-    block_max2<NWAVES>(mp, mq, s_redf, s_redf2);
-    double A = row_exp<ITEMS>(a, mp, c2);                 // a = e_p, A = Z_p
-    double Zq0 = (k > 0 && !naive) ? row_exp<ITEMS>(eq, mq, c2) : 0.0;
-    block_sum2<NWAVES>(A, Zq0, s_red, s_red2);
-    if (!(A > 0.0) || !isfinite(A) || (k > 0 && !naive && (!(Zq0 > 0.0) || !isfinite(Zq0)))) {
-        if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_NONFINITE);
-    }
-
-    int accepted = -1;
-    if (k > 0 && !naive) {
-        // fp64 track of the candidate tokens: thread c follows candidate c
-        double my_a = 0.0, my_q = 0.0;
-        if (t < k && my_tok >= 0 && my_tok < V) {
-            // same constants as the vector pass (float c2), evaluated exactly
-            my_a = exp2_neg(((double)my_zp - (double)mp) * (double)c2);
-            my_q = exp2_neg(((double)my_zq - (double)mq) * (double)c2);
-        }
-        // Z_q: mass of the draft tokens not yet removed.  After a removal it is summed
-        // again over the resident row rather than updated by subtraction, so that it
-        // keeps its relative accuracy when most of the mass has been removed.
-        double Zq = Zq0;
-
-        for (int i = 0; i < k; ++i) {
-            if (t == i) {
-                double ratio;
-                uint32_t fl = 0u;
-                const bool valid = (my_tok >= 0 && my_tok < V);
-                if (!valid) {
-                    ratio = 0.0;
-                    fl |= MCSD_FLAG_BAD_TOKEN;
-                } else if (my_q > 0.0) {
-                    ratio = (my_a * Zq) / (A * my_q);
-                    if (!(ratio < 1.0)) ratio = 1.0;
-                } else {
-                    ratio = my_a > 0.0 ? 1.0 : 0.0;
-                    fl |= MCSD_FLAG_ZERO_DRAFT_PROB;
+    // (no return above: with one, the compiler keeps what the other path needs alive beside this one)
+    if (T != 0.f) {
+        const float c2 = (1.0f / T) * LOG2E_F;
+        const bool rounds = k > 0 && !naive;            // (then there is a draft row)
+        float mp = row_max<ITEMS>(a), mq = -INFINITY;
+        if (rounds) {
+            settle_pieces<RQ, VT, (FULL < RQ ? FULL : RQ), ALIGNED>(V, t, eq, tail_q);
+            mq = row_max<RQ>(eq);
+            if (LQ) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the part in LDS has arrived
+#pragma unroll
+                for (int i = 0; i < LQ; ++i) {
+                    if (RQ + i >= FULL && 4 * VT * (RQ + i + 1) > V4) {  // uniform: the item that reaches past the row, and those behind it
+                        const int e = 4 * (t + VT * (RQ + i));
+                        if (e >= V4) s_q[i * VT + t] = (!ALIGNED && e == V4) ? tail_q : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                    }
+                    const float4 z = s_q[i * VT + t];
+                    mq = max3_raw(max3_raw(mq, z.x, z.y), z.z, z.w);
                 }
-                const double u = (double)my_u;
-                // (a token of probability zero - a duplicate of a rejected one, Sec. 3.2 - is never
-                // accepted, also not by a uniform of exactly 0 from outside the open interval)
-                const bool acc = (ratio > 0.0) && (u <= ratio);
-                if (fabs(u - ratio) < (double)p.eps) fl |= MCSD_FLAG_NEAR_TIE_ACCEPT;
-                if (fl) atomicOr(&s_flags, fl);
-                if (p.ratio) p.ratio[(size_t)b * N + s_kids[i]] = (float)ratio;
-                s_accept = acc ? 1 : 0;
-                const bool remove = (!acc) && valid && (p.variant == MCSD_WITHOUT_REPLACEMENT);
-                s_xrem = remove ? my_tok : -1;
             }
+        }
+        mp = wave_max(mp);
+        mq = wave_max(mq);
+        if (lane == 63) { s_max[0][wave] = mp; s_max[1][wave] = mq; }
+        __syncthreads();
+        mp = s_max[0][0]; mq = s_max[1][0];
+#pragma unroll
+        for (int w = 1; w < NWAVES; ++w) { mp = fmaxf(mp, s_max[0][w]); mq = fmaxf(mq, s_max[1][w]); }
+        mp = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mp)));
+        mq = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mq)));
+
+        if (rounds && wave < 2) {
+            // e_p and e_q of the candidates in fp64, with the constants of the vector pass (float c2)
+            // evaluated exactly; s_q32: e_q with the rounding of the vector passes
+            const int c = 64 * wave + lane;
+            if (c < k) {
+                const double zp = s_pa[c], zq = s_qa[c];
+                s_pa[c] = exp2_neg((zp - (double)mp) * (double)c2);
+                s_qa[c] = exp2_neg((zq - (double)mq) * (double)c2);
+                s_q32[c] = __builtin_amdgcn_exp2f(((float)zq - mq) * c2);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) a[i] = exp_weights(a[i], mp, c2);        // a = e_p
+        double A = 0.0, Zq = 0.0;
+        // the sums of a and e_q over the workgroup, as scalars; one barrier (slot: 0 or 1 in turn)
+        auto total = [&](double x, double y, int slot) __attribute__((always_inline)) {
+            x = wave_sum(x);
+            y = wave_sum(y);
+            if (lane == 63) { s_sum[slot][0][wave] = x; s_sum[slot][1][wave] = y; }
             __syncthreads();
-            if (s_accept) {
-                accepted = i;
-                break;
-            }
-            // rejected: a := max(0, a - beta e_q) with beta = A / Z_q in fp64, applied as a
-            // two-term float product so that no common rounding of beta biases the sum
-            const double beta = (Zq > 0.0) ? A / Zq : 0.0;   // nothing left in q: the residual is p itself
-            const int xrem = s_xrem;
-            const float bh = (float)beta;
-            const float bl = (float)(beta - (double)bh);
+            double sx = 0.0, sy = 0.0;
+#pragma unroll
+            for (int w = 0; w < NWAVES; ++w) { sx += s_sum[slot][0][w]; sy += s_sum[slot][1][w]; }
+            A = uniform(sx);
+            Zq = uniform(sy);
+        };
+        if (rounds) {
             double part = 0.0, partq = 0.0;
 #pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-                a[j].x = fmaxf(0.f, fmaf(-bl, eq[j].x, fmaf(-bh, eq[j].x, a[j].x)));
-                a[j].y = fmaxf(0.f, fmaf(-bl, eq[j].y, fmaf(-bh, eq[j].y, a[j].y)));
-                a[j].z = fmaxf(0.f, fmaf(-bl, eq[j].z, fmaf(-bh, eq[j].z, a[j].z)));
-                a[j].w = fmaxf(0.f, fmaf(-bl, eq[j].w, fmaf(-bh, eq[j].w, a[j].w)));
-                part += sum4(a[j]);
+            for (int i = 0; i < ITEMS; ++i) {
+                part += sum4(a[i]);
+                if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);     // (a few items at a time: more would not fit the registers)
             }
-            const double my_a_new = fmax(0.0, my_a - beta * my_q);
-            if (t < k && xrem >= 0 && my_tok == xrem) my_q = 0.0;
-            double A_new;
-            if (xrem >= 0) {
-                const int q4 = xrem >> 2;                 // float4 index of the removed token
-                if ((q4 & (VT - 1)) == t) {
-                    const int j = q4 / VT, c = xrem & 3;
 #pragma unroll
-                    for (int jj = 0; jj < ITEMS; ++jj)
-                        if (jj == j) {
-                            if (c == 0) eq[jj].x = 0.f;
-                            if (c == 1) eq[jj].y = 0.f;
-                            if (c == 2) eq[jj].z = 0.f;
-                            if (c == 3) eq[jj].w = 0.f;
+            for (int i = 0; i < RQ; ++i) {
+                eq[i] = exp_weights(eq[i], mq, c2);
+                partq += sum4(eq[i]);
+                if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < LQ; ++i) {
+                const float4 e = exp_weights(s_q[i * VT + t], mq, c2);
+                s_q[i * VT + t] = e;
+                partq += sum4(e);
+                if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            total(part, partq, 0);
+            if (!(A > 0.0) || !isfinite(A) || !(Zq > 0.0) || !isfinite(Zq)) fl |= (uint32_t)MCSD_FLAG_NONFINITE;
+        }
+
+        int accepted = -1;
+        if (rounds) {
+            // Lane c of every wavefront follows candidate c in fp64 (in blocks of 64 candidates), so that
+            // all of them take the same decisions without a barrier; a round costs the one of its sum.
+            int my_tok = -1;
+            double my_a = 0.0, my_q = 0.0;
+            float my_u = 0.f, my_q32 = 0.f;             // my_q32: e_q with the rounding of the vector passes
+            double z_base = Zq;
+            int buf = 1;
+            const bool removes = p.variant == MCSD_WITHOUT_REPLACEMENT;
+            int i = 0;
+            bool acc;
+            do {
+                if ((i & 63) == 0) {
+                    const int c = i + lane;
+                    my_tok = -1;
+                    my_a = my_q = 0.0;
+                    if (c < k) {
+                        my_tok = s_tok[c];
+                        my_u = s_u[c];
+                        if (my_tok >= 0 && my_tok < V) {
+                            my_a = s_pa[c];
+                            my_q = s_qa[c];
+                            my_q32 = s_q32[c];
+                            for (int j = 0; j < i; ++j) {       // the rejections before this block
+                                my_a = fmax(0.0, my_a - s_beta[j] * my_q);
+                                if (removes && s_tok[j] == my_tok) { my_q = 0.0; my_q32 = 0.f; }
+                            }
                         }
+                    }
+                    if (i > 0) __syncthreads();         // (this round may be the last and write the pieces)
                 }
+                const int tok = __builtin_amdgcn_readlane(my_tok, i & 63);
+                const double ai = readlane_d(my_a, i & 63), qi = readlane_d(my_q, i & 63);
+                const double u = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_u), i & 63));
+                const bool valid = tok >= 0 && tok < V;
+                double ratio;
+                if (!valid) {
+                    ratio = 0.0;
+                    fl |= (uint32_t)MCSD_FLAG_BAD_TOKEN;
+                } else if (qi > 0.0) {
+                    ratio = (ai * Zq) / (A * qi);
+                    if (!(ratio < 1.0)) ratio = 1.0;
+                } else {
+                    ratio = ai > 0.0 ? 1.0 : 0.0;
+                    fl |= (uint32_t)MCSD_FLAG_ZERO_DRAFT_PROB;
+                }
+                // (a token of probability zero - a duplicate of a rejected one, Sec. 3.2 - is never
+                // accepted, also not by a uniform of exactly 0 from outside the open interval)
+                acc = uniform((ratio > 0.0) && (u <= ratio));
+                if (fabs(u - ratio) < (double)p.eps) fl |= (uint32_t)MCSD_FLAG_NEAR_TIE_ACCEPT;
+                if (p.ratio && t == 0) p.ratio[(size_t)b * N + s_kid[i]] = (float)ratio;
+                if (!acc) {
+                    // rejected: a := max(0, a - beta e_q) with beta = A / Z_q in fp64, applied as a
+                    // two-term float product so that no common rounding of beta biases the sum; 0 <= a <= 1,
+                    // so that the max is the clamp of the second product.  (The
+                    // token that leaves q keeps its e_q in the row: its residual is 0 now and stays 0
+                    // whatever is subtracted later.)
+                    const double beta = (Zq > 0.0) ? A / Zq : 0.0;   // nothing left in q: the residual is p itself
+                    float bh = (float)beta;
+                    float bl = (float)(beta - (double)bh);
+                    const bool last = i + 1 == k, remove = valid && removes;
+                    const double A_old = A, Zq_old = Zq;
+                    bool vanished = false;
+                    for (;;) {
+                        double part = 0.0;
+                        int tq = t;
+                        asm volatile("" : "+v"(tq));    // (the reads of s_q stay inside the loop over the rounds)
 #pragma unroll
-                for (int j = 0; j < ITEMS; ++j)
-                    partq += sum4(eq[j]);
-                block_sum2<NWAVES>(part, partq, s_red, s_red2);   // barriers inside also order the reuse of s_accept / s_xrem
-                A_new = part;
-                Zq = partq;
-            } else {
-                A_new = block_sum<NWAVES>(part, s_red);
+                        for (int j = 0; j < ITEMS; ++j) {
+                            const float4 e = j < RQ ? eq[j < RQ ? j : 0] : s_q[(j < RQ ? 0 : j - RQ) * VT + tq];
+                            a[j].x = __builtin_amdgcn_fmed3f(fmaf(-bl, e.x, fmaf(-bh, e.x, a[j].x)), 0.f, 1.f);
+                            a[j].y = __builtin_amdgcn_fmed3f(fmaf(-bl, e.y, fmaf(-bh, e.y, a[j].y)), 0.f, 1.f);
+                            a[j].z = __builtin_amdgcn_fmed3f(fmaf(-bl, e.z, fmaf(-bh, e.z, a[j].z)), 0.f, 1.f);
+                            a[j].w = __builtin_amdgcn_fmed3f(fmaf(-bl, e.w, fmaf(-bh, e.w, a[j].w)), 0.f, 1.f);
+                            part += sum4(a[j]);
+                            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                        }
+                        total(part, 0.0, buf);
+                        buf ^= 1;                       // (the next writers can not overtake a reader of this one)
+                        if (A > 0.0 || vanished) break;
+                        // max(0, p - q) vanished everywhere, which a rejection excludes in exact arithmetic
+                        // (it needs p = q) and rounding or a bad candidate can produce: p stays as it
+                        // was.  With every a(x) <= beta e_q(x) and equal sums, the old a is beta e_q:
+                        // the same pass with the sign turned, on the zeros that are left.
+                        vanished = true;
+                        bh = -bh;
+                        bl = -bl;
+                    }
+                    Zq = Zq_old;
+                    if (vanished) {
+                        A = A_old;
+                        fl |= (uint32_t)MCSD_FLAG_ZERO_RESIDUAL;
+                    } else {
+                        my_a = fmax(0.0, my_a - beta * my_q);
+                    }
+                    if (t == 0 && !last && i < 64) s_beta[i] = vanished ? 0.0 : beta;      // (0: the candidates' track did not move)
+                    if (remove) {
+                        // Z_q loses exactly the fp32 weight that its sum contained
+                        Zq -= (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_q32), i & 63));
+                        Zq = uniform(Zq);
+                        if (!last && uniform(Zq < z_base * 0x1p-16)) {
+                            // little of the mass is left and the difference has lost digits: the sum
+                            // again without the removed tokens, from memory (rare; a pass over the
+                            // resident row here would cost every row registers)
+                            const __amdgpu_buffer_rsrc_t rs = row_resource(zq_row, V);
+                            double partq = 0.0;
+#pragma unroll 1
+                            for (int e0 = t; e0 < V; e0 += VT) {
+                                const float w = __builtin_amdgcn_exp2f((__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, e0 * 4, 0, 0)) - mq) * c2);
+                                bool in = true;
+#pragma unroll 1
+                                for (int n = 0; n <= i; ++n) in &= s_tok[n] != e0;
+                                if (in) partq += (double)w;
+                            }
+                            const double A_now = A;
+                            total(0.0, partq, buf);
+                            buf ^= 1;
+                            A = A_now;
+                            z_base = Zq;
+                        }
+                    }
+                    if (remove && my_tok == tok) { my_q = 0.0; my_q32 = 0.f; }
+                }
+            } while (!acc && ++i < k);
+            if (acc) accepted = i;
+            // candidates after the accepted one were never tested
+            if (p.ratio && accepted >= 0 && wave == 0)
+                for (int c = accepted + 1 + lane; c < k; c += 64) p.ratio[(size_t)b * N + s_kid[c]] = NaN;
+        }
+
+        int endpoint = -1;
+        if (accepted < 0) {
+            const double u = (double)p.u_endpoint[rix];
+            Row::store(a, lane, wave, s_piece);
+            __syncthreads();
+            Row P;
+            P.read(s_piece, lane);
+            const double incl = P.scan();
+            if (!rounds) {
+                A = readlane_d(incl, 63);
+                if (!(A > 0.0) || !isfinite(A)) fl |= (uint32_t)MCSD_FLAG_NONFINITE;
             }
-            if (A_new > 0.0) {
-                A = A_new;
-                my_a = my_a_new;
+            if (isfinite(A)) {
+                draw_token<ITEMS, VT>(a, P, incl, u * A, (double)p.eps * A, lane, wave, &s_drawn);
             } else {
-                // max(0, p - q) vanished everywhere, which a rejection excludes in exact arithmetic
-                // (it needs p = q) and rounding or a bad candidate can produce: p stays as it
-                // was.  With every a(x) <= beta e_q(x) and equal sums, the old a is beta e_q.
-                if (t == 0) atomicOr(&s_flags, (uint32_t)MCSD_FLAG_ZERO_RESIDUAL);
+                // no distribution (a NaN logit): the last token that carries weight, reported
+                if (t == 0) { s_drawn.token = -1; s_drawn.near = 1; }
+                int best = -1;
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j) {
-                    a[j].x = fmaf(bl, eq[j].x, bh * eq[j].x);
-                    a[j].y = fmaf(bl, eq[j].y, bh * eq[j].y);
-                    a[j].z = fmaf(bl, eq[j].z, bh * eq[j].z);
-                    a[j].w = fmaf(bl, eq[j].w, bh * eq[j].w);
+                    const float v[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (v[c] > 0.f) best = 4 * j + c;
                 }
+                __syncthreads();
+                if (best >= 0) atomicMax(&s_drawn.token, 4 * (t + VT * (best >> 2)) + (best & 3));
+            }
+            __syncthreads();
+            endpoint = s_drawn.token;
+            if (s_drawn.near) fl |= (uint32_t)MCSD_FLAG_NEAR_TIE_ENDPOINT;
+            if (endpoint < 0 || endpoint >= V) endpoint = V - 1;
+        }
+        int acc_node = accepted >= 0 ? s_kid[accepted] : -1;
+        if (naive && k > 0) {
+            // multi-candidate naive sampling (the comparison rule of the ablation, Sec. 4.5): the
+            // token just drawn from p is kept; a candidate equal to it is accepted, the first such
+            const unsigned long long m0 = __ballot(f0 && tok0 == endpoint && tok0 >= 0 && tok0 < V);
+            const unsigned long long m1 = __ballot(f1 && tok1 == endpoint && tok1 >= 0 && tok1 < V);
+            if (__ballot((f0 && (tok0 < 0 || tok0 >= V)) || (f1 && (tok1 < 0 || tok1 >= V)))) fl |= (uint32_t)MCSD_FLAG_BAD_TOKEN;
+            acc_node = m0 ? __ffsll((long long)m0) - 1 : (m1 ? 63 + __ffsll((long long)m1) : -1);      // (right in wavefront 0, which writes it)
+            if (acc_node >= 0) endpoint = -1;
+            if (p.ratio && wave == 0) {
+                if (f0) p.ratio[(size_t)b * N + lane] = NaN;
+                if (f1) p.ratio[(size_t)b * N + 64 + lane] = NaN;
             }
         }
-        // candidates after the accepted one were never tested
-        if (p.ratio && accepted >= 0 && t > accepted && t < k) p.ratio[(size_t)b * N + s_kids[t]] = NaN;
-    }
-
-    int endpoint = -1;
-    if (accepted < 0) {
-        const double u = (double)p.u_endpoint[rix];
-        endpoint = inverse_cdf<ITEMS, VT>(a, A, u, (double)p.eps, s_red, s_seg, s_int, &s_flags);
-        if (endpoint < 0 || endpoint >= V) endpoint = V - 1;
-    }
-    if (naive && k > 0) {
-        // multi-candidate naive sampling (the comparison rule of the ablation, Sec. 4.5): the
-        // token just drawn from p is kept; a candidate equal to it is accepted, the first such
+        if (p.residual_out) {
+            const float inv = (A > 0.0) ? (float)(1.0 / A) : 0.f;
+            store_residual<ITEMS, VT, ALIGNED>(p.residual_out + rix * (size_t)V, V, a, inv);
+        }
         if (t == 0) {
-            int acc = -1;
-            uint32_t fl = 0u;
-            for (int i = 0; i < k; ++i) {
-                const int tok = p.cand_tok[(size_t)b * N + s_kids[i]];
-                if (tok < 0 || tok >= V) fl |= MCSD_FLAG_BAD_TOKEN;
-                else if (acc < 0 && tok == endpoint) acc = i;
-            }
-            if (fl) atomicOr(&s_flags, fl);
-            s_accept = acc;
+            p.acc_child[rix] = acc_node;
+            p.endpoint[rix] = endpoint;
+            p.flags[rix] = fl;
         }
-        if (p.ratio && t < k) p.ratio[(size_t)b * N + s_kids[t]] = NaN;
-        __syncthreads();
-        accepted = s_accept;
-        if (accepted >= 0) endpoint = -1;
-    }
-    if (p.residual_out) {
-        const float inv = (A > 0.0) ? (float)(1.0 / A) : 0.f;
-        store_residual<ITEMS, VT, ALIGNED>(p.residual_out + rix * (size_t)V, V, a, inv);
-    }
-    __syncthreads();
-    if (t == 0) {
-        p.acc_child[rix] = accepted >= 0 ? s_kids[accepted] : -1;
-        p.endpoint[rix] = endpoint;
-        p.flags[rix] = s_flags;
     }
 }
 
@@ -858,24 +576,14 @@ __global__ void walk_kernel(WalkParams w)
     if (b < w.B) walk_sequence(w, b);
 }
 
-template <int ITEMS, int VT>
+template <int ITEMS, int VT, int LQ, int FULL, int WGS>
 void launch_rows(const VerifyParams &p, hipStream_t stream)
 {
     dim3 grid(1 + p.N, p.B), block(VT);
     if (p.V % 4 == 0)
-        launch_kernel(K_VERIFY_ROWS, verify_rows_kernel<ITEMS, VT, true>, grid, block, stream, p);
+        launch_kernel(K_VERIFY_ROWS, verify_rows_kernel<ITEMS, VT, LQ, FULL, WGS, true>, grid, block, stream, p);
     else
-        launch_kernel(K_VERIFY_ROWS, verify_rows_kernel<ITEMS, VT, false>, grid, block, stream, p);
-}
-
-template <int ITEMS, int VT>
-void launch_rows_stream(const VerifyParams &p, hipStream_t stream)
-{
-    dim3 grid(1 + p.N, p.B), block(VT);
-    if (p.V % 4 == 0)
-        launch_kernel(K_VERIFY_ROWS, verify_rows_stream_kernel<ITEMS, VT, true>, grid, block, stream, p);
-    else
-        launch_kernel(K_VERIFY_ROWS, verify_rows_stream_kernel<ITEMS, VT, false>, grid, block, stream, p);
+        launch_kernel(K_VERIFY_ROWS, verify_rows_kernel<ITEMS, VT, LQ, FULL, WGS, false>, grid, block, stream, p);
 }
 
 }  // namespace
@@ -901,15 +609,16 @@ int32_t launch_verify(const mcsd_verify_desc &d, const mcsd_verify_bufs &b, hipS
     p.acc_child = b.acc_child; p.endpoint = b.endpoint; p.ratio = b.ratio; p.flags = b.flags;
     p.residual_out = b.residual_out;
 
-    // Up to 32768 tokens both logit rows of a node stay in the registers of one workgroup (1024
-    // threads up to 16384 tokens, 512 threads with twice the registers each beyond that); larger
-    // vocabularies keep the target row only and stream the draft row.
-    const int items1024 = (d.V + 4095) / 4096;
-    if (items1024 <= 1) launch_rows<1, 1024>(p, stream);
-    else if (items1024 <= 2) launch_rows<2, 1024>(p, stream);
-    else if (items1024 <= 4) launch_rows<4, 1024>(p, stream);
-    else if (items1024 <= 8) launch_rows<16, 512>(p, stream);
-    else launch_rows_stream<32, 512>(p, stream);
+    // Threads and the split between registers and LDS by the size of the row pair: up to 16384 tokens
+    // everything in registers, several workgroups per compute unit; up to 32768 two per unit with 18 of
+    // 32 items of the draft row in LDS; beyond, one per unit with the same split.  Measured for 16 x 61
+    // rows of 32000: 33.5 us; 512 threads with 9 of 16 items in LDS (128 registers, 16 spilled) 38.3 us;
+    // 1024 threads, all in registers, one workgroup per unit 42.5 us.
+    if (d.V <= 4096) launch_rows<4, 256, 0, 0, 4>(p, stream);
+    else if (d.V <= 8192) launch_rows<8, 256, 0, 4, 4>(p, stream);
+    else if (d.V <= 16384) launch_rows<8, 512, 0, 4, 2>(p, stream);
+    else if (d.V <= 32768) launch_rows<32, 256, 18, 16, 2>(p, stream);
+    else launch_rows<32, 512, 18, 16, 1>(p, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("verify_rows launch failed: %s", hipGetErrorString(e));

@@ -128,96 +128,11 @@ __device__ __forceinline__ double row_totals_scattered(double (&x)[ITEMS], int l
     return x[0];
 }
 
-// Every thread returns the same value (fixed summation order over the waves).
-template <int NWAVES>
-__device__ __forceinline__ double block_sum(double v, double *s_red)
-{
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 63) s_red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double r = 0.0;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) r += s_red[w];
-    __syncthreads();
-    return r;
-}
-
-// Two sums in one pass (same barriers): a -> first, b -> second.
-template <int NWAVES>
-__device__ __forceinline__ void block_sum2(double &a, double &b, double *s_red, double *s_red2)
-{
-    a = wave_sum(a);
-    b = wave_sum(b);
-    if ((threadIdx.x & 63) == 63) { s_red[threadIdx.x >> 6] = a; s_red2[threadIdx.x >> 6] = b; }
-    __syncthreads();
-    double ra = 0.0, rb = 0.0;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) { ra += s_red[w]; rb += s_red2[w]; }
-    __syncthreads();
-    a = ra;
-    b = rb;
-}
-
-template <int NWAVES>
-__device__ __forceinline__ float block_max(float v, float *s_red)
-{
-    v = wave_max(v);
-    if ((threadIdx.x & 63) == 63) s_red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = s_red[0];
-#pragma unroll
-    for (int w = 1; w < NWAVES; ++w) r = fmaxf(r, s_red[w]);
-    __syncthreads();
-    return r;
-}
-
-// Two maxima in one pass.
-template <int NWAVES>
-__device__ __forceinline__ void block_max2(float &a, float &b, float *s_red, float *s_red2)
-{
-    a = wave_max(a);
-    b = wave_max(b);
-    if ((threadIdx.x & 63) == 63) { s_red[threadIdx.x >> 6] = a; s_red2[threadIdx.x >> 6] = b; }
-    __syncthreads();
-    float ra = s_red[0], rb = s_red2[0];
-#pragma unroll
-    for (int w = 1; w < NWAVES; ++w) { ra = fmaxf(ra, s_red[w]); rb = fmaxf(rb, s_red2[w]); }
-    __syncthreads();
-    a = ra;
-    b = rb;
-}
-
 // Sum of the four lanes of a float4, exact in fp64: the normalisers A and Z_q enter the accept
 // ratios divided by the rejection probabilities, so their rounding must stay far below 1e-6.
 __device__ __forceinline__ double sum4(const float4 &v)
 {
     return ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
-}
-
-template <int ITEMS, int VT, bool ALIGNED>
-__device__ __forceinline__ void load_row(const float *z, int V, float4 (&r)[ITEMS])
-{
-    const float ninf = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        int e = 4 * (threadIdx.x + VT * i);
-        if (ALIGNED) {
-            // a logit row is read exactly once by one workgroup: non-temporal, it does not displace
-            // anything in L2 (measured 59 -> 56 us on the batched workload)
-            typedef float nt_f32x4 __attribute__((ext_vector_type(4)));
-            if (e < V) {
-                const nt_f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4 *>(z + e));
-                r[i] = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-                r[i] = make_float4(ninf, ninf, ninf, ninf);
-            }
-        } else {
-            r[i].x = (e + 0 < V) ? z[e + 0] : ninf;
-            r[i].y = (e + 1 < V) ? z[e + 1] : ninf;
-            r[i].z = (e + 2 < V) ? z[e + 2] : ninf;
-            r[i].w = (e + 3 < V) ? z[e + 3] : ninf;
-        }
-    }
 }
 
 // A logit row is read through a buffer resource whose extent is the row: the address of float4
@@ -229,35 +144,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_resource(const float *row, int V)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row), 0, V * 4, 0x00020000);
-}
-
-template <int VT, bool ALIGNED, bool NONTEMPORAL>
-__device__ __forceinline__ float4 load_row_piece(__amdgpu_buffer_rsrc_t rs, int i, int V, int tid)
-{
-    constexpr int AUX = NONTEMPORAL ? 2 : 0;
-    const int voff = tid * 16, soff = i * (VT * 16);
-    // the thread's first element of this piece lies past V iff 4 t >= V - 4 VT i: one per-thread
-    // value against a scalar, no per-piece index registers
-    const int e0 = 4 * tid, lim = V - 4 * VT * i;
-    const float ninf = -INFINITY;
-    float4 r;
-    if (ALIGNED) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, AUX);
-        const bool past = e0 >= lim;
-        r = make_float4(past ? ninf : __uint_as_float(v[0]), past ? ninf : __uint_as_float(v[1]),
-                        past ? ninf : __uint_as_float(v[2]), past ? ninf : __uint_as_float(v[3]));
-    } else {
-        // (row start and length are not multiples of 16 bytes: element by element)
-        r.x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, AUX));
-        r.y = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4, soff, AUX));
-        r.z = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 8, soff, AUX));
-        r.w = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 12, soff, AUX));
-        if (e0 + 0 >= lim) r.x = ninf;
-        if (e0 + 1 >= lim) r.y = ninf;
-        if (e0 + 2 >= lim) r.z = ninf;
-        if (e0 + 3 >= lim) r.w = ninf;
-    }
-    return r;
 }
 
 // max(a, b, c) as the one hardware instruction.  fmaxf() has to quiet signalling NaNs, and for
@@ -280,162 +166,6 @@ __device__ __forceinline__ float row_max(const float4 (&r)[ITEMS])
     return m;
 }
 
-// r := 2^((r - m) c) with c = log2(e) / T, i.e. exp((r - m) / T); returns this thread's partial
-// sum in fp64.  The subtraction comes first on purpose: the row maximum maps to exactly 1, so
-// when one token dominates both distributions (p ~ q, small rejection probability) the residual
-// max(0, p - q) does not inherit a rounding error from its largest, cancelling term.
-template <int ITEMS>
-__device__ __forceinline__ double row_exp(float4 (&r)[ITEMS], float m, float c)
-{
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        // v_exp_f32 directly: results below the normal range flush to zero, which is what
-        // a probability of 2^-126 relative to the mode should become anyway
-        r[i].x = __builtin_amdgcn_exp2f((r[i].x - m) * c);
-        r[i].y = __builtin_amdgcn_exp2f((r[i].y - m) * c);
-        r[i].z = __builtin_amdgcn_exp2f((r[i].z - m) * c);
-        r[i].w = __builtin_amdgcn_exp2f((r[i].w - m) * c);
-        s += sum4(r[i]);
-    }
-    return s;
-}
-
-template <int ITEMS, int VT, bool ALIGNED>
-__device__ __forceinline__ void store_row_scaled(float *dst, int V, const float4 (&r)[ITEMS], float s)
-{
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        int e = 4 * (threadIdx.x + VT * i);
-        float4 v = make_float4(r[i].x * s, r[i].y * s, r[i].z * s, r[i].w * s);
-        if (ALIGNED) {
-            if (e < V) *reinterpret_cast<float4 *>(dst + e) = v;
-        } else {
-            if (e + 0 < V) dst[e + 0] = v.x;
-            if (e + 1 < V) dst[e + 1] = v.y;
-            if (e + 2 < V) dst[e + 2] = v.z;
-            if (e + 3 < V) dst[e + 3] = v.w;
-        }
-    }
-}
-
-// Inverse CDF of the unnormalised weights a (sum A) at u: the smallest token id x
-// with sum_{y <= x} a(y) > u * A, found by a two-level search: (1) totals of the
-// ITEMS contiguous segments of 4 VT tokens, (2) a block-wide inclusive scan inside
-// the segment that holds the crossing.  fp64 throughout.
-//
-// cdf_segments prepares level (1): s_tot[i] = the total of segment i (four-token sums of the
-// threads, added up per row of 16 lanes and then over the rows and waves in a fixed order).
-// cdf_search does the rest and may be called repeatedly on the same prepared state; a caller
-// that removes a token between searches keeps s_tot and A in step itself.
-// s_seg holds 4 (VT / 64) ITEMS doubles.
-template <int ITEMS, int VT>
-__device__ __forceinline__ void cdf_segments(const float4 (&a)[ITEMS], double *s_seg, double *s_tot)
-{
-    constexpr int NROWS = VT / 16;
-    constexpr int SC = ITEMS < 4 ? ITEMS : 4;        // segments reduced together (bounds the registers in use)
-    const int t = threadIdx.x, lane = t & 63;
-#pragma unroll
-    for (int i0 = 0; i0 < ITEMS; i0 += SC) {
-        double x[SC];
-#pragma unroll
-        for (int i = 0; i < SC; ++i) x[i] = sum4(a[i0 + i]);
-        int which;
-        const double w = row_totals_scattered<SC>(x, lane, which);
-        s_seg[(t >> 4) * ITEMS + i0 + which] = w;     // (with fewer than 16 values several lanes of a row store the same total)
-    }
-    __syncthreads();
-    if (t < ITEMS) {
-        double tot = 0.0;
-        for (int r = 0; r < NROWS; ++r) tot += s_seg[r * ITEMS + t];
-        s_tot[t] = tot;
-    }
-    __syncthreads();
-}
-
-template <int ITEMS, int VT>
-__device__ __forceinline__ int cdf_search(const float4 (&a)[ITEMS], double A, double u, double eps, double *s_red,
-                                          const double *s_tot, int *s_int, uint32_t *flag_bits)
-{
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const double tau = u * A;
-    if (t == 0) { s_int[0] = 0x7fffffff; s_int[1] = -1; }
-    int istar = -1;
-    double base = 0.0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const double tot = s_tot[i];
-        if (istar < 0) {
-            if (base + tot > tau) istar = i;
-            else base += tot;
-        }
-    }
-    __syncthreads();
-    if (istar >= 0) {
-        float4 mine = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            if (i == istar) mine = a[i];
-        const double incl = wave_scan_inclusive(sum4(mine));
-        if (lane == 63) s_red[wave] = incl;
-        __syncthreads();
-        double woff = base;
-        for (int w = 0; w < wave; ++w) woff += s_red[w];
-        __syncthreads();
-        const double cum_hi = woff + incl;              // inclusive running sum up to this thread's 4 tokens
-        if (lane == 63) s_red[wave] = cum_hi;
-        __syncthreads();
-        double cum_lo = __shfl_up(cum_hi, 1);            // the neighbour's inclusive value, bit for bit
-        if (lane == 0) cum_lo = (wave == 0) ? base : s_red[wave - 1];
-        if (cum_hi > tau && !(cum_lo > tau)) {
-            const float v[4] = {mine.x, mine.y, mine.z, mine.w};
-            double cum = cum_lo, lo = cum_lo, hi = cum_hi;
-            int pick = -1, last_pos = -1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                double nxt = cum + (double)v[e];
-                if (v[e] > 0.f) last_pos = e;
-                if (pick < 0 && nxt > tau) { pick = e; lo = cum; hi = nxt; }
-                cum = nxt;
-            }
-            if (pick < 0) pick = last_pos < 0 ? 3 : last_pos;
-            int token = 4 * (t + VT * istar) + pick;
-            atomicMin(&s_int[0], token);
-            if (fabs(tau - lo) < eps * A || fabs(hi - tau) < eps * A) atomicOr(flag_bits, (uint32_t)MCSD_FLAG_NEAR_TIE_ENDPOINT);
-        }
-    }
-    __syncthreads();
-    int token = s_int[0];
-    if (token == 0x7fffffff) {
-        // rounding left no crossing: the last token that carries mass
-        int best = -1;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            int e = 4 * (t + VT * i);
-            if (a[i].x > 0.f) best = max(best, e);
-            if (a[i].y > 0.f) best = max(best, e + 1);
-            if (a[i].z > 0.f) best = max(best, e + 2);
-            if (a[i].w > 0.f) best = max(best, e + 3);
-        }
-        if (best >= 0) atomicMax(&s_int[1], best);
-        if (t == 0) atomicOr(flag_bits, (uint32_t)MCSD_FLAG_NEAR_TIE_ENDPOINT);
-        __syncthreads();
-        token = s_int[1];
-    }
-    __syncthreads();
-    return token;
-}
-
-// One-shot form: s_seg holds 4 (VT / 64) ITEMS + ITEMS doubles.
-template <int ITEMS, int VT>
-__device__ __forceinline__ int inverse_cdf(const float4 (&a)[ITEMS], double A, double u, double eps,
-                                           double *s_red, double *s_seg, int *s_int, uint32_t *flag_bits)
-{
-    double *s_tot = s_seg + 4 * (VT / 64) * ITEMS;
-    cdf_segments<ITEMS, VT>(a, s_seg, s_tot);
-    return cdf_search<ITEMS, VT>(a, A, u, eps, s_red, s_tot, s_int, flag_bits);
-}
-
 // ------------------------------------------------------------------ rows in pieces
 // The same search with fewer synchronisations.  A piece is what one wavefront holds of one item:
 // 256 consecutive tokens; piece number j = item * waves + wave is their order in the row.  Every
@@ -447,11 +177,10 @@ __device__ __forceinline__ int inverse_cdf(const float4 (&a)[ITEMS], double A, d
 // inside every row of this configuration.  A row whose length is no multiple of four starts at any
 // 4-byte address, which 128-bit buffer loads allow; its last tokens (fewer than four) come by
 // single loads, so that no load straddles the end of the resource.
-template <int ITEMS, int VT, int FULL, bool ALIGNED>
-__device__ __forceinline__ void load_pieces(const float *row, int V, int tid, float4 (&r)[ITEMS])
+template <int ITEMS, int VT, bool ALIGNED>
+__device__ __forceinline__ void request_pieces(const float *row, int V, int tid, float4 (&r)[ITEMS], float4 &tail)
 {
     constexpr int NT = 2;                   // non-temporal: a logit row is read once
-    const float ninf = -INFINITY;
     const int V4 = V & ~3;
     const __amdgpu_buffer_rsrc_t rs = row_resource(row, ALIGNED ? V : V4);
 #pragma unroll
@@ -459,13 +188,21 @@ __device__ __forceinline__ void load_pieces(const float *row, int V, int tid, fl
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, i * (VT * 16), NT);
         r[i] = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
     }
-    float4 tail = make_float4(ninf, ninf, ninf, ninf);
     if (!ALIGNED) {
+        const float ninf = -INFINITY;
         const __amdgpu_buffer_rsrc_t rt = row_resource(row, V);
         tail.x = (V4 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 0, V4 * 4, NT)) : ninf;
         tail.y = (V4 + 1 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 4, V4 * 4, NT)) : ninf;
         tail.z = (V4 + 2 < V) ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, 8, V4 * 4, NT)) : ninf;
+        tail.w = ninf;
     }
+}
+
+template <int ITEMS, int VT, int FULL, bool ALIGNED>
+__device__ __forceinline__ void settle_pieces(int V, int tid, float4 (&r)[ITEMS], const float4 &tail)
+{
+    const float ninf = -INFINITY;
+    const int V4 = V & ~3;
 #pragma unroll
     for (int i = FULL; i < ITEMS; ++i) {
         if (4 * VT * (i + 1) > V4) {        // uniform
@@ -475,6 +212,14 @@ __device__ __forceinline__ void load_pieces(const float *row, int V, int tid, fl
                                past ? ninf : (at ? tail.z : r[i].z), past ? ninf : (at ? ninf : r[i].w));
         }
     }
+}
+
+template <int ITEMS, int VT, int FULL, bool ALIGNED>
+__device__ __forceinline__ void load_pieces(const float *row, int V, int tid, float4 (&r)[ITEMS])
+{
+    float4 tail;
+    request_pieces<ITEMS, VT, ALIGNED>(row, V, tid, r, tail);
+    settle_pieces<ITEMS, VT, FULL, ALIGNED>(V, tid, r, tail);
 }
 
 template <int ITEMS, int VT>
@@ -498,6 +243,7 @@ struct Pieces {
 #pragma unroll
             for (int i = 0; i < 4; ++i) x[i] = (i0 + i < ITEMS) ? sum4(a[i0 + i < ITEMS ? i0 + i : 0]) : 0.0;
             store4(x, i0, lane, wave, s_piece);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     __device__ __forceinline__ void read(const double *s_piece, int lane)

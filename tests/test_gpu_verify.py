@@ -299,3 +299,22 @@ def test_argmax_rows_flag_bad_tokens():
     assert gpu["flags"][0, 0] & M.FLAG_BAD_TOKEN and not (gpu["flags"][1, 0] & M.FLAG_BAD_TOKEN)
     best = int(np.argmax(vi.target_logits[0, 0]))
     assert gpu["acc_child"][0, 0] == (0 if vi.cand_tok[0, 0] == best else -1)
+
+
+@pytest.mark.parametrize("variant", [W.WITH_REPLACEMENT, W.WITHOUT_REPLACEMENT], ids=["wr", "wor"])
+@pytest.mark.parametrize("V,k", [(3000, 100), (8190, 70), (16383, 65), (32000, 128), (32767, 5), (50002, 66), (65536, 64)])
+def test_long_rejection_runs_on_a_concentrated_draft(V, k, variant):
+    """Almost every candidate is rejected (more than 64 of them where k allows), and three tokens hold
+    all of the draft's mass but about 1e-9: without replacement their removal leaves next to
+    nothing, which has to be known as exactly as the whole.  Every register / LDS split of the row."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=3, kconfig=(k,), variant=variant)
+    rng = np.random.default_rng(V + k)
+    vi = W.gen_verify_inputs(w, rng, temperature=[1.0, 1.0, 0.0], draw_candidates_on_host=False)
+    for b in range(vi.B):
+        toks = rng.permutation(V)[:k]
+        toks[-1] = V - 1
+        vi.cand_tok[b] = toks
+        vi.draft_logits[b, 0, toks[:3]] = vi.draft_logits[b, 0].max() + 30.0
+    vi.u_accept[:] = np.float32(0.99999)
+    gpu, orc, _ = check(vi, f"V={V} k={k}", want_residual=True)
+    assert (np.isfinite(gpu["ratio"][:2]).sum(axis=1) >= min(k, 5) - 1).all()
