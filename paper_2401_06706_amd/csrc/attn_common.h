@@ -29,6 +29,8 @@ struct AttnParams {
     int root_row;         // 1: row 0 of the tree block is the root, N counts it
     int R;                // rows per (b, g) in the partial buffers
     int split_bias;       // see split_tiles
+    int rank_pairs;       // hand the (sequence, segment) pairs out longest first
+    int *chunk_of_launch; // workspace word with the chunk_tiles of this launch, or nullptr: chunk_tiles holds
     float scale_log2;     // scale * log2(e)
     // paged prefix cache (block_table != nullptr): k_prefix / v_prefix are pools
     // [n_pages][H_kv][page_size][d]; logical row r of sequence b lives in page

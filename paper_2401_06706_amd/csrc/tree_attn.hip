@@ -34,6 +34,47 @@
 namespace mcsd {
 namespace {
 
+// Tiles per segment from the lengths the sequences really have.  The host's plan knows the capacity
+// of the cache only; the compute units hold 512 workgroups at a time, and a launch a little above a
+// multiple of that runs a nearly empty last round.  The segments are made so long that the launch
+// just fits one round; two where a workgroup would walk more than 128 tiles (older and younger
+// workgroups of a unit then even out), one workgroup per CU below 12 tiles (half the partials).
+// Measured, attention and merge, against 1024 workgroups by capacity: one sequence of 16000 keys, GQA
+// 64/8, 84 nodes: 68 against 83 us; 8 x 1000..3000 keys, 28 nodes: 44 against 52 us; one sequence of
+// 8000 keys, 28 nodes: 25 against 39 us.  Every wavefront works it out from the lengths of up to 64 sequences.
+// (*len: the length of sequence number `lane`)
+__device__ __forceinline__ int segment_tiles(const AttnParams &p, int lane, int *len)
+{
+    int T = 0;
+    *len = 0;
+    if (lane < p.B) {
+        *len = max(0, min(p.prefix_len[lane], p.L_stride));
+        T = (*len + KT - 1) / KT + p.tiles_tree;
+    }
+    // sum over the wavefront without a trip through LDS: inside the rows of 16 lanes, then across them
+    auto sum = [](int v) {
+        v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);      // lanes 1 apart
+        v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false);      // 2 apart
+        v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);     // mirror of 8
+        v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);     // mirror of 16
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // rows 0, 2 into 1, 3
+        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // and into 2, 3
+        return __builtin_amdgcn_readlane(v, 63);
+    };
+    const int units = p.H_kv * p.n_row_tiles;
+    const long work = (long)sum(T) * units;
+    const int slots = work > 512 * 128 ? 1024 : (work < 512 * 12 ? 256 : 512);
+    int chunk = max(p.chunk_tiles, (int)((work + slots - 1) / slots));
+    if (slots == 1024 && chunk == p.chunk_tiles) return chunk;      // the caches are as full as the host assumed
+#pragma unroll 1
+    for (int i = 0; i < 8; ++i) {
+        const int n = lane < p.B ? max(1, (T + chunk / 2) / chunk) : 0;
+        if (sum(n) * units <= slots) break;
+        chunk += (chunk + 15) / 16;
+    }
+    return chunk;
+}
+
 // --------------------------------------------------------------------- MFMA path
 // RH = row groups per workgroup, KS = key streams per workgroup.  Wave (rh, ks) owns query rows
 // [32 rh, 32 (rh+1)) of the workgroup's row tile and the key tiles t_begin + ks, + KS, ... of the
@@ -136,25 +177,34 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
 
     // ---- this workgroup's segment: unit (b, g, rt), tiles [t_begin, t_end) of total_tiles
     int b, g, rt, t_begin, t_end, total_tiles, L;
+    int chunk_tiles = p.chunk_tiles, split_bias = p.split_bias, len_of_lane = 0;
+    const bool lens_known = COOP && p.chunk_of_launch;
+    if (lens_known) {
+        chunk_tiles = segment_tiles(p, lane, &len_of_lane);
+        split_bias = chunk_tiles / 2;
+        if (tid == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0) *p.chunk_of_launch = chunk_tiles;       // for the merge
+    }
     bool direct;
     size_t part_row;                    // first row of this segment's partial in the workspace
     {
         // Workgroups start in the order z, y, x.  The (sequence, chunk) pairs are handed out
         // longest first (the short last chunks of the sequences fill the end of the launch
         // instead of a mostly idle last wave of workgroups): pair number r in dispatch order
-        // takes the pair of rank r by length.  Done when the pairs fit one workgroup's threads.
+        // takes the pair of rank r by length.  Done when the pairs fit one workgroup's threads and the
+        // launch does not fit the chip at once (two workgroups per CU start together anyway; the
+        // ranking is 1.4 us ahead of the first request).
         g = blockIdx.x; b = blockIdx.z;
         rt = blockIdx.y % p.n_row_tiles;
         int chunk = blockIdx.y / p.n_row_tiles;
         const int n_pairs = p.B * p.n_chunks_max;
-        if (n_pairs <= NT && p.n_chunks_max > 1) {
+        if (p.rank_pairs) {
             int my_len = 0;
+            int Lb = lens_known ? __shfl(len_of_lane, tid / p.n_chunks_max) : 0;
             if (tid < n_pairs) {
-                int Lb = p.prefix_len[tid / p.n_chunks_max];
-                Lb = max(0, min(Lb, p.L_stride));
+                if (!lens_known) Lb = max(0, min(p.prefix_len[tid / p.n_chunks_max], p.L_stride));
                 const int Tb = (Lb + KT - 1) / KT + p.tiles_tree;
                 int nb, segb;
-                split_tiles(Tb, p.chunk_tiles, p.split_bias, &nb, &segb);
+                split_tiles(Tb, chunk_tiles, split_bias, &nb, &segb);
                 my_len = max(0, min(segb, Tb - (tid % p.n_chunks_max) * segb));
                 s_pair_len[tid] = my_len;
                 if (tid % p.n_chunks_max == 0) s_seq_L[tid / p.n_chunks_max] = Lb;
@@ -174,12 +224,11 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
             chunk = __builtin_amdgcn_readfirstlane(pair % p.n_chunks_max);
             L = __builtin_amdgcn_readfirstlane(s_seq_L[b]);      // already loaded and clamped: no second trip to memory
         } else {
-            L = p.prefix_len[b];
-            L = max(0, min(L, p.L_stride));
+            L = lens_known ? __builtin_amdgcn_readlane(len_of_lane, b) : max(0, min(p.prefix_len[b], p.L_stride));
         }
         total_tiles = (L + KT - 1) / KT + p.tiles_tree;
         int n_seg, seg;
-        split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_seg, &seg);
+        split_tiles(total_tiles, chunk_tiles, split_bias, &n_seg, &seg);
         t_begin = chunk * seg;
         if (t_begin >= total_tiles) return;
         t_end = min(total_tiles, t_begin + seg);
@@ -633,6 +682,9 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
             // during the pair.
             {
                 const int t_plain = min(t_end, L / KT);
+                // (the loop, 4.5 KB, starts on an instruction-cache line: 213.7 us against 216.1 us for the
+                // long-prompt GQA batch where it happened not to)
+                asm volatile(".p2align 6");
                 for (; t + 4 < t_plain; t += 2) {
                     tile_step(t, std::integral_constant<int, 0>(), std::true_type());
                     tile_step(t + 1, std::integral_constant<int, 1>(), std::true_type());
@@ -731,11 +783,17 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
 }
 
 // Merges the chunks of one unit: out = sum_c 2^(m_c - m*) O_c / sum_c 2^(m_c - m*) l_c.
+// A block of 256 threads takes 8 / S rows: S threads share a 16-byte piece of a row, each with every
+// S-th chunk, eight of them requested before the first use (one trip to memory for up to 8 S chunks),
+// and meet in LDS.  Bound by latency for few chunks (4 us), by the partials beyond.  S grows with the
+// number of chunks: with one thread per piece walking all of them, 43 chunks of 224 rows and 8 KV
+// heads took 32 us (40 MB of partials, two dependent trips per chunk).
 // Blocks with blockIdx.x >= nx_combine carry the walk of a verification that ran before this
 // launch on the same stream (one thread per sequence), when the caller asked for that.
+template <int S>
 __global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnParams p, int nx_combine, WalkParams w)
 {
-    constexpr int D = 128;
+    constexpr int D = 128, ROWS = 8 / S;
     if ((int)blockIdx.x >= nx_combine) {
         if (blockIdx.y == 0 && blockIdx.z == 0) {
             const int wb = ((int)blockIdx.x - nx_combine) * 256 + (int)threadIdx.x;
@@ -744,58 +802,80 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnParams p, in
         return;
     }
     const int g = blockIdx.y, b = blockIdx.z;
-    int L = p.prefix_len[b];
-    L = max(0, min(L, p.L_stride));
+    // both by scalar loads, together (the plain pointers would become one vector load after the other)
+    typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
+    const const_i32_ptr lens = (const_i32_ptr)(uintptr_t)p.prefix_len;
+    const const_i32_ptr chunk_word = p.chunk_of_launch ? (const_i32_ptr)(uintptr_t)p.chunk_of_launch : lens;
+    const int L = max(0, min(lens[b], p.L_stride)), chunk_of_launch = *chunk_word;
+    const int chunk_tiles = p.chunk_of_launch ? chunk_of_launch : p.chunk_tiles;
     const int total_tiles = (L + KT - 1) / KT + p.tiles_tree;
     int n_chunks, seg;
-    split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_chunks, &seg);
+    split_tiles(total_tiles, chunk_tiles, chunk_tiles / 2, &n_chunks, &seg);
     n_chunks = (total_tiles + seg - 1) / seg;      // segments that are not empty
     if (n_chunks <= 1) return;      // the attention kernel wrote the output itself
-    const int r = blockIdx.x * 8 + (threadIdx.x >> 5);
     const int d4 = threadIdx.x & 31;        // 16-byte piece of the row
-    if (r >= p.M) return;
-    const size_t base = (((size_t)b * p.H_kv + g) * p.n_chunks_max) * (size_t)p.R + r;
+    const int share = (threadIdx.x >> 5) % S, rl = (threadIdx.x >> 5) / S, r = blockIdx.x * ROWS + rl;
+    if (S == 1 && r >= p.M) return;
+    const int rr = min(r, p.M - 1);         // (a row past the end is read again and not written)
+    const size_t base = (((size_t)b * p.H_kv + g) * p.n_chunks_max) * (size_t)p.R + rr;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float ls = 0.f;
-    // Up to eight chunks (the usual case) every load is issued before the first use: one memory
-    // round trip instead of one per chunk.  Slots past n_chunks re-read chunk 0 (a cache hit) with
-    // weight zero, so the loads stay unconditional; two sizes keep that waste below a factor of two.
-    auto merge_upfront = [&](auto maxc) __attribute__((always_inline)) {
+    float ls = 0.f, ms = M_INIT;
+    // Slots past n_chunks re-read chunk 0 (a cache hit) with weight zero, so the loads stay
+    // unconditional; two sizes keep that waste below a factor of two.
+    auto merge = [&](int c0, auto maxc, auto first) __attribute__((always_inline)) {
         constexpr int MAXC = decltype(maxc)::value;
         float mc[MAXC], lc[MAXC];
         f32x4 oc[MAXC];
 #pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
+        for (int i = 0; i < MAXC; ++i) {
+            const int c = c0 + i * S;
             const bool on = c < n_chunks;
             const size_t u = base + (size_t)(on ? c : 0) * p.R;
-            mc[c] = on ? p.part_m[u] : M_INIT;
-            lc[c] = on ? p.part_l[u] : 0.f;
-            oc[c] = *reinterpret_cast<const f32x4 *>(p.part_o + u * D + 4 * d4);
+            mc[i] = on ? p.part_m[u] : M_INIT;
+            lc[i] = on ? p.part_l[u] : 0.f;
+            oc[i] = *reinterpret_cast<const f32x4 *>(p.part_o + u * D + 4 * d4);
         }
-        float ms = mc[0];
+        const float m_old = ms;
 #pragma unroll
-        for (int c = 1; c < MAXC; ++c) ms = fmaxf(ms, mc[c]);
+        for (int i = 0; i < MAXC; ++i) ms = fmaxf(ms, mc[i]);
+        if constexpr (!decltype(first)::value) {
+            const float alpha = exp2f(m_old - ms);
+            ls *= alpha;
+            acc *= alpha;
+        }
 #pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const float fsc = (c < n_chunks) ? exp2f(mc[c] - ms) : 0.f;
-            ls += fsc * lc[c];
-            acc += fsc * oc[c];
+        for (int i = 0; i < MAXC; ++i) {
+            const float fsc = (c0 + i * S < n_chunks) ? exp2f(mc[i] - ms) : 0.f;
+            ls += fsc * lc[i];
+            acc += fsc * oc[i];
         }
     };
-    if (n_chunks <= 4) {
-        merge_upfront(std::integral_constant<int, 4>());
-    } else if (n_chunks <= 8) {
-        merge_upfront(std::integral_constant<int, 8>());
+    if (n_chunks <= 4 * S) {
+        merge(share, std::integral_constant<int, 4>(), std::true_type());
     } else {
-        float ms = M_INIT;
-        for (int c = 0; c < n_chunks; ++c) ms = fmaxf(ms, p.part_m[base + (size_t)c * p.R]);
-        for (int c = 0; c < n_chunks; ++c) {
-            const size_t u = base + (size_t)c * p.R;
-            const float fsc = exp2f(p.part_m[u] - ms);
-            ls += fsc * p.part_l[u];
-            acc += fsc * *reinterpret_cast<const f32x4 *>(p.part_o + u * D + 4 * d4);
+        merge(share, std::integral_constant<int, 8>(), std::true_type());
+        if constexpr (S == 8)               // (a smaller S never has more than 8 S)
+            for (int c0 = share + 8 * S; c0 < n_chunks; c0 += 8 * S) merge(c0, std::integral_constant<int, 8>(), std::false_type());
+    }
+    if constexpr (S > 1) {
+        __shared__ f32x4 s_acc[8][32];
+        __shared__ float s_ms[8], s_ls[8];
+        s_acc[rl * S + share][d4] = acc;
+        if (d4 == 0) { s_ms[rl * S + share] = ms; s_ls[rl * S + share] = ls; }
+        __syncthreads();
+        if (share > 0) return;
+#pragma unroll
+        for (int i = 0; i < S; ++i) ms = fmaxf(ms, s_ms[rl * S + i]);
+        acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+        ls = 0.f;
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const float fsc = exp2f(s_ms[rl * S + i] - ms);
+            ls += fsc * s_ls[rl * S + i];
+            acc += fsc * s_acc[rl * S + i][d4];
         }
     }
+    if (r >= p.M) return;
     const float inv = 1.0f / ls;
     const uint2 pk = {pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
     const int node = r / p.G, hh = r % p.G;
@@ -895,6 +975,14 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     long chunk = (total_max * units + target_wgs - 1) / target_wgs;
     chunk = ((chunk + key_streams - 1) / key_streams) * key_streams;
     if (chunk < min_run) chunk = min_run;
+    // One launch of 257..447 workgroups leaves the CUs that hold two of them behind: such a plan is
+    // lengthened to one workgroup per CU (one sequence of 8000 keys, 32 heads: 320 workgroups 36.7 us,
+    // 256 workgroups 32.0 us).
+    const long wgs = units * ((total_max + chunk / 2) / chunk);
+    if (pl.variant < 2 && forced_target <= 0 && wgs > 256 && wgs < 448 && units <= 128) {
+        const long n = 256 / units;
+        chunk = ((total_max + n - 1) / n + key_streams - 1) / key_streams * key_streams;
+    }
     const int forced = g_force_chunk_tiles.load();
     if (forced > 0) chunk = forced;
     if (chunk > total_max) chunk = total_max;
@@ -904,6 +992,12 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     if (pl.n_chunks_max > 1) {
         size_t elems = (size_t)d.B * d.H_kv * pl.n_chunks_max * pl.partial_stride_rows * (size_t)(d.d + 2);
         pl.ws_bytes = (elems * sizeof(float) + 255) & ~(size_t)255;
+        // (see segment_tiles; not with a forced plan, and not where the units alone fill the chip)
+        if (pl.variant == 2 && d.B <= 64 && units <= 256 && units * pl.n_chunks_max > 512 &&
+            forced <= 0 && forced_target <= 0) {
+            pl.chunk_on_device = true;
+            pl.ws_bytes += 256;
+        }
     } else {
         pl.ws_bytes = 0;
     }
@@ -938,12 +1032,15 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
     p.n_row_tiles = plan.n_row_tiles; p.chunk_tiles = plan.chunk_tiles; p.n_chunks_max = plan.n_chunks_max;
     p.tiles_tree = plan.tiles_tree; p.R = (int)plan.partial_stride_rows;
     p.split_bias = plan.chunk_tiles / 2;
+    p.rank_pairs = d.B * plan.n_chunks_max <= 256 && plan.n_chunks_max > 1 &&
+                   (long)d.H_kv * plan.n_row_tiles * plan.n_chunks_max * d.B > 512;
     if (plan.ws_bytes > 0) {
         const size_t rows = (size_t)d.B * d.H_kv * plan.n_chunks_max * plan.partial_stride_rows;
         float *ws = static_cast<float *>(b.workspace);
         p.part_o = ws;
         p.part_m = ws + rows * d.d;
         p.part_l = p.part_m + rows;
+        if (plan.chunk_on_device) p.chunk_of_launch = reinterpret_cast<int *>(static_cast<char *>(b.workspace) + plan.ws_bytes - 256);
     }
     if (!plan.use_mfma) return launch_attn_any(p, plan, stream);
     hipError_t e;
@@ -966,12 +1063,17 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         if (e != hipSuccess) { set_error("tree_attn_mfma launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
     }
     if ((phases & ATTN_PHASE_COMBINE) && plan.n_chunks_max > 1) {
-        const int nx = (plan.rows_per_kv + 7) / 8;
         WalkParams w = {};
         int walk_blocks = 0;
         if (tail_walk) { w = *tail_walk; walk_blocks = (w.B + 255) / 256; }
-        dim3 cgrid(nx + walk_blocks, d.H_kv, d.B);
-        launch_kernel(K_ATTN_COMBINE, tree_attn_combine_kernel, cgrid, dim3(256), stream, p, nx, w);
+        auto merge = [&](auto kernel, int rows) {
+            const int nx = (plan.rows_per_kv + rows - 1) / rows;
+            launch_kernel(K_ATTN_COMBINE, kernel, dim3(nx + walk_blocks, d.H_kv, d.B), dim3(256), stream, p, nx, w);
+        };
+        if (plan.n_chunks_max <= 8) merge(tree_attn_combine_kernel<1>, 8);
+        else if (plan.n_chunks_max <= 16) merge(tree_attn_combine_kernel<2>, 4);
+        else if (plan.n_chunks_max <= 32) merge(tree_attn_combine_kernel<4>, 2);
+        else merge(tree_attn_combine_kernel<8>, 1);
         e = hipGetLastError();
         if (e != hipSuccess) { set_error("tree_attn_combine launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
     }

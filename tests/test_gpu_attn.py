@@ -308,3 +308,19 @@ def test_root_row(H_q, H_kv, kconfig, prefix):
         outs.append(out)
     assert torch.equal(outs[0].view(torch.int16) if dtype == "bf16" else outs[0], outs[1].view(torch.int16) if dtype == "bf16" else outs[1])
     assert_attn_close(outs[0].float().cpu().numpy().astype(np.float64), ref, dtype, f"root row {kconfig} {H_q}/{H_kv}")
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,prefix,L_stride", [
+    (1, 32, 2, (4, 2, 2), (3000, 3000), 9000), (5, 32, 4, (4, 2, 2), (0, 2000), 6000), (2, 64, 8, (4, 4, 2, 1), (100, 4000), 4000),
+    (64, 16, 2, (2, 2), (0, 300), 5000), (65, 16, 2, (4, 2), (0, 300), 4000), (3, 32, 4, (4, 2, 2), (0, 40), 20000)])
+def test_segments_by_the_real_lengths(B, H_q, H_kv, kconfig, prefix, L_stride):
+    """Caches far larger than what they hold, so that the segments are lengthened on the device (up to 64
+    sequences) or not: the same attention, contiguous, paged and with the library's own scratch."""
+    ai = W.gen_attn_inputs(wl(H_q=H_q, H_kv=H_kv, kconfig=kconfig, prefix=prefix, B=B), np.random.default_rng(B + H_q), L_stride=L_stride)
+    _, ref = check_full(ai, f"lengths {prefix} of {L_stride}")
+    tree = D.make_attn_call(ai)
+    M.mcsd_tree_attn(tree.args)
+    paged_call, paged, _ = D.make_paged_attn_call(tree, ai, 64, seed=B)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
