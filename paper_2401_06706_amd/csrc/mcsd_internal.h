@@ -41,31 +41,43 @@ struct WalkParams {
 };
 
 // From the root: an accepted child moves down one level, otherwise (or at a leaf) the row's
-// endpoint closes the block.
+// endpoint closes the block.  One wavefront per sequence: the accepted children of all rows (up to
+// 129) are loaded at once and the path is followed between lanes, so that a walk of any depth costs
+// two trips to memory (one thread that loaded level after level: 4.1 us for a launch of its own).
 __device__ __forceinline__ void walk_sequence(const WalkParams &w, int b)
 {
-    const int N = w.N, G = w.gamma_max;
+    const int N = w.N, G = w.gamma_max, lane = threadIdx.x & 63;
     int32_t *path = w.accepted_path + (size_t)b * G;
     int32_t *out = w.out_tokens + (size_t)b * (G + 1);
-    for (int i = 0; i < G; ++i) path[i] = -1;
-    for (int i = 0; i <= G; ++i) out[i] = -1;
+    const int32_t *child = w.acc_child + (size_t)b * (1 + N), *end = w.endpoint + (size_t)b * (1 + N);
+    const int32_t *tok = w.cand_tok + (size_t)b * N;
+    // rows lane, 64 + lane and 128 (the last row there can be)
+    const int c0 = lane <= N ? child[lane] : -1, c1 = 64 + lane <= N ? child[64 + lane] : -1, c2 = N == 128 ? child[128] : -1;
+    const int e0 = lane <= N ? end[lane] : -1, e1 = 64 + lane <= N ? end[64 + lane] : -1, e2 = N == 128 ? end[128] : -1;
+    const int t0 = lane < N ? tok[lane] : -1, t1 = 64 + lane < N ? tok[64 + lane] : -1;
+    auto of_row = [](int r, int v0, int v1, int v2) {
+        return r < 64 ? __builtin_amdgcn_readlane(v0, r) : (r < 128 ? __builtin_amdgcn_readlane(v1, r - 64) : __builtin_amdgcn_readfirstlane(v2));
+    };
     int row = 0, n = 0;
     for (;;) {
-        const size_t rix = (size_t)b * (1 + N) + row;
-        const int c = w.acc_child[rix];
+        const int c = of_row(row, c0, c1, c2);
         if (c < 0 || c >= N || n >= G) {
             // A row that accepted a child has no endpoint: reaching gamma_max there means the tree
             // is deeper than the caller said (the block then ends with -1 and the row is flagged).
-            if (c >= 0 && c < N) atomicOr(&w.flags[rix], (uint32_t)MCSD_FLAG_BAD_TREE);
-            out[n] = w.endpoint[rix];
+            if (lane == 0 && c >= 0 && c < N) atomicOr(&w.flags[(size_t)b * (1 + N) + row], (uint32_t)MCSD_FLAG_BAD_TREE);
             break;
         }
-        path[n] = c;
-        out[n] = w.cand_tok[(size_t)b * N + c];
+        const int x = of_row(c, t0, t1, 0);
+        if (lane == 0) { path[n] = c; out[n] = x; }
         ++n;
         row = 1 + c;
     }
-    w.n_accepted[b] = n;
+    const int last = of_row(row, e0, e1, e2);
+    for (int i = n + lane; i <= G; i += 64) {
+        if (i < G) path[i] = -1;
+        out[i] = i == n ? last : -1;
+    }
+    if (lane == 0) w.n_accepted[b] = n;
 }
 
 // ---- tree attention -------------------------------------------------------

@@ -104,14 +104,13 @@ __global__ __launch_bounds__(RH * KS * 64) __attribute__((amdgpu_waves_per_eu(2,
 void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
 {
     static_assert(!COOP || (KS == 1 && RH == 4), "the shared-tile scheme splits a tile over four waves of one key stream");
-    // Rows of workgroups appended to the grid along y carry the walk of a verification that ran
-    // before this launch on the same stream (one thread per sequence), when the caller asked for
-    // that: a step whose attention needs no merge launch then has no launch for the walk either.
+    // A row of workgroups appended to the grid along y carries the walk of a verification that ran
+    // before this launch on the same stream (one wavefront per sequence; the row has H_kv B workgroups
+    // of four, for as many sequences as the verification has), when the caller asked for that: a step whose attention needs no merge launch then has
+    // no launch for the walk either.
     if ((int)blockIdx.y >= p.n_chunks_max * p.n_row_tiles) {
-        if (blockIdx.x == 0 && blockIdx.z == 0) {
-            const int wb = ((int)blockIdx.y - p.n_chunks_max * p.n_row_tiles) * (RH * KS * 64) + (int)threadIdx.x;
-            if (wb < w.B) walk_sequence(w, wb);
-        }
+        const int first = (int)(blockIdx.z * gridDim.x + blockIdx.x) * (RH * KS) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        for (int wb = first; wb < w.B; wb += (int)(gridDim.z * gridDim.x) * (RH * KS)) walk_sequence(w, wb);
         return;
     }
     constexpr int MT = 2;                   // 16-row MFMA tiles per wave
@@ -239,21 +238,17 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         const int tilesP = (L + KT - 1) / KT;
         const int row0 = rt * ROWS;
 
-        // Q operand, held in registers: lane (lj, lc) has Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. +7]
+        // Q operand, held in registers: lane (lj, lc) has Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. +7].
+        // Lanes past the last row repeat it (their results are not written): nothing looks at the
+        // values here, so that the first K/V requests go out right behind these loads.
         bf16x8 qreg[MT][4];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int r = row0 + WROWS * rh + 16 * mt + lc;
-            const bool ok = r < p.M;
-            const int rr = ok ? r : p.M - 1;
+            const int rr = min(row0 + WROWS * rh + 16 * mt + lc, p.M - 1);
             const int node = rr / p.G, hh = rr % p.G;
             const uint16_t *src = qb + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * D + 8 * lj;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                u32x4 v = *reinterpret_cast<const u32x4 *>(src + 32 * kk);
-                if (!ok) v = (u32x4){0u, 0u, 0u, 0u};
-                qreg[mt][kk] = __builtin_bit_cast(bf16x8, v);
-            }
+            for (int kk = 0; kk < 4; ++kk) qreg[mt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(src + 32 * kk));
         }
 
         f32x4 oacc[8][MT];
@@ -788,17 +783,15 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
 // and meet in LDS.  Bound by latency for few chunks (4 us), by the partials beyond.  S grows with the
 // number of chunks: with one thread per piece walking all of them, 43 chunks of 224 rows and 8 KV
 // heads took 32 us (40 MB of partials, two dependent trips per chunk).
-// Blocks with blockIdx.x >= nx_combine carry the walk of a verification that ran before this
-// launch on the same stream (one thread per sequence), when the caller asked for that.
+// Blocks with blockIdx.x == nx_combine (H_kv B of them) carry the walk of a verification that ran
+// before this launch on the same stream (one wavefront per sequence), when the caller asked for that.
 template <int S>
 __global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnParams p, int nx_combine, WalkParams w)
 {
     constexpr int D = 128, ROWS = 8 / S;
     if ((int)blockIdx.x >= nx_combine) {
-        if (blockIdx.y == 0 && blockIdx.z == 0) {
-            const int wb = ((int)blockIdx.x - nx_combine) * 256 + (int)threadIdx.x;
-            if (wb < w.B) walk_sequence(w, wb);
-        }
+        const int first = (int)(blockIdx.z * gridDim.y + blockIdx.y) * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        for (int wb = first; wb < w.B; wb += (int)(gridDim.z * gridDim.y) * 4) walk_sequence(w, wb);
         return;
     }
     const int g = blockIdx.y, b = blockIdx.z;
@@ -1048,7 +1041,7 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         // an unsplit attention has no merge launch to carry the walk: it rides on this one
         WalkParams mw = {};
         int walk_rows = 0;
-        if (tail_walk && plan.n_chunks_max == 1) { mw = *tail_walk; walk_rows = (mw.B + 255) / 256; }
+        if (tail_walk && plan.n_chunks_max == 1) { mw = *tail_walk; walk_rows = 1; }
         const dim3 grid(d.H_kv, plan.n_chunks_max * plan.n_row_tiles + walk_rows, d.B);
         if (paged) {
             if (plan.variant == 0) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<1, 4, true>, grid, dim3(256), stream, p, mw);
@@ -1065,7 +1058,7 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
     if ((phases & ATTN_PHASE_COMBINE) && plan.n_chunks_max > 1) {
         WalkParams w = {};
         int walk_blocks = 0;
-        if (tail_walk) { w = *tail_walk; walk_blocks = (w.B + 255) / 256; }
+        if (tail_walk) { w = *tail_walk; walk_blocks = 1; }
         auto merge = [&](auto kernel, int rows) {
             const int nx = (plan.rows_per_kv + rows - 1) / rows;
             launch_kernel(K_ATTN_COMBINE, kernel, dim3(nx + walk_blocks, d.H_kv, d.B), dim3(256), stream, p, nx, w);

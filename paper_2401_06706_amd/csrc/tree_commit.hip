@@ -71,17 +71,40 @@ struct CommitParams {
     int page_size, n_pages, max_pages;
 };
 
-// Rows of a paged cache that can be committed for sequence b starting at logical row L: the
-// first `n` rows whose pages are inside the pool.
-__device__ __forceinline__ int paged_rows_ok(const CommitParams &p, int b, long L, int n)
+// What sequence b commits, found by one wavefront: every lane looks at one row, so that the path and
+// the block table cost one trip to memory each instead of one per row.
+struct CommitRows {
+    int L;          // cache rows before the commit
+    int wanted;     // rows this sequence would gain: the root (if it has a row), then the path
+    int rows;       // the first of them that are good: path entries inside the tree, pages inside the pool
+    bool bad_count, full;
+};
+
+__device__ __forceinline__ CommitRows commit_rows(const CommitParams &p, int b, int lane)
 {
-    int good = 0;
-    while (good < n) {
-        const int blk = p.block_table[(size_t)b * p.max_pages + (L + good) / p.page_size];
-        if ((unsigned)blk >= (unsigned)p.n_pages) break;
-        ++good;
+    CommitRows c;
+    int n = p.n_accepted[b];
+    c.L = p.prefix_len[b];
+    c.bad_count = n < 0 || n > p.gamma_max;
+    if (c.bad_count) n = 0;
+    c.wanted = n + p.root_row;
+    c.full = c.L < 0 || (long)c.L + c.wanted > p.L_stride;
+    c.rows = 0;
+    if (c.full) return c;
+    for (int r0 = 0; r0 < c.wanted; r0 += 64) {
+        const int r = r0 + lane;                            // row r holds path entry r - root_row
+        bool good = r < c.wanted;
+        if (good && r >= p.root_row) {
+            const int nd = p.accepted_path[(size_t)b * p.gamma_max + (r - p.root_row)];
+            good = nd >= 0 && nd < p.N;
+        }
+        if (p.block_table && r < c.wanted)
+            good = good && (unsigned)p.block_table[(size_t)b * p.max_pages + (c.L + r) / p.page_size] < (unsigned)p.n_pages;
+        const unsigned long long bad = ~__ballot(good);
+        c.rows = r0 + (bad ? __ffsll((long long)bad) - 1 : 64);
+        if (bad) break;
     }
-    return good;
+    return c;
 }
 
 // grid (gamma_max + root_row, B, n_layers): block (j, b, layer) copies entry j of sequence b, all
@@ -92,61 +115,42 @@ __device__ __forceinline__ int paged_rows_ok(const CommitParams &p, int b, long 
 __global__ __launch_bounds__(256) void kv_copy_kernel(CommitParams p)
 {
     const int j = blockIdx.x, b = blockIdx.y, layer = blockIdx.z;
-    const int n = p.n_accepted[b];
-    if (n < 0 || n > p.gamma_max) return;
-    const int n_rows = n + p.root_row;          // cache rows this sequence gains
-    if (j >= n_rows) return;
-    const long L = p.prefix_len[b];
-    if (L < 0 || L + n_rows > p.L_stride) return;
-    // a bad entry anywhere before j stops the copy there (the finish kernel reports it)
-    for (int e = 0; e <= j - p.root_row; ++e) {
-        const int nd = p.accepted_path[(size_t)b * p.gamma_max + e];
-        if (nd < 0 || nd >= p.N) return;
-    }
+    const CommitRows c = commit_rows(p, b, threadIdx.x & 63);
+    if (c.bad_count || j >= c.rows) return;     // a bad entry anywhere up to j stops the copy there (the finish kernel reports it)
+    const int L = c.L;
     const int tree_rows = p.N + p.root_row;
     const int src_row = (p.root_row && j == 0) ? 0 : p.root_row + p.accepted_path[(size_t)b * p.gamma_max + (j - p.root_row)];
     const int vec_per_row = p.row_bytes / 16;
     const size_t lb = (size_t)layer * p.B + b;
     size_t page_base = 0;       // paged: first row of the destination page slice of KV head 0
     if (p.block_table) {
-        if (paged_rows_ok(p, b, L, j + 1) <= j) return;      // this row's page, or an earlier one, is not in the pool
         const int blk = p.block_table[(size_t)b * p.max_pages + (L + j) / p.page_size];
         page_base = ((size_t)layer * p.n_pages + blk) * (size_t)p.H_kv * p.page_size + (size_t)((L + j) % p.page_size);
     }
     for (int e = threadIdx.x; e < p.H_kv * vec_per_row; e += blockDim.x) {
-        const int g = e / vec_per_row, c = e % vec_per_row;
-        const size_t src = ((lb * p.H_kv + g) * (size_t)tree_rows + src_row) * p.row_bytes + (size_t)c * 16;
+        const int g = e / vec_per_row, c4 = e % vec_per_row;
+        const size_t src = ((lb * p.H_kv + g) * (size_t)tree_rows + src_row) * p.row_bytes + (size_t)c4 * 16;
         const size_t dst = (p.block_table ? page_base + (size_t)g * p.page_size
-                                          : (lb * p.H_kv + g) * (size_t)p.L_stride + (size_t)(L + j)) * p.row_bytes + (size_t)c * 16;
+                                          : (lb * p.H_kv + g) * (size_t)p.L_stride + (size_t)(L + j)) * p.row_bytes + (size_t)c4 * 16;
         *reinterpret_cast<uint4 *>(p.k_prefix + dst) = *reinterpret_cast<const uint4 *>(p.k_tree + src);
         *reinterpret_cast<uint4 *>(p.v_prefix + dst) = *reinterpret_cast<const uint4 *>(p.v_tree + src);
     }
 }
 
-__global__ void kv_finish_kernel(CommitParams p)
+// One wavefront per sequence.
+__global__ __launch_bounds__(64) void kv_finish_kernel(CommitParams p)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= p.B) return;
-    int n = p.n_accepted[b];
-    uint32_t fl = 0u;
-    if (n < 0 || n > p.gamma_max) { n = 0; fl |= (uint32_t)MCSD_FLAG_BAD_TREE; }
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const CommitRows c = commit_rows(p, b, lane);
+    if (lane != 0) return;
+    const int n = c.bad_count ? 0 : c.wanted - p.root_row;
     p.next_root[b] = p.out_tokens[(size_t)b * (p.gamma_max + 1) + n];
-    const long L = p.prefix_len[b];
-    if (L < 0 || L + n + p.root_row > p.L_stride) {
+    uint32_t fl = c.bad_count ? (uint32_t)MCSD_FLAG_BAD_TREE : 0u;
+    if (c.full) {
         fl |= (uint32_t)MCSD_FLAG_CACHE_FULL;
     } else {
-        int good = 0;
-        while (good < n) {
-            const int nd = p.accepted_path[(size_t)b * p.gamma_max + good];
-            if (nd < 0 || nd >= p.N) { fl |= (uint32_t)MCSD_FLAG_BAD_TREE; break; }
-            ++good;
-        }
-        int rows = good + p.root_row;           // cache rows gained: the root (if it has a row), then the path
-        if (p.block_table) {
-            const int ok = paged_rows_ok(p, b, L, rows);
-            if (ok < rows) { fl |= (uint32_t)MCSD_FLAG_BAD_TREE; rows = ok; }
-        }
-        p.prefix_len[b] = (int32_t)(L + rows);
+        if (c.rows < c.wanted) fl |= (uint32_t)MCSD_FLAG_BAD_TREE;
+        p.prefix_len[b] = c.L + c.rows;
     }
     p.flags[b] = fl;
 }
@@ -185,7 +189,7 @@ int32_t launch_kv_commit(const mcsd_commit_desc &d, const mcsd_commit_bufs &b, h
     launch_kernel(K_KV_COPY, kv_copy_kernel, dim3(d.gamma_max + p.root_row, d.B, d.n_layers), dim3(256), stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("kv_copy launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
-    launch_kernel(K_KV_FINISH, kv_finish_kernel, dim3((d.B + 63) / 64), dim3(64), stream, p);
+    launch_kernel(K_KV_FINISH, kv_finish_kernel, dim3(d.B), dim3(64), stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) { set_error("kv_finish launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
     return MCSD_OK;

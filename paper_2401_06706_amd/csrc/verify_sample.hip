@@ -570,10 +570,10 @@ void verify_rows_kernel(VerifyParams p)
     }
 }
 
-__global__ void walk_kernel(WalkParams w)
+// one wavefront per sequence
+__global__ __launch_bounds__(64) void walk_kernel(WalkParams w)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < w.B) walk_sequence(w, b);
+    walk_sequence(w, blockIdx.x);
 }
 
 template <int ITEMS, int VT, int LQ, int FULL, int WGS>
@@ -625,7 +625,7 @@ int32_t launch_verify(const mcsd_verify_desc &d, const mcsd_verify_bufs &b, hipS
         return MCSD_E_HIP;
     }
     if (!with_walk) return MCSD_OK;
-    launch_kernel(K_WALK, walk_kernel, dim3((d.B + 63) / 64), dim3(64), stream, make_walk_params(d, b));
+    launch_kernel(K_WALK, walk_kernel, dim3(d.B), dim3(64), stream, make_walk_params(d, b));
     e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("walk launch failed: %s", hipGetErrorString(e));
