@@ -161,9 +161,17 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "tensor") -> Optiona
     return t.data_ptr()
 
 
+# torch.cuda.current_stream().cuda_stream builds a Stream object for its handle: 2.7 us of a 6.7 us
+# call, as much as the launch itself.  torch's own raw accessors give the handle in 0.2 us.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(_current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
