@@ -22,7 +22,6 @@
 // so that the comparison u <= min(1, p/q) is taken at far better than the 1e-6
 // near-tie band; vocabulary-wide passes are fp32 with fp64 accumulation.
 #include <math.h>
-#include <stdlib.h>
 
 #include "mcsd_internal.h"
 #include "vocab_row.h"
@@ -163,8 +162,8 @@ __device__ __forceinline__ void ranked_sequence(const float *temperature, int B,
 // computes: the two row pairs of 32000 tokens are 512 KB, as much as all registers of the unit.
 //
 // Bound: HBM in a batch (16 sequences of 61 rows, 8 of them argmax: 171 MB in 33.5 us = 5.1 TB/s;
-// 42.5 us with one workgroup per unit), the vector units of one CU for a single sequence (four
-// rejections: 4 us until the rows are there, 3.7 us maxima, exponentials and sums, 1.9 us per
+// 42.5 us with one workgroup per unit), the vector units of one CU for a single sequence (256 threads,
+// four rejections: 4 us until the rows are there, 3.7 us maxima, exponentials and sums, 1.9 us per
 // rejection, of which fp64 conversions and additions are half, 2.3 us endpoint).
 // 50001 tokens, 6 sequences of 29 rows: 30.5 us; 90 us when the draft row was streamed again for every
 // pass.
@@ -614,9 +613,15 @@ int32_t launch_verify(const mcsd_verify_desc &d, const mcsd_verify_bufs &b, hipS
     // 32 items of the draft row in LDS; beyond, one per unit with the same split.  Measured for 16 x 61
     // rows of 32000: 33.5 us; 512 threads with 9 of 16 items in LDS (128 registers, 16 spilled) 38.3 us;
     // 1024 threads, all in registers, one workgroup per unit 42.5 us.
+    // With few rows nothing else loads beside a row, and two wavefronts per SIMD fill each other's waits:
+    // 512 threads, both rows in registers (175), one workgroup per unit.  Rows of 32000, a call with its walk,
+    // two workgroups per unit / this: 29 rows 19.1 / 16.8 us, 116 24.7 / 21.8, 261 26.8 / 23.8, 340 31.3 / 27.6,
+    // 348 32.4 / 28.7, 464 36.6 / 37.1, 976 36.4 / 42.6 (1024 threads: 18.8, 24.4, 26.8, 29.2, 31.1, 38.7, 45.4).
+    const long rows = (long)d.B * (1 + d.N);
     if (d.V <= 4096) launch_rows<4, 256, 0, 0, 4>(p, stream);
     else if (d.V <= 8192) launch_rows<8, 256, 0, 4, 4>(p, stream);
     else if (d.V <= 16384) launch_rows<8, 512, 0, 4, 2>(p, stream);
+    else if (d.V <= 32768 && rows <= 448) launch_rows<16, 512, 0, 8, 1>(p, stream);
     else if (d.V <= 32768) launch_rows<32, 256, 18, 16, 2>(p, stream);
     else launch_rows<32, 512, 18, 16, 1>(p, stream);
     hipError_t e = hipGetLastError();

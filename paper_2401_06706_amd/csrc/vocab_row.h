@@ -1,6 +1,6 @@
 // Device helpers for kernels in which one workgroup holds one vocabulary row (float4 x ITEMS
-// per thread, VT threads): wavefront / workgroup reductions, the row load, the exponential
-// pass and the inverse-CDF search.  Shared by the verification and the draft-sampling kernels.
+// per thread, VT threads): wavefront reductions, the row load, the totals by pieces and the
+// inverse-CDF search.  Shared by the verification and the draft-sampling kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -138,7 +138,7 @@ __device__ __forceinline__ double sum4(const float4 &v)
 // A logit row is read through a buffer resource whose extent is the row: the address of float4
 // number t + VT i is one per-thread offset plus a scalar, reads past the end return zero instead
 // of leaving the array, and no per-load address registers or bounds branches are needed.
-// Elements past V are then set to -inf (only in the float4s that can reach past V at all).
+// Elements past V are then set to -inf by settle_pieces().
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_resource(const float *row, int V)

@@ -318,3 +318,22 @@ def test_long_rejection_runs_on_a_concentrated_draft(V, k, variant):
     vi.u_accept[:] = np.float32(0.99999)
     gpu, orc, _ = check(vi, f"V={V} k={k}", want_residual=True)
     assert (np.isfinite(gpu["ratio"][:2]).sum(axis=1) >= min(k, 5) - 1).all()
+
+
+@pytest.mark.parametrize("V,B,variant", [(16385, 64, W.WITHOUT_REPLACEMENT), (16385, 65, W.WITHOUT_REPLACEMENT), (32767, 65, W.WITH_REPLACEMENT),
+                                         (32767, 64, W.WITH_REPLACEMENT), (32768, 65, W.WITHOUT_REPLACEMENT)])
+def test_rows_of_one_and_of_two_workgroups_per_unit(V, B, variant):
+    """448 rows and a few more: the two splits of a row of 16385..32768 tokens, with runs of rejections
+    on a draft that is concentrated on two of its candidates.  (By 8: the mass that is left when they are
+    removed lies within 2^-32 of the maximum, where an exponent in fp32 is rounded by 2^-20 at most and a
+    weight by 6.6e-7 of itself, below the bar of 1e-6 for a ratio; with 25 it would be 1.3e-6.)"""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(6,), variant=variant)
+    rng = np.random.default_rng(V + B)
+    vi = W.gen_verify_inputs(w, rng, temperature=[1.0 if b % 8 else 0.0 for b in range(B)], draw_candidates_on_host=False)
+    for b in range(B):
+        toks = rng.permutation(V)[:6]
+        toks[-1] = V - 1
+        vi.cand_tok[b] = toks
+        vi.draft_logits[b, 0, toks[:2]] = vi.draft_logits[b, 0].max() + 8.0
+    vi.u_accept[:, ::2] = np.float32(0.99999)
+    check(vi, f"V={V} B={B}", want_residual=True)
