@@ -137,14 +137,10 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(CommitParams p)
     }
 }
 
-// One wavefront per sequence.
-__global__ __launch_bounds__(64) void kv_finish_kernel(CommitParams p)
+// What a commit leaves for the next step, by one lane.
+__device__ __forceinline__ void finish_sequence(const CommitParams &p, int b, const CommitRows &c, int next_root)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const CommitRows c = commit_rows(p, b, lane);
-    if (lane != 0) return;
-    const int n = c.bad_count ? 0 : c.wanted - p.root_row;
-    p.next_root[b] = p.out_tokens[(size_t)b * (p.gamma_max + 1) + n];
+    p.next_root[b] = next_root;
     uint32_t fl = c.bad_count ? (uint32_t)MCSD_FLAG_BAD_TREE : 0u;
     if (c.full) {
         fl |= (uint32_t)MCSD_FLAG_CACHE_FULL;
@@ -153,6 +149,88 @@ __global__ __launch_bounds__(64) void kv_finish_kernel(CommitParams p)
         p.prefix_len[b] = c.L + c.rows;
     }
     p.flags[b] = fl;
+}
+
+__device__ __forceinline__ int next_root_of(const CommitParams &p, int b, const CommitRows &c)
+{
+    const int n = c.bad_count ? 0 : c.wanted - p.root_row;
+    return p.out_tokens[(size_t)b * (p.gamma_max + 1) + n];
+}
+
+// One wavefront per sequence.
+__global__ __launch_bounds__(64) void kv_finish_kernel(CommitParams p)
+{
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const CommitRows c = commit_rows(p, b, lane);
+    if (lane == 0) finish_sequence(p, b, c, next_root_of(p, b, c));
+}
+
+// A small commit in one launch: one workgroup per sequence copies all layers, so that nothing but
+// its own first wavefront reads prefix_len[b], which may then move on at once.  A wavefront takes one
+// (row, layer) pair at a time: all its KV heads, K and V.
+constexpr int COMMIT_ROWS = 64, COMMIT_WAVES = 16;
+constexpr size_t COMMIT_BYTES = 128 << 10;      // per sequence
+
+__global__ __launch_bounds__(64 * COMMIT_WAVES) void kv_commit_kernel(CommitParams p)
+{
+    __shared__ int s_src[COMMIT_ROWS], s_page[COMMIT_ROWS];
+    __shared__ int s_rows, s_L;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave == 0) {
+        const CommitRows c = commit_rows(p, b, lane);
+        if (lane < c.rows) {
+            s_src[lane] = lane < p.root_row ? 0 : p.root_row + p.accepted_path[(size_t)b * p.gamma_max + (lane - p.root_row)];
+            s_page[lane] = p.block_table ? p.block_table[(size_t)b * p.max_pages + (c.L + lane) / p.page_size] : 0;
+        }
+        if (lane == 0) {
+            s_rows = c.bad_count ? 0 : c.rows;
+            s_L = c.L;
+            finish_sequence(p, b, c, next_root_of(p, b, c));
+        }
+    }
+    __syncthreads();
+    const int rows = __builtin_amdgcn_readfirstlane(s_rows), L = __builtin_amdgcn_readfirstlane(s_L);
+    const int vec_per_row = p.row_bytes / 16, n_vec = p.H_kv * vec_per_row, tree_rows = p.N + p.root_row;
+    const int g_step = 64 / vec_per_row, c_step = 64 % vec_per_row;
+    for (int q = wave; q < rows * p.n_layers; q += COMMIT_WAVES) {
+        const int j = q / p.n_layers, layer = q % p.n_layers;
+        const size_t lb = (size_t)layer * p.B + b;
+        const int src_row = __builtin_amdgcn_readfirstlane(s_src[j]);
+        const size_t src0 = lb * p.H_kv * (size_t)tree_rows + src_row;
+        size_t dst0, dst_pitch;
+        if (p.block_table) {
+            const int blk = __builtin_amdgcn_readfirstlane(s_page[j]);
+            dst0 = ((size_t)layer * p.n_pages + blk) * (size_t)p.H_kv * p.page_size + (size_t)((L + j) % p.page_size);
+            dst_pitch = p.page_size;
+        } else {
+            dst0 = lb * p.H_kv * (size_t)p.L_stride + (size_t)(L + j);
+            dst_pitch = p.L_stride;
+        }
+        int g = lane / vec_per_row, c4 = lane % vec_per_row;
+        for (int e0 = 0; e0 < n_vec; e0 += 128) {
+            // two pieces of K and of V requested before the first is stored
+            uint4 k[2], v[2];
+            size_t dst[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                dst[i] = (dst0 + (size_t)g * dst_pitch) * p.row_bytes + (size_t)c4 * 16;
+                const size_t src = (src0 + (size_t)g * tree_rows) * p.row_bytes + (size_t)c4 * 16;
+                if (e0 + 64 * i + lane < n_vec) {
+                    k[i] = *reinterpret_cast<const uint4 *>(p.k_tree + src);
+                    v[i] = *reinterpret_cast<const uint4 *>(p.v_tree + src);
+                }
+                g += g_step;
+                c4 += c_step;
+                if (c4 >= vec_per_row) { c4 -= vec_per_row; ++g; }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (e0 + 64 * i + lane < n_vec) {
+                    *reinterpret_cast<uint4 *>(p.k_prefix + dst[i]) = k[i];
+                    *reinterpret_cast<uint4 *>(p.v_prefix + dst[i]) = v[i];
+                }
+        }
+    }
 }
 
 }  // namespace
@@ -186,6 +264,17 @@ int32_t launch_kv_commit(const mcsd_commit_desc &d, const mcsd_commit_bufs &b, h
     p.k_tree = static_cast<const char *>(b.k_tree); p.v_tree = static_cast<const char *>(b.v_tree);
     p.n_accepted = b.n_accepted; p.accepted_path = b.accepted_path; p.out_tokens = b.out_tokens;
     p.prefix_len = b.prefix_len; p.next_root = b.next_root; p.flags = b.flags;
+    // One launch where a sequence can bring at most 128 KB (all layers, K and V): a launch less is 3 us,
+    // and one compute unit copies about 50 GB/s.  Reset of prefix_len and commit, 4 sequences, 4 layers,
+    // 8 KV heads of 128, 4 rows each (64 KB): 9.8 us with the two launches below, 7.0 us; 8 layers (128 KB)
+    // 10.2 and 7.8; 32 KV heads (256 KB) 10.2 and 10.0; 768 KB 10.1 and 21.5.
+    const size_t most = (size_t)(d.gamma_max + p.root_row) * d.n_layers * d.H_kv * p.row_bytes * 2;
+    if (d.gamma_max + p.root_row <= COMMIT_ROWS && most <= COMMIT_BYTES) {
+        launch_kernel(K_KV_COPY, kv_commit_kernel, dim3(d.B), dim3(64 * COMMIT_WAVES), stream, p);
+        const hipError_t e1 = hipGetLastError();
+        if (e1 != hipSuccess) { set_error("kv_commit launch failed: %s", hipGetErrorString(e1)); return MCSD_E_HIP; }
+        return MCSD_OK;
+    }
     launch_kernel(K_KV_COPY, kv_copy_kernel, dim3(d.gamma_max + p.root_row, d.B, d.n_layers), dim3(256), stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("kv_copy launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }

@@ -365,3 +365,30 @@ def test_kv_commit_with_root_row_matches_oracle(dtype, n_layers, B, H_kv, d, kco
         np.testing.assert_array_equal(O.gather_pages(down(t_kpool)[layer], table, Ls), ref[0][layer])
         np.testing.assert_array_equal(O.gather_pages(down(t_vpool)[layer], table, Ls), ref[1][layer])
     np.testing.assert_array_equal(t_L2.cpu().numpy(), ref[2])
+
+
+@pytest.mark.parametrize("dtype,n_layers,H_kv,d,gamma", [
+    ("bf16", 8, 8, 128, 4),         # 128 KB per sequence: the most that one launch takes
+    ("bf16", 9, 8, 128, 4),         # and a layer more
+    ("bf16", 3, 7, 200, 3),         # 25 pieces per row, a remainder in every pass
+    ("fp32", 2, 2, 512, 2),         # rows of more than 64 pieces
+    ("fp32", 1, 2, 4, 64), ("fp32", 1, 2, 4, 65)])      # the longest path that one launch takes, and one longer
+def test_kv_commit_in_one_launch_and_in_two(dtype, n_layers, H_kv, d, gamma):
+    rng = np.random.default_rng(d + gamma)
+    B, Ls, kconfig = 4, 96, (2,) + (1,) * (min(gamma, 16) - 1)
+    depth = len(kconfig)
+    L = np.array([0, Ls - depth, Ls - 1, 17], np.int32)
+    n_acc = np.array([depth, depth, min(2, depth), 1], np.int32)            # sequence 2 has no room
+    kp, vp, kt, vt, paths, out_tok, N, _ = make_commit_case(rng, n_layers, B, H_kv, d, Ls, kconfig, dtype, L, n_acc)
+    paths = np.concatenate([paths, np.full((B, gamma - depth), -1, np.int32)], axis=1)
+    out_tok = rng.integers(0, 32000, (B, gamma + 1)).astype(np.int32)
+    ref = O.kv_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L)
+    got = run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype)
+    for i in range(4):
+        np.testing.assert_array_equal(got[i], ref[i])
+    np.testing.assert_array_equal(got[4] != 0, ref[4] != 0)
+    # a count outside the path: nothing is copied, the flag says so
+    n_acc[0] = gamma + 1
+    got = run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype)
+    np.testing.assert_array_equal(got[0].reshape(kp.shape)[:, 0], kp[:, 0])
+    assert got[2][0] == 0 and got[4][0] == 64
