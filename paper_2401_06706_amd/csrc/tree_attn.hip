@@ -968,6 +968,19 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     long chunk = (total_max * units + target_wgs - 1) / target_wgs;
     chunk = ((chunk + key_streams - 1) / key_streams) * key_streams;
     if (chunk < min_run) chunk = min_run;
+    // A split plan that leaves CUs idle: with the merge launch paid anyway, segments of 3 tiles per key
+    // stream (2 with four streams) as long as all fit one per CU; on shared tiles only up to the eight
+    // that the merge takes in one trip.  With the merge, segments of 6 tiles per stream / these: 60 rows,
+    // 32 KV heads, 1000 keys 15.9 / 13.8 us; 48 rows, 2 x 8 KV heads, 1000 keys 15.6 / 12.4; 24 rows, 8 KV
+    // heads, 2000 keys 14.3 / 12.6; 112 rows, 8 KV heads, 500 keys 14.7 / 13.1, but 2000 keys 15.4 / 16.0.
+    if (forced_target <= 0 && (total_max + chunk / 2) / chunk > 1) {
+        long fine = (total_max * units + 255) / 256;
+        if (pl.variant == 2 && fine < (total_max + 7) / 8) fine = (total_max + 7) / 8;
+        fine = (fine + key_streams - 1) / key_streams * key_streams;
+        const long least = key_streams == 4 ? 8 : 3 * key_streams;
+        if (fine < least) fine = least;
+        if (fine < chunk) chunk = fine;
+    }
     // One launch of 257..447 workgroups leaves the CUs that hold two of them behind: such a plan is
     // lengthened to one workgroup per CU (one sequence of 8000 keys, 32 heads: 320 workgroups 36.7 us,
     // 256 workgroups 32.0 us).

@@ -324,3 +324,20 @@ def test_segments_by_the_real_lengths(B, H_q, H_kv, kconfig, prefix, L_stride):
     M.mcsd_tree_attn_paged(paged_call.args, paged)
     torch.cuda.synchronize()
     assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,prefix,L_stride", [
+    (1, 32, 8, (2, 2), (2000, 2000), 2000), (1, 32, 8, (2, 2), (0, 900), 1300),             # 32-row kernel
+    (1, 32, 32, (4, 2, 2, 1, 1), (1000, 1000), 1000), (2, 64, 8, (2, 2), (30, 1000), 1000),  # 64-row kernel
+    (1, 32, 8, (4, 2, 2), (500, 500), 500), (2, 32, 4, (4, 2, 2), (0, 260), 260)])          # shared tiles
+def test_short_segments_of_small_launches(B, H_q, H_kv, kconfig, prefix, L_stride):
+    """Launches that would leave compute units idle are cut into segments of two or three tiles per key
+    stream: against the oracle, with lengths at and far below the capacity, contiguous and paged."""
+    ai = W.gen_attn_inputs(wl(H_q=H_q, H_kv=H_kv, kconfig=kconfig, prefix=prefix, B=B), np.random.default_rng(B + H_q + H_kv), L_stride=L_stride)
+    check_full(ai, f"short segments {prefix} of {L_stride}")
+    tree = D.make_attn_call(ai)
+    M.mcsd_tree_attn(tree.args)
+    paged_call, paged, _ = D.make_paged_attn_call(tree, ai, 64, seed=B)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
