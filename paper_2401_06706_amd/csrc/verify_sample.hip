@@ -186,7 +186,9 @@ void verify_rows_kernel(VerifyParams p)
     __shared__ uint8_t s_kid[MCSD_MAX_NODES];
     __shared__ float s_u[MCSD_MAX_NODES], s_q32[MCSD_MAX_NODES];
     __shared__ double s_pa[MCSD_MAX_NODES], s_qa[MCSD_MAX_NODES];       // the logits of the candidates, then e_p and e_q in fp64
-    double *s_beta = s_piece;                           // of the first 64 rejections (the pieces come last)
+    // of the first 64 rejections (the pieces come last: every path to them from a round that reads s_beta
+    // leads through the barrier of that round's sum)
+    double *s_beta = s_piece;
     __shared__ Drawn s_drawn;
 
     int b;
@@ -393,6 +395,7 @@ void verify_rows_kernel(VerifyParams p)
             bool acc;
             do {
                 if ((i & 63) == 0) {
+                    if (i > 0) __syncthreads();         // s_beta[63] is written behind the barrier of its own round
                     const int c = i + lane;
                     my_tok = -1;
                     my_a = my_q = 0.0;
@@ -409,7 +412,6 @@ void verify_rows_kernel(VerifyParams p)
                             }
                         }
                     }
-                    if (i > 0) __syncthreads();         // (this round may be the last and write the pieces)
                 }
                 const int tok = __builtin_amdgcn_readlane(my_tok, i & 63);
                 const double ai = readlane_d(my_a, i & 63), qi = readlane_d(my_q, i & 63);

@@ -337,3 +337,31 @@ def test_rows_of_one_and_of_two_workgroups_per_unit(V, B, variant):
         vi.draft_logits[b, 0, toks[:2]] = vi.draft_logits[b, 0].max() + 8.0
     vi.u_accept[:, ::2] = np.float32(0.99999)
     check(vi, f"V={V} B={B}", want_residual=True)
+
+
+@pytest.mark.parametrize("V,k", [(700, 65), (8000, 128), (16001, 66), (32000, 65), (40000, 100)])
+def test_the_64th_rejection_counts_for_the_65th_candidate(V, k):
+    """Candidates past the 64th are caught up with all rejections before them, the last of them made one
+    round ago and worth about 0.5 of the 65th ratio here: a wavefront that missed it could not agree
+    with the oracle.  The bar of 1e-6 for the ratio r = a Z_q / (A e_q) holds because one token that the
+    draft hardly has carries 97 % of the target: its residual is exact, so that the roundings of all the
+    others (65 x 2^-25 of 3 %) move A and with it every beta by 6e-8 at most, and the subtractions leave
+    a(x) more than a twentieth of e_p(x): 1.2e-6 r, r < 0.7."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=2, kconfig=(k,), variant=W.WITHOUT_REPLACEMENT)
+    rng = np.random.default_rng(V + k)
+    vi = W.gen_verify_inputs(w, rng, temperature=[1.0, 1.0], draw_candidates_on_host=False)
+    vi.u_accept[:] = np.float32(0.999)
+    for b in range(vi.B):
+        toks = rng.permutation(V)[:k + 1]
+        vi.cand_tok[b] = toks[:k]
+        zp, zq = vi.target_logits[b, 0], vi.draft_logits[b, 0]
+        zp[toks[:64]] = -np.inf                         # ratio 0: 64 rejections whatever the uniforms are
+        zp[toks[k]] = np.log(np.delete(np.exp(zp.astype(np.float64)), toks[k]).sum() * 97 / 3)
+        zq[toks[k]] = zq.max() - 40.0
+        zq[toks[:64]] = np.log(np.exp(zq.astype(np.float64)).sum() * 49 / 64)               # 98 % of the draft
+        # the 65th candidate: what 64 rejections take from it (sum of 1 / Z_q, times q), and a ratio of one half
+        left = 1.0 - 0.98 / 64 * np.arange(65)
+        p = np.exp(zp[toks[64]] - np.log(np.exp(zp.astype(np.float64)).sum()))
+        zq[toks[64]] = np.log(p / ((1.0 / left[:64]).sum() + 0.5 / left[64])) + np.log(np.exp(zq.astype(np.float64)).sum())
+    gpu, orc, _ = check(vi, f"V={V} k={k}", want_residual=True)
+    assert (orc.ratio[:, :64] == 0).all() and ((orc.ratio[:, 64] > 0.3) & (orc.ratio[:, 64] < 0.7)).all()
