@@ -8,7 +8,7 @@
 //
 // Algorithm 2's removal of a rejected token from q needs no pass: that token's residual is already
 // 0 and stays 0 whatever is subtracted from it later, so only Z_q changes, by exactly the fp32 weight
-// of the token.
+// of the token.  (A residual that vanished is put back without the removed tokens.)
 //
 // Instead of renormalising after each rejection the kernels carry an
 // unnormalised residual a(x) and its sum A (p-hat = a / A), and the unnormalised
@@ -101,6 +101,23 @@ __device__ __forceinline__ float4 exp_weights(const float4 &z, float m, float c)
 {
     return make_float4(__builtin_amdgcn_exp2f((z.x - m) * c), __builtin_amdgcn_exp2f((z.y - m) * c),
                        __builtin_amdgcn_exp2f((z.z - m) * c), __builtin_amdgcn_exp2f((z.w - m) * c));
+}
+
+// Gives token x (the same in all lanes) of a row the weight w; its own thread gets the weight it had.
+template <int ITEMS, int VT>
+__device__ __forceinline__ float set_token(float4 (&a)[ITEMS], int x, float w)
+{
+    const int item = (x >> 2) / VT, c = ((x >> 2) & (VT - 1)) == (int)threadIdx.x ? (x & 3) : -1;
+    float was = 0.f;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        if (j == item) {
+            float *v[4] = {&a[j].x, &a[j].y, &a[j].z, &a[j].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c == e) { was = *v[e]; *v[e] = w; }
+        }
+    return was;
 }
 
 // A condition that is the same in all lanes though the compiler can not know it: as a scalar, so that
@@ -391,6 +408,7 @@ void verify_rows_kernel(VerifyParams p)
             double z_base = Zq;
             int buf = 1;
             const bool removes = p.variant == MCSD_WITHOUT_REPLACEMENT;
+            double kept_a = 0.0;                        // residual of tokens that have left q, put aside from the row (see below)
             int i = 0;
             bool acc;
             do {
@@ -438,7 +456,7 @@ void verify_rows_kernel(VerifyParams p)
                     // two-term float product so that no common rounding of beta biases the sum; 0 <= a <= 1,
                     // so that the max is the clamp of the second product.  (The
                     // token that leaves q keeps its e_q in the row: its residual is 0 now and stays 0
-                    // whatever is subtracted later.)
+                    // whatever is subtracted later; what is added below is taken from it again.)
                     const double beta = (Zq > 0.0) ? A / Zq : 0.0;   // nothing left in q: the residual is p itself
                     float bh = (float)beta;
                     float bl = (float)(beta - (double)bh);
@@ -460,6 +478,7 @@ void verify_rows_kernel(VerifyParams p)
                             if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                         }
                         total(part, 0.0, buf);
+                        A += kept_a;
                         buf ^= 1;                       // (the next writers can not overtake a reader of this one)
                         if (A > 0.0 || vanished) break;
                         // max(0, p - q) vanished everywhere, which a rejection excludes in exact arithmetic
@@ -504,9 +523,32 @@ void verify_rows_kernel(VerifyParams p)
                         }
                     }
                     if (remove && my_tok == tok) { my_q = 0.0; my_q32 = 0.f; }
+                    if (uniform(removes && (vanished || (valid && ratio >= 1.0)))) {
+                        // Put back, the row holds beta e_q for tokens that had left q and have p = 0.  And the
+                        // token of this round leaves q with some of its p left, or all (so does one that
+                        // only a uniform above 1 rejects): no later round may lower that.
+#pragma unroll 1
+                        for (int n = vanished ? 0 : i; n <= i; ++n) {
+                            const int x = __builtin_amdgcn_readfirstlane(s_tok[n]);
+                            if (n == i && t == 0 && !valid) s_u[i] = 0.f;
+                            if (x < 0 || x >= V) continue;
+                            const float was = set_token<ITEMS, VT>(a, x, 0.f);
+                            if (n == i && ((x >> 2) & (VT - 1)) == t) s_u[i] = was;      // (its uniform has been used)
+                        }
+                        __syncthreads();
+                        const double was = uniform((double)s_u[i]);
+                        if (was > 0.0 && t == 0) s_q32[i] = -1.f;      // marked (its weight has been used)
+                        kept_a += was;
+                    }
                 }
             } while (!acc && ++i < k);
             if (acc) accepted = i;
+            if (kept_a > 0.0) {
+                __syncthreads();
+#pragma unroll 1
+                for (int n = 0; n < k; ++n)
+                    if (uniform(s_q32[n] < 0.f)) set_token<ITEMS, VT>(a, __builtin_amdgcn_readfirstlane(s_tok[n]), s_u[n]);
+            }
             // candidates after the accepted one were never tested
             if (p.ratio && accepted >= 0 && wave == 0)
                 for (int c = accepted + 1 + lane; c < k; c += 64) p.ratio[(size_t)b * N + s_kid[c]] = NaN;

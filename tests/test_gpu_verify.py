@@ -365,3 +365,50 @@ def test_the_64th_rejection_counts_for_the_65th_candidate(V, k):
         zq[toks[64]] = np.log(p / ((1.0 / left[:64]).sum() + 0.5 / left[64])) + np.log(np.exp(zq.astype(np.float64)).sum())
     gpu, orc, _ = check(vi, f"V={V} k={k}", want_residual=True)
     assert (orc.ratio[:, :64] == 0).all() and ((orc.ratio[:, 64] > 0.3) & (orc.ratio[:, 64] < 0.7)).all()
+
+
+@pytest.mark.parametrize("variant", [W.WITH_REPLACEMENT, W.WITHOUT_REPLACEMENT], ids=["wr", "wor"])
+@pytest.mark.parametrize("V,B", [(12, 5), (4095, 10), (8192, 10), (16381, 10), (20003, 10), (32768, 10), (20003, 60), (32768, 60), (50002, 10), (65536, 10)])
+def test_residual_that_vanishes_after_removals(V, B, variant):
+    """p is 1/2 on two tokens, q equal on these and three more.  The three are rejected; without replacement
+    q is then p, and whatever is rejected next (a duplicate, an id that is none, a token of p by a
+    uniform above 1) finds max(0, p - q) = 0 everywhere.  p stays as it was: the removed tokens have none
+    of it, a token removed in such a round keeps its share.  All values are exact, in fp32 and in fp64.
+    Every fifth sequence: a token of p that goes first, by a uniform above 1, keeps what is left to it."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(7,), variant=variant)
+    rng = np.random.default_rng(V + B)
+    vi = W.gen_verify_inputs(w, rng, temperature=[0.7 if b % 3 else 1.0 for b in range(B)], draw_candidates_on_host=False)
+    vi.target_logits[:, 0] = vi.draft_logits[:, 0] = -np.inf
+    vi.u_accept[:] = np.float32(0.9)
+    vi.u_endpoint[:, 0] = np.where(np.arange(B) // 5 % 2, 0.8, 0.3)
+    ids = vi.cand_tok.copy()                # what the oracle gets: a rejected token in the place of an id that is none
+    for b in range(B):
+        y0, y1, r0, r1, r2 = rng.permutation(V)[:5]
+        if b % 10 < 5:
+            y1, r1 = (x for x in (V - 1, V - 2) if x not in (y0, r0, r2)) if not {V - 1, V - 2} & {y0, r0, r2} else (y1, r1)
+        vi.target_logits[b, 0, [y0, y1]] = 1.5
+        vi.draft_logits[b, 0, [y0, y1, r0, r1, r2]] = -0.5
+        vi.cand_tok[b] = ids[b] = [(r0, r1, r2, r0, r1, r2, r0), (r0, -1, r1, V, r2, -1, r1), (r0, r1, r2, y0, y1, r0, r1),
+                                   (r0, r1, r2, r1, y1, y0, r2), (y0, r0, r1, r0, r2, r1, r0)][b % 5]
+        ids[b][(vi.cand_tok[b] < 0) | (vi.cand_tok[b] >= V)] = r0
+        if b % 5 == 2:
+            vi.u_accept[b, 3] = 1.5         # y0 goes at ratio 1; then y1 has p = 1/2 and q = 1
+        if b % 5 == 3:
+            vi.u_accept[b, 4] = 1.5
+            vi.u_accept[b, 5] = 0.4         # ... and here y0 is accepted
+        if b % 5 == 4:
+            vi.u_accept[b, 0] = 1.5
+    gpu = run_gpu(vi, want_residual=True)
+    tok, vi.cand_tok = vi.cand_tok, ids
+    orc = run_oracle(vi, want_residual=True)
+    bad = ((tok < 0) | (tok >= V)).any(axis=1)
+    np.testing.assert_array_equal((gpu["flags"][:, 0] & M.FLAG_BAD_TOKEN) != 0, bad)
+    np.testing.assert_array_equal((gpu["flags"][:, 0] & M.FLAG_ZERO_RESIDUAL) != 0, (variant == W.WITHOUT_REPLACEMENT) & (np.arange(B) % 5 != 4))
+    # (the bars of compare_verify, which takes no flagged rows; no uniform lies near an edge here)
+    assert orc.margin[:, 0].min() > 0.05
+    np.testing.assert_array_equal(gpu["acc_child"][:, 0], orc.acc_child[:, 0])
+    np.testing.assert_array_equal(gpu["endpoint"][:, 0], orc.endpoint[:, 0])
+    assert np.abs(gpu["residual_out"][:, 0] - orc.residual[:, 0]).max() <= 1e-6
+    tested = ~np.isnan(orc.ratio)
+    np.testing.assert_array_equal(~np.isnan(gpu["ratio"]), tested)
+    assert np.abs(gpu["ratio"] - orc.ratio)[tested].max() <= 1e-6
