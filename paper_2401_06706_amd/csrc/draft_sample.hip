@@ -49,6 +49,7 @@ void draft_rows_kernel(DraftParams p)
     __shared__ int s_kid[MCSD_MAX_NODES];
     __shared__ float s_u[MCSD_MAX_NODES];
     __shared__ Drawn s_drawn[MCSD_MAX_NODES];
+    __shared__ double s_rest;
     __shared__ float s_bestv[2][NWAVES];
     __shared__ int s_besti[2][NWAVES];
 
@@ -205,6 +206,7 @@ void draft_rows_kernel(DraftParams p)
         P.read(s_piece, lane);
         double incl = P.scan();
         double Z = readlane_d(incl, 63);
+        const double least = Z * 0x1p-20;
         const bool finite = (Z > 0.0) && (Z < INFINITY);
         for (int i = 0; i < k; ++i) {
             const int node = s_kid[i];
@@ -223,9 +225,20 @@ void draft_rows_kernel(DraftParams p)
             if (p.variant == MCSD_WITHOUT_REPLACEMENT && i + 1 < k && ok) {
                 // q-bar of Eq. (1): the drawn token's weight leaves its piece and the mass (draw_token skips
                 // the token itself; taking it out of its register in this loop would cost a copy of the row)
-                P.remove(d.token, d.weight, lane);
+                const bool little = P.remove(d.token, d.weight, lane);
                 Z -= (double)d.weight;
+                if (__builtin_expect(little, 0)) {
+                    // what is left of the piece, from its tokens: a rest of roundings could be drawn in their place
+                    const int j = d.token >> 8;
+                    if (j % NWAVES == wave) {
+                        const double rest = wave_sum(sum4(piece_values<ITEMS, VT>(a, j, lane, s_drawn, i + 1)));
+                        if (lane == 63) s_rest = rest;
+                    }
+                    __syncthreads();            // (the next writer is behind the barrier of another draw)
+                    P.set(j, s_rest, lane);
+                }
                 incl = P.scan();
+                if (__builtin_expect(Z < least, 0)) Z = readlane_d(incl, 63);       // (likewise)
             }
         }
     }

@@ -225,7 +225,7 @@ __device__ __forceinline__ void load_pieces(const float *row, int V, int tid, fl
 template <int ITEMS, int VT>
 struct Pieces {
     static constexpr int NW = VT / 64, NP = ITEMS * NW, PPL = NP <= 64 ? 1 : NP / 64;
-    double tot[PPL];                        // totals of pieces lane * PPL ...
+    double tot[PPL], least[PPL];            // totals of pieces lane * PPL ...; for remove()
 
     // s_piece holds 4 NP doubles: the totals per row of 16 lanes
     static __device__ __forceinline__ void store4(const double (&x)[4], int i0, int lane, int wave, double *s_piece)
@@ -254,6 +254,7 @@ struct Pieces {
             const double *s = s_piece + 4 * (j < NP ? j : 0);
             const double t = (s[0] + s[1]) + (s[2] + s[3]);
             tot[q] = j < NP ? t : 0.0;
+            least[q] = tot[q] * 0x1p-20;
         }
     }
     __device__ __forceinline__ double scan() const      // inclusive, over the lanes
@@ -263,13 +264,26 @@ struct Pieces {
         for (int q = 1; q < PPL; ++q) v += tot[q];
         return wave_scan_inclusive(v);
     }
-    // the token's weight leaves its piece
-    __device__ __forceinline__ void remove(int token, float weight, int lane)
+    // The token's weight leaves its piece.  true (in every lane): the difference may be little but rounding
+    // and the piece has to be summed anew (set).  That is where less than 2^-20 is left of what
+    // the piece had at first (`least`); above, the rounding is below 2^-33 of what is left.
+    __device__ __forceinline__ bool remove(int token, float weight, int lane)
     {
         const int j = token >> 8;
+        bool little = false;
 #pragma unroll
         for (int q = 0; q < PPL; ++q)
-            if (j == lane * PPL + q) tot[q] -= (double)weight;
+            if (j == lane * PPL + q) {
+                tot[q] -= (double)weight;
+                little = tot[q] < least[q];
+            }
+        return __ballot(little) != 0ull;
+    }
+    __device__ __forceinline__ void set(int j, double total, int lane)
+    {
+#pragma unroll
+        for (int q = 0; q < PPL; ++q)
+            if (j == lane * PPL + q) tot[q] = total;
     }
 };
 
@@ -280,17 +294,42 @@ __device__ __forceinline__ double readlane_d(double v, int lane)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// The smallest token whose cumulative weight exceeds tau = u A, or the last one that carries weight
-// where rounding leaves none.  `incl` = P.scan().  Every wavefront calls it; the one that owns the
-// token writes it, its weight and whether tau lies within tol of an edge of its interval to *out
-// (-1 if nothing carries weight: then wavefront 0 does); the caller publishes with one barrier.
-// The tokens of taken[0 .. n_taken) have left the row: their weights count as zero.
 struct Drawn {
     int token;
     float weight;
     int near;
 };
 
+// This lane's weights of piece j, which the calling wavefront holds.  The tokens of taken[0 .. n_taken)
+// have left the row: their weights count as zero.
+template <int ITEMS, int VT>
+__device__ __forceinline__ float4 piece_values(const float4 (&a)[ITEMS], int j, int lane, const Drawn *taken, int n_taken)
+{
+    const int is = j / Pieces<ITEMS, VT>::NW;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (i == is) v = a[i];
+    for (int n0 = 0; n0 < n_taken; n0 += 64) {
+        const int x_lane = n0 + lane < n_taken ? taken[n0 + lane].token : -1;
+        for (unsigned long long m = __ballot((x_lane >> 8) == j); m; m &= m - 1) {      // those of this piece
+            const int x = __builtin_amdgcn_readlane(x_lane, __ffsll((long long)m) - 1);
+            if ((x >> 2) == 64 * j + lane) {
+                if ((x & 3) == 0) v.x = 0.f;
+                if ((x & 3) == 1) v.y = 0.f;
+                if ((x & 3) == 2) v.z = 0.f;
+                if ((x & 3) == 3) v.w = 0.f;
+            }
+        }
+    }
+    return v;
+}
+
+// The smallest token whose cumulative weight exceeds tau = u A, or the last one that carries weight
+// where rounding leaves none.  `incl` = P.scan().  Every wavefront calls it; the one that owns the
+// token writes it, its weight and whether tau lies within tol of an edge of its interval to *out
+// (-1 if nothing carries weight: then wavefront 0 does); the caller publishes with one barrier.
+// taken, n_taken: as above.
 template <int ITEMS, int VT>
 __device__ __forceinline__ void draw_token(const float4 (&a)[ITEMS], const Pieces<ITEMS, VT> &P, double incl, double tau, double tol,
                                            int lane, int wave, Drawn *out, const Drawn *taken = nullptr, int n_taken = 0)
@@ -323,23 +362,7 @@ __device__ __forceinline__ void draw_token(const float4 (&a)[ITEMS], const Piece
     if (!exact) { qs = q_last; base = run_last; }
     const int j = __builtin_amdgcn_readfirstlane(ls * PPL + qs);
     if (j % NW != wave) return;
-    const int is = j / NW;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-        if (i == is) v = a[i];
-    for (int n0 = 0; n0 < n_taken; n0 += 64) {
-        const int x_lane = n0 + lane < n_taken ? taken[n0 + lane].token : -1;
-        for (unsigned long long m = __ballot((x_lane >> 8) == j); m; m &= m - 1) {      // those of this piece
-            const int x = __builtin_amdgcn_readlane(x_lane, __ffsll((long long)m) - 1);
-            if ((x >> 2) == 64 * j + lane) {
-                if ((x & 3) == 0) v.x = 0.f;
-                if ((x & 3) == 1) v.y = 0.f;
-                if ((x & 3) == 2) v.z = 0.f;
-                if ((x & 3) == 3) v.w = 0.f;
-            }
-        }
-    }
+    const float4 v = piece_values<ITEMS, VT>(a, j, lane, taken, n_taken);
     const double part = sum4(v);
     const double hi_lane = base + wave_scan_inclusive(part);
     const unsigned long long c2 = __ballot(hi_lane > tau), w2 = __ballot(part > 0.0);

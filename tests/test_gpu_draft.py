@@ -220,3 +220,25 @@ def test_draws_that_meet_in_one_piece_and_in_the_last_tokens(V):
     got, rt, rm = run(vi, u)
     compare(vi, got, rt, rm, f"V={V}")
     np.testing.assert_array_equal(got["cand_tok"][[1, 3]], rt[[1, 3]])
+
+
+@pytest.mark.parametrize("V", [700, 5001, 9002, 20003, 32000, 50001])
+def test_draws_after_a_piece_has_given_all_it_had(V):
+    """Two tokens of one piece of 256 hold all of the mass but about 1e-16, in amounts whose sum is not
+    exact in fp64.  When both are drawn, nothing of that piece is left: the next draws come from the
+    other tokens, as the oracle draws them (it sums what is left anew), and no token comes twice."""
+    B, k = 24, 5
+    w = W.WORKLOADS["c2"].with_(B=B, V=V, kconfig=(k,), variant=W.WITHOUT_REPLACEMENT)
+    rng = np.random.default_rng(V)
+    vi = W.gen_verify_inputs(w, rng, temperature=[1.0] * B, draw_candidates_on_host=False)
+    vi.draft_logits[:] = -200.0
+    for b in range(B):
+        piece, other = rng.permutation(V // 256)[:2]
+        vi.draft_logits[b, 0, 256 * piece + rng.permutation(256)[:2]] = [0.0, -20.0 - 4.0 * rng.random()]
+        vi.draft_logits[b, 0, 256 * other + rng.permutation(256)[:2]] = -38.0 - 2.0 * rng.random(2)
+        vi.draft_logits[b, 0, [0 if piece else V - 1, V - 1 if V % 256 else 256 * other + 255]] = -37.5
+    u = (0.1 + 0.8 * rng.random((B, vi.N))).astype(np.float32)
+    got, rt, rm = run(vi, u)
+    compare(vi, got, rt, rm, f"V={V}")
+    assert all(len(set(t)) == k for t in got["cand_tok"].tolist())
+    assert (np.take_along_axis(vi.draft_logits[:, 0], got["cand_tok"][:, :4].astype(np.int64), 1) > -100).all()
