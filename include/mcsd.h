@@ -340,7 +340,8 @@ int32_t mcsd_tree_build(const int32_t *kconfig_host, int32_t gamma, int32_t B, c
  *   prefix_len[b] = L + n;  next_root[b] = out_tokens[b][n]  (the endpoint, root of the next tree)
  * If L + n > L_stride nothing is copied, prefix_len[b] is left alone and flags[b] gets
  * MCSD_FLAG_CACHE_FULL (0 otherwise); path entries outside [0, N) end the copy there and set
- * MCSD_FLAG_BAD_TREE.  n_accepted, accepted_path and out_tokens are the outputs of
+ * MCSD_FLAG_BAD_TREE; with n outside [0, gamma_max] nothing is copied either, prefix_len[b] is left
+ * alone, next_root[b] = out_tokens[b][0] and MCSD_FLAG_BAD_TREE is set.  n_accepted, accepted_path and out_tokens are the outputs of
  * mcsd_verify_sample.  The caches of n_layers layers lie back to back.
  * With root_row = 1 (k_tree, v_tree have 1 + N rows, row 0 = the root, see the conventions):
  *   k_prefix[..][L] = k_tree[..][0],  k_prefix[..][L + 1 + j] = k_tree[..][1 + accepted_path[b][j]],

@@ -77,6 +77,7 @@ struct CommitRows {
     int L;          // cache rows before the commit
     int wanted;     // rows this sequence would gain: the root (if it has a row), then the path
     int rows;       // the first of them that are good: path entries inside the tree, pages inside the pool
+                    // (none with a count outside the path, not even the root)
     bool bad_count, full;
 };
 
@@ -90,7 +91,7 @@ __device__ __forceinline__ CommitRows commit_rows(const CommitParams &p, int b, 
     c.wanted = n + p.root_row;
     c.full = c.L < 0 || (long)c.L + c.wanted > p.L_stride;
     c.rows = 0;
-    if (c.full) return c;
+    if (c.full || c.bad_count) return c;
     for (int r0 = 0; r0 < c.wanted; r0 += 64) {
         const int r = r0 + lane;                            // row r holds path entry r - root_row
         bool good = r < c.wanted;
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(CommitParams p)
 {
     const int j = blockIdx.x, b = blockIdx.y, layer = blockIdx.z;
     const CommitRows c = commit_rows(p, b, threadIdx.x & 63);
-    if (c.bad_count || j >= c.rows) return;     // a bad entry anywhere up to j stops the copy there (the finish kernel reports it)
+    if (j >= c.rows) return;     // a bad entry anywhere up to j stops the copy there (the finish kernel reports it)
     const int L = c.L;
     const int tree_rows = p.N + p.root_row;
     const int src_row = (p.root_row && j == 0) ? 0 : p.root_row + p.accepted_path[(size_t)b * p.gamma_max + (j - p.root_row)];
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(64 * COMMIT_WAVES) void kv_commit_kernel(CommitPara
             s_page[lane] = p.block_table ? p.block_table[(size_t)b * p.max_pages + (c.L + lane) / p.page_size] : 0;
         }
         if (lane == 0) {
-            s_rows = c.bad_count ? 0 : c.rows;
+            s_rows = c.rows;
             s_L = c.L;
             finish_sequence(p, b, c, next_root_of(p, b, c));
         }

@@ -65,7 +65,7 @@ def make_commit_case(rng, n_layers, B, H_kv, d, Ls, kconfig, dtype, L, n_acc):
     return kp, vp, kt, vt, paths, out_tok, N, gamma
 
 
-def run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype):
+def run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype, root_row=False):
     def up(a):
         t = torch.from_numpy(a.view(np.int16) if dtype == "bf16" else a).to(DEV)
         return t.view(torch.bfloat16) if dtype == "bf16" else t
@@ -74,7 +74,7 @@ def run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype):
     t_L = dev_i32(L)
     nxt = torch.full((B,), -9, dtype=torch.int32, device=DEV)
     fl = torch.full((B,), -9, dtype=torch.int32, device=DEV)
-    args = M.commit_args(t_kp, t_vp, t_kt, t_vt, dev_i32(n_acc), dev_i32(paths), dev_i32(out_tok), t_L, nxt, fl)
+    args = M.commit_args(t_kp, t_vp, t_kt, t_vt, dev_i32(n_acc), dev_i32(paths), dev_i32(out_tok), t_L, nxt, fl, root_row=root_row)
     M.mcsd_kv_commit(args)
     torch.cuda.synchronize()
     def down(t):
@@ -392,3 +392,25 @@ def test_kv_commit_in_one_launch_and_in_two(dtype, n_layers, H_kv, d, gamma):
     got = run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, dtype)
     np.testing.assert_array_equal(got[0].reshape(kp.shape)[:, 0], kp[:, 0])
     assert got[2][0] == 0 and got[4][0] == 64
+
+
+@pytest.mark.parametrize("n_layers", [1, 40], ids=["one-launch", "two-launches"])
+@pytest.mark.parametrize("root_row", [False, True])
+def test_kv_commit_with_a_count_outside_the_path(root_row, n_layers):
+    """Nothing is copied, not even the root, and the cache does not grow: it would count rows that were
+    never written.  The other sequences commit as usual."""
+    rng = np.random.default_rng(31)
+    B, H_kv, d, Ls, kconfig = 3, 8, 64, 40, (2, 2)
+    L, n_acc = np.array([5, 5, 5], np.int32), np.array([2, 2, 2], np.int32)
+    kp, vp, kt, vt, paths, out_tok, N, gamma = make_commit_case(rng, n_layers, B, H_kv, d, Ls, kconfig, "bf16", L, n_acc)
+    if root_row:
+        kt, vt = (np.ascontiguousarray(np.concatenate([a[:, :, :, -1:], a], axis=3)) for a in (kt, vt))
+    ref = O.kv_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, root_row=root_row)
+    for bad in (-1, gamma + 1, 1 << 30):
+        n_acc[1] = bad
+        k, v, new_L, nxt, fl = run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, "bf16", root_row)
+        np.testing.assert_array_equal(k[:, 1], kp[:, 1])
+        np.testing.assert_array_equal(v[:, 1], vp[:, 1])
+        assert new_L[1] == 5 and fl.tolist() == [0, 64, 0] and nxt[1] == out_tok[1, 0]
+        for got, want in ((k[:, ::2], ref[0][:, ::2]), (v[:, ::2], ref[1][:, ::2]), (new_L[::2], ref[2][::2]), (nxt[::2], ref[3][::2])):
+            np.testing.assert_array_equal(got, want)
