@@ -119,7 +119,8 @@ int32_t mcsd_tree_validate(const int32_t *parent_host, int32_t n_nodes);
  * Inputs are expected to be position-encoded already (each candidate keeps the
  * position it has in its own sequence, i.e. prefix_len + depth - 1).
  * fp32 accumulation on the matrix cores.  The softmax weights enter PV as bf16 for bf16 storage
- * with d == 128 and at fp32 accuracy otherwise.
+ * with d == 128, as two bf16 terms (relative error at most 2^-17) for bf16 storage with other d,
+ * and as fp32 for fp32 storage.
  */
 typedef struct {
     uint32_t struct_size;
@@ -148,9 +149,8 @@ typedef struct {
     size_t workspace_bytes;
 } mcsd_attn_bufs;
 
-/* Bytes of scratch mcsd_tree_attn needs for this descriptor (0 on a bad descriptor).  For bf16 with
- * d != 128 a workspace of this size is only used to split long prefixes over more workgroups: the
- * call also runs with less, or with none. */
+/* Bytes of scratch mcsd_tree_attn needs for this descriptor (0 on a bad descriptor).  0 for fp32
+ * storage and for d != 128: such calls neither read nor write a workspace. */
 size_t mcsd_attn_workspace_bytes(const mcsd_attn_desc *desc);
 int32_t mcsd_tree_attn(const mcsd_attn_desc *desc, const mcsd_attn_bufs *bufs, void *stream);
 

@@ -125,10 +125,6 @@ static int32_t check_attn(const mcsd_attn_desc *d, const mcsd_attn_bufs *b, Attn
     if (b->struct_size != sizeof(mcsd_attn_bufs)) { set_error("attn bufs struct_size %u != %zu", b->struct_size, sizeof(mcsd_attn_bufs)); return MCSD_E_SHAPE; }
     if (!b->q || !b->k_tree || !b->v_tree || !b->prefix_len || !b->parent || !b->out) { set_error("attn: NULL buffer"); return MCSD_E_NULL; }
     if (d->L_stride > 0 && (!b->k_prefix || !b->v_prefix)) { set_error("attn: NULL prefix cache"); return MCSD_E_NULL; }
-    // Shapes outside the d = 128 kernel may come without a workspace (or with any): the keys of a
-    // unit are then not split.
-    if (!plan->use_mfma && plan->ws_bytes > 0 &&
-        (!b->workspace || b->workspace_bytes < plan->ws_bytes || ((uintptr_t)b->workspace & 255u))) unsplit_attn_plan(plan);
     if (plan->ws_bytes > 0) {
         if (!b->workspace) { set_error("attn: workspace is NULL, %zu bytes needed", plan->ws_bytes); return MCSD_E_WORKSPACE; }
         if (b->workspace_bytes < plan->ws_bytes) { set_error("attn: workspace %zu < %zu bytes", b->workspace_bytes, plan->ws_bytes); return MCSD_E_WORKSPACE; }

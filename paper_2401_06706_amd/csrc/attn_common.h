@@ -137,7 +137,7 @@ __device__ __forceinline__ void build_ancestor_masks(const int32_t *parent, int 
     }
 }
 
-// fp32 storage and head dimensions other than 128 (tree_attn_any.hip): the attention, and the merge if it is split
-int32_t launch_attn_any(const AttnParams &p, const AttnPlan &plan, hipStream_t stream);
+// fp32 storage and head dimensions other than 128 (tree_attn_any.hip): one launch, no workspace
+int32_t launch_attn_any(const AttnParams &p, hipStream_t stream);
 
 }  // namespace mcsd

@@ -82,7 +82,7 @@ __device__ __forceinline__ void walk_sequence(const WalkParams &w, int b)
 
 // ---- tree attention -------------------------------------------------------
 struct AttnPlan {
-    bool use_mfma;        // bf16, d == 128: tree_attn.hip; otherwise tree_attn_any.hip (fp32: nothing below but rows_per_kv is used)
+    bool use_mfma;        // bf16, d == 128: tree_attn.hip; otherwise tree_attn_any.hip (nothing below but rows_per_kv is used)
     int rows_per_kv;      // M = N * (H_q / H_kv) query rows that share one KV head
     int row_tile;         // query rows per workgroup (32 or 64) for the MFMA kernel
     int variant;          // which instantiation of the MFMA kernel
@@ -97,8 +97,6 @@ struct AttnPlan {
 };
 
 bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan);
-// The same plan with every unit in one segment (no partials, no workspace).
-void unsplit_attn_plan(AttnPlan *plan);
 // Process-wide overrides of the plan (0 = automatic): kernel variant 1..3, 32-key tiles per
 // segment, workgroups aimed at when the segment length is derived.  A test and tuning aid.
 int32_t attn_plan_override(int variant, int chunk_tiles, int target_wgs);

@@ -881,48 +881,6 @@ std::atomic<int> g_force_variant{0}, g_force_chunk_tiles{0}, g_force_target_wgs{
 
 }  // namespace
 
-// bf16 with d != 128: rows per workgroup by the rows that share a KV head, segments as for d = 128.
-// 512 workgroups aimed at (two per CU) and at least 8 tiles (two steps) per segment: at d 64, GQA
-// 32/8, 8 sequences of 200..2000 tokens, targets of 256 / 512 / 1024 / 2048 with segments down to 2
-// tiles took 25.1 / 22.0 / 22.0 / 28.9 us with the merge; one sequence of 2000 tokens 16.7 us with 8
-// tiles per segment and 17.9 us with 2, where the merge costs as much as the attention.
-// The partials are kept within MCSD_STATIC_SCRATCH_BYTES, so that every shape also goes through the
-// entry point that brings no workspace.
-static void plan_bf16_any(const mcsd_attn_desc &d, AttnPlan *pl)
-{
-    const int n_rows_tree = d.N + (d.root_row ? 1 : 0);
-    const bool wide = d.d > 128;
-    pl->variant = pl->rows_per_kv <= 32 ? (wide ? 1 : 0) : (pl->rows_per_kv <= 64 && !wide ? 1 : 2);
-    pl->row_tile = (wide ? 16 : 32) << pl->variant;
-    const int key_streams = 4 >> pl->variant;
-    pl->n_row_tiles = (pl->rows_per_kv + pl->row_tile - 1) / pl->row_tile;
-    pl->tiles_prefix_max = (d.L_stride + KT - 1) / KT;
-    pl->tiles_tree = (n_rows_tree + KT - 1) / KT;
-    pl->partial_stride_rows = (size_t)pl->n_row_tiles * pl->row_tile;
-    const long total_max = pl->tiles_prefix_max + pl->tiles_tree;
-    const long units = (long)d.B * d.H_kv * pl->n_row_tiles;
-    const int forced_target = g_force_target_wgs.load(), forced_chunk = g_force_chunk_tiles.load();
-    const long target_wgs = forced_target > 0 ? forced_target : 512;
-    long chunk = (total_max * units + target_wgs - 1) / target_wgs;
-    chunk = (chunk + key_streams - 1) / key_streams * key_streams;
-    if (chunk < 8) chunk = 8;
-    if (forced_chunk > 0) chunk = forced_chunk;
-    const size_t bytes_per_chunk = (size_t)d.B * d.H_kv * pl->partial_stride_rows * (size_t)(d.d + 2) * sizeof(float);
-    const long n_fit = (long)((MCSD_STATIC_SCRATCH_BYTES - 255) / bytes_per_chunk);
-    if (chunk > total_max || n_fit < 2) chunk = total_max;
-    else if ((total_max + chunk - 1) / chunk > n_fit) chunk = (total_max + n_fit - 1) / n_fit;
-    pl->chunk_tiles = (int)chunk;
-    pl->n_chunks_max = (int)((total_max + chunk - 1) / chunk);
-    pl->ws_bytes = pl->n_chunks_max > 1 ? (bytes_per_chunk * pl->n_chunks_max + 255) & ~(size_t)255 : 0;
-}
-
-void unsplit_attn_plan(AttnPlan *pl)
-{
-    pl->chunk_tiles = pl->tiles_prefix_max + pl->tiles_tree;
-    pl->n_chunks_max = 1;
-    pl->ws_bytes = 0;
-}
-
 bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
 {
     AttnPlan pl = {};
@@ -932,7 +890,6 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     pl.use_mfma = (d.dtype == MCSD_DTYPE_BF16 && d.d == 128);
     if (!pl.use_mfma) {
         if (d.d > MCSD_MAX_HEAD_DIM) return false;
-        if (d.dtype == MCSD_DTYPE_BF16) plan_bf16_any(d, &pl);
         *plan = pl;
         return true;
     }
@@ -1048,7 +1005,7 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         p.part_l = p.part_m + rows;
         if (plan.chunk_on_device) p.chunk_of_launch = reinterpret_cast<int *>(static_cast<char *>(b.workspace) + plan.ws_bytes - 256);
     }
-    if (!plan.use_mfma) return launch_attn_any(p, plan, stream);
+    if (!plan.use_mfma) return launch_attn_any(p, stream);
     hipError_t e;
     if (phases & ATTN_PHASE_MAIN) {
         // an unsplit attention has no merge launch to carry the walk: it rides on this one

@@ -5,9 +5,9 @@
 //   tree_attn_f32_kernel   fp32 storage, d a multiple of 4 up to 256 (same paddings)
 //
 // In both, a lane of S^T = K Q^T holds scores of one query row, which is the B operand layout of
-// O^T += V^T P^T: the weights never leave their lane.  Both keep the weights at fp32 accuracy:
-// the fp32 kernel multiplies in fp32 (v_mfma_f32_16x16x4_f32), the bf16 kernel feeds PV with two
-// bf16 terms per weight (see split_weight).
+// O^T += V^T P^T: the weights never leave their lane.  The fp32 kernel multiplies in fp32
+// (v_mfma_f32_16x16x4_f32); the bf16 kernel feeds PV with two bf16 terms per weight, which hold it to
+// 2^-17 (see weight_hi_bits).
 #include <type_traits>
 
 #include "attn_common.h"
@@ -69,32 +69,36 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
     return __builtin_elementwise_sub_sat(__float_as_uint(p), 1u) & 0xffff0000u;
 }
 
-// Workgroup of 4 waves, one unit (sequence, KV head, row tile) and one segment of its key tiles.
-// Wave (rh, ks) owns 16 MT query rows and every KS-th tile; the TS tiles of a step are loaded by
-// all threads together, one step ahead in registers, and go through LDS in their natural order
+// Workgroup of NW waves, one unit (sequence, KV head, row tile) with all of its keys, DS of the output
+// columns.  Wave (rh, ks) owns 16 MT query rows and every KS-th tile; the TS tiles of a step are loaded
+// by all threads together, one step ahead in registers, and go through LDS in their natural order
 // with row pitches that keep all accesses free of bank conflicts (K: 4 words, V: 8 words past a
-// multiple of 32).  V is read back with the transposing LDS load.
-// The shape decides RH: 32 rows x 4 key streams up to 32 rows per KV head, 64 x 2 up to 64,
-// 128 x 1 beyond (d > 128: half the rows each, the accumulators are twice as wide).
-// Bound by latency, not bandwidth, at the sizes it meets: a launch of two steps per workgroup takes
-// 16 us of which about 8 are the chain prefix length -> first tiles -> epilogue.  Measured (d 64,
-// 8 sequences of 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector
-// units, every one reading the cache again, 1262 us; this kernel and its merge 20.7 us.  One tile
-// per step instead of four: 18.8 + 5.6 us against 17.5 + 4.2 us at the same number of segments.
-template <int DP, int RH, int MT, int TS>
-__global__ __launch_bounds__(256, 2)
+// multiple of 32).  V is read back with the transposing LDS load.  The streams meet in LDS at the
+// end: no memory besides the arguments, so that calls on several streams share nothing, and the
+// bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any.)
+// Bound by latency, not bandwidth, at the sizes it meets: about 8 us are the chain prefix length ->
+// first tiles -> epilogue, a step of 64 KB takes 1.2 to 1.5 us.  Measured (d 64, 8 sequences of
+// 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
+// reading the cache again, 1262 us; the keys split over 512 workgroups of four waves, partials in
+// the caller's workspace and a merge launch, 21.0 us; this kernel 19.7 us.  That split is faster only
+// for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 115, 4720 on the
+// vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
+// never asked for.
+template <int DP, int DS, int NW, int RH, int MT, int TS>
+__global__ __launch_bounds__(64 * NW, 2)
 void tree_attn_bf16_kernel(AttnParams p)
 {
-    constexpr int KS = 4 / RH;
+    constexpr int KS = NW / RH, NT = 64 * NW;
     static_assert(TS % KS == 0, "every key stream takes the same number of tiles of a step");
     constexpr int WROWS = 16 * MT, ROWS = WROWS * RH;
-    constexpr int GR = DP / 8;                           // 16-byte granules per row
-    constexpr int NL = TS * KT * GR / 256;               // K (and V) loads per thread and step
-    constexpr int PK = DP / 2 + 4, PV = DP / 2 + 8;      // row pitches in words
+    constexpr int GR = DP / 8, GV = DS / 8;              // 16-byte granules per row of K and of V
+    constexpr int NL = TS * KT * GR / NT, NV = TS * KT * GV / NT;        // K and V loads per thread and step
+    static_assert(KT * GV % 64 == 0 && NV > 0, "a wave's share of a load lies in one tile");
+    constexpr int PK = DP / 2 + 4, PV = DS / 2 + 8;      // row pitches in words
     constexpr int STREAM_WORDS = KT * (PK + PV);
-    constexpr int PO = DP + 4;                           // row pitch of the epilogue's fp32 area
-    constexpr int LDS_WORDS = TS * STREAM_WORDS > ROWS * PO ? TS * STREAM_WORDS : ROWS * PO;
-    constexpr int NKK = DP / 32, NNT = DP / 16;
+    constexpr int PO = DS + 4;                           // row pitch of the epilogue's fp32 area
+    constexpr int LDS_WORDS = TS * STREAM_WORDS > KS * ROWS * PO ? TS * STREAM_WORDS : KS * ROWS * PO;
+    constexpr int NKK = DP / 32, NNT = DS / 16;
 
     __shared__ __attribute__((aligned(16))) uint32_t s_big[LDS_WORDS];
     __shared__ uint32_t s_anc[MCSD_MAX_NODES][4];
@@ -106,38 +110,50 @@ void tree_attn_bf16_kernel(AttnParams p)
     const int rh = wave / KS, ks = wave % KS;
     const int lj = lane >> 4, lc = lane & 15;
     const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
-    const int rt = blockIdx.x / p.H_kv % p.n_row_tiles, chunk = blockIdx.x / p.H_kv / p.n_row_tiles;
-    const int row0 = rt * ROWS;
+    const int row0 = blockIdx.x / p.H_kv * ROWS, d0 = blockIdx.y * DS;
 
     const int L = max(0, min(p.prefix_len[b], p.L_stride));
-    const int tiles_prefix = (L + KT - 1) / KT, total_tiles = tiles_prefix + p.tiles_tree;
-    int n_seg, seg;
-    split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_seg, &seg);
-    const int t_begin = chunk * seg;
-    if (t_begin >= total_tiles) return;
-    const int t_end = min(total_tiles, t_begin + seg);
+    const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
     const uint32_t row_bytes = (uint32_t)p.d * 2u;
 
-    // load i of a thread: granule tid + 256 i of the step's TS x 32 rows, row-major
-    uint32_t g_off[NL];
-    int l_row[NL];
+    // load i of a thread: granule tid + NT i of the step's TS x 32 rows, row-major
+    uint32_t k_off[NL], v_off[NV];
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        const int gid = tid + 256 * i, r = (gid / GR) % KT, c = gid % GR;
-        g_off[i] = (8 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
-        l_row[i] = r;
+        const int gid = tid + NT * i, r = (gid / GR) % KT, c = gid % GR;
+        k_off[i] = (8 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
     }
-    u32x4 kraw[NL], vraw[NL];
-    auto request = [&](int t0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int ks2 = ((wave * 64 + 256 * i) / GR) / KT;       // one tile per wave and load
-            const TileSrc s = tile_source<KT>(p, b, g, L, tiles_prefix, t0 + ks2, t_end, row_bytes);
-            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), g_off[i], 0, 0);
-            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), g_off[i], 0, 0);
+    for (int i = 0; i < NV; ++i) {
+        const int gid = tid + NT * i, r = (gid / GV) % KT, c = gid % GV;
+        v_off[i] = (d0 + 8 * c < p.d) ? (uint32_t)r * row_bytes + 2u * d0 + 16u * c : OFF_NOWHERE;
+    }
+    u32x4 kraw[NL], vraw[NV];
+    auto request = [&](int t0) __attribute__((always_inline)) {
+        auto source = [&](int granule) __attribute__((always_inline)) {       // one tile per wave and load
+            return tile_source<KT>(p, b, g, L, tiles_prefix, t0 + granule / KT, t_end, row_bytes);
+        };
+        if constexpr (DS == DP) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const TileSrc s = source((wave * 64 + NT * i) / GR);
+                kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), k_off[i], 0, 0);
+                vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), v_off[i], 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const TileSrc s = source((wave * 64 + NT * i) / GR);
+                kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), k_off[i], 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const TileSrc s = source((wave * 64 + NT * i) / GV);
+                vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), v_off[i], 0, 0);
+            }
         }
     };
-    request(t_begin);
+    request(0);
 
     // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
     bf16x8 qreg[MT][NKK];
@@ -153,8 +169,7 @@ void tree_attn_bf16_kernel(AttnParams p)
             qreg[mt][kk] = __builtin_bit_cast(bf16x8, v);
         }
     }
-    if (t_end > tiles_prefix)
-        build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+    build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
 
     f32x4 oacc[NNT][MT];
     float m_used[MT], l_part[MT];
@@ -170,14 +185,17 @@ void tree_attn_bf16_kernel(AttnParams p)
     typedef short v4i16 __attribute__((ext_vector_type(4)));
     typedef v4i16 __attribute__((address_space(3))) *lds_v4i16_ptr;
 
-    for (int t0 = t_begin; t0 < t_end; t0 += TS) {
+    for (int t0 = 0; t0 < t_end; t0 += TS) {
         __syncthreads();                    // the last step's operands (and the masks) have been read (written)
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int gid = tid + 256 * i, c = gid % GR, ks2 = (gid / GR) / KT;
-            uint32_t *kt = s_big + ks2 * STREAM_WORDS, *vt = kt + KT * PK;
-            *reinterpret_cast<u32x4 *>(kt + l_row[i] * PK + 4 * c) = kraw[i];
-            *reinterpret_cast<u32x4 *>(vt + l_row[i] * PV + 4 * c) = vraw[i];
+            const int gid = tid + NT * i, c = gid % GR, row = gid / GR;
+            *reinterpret_cast<u32x4 *>(s_big + row / KT * STREAM_WORDS + row % KT * PK + 4 * c) = kraw[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int gid = tid + NT * i, c = gid % GV, row = gid / GV;
+            *reinterpret_cast<u32x4 *>(s_big + row / KT * STREAM_WORDS + KT * PK + row % KT * PV + 4 * c) = vraw[i];
         }
         request(t0 + TS);
         __syncthreads();
@@ -303,87 +321,28 @@ void tree_attn_bf16_kernel(AttnParams p)
         for (int nt = 0; nt < NNT; ++nt) oacc[nt][mt] *= fsc;
     }
 #pragma unroll
-    for (int k2 = 0; k2 < KS; ++k2) {
-        if (ks == k2) {
+    for (int nt = 0; nt < NNT; ++nt)
 #pragma unroll
-            for (int nt = 0; nt < NNT; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    f32x4 *dst = reinterpret_cast<f32x4 *>(area + (WROWS * rh + 16 * mt + lc) * PO + 16 * nt + 4 * lj);
-                    *dst = (k2 == 0) ? oacc[nt][mt] : oacc[nt][mt] + *dst;
-                }
-        }
-        __syncthreads();
-    }
-    const int rows_valid = min(ROWS, p.M - row0), d4n = p.d / 4;
-    const bool direct = (n_seg == 1);
-    const size_t part_row = (((size_t)b * p.H_kv + g) * p.n_chunks_max + chunk) * (size_t)p.R + (size_t)row0;
-    for (int idx = tid; idx < rows_valid * d4n; idx += 256) {
+        for (int mt = 0; mt < MT; ++mt)
+            *reinterpret_cast<f32x4 *>(area + (ks * ROWS + WROWS * rh + 16 * mt + lc) * PO + 16 * nt + 4 * lj) = oacc[nt][mt];
+    __syncthreads();
+    const int rows_valid = min(ROWS, p.M - row0), d4n = min(DS, p.d - d0) / 4;
+    for (int idx = tid; idx < rows_valid * d4n; idx += NT) {
         const int r = idx / d4n, d4 = idx % d4n;
-        const f32x4 acc = *reinterpret_cast<const f32x4 *>(area + r * PO + 4 * d4);
         float ms = s_m[0][r], ls = 0.f;
 #pragma unroll
         for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k2 = 0; k2 < KS; ++k2) ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
-        if (direct) {
-            const float inv = 1.0f / ls;
-            const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
-            uint16_t *ob = static_cast<uint16_t *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + 4 * d4;
-            __builtin_nontemporal_store((u32x2){pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)}, reinterpret_cast<u32x2 *>(ob));
-        } else {
-            __builtin_nontemporal_store(acc, reinterpret_cast<f32x4 *>(p.part_o + (part_row + r) * p.d + 4 * d4));
-            if (d4 == 0) { p.part_m[part_row + r] = ms; p.part_l[part_row + r] = ls; }
+        for (int k2 = 0; k2 < KS; ++k2) {
+            ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
+            acc += *reinterpret_cast<const f32x4 *>(area + (k2 * ROWS + r) * PO + 4 * d4);
         }
+        const float inv = 1.0f / ls;
+        const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
+        uint16_t *ob = static_cast<uint16_t *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + d0 + 4 * d4;
+        __builtin_nontemporal_store((u32x2){pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)}, reinterpret_cast<u32x2 *>(ob));
     }
-}
-
-// Merges the segments of a unit by log-sum-exp, one 16-byte piece of a row per thread.
-__global__ __launch_bounds__(256) void tree_attn_bf16_combine_kernel(AttnParams p)
-{
-    const int g = blockIdx.x % p.H_kv, b = blockIdx.z, d4n = p.d / 4, rows = 256 / d4n;
-    const int L = max(0, min(p.prefix_len[b], p.L_stride));
-    const int total_tiles = (L + KT - 1) / KT + p.tiles_tree;
-    int n_chunks, seg;
-    split_tiles(total_tiles, p.chunk_tiles, p.split_bias, &n_chunks, &seg);
-    n_chunks = (total_tiles + seg - 1) / seg;
-    if (n_chunks <= 1) return;              // the attention kernel wrote the output itself
-    const int rl = threadIdx.x / d4n, r = blockIdx.x / p.H_kv * rows + rl, d4 = threadIdx.x % d4n;
-    if (rl >= rows || r >= p.M) return;
-    const size_t base = (((size_t)b * p.H_kv + g) * p.n_chunks_max) * (size_t)p.R + r;
-    // four segments are requested together; the running maximum starts at M_INIT like a segment's
-    float ms = M_INIT, ls = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < n_chunks; c0 += 4) {
-        float mc[4], lc[4];
-        f32x4 oc[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const bool on = c0 + c < n_chunks;
-            const size_t u = base + (size_t)(on ? c0 + c : 0) * p.R;
-            mc[c] = p.part_m[u];
-            lc[c] = on ? p.part_l[u] : 0.f;
-            oc[c] = *reinterpret_cast<const f32x4 *>(p.part_o + u * p.d + 4 * d4);
-            if (!on) { mc[c] = M_INIT; oc[c] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
-        }
-        float mn = ms;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) mn = fmaxf(mn, mc[c]);
-        const float alpha = exp2f(ms - mn);
-        ls *= alpha;
-        acc *= alpha;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float f = exp2f(mc[c] - mn);
-            ls += f * lc[c];
-            acc += f * oc[c];
-        }
-        ms = mn;
-    }
-    const float inv = 1.0f / ls;
-    const int node = r / p.G, hh = r % p.G;
-    uint16_t *ob = static_cast<uint16_t *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + 4 * d4;
-    __builtin_nontemporal_store((u32x2){pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)}, reinterpret_cast<u32x2 *>(ob));
 }
 
 // ------------------------------------------------------------------------------ fp32
@@ -586,10 +545,11 @@ void tree_attn_f32_kernel(AttnParams p)
     }
 }
 
-template <int DP, int RH, int MT, int TS>
-void launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream)
+template <int DP, int DS, int NW, int RH, int MT, int TS>
+void launch_bf16(const AttnParams &p, hipStream_t stream)
 {
-    launch_kernel(K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, RH, MT, TS>, grid, dim3(256), stream, p);
+    constexpr int ROWS = 16 * MT * RH;
+    launch_kernel(K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS>, dim3((unsigned)p.H_kv * ((p.M + ROWS - 1) / ROWS), (p.d + DS - 1) / DS, p.B), dim3(64 * NW), stream, p);
 }
 
 template <int DP, int DS>
@@ -600,7 +560,7 @@ void launch_f32(const AttnParams &p, hipStream_t stream)
 
 }  // namespace
 
-int32_t launch_attn_any(const AttnParams &p, const AttnPlan &plan, hipStream_t stream)
+int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
 {
     if (p.B > 65535) { set_error("attn: B %d > 65535", p.B); return MCSD_E_UNSUPPORTED; }
     const int dp = p.d <= 64 ? 64 : (p.d <= 128 ? 128 : 256);
@@ -613,28 +573,46 @@ int32_t launch_attn_any(const AttnParams &p, const AttnPlan &plan, hipStream_t s
         else if (dp == 128) { if (slices) launch_f32<128, 64>(p, stream); else launch_f32<128, 128>(p, stream); }
         else { if (slices) launch_f32<256, 64>(p, stream); else launch_f32<256, 128>(p, stream); }
     } else {
-        const dim3 grid((unsigned)p.H_kv * plan.n_chunks_max * plan.n_row_tiles, 1, p.B);
+        // Rows of a KV head per workgroup and wavefronts.  While the launch fits one workgroup per CU, few
+        // rows by eight wavefronts: the walk over the keys is the time, and the key tiles that several
+        // workgroups read come out of L2.  Beyond, four wavefronts (two workgroups per CU) and the
+        // more rows the more workgroups there are, so that a tile is read for more of them.
+        // d 64, us at 200 / 1500 keys, 32 rows x 8 wavefronts, 64 x 8, 32 x 4, 64 x 4, 128 x 4:
+        //   64 units of 112 rows   (256, 128 workgroups of 32, 64 rows)  7.8/17.4  8.6/22  8.1/20  9.3/28  12/42
+        //   256 units of 28        (256)                                 8.2/20.6  8.1/22  8.3/21  8.8/28  11/40
+        //   128 units of 112       (512, 256)                            14/33     9.0/24  9.8/25  9.5/28  12/42
+        //   192 units of 112       (768, 384)                            20/46     16/43   12/31   12/36   12/42
+        //   256 units of 112       (1024, 512)                           26/60     16/43   16/42   12/36   13/43
+        //   384 units of 112       (1536, 768)                           38/97     24/68   21/59   15/48   18/59
+        //   512 units of 112       (2048, 1024)                          50/129    32/90   26/80   20/67   18/63
+        // d 96, 384 units of 112 rows (768 of 64): 25/86 with 64 rows, 23/84 with 128; 256 units 16/54 and 17/61;
+        // 192 units (768 of 32) 21/64 with 32 rows, 16/52 with 64.
+        // d 256, eight wavefronts and 32 rows, slices of 64, 128, 256 columns, four wavefronts: 64 units 11/35
+        // 12/41 13/41 15/51; 128 units 20/73 13/46 15/55 15/58; 192 units 29/103 23/86 16/61 16/62; 512 units
+        // 73/273 46/174 33/145 26/142.
+        const long units = (long)p.B * p.H_kv, wgs32 = units * ((p.M + 31) / 32), wgs64 = units * ((p.M + 63) / 64);
         if (dp == 64) {
-            if (plan.variant == 0) launch_bf16<64, 1, 2, 4>(p, grid, stream);
-            else if (plan.variant == 1) launch_bf16<64, 2, 2, 4>(p, grid, stream);
-            else launch_bf16<64, 4, 2, 4>(p, grid, stream);
+            if (wgs32 <= 256) launch_bf16<64, 64, 8, 1, 2, 8>(p, stream);
+            else if (p.M > 32 && wgs64 <= 256) launch_bf16<64, 64, 8, 2, 2, 8>(p, stream);
+            else if (p.M <= 32 || wgs32 <= 768) launch_bf16<64, 64, 4, 1, 2, 4>(p, stream);
+            else if (p.M <= 64 || wgs64 < 1024) launch_bf16<64, 64, 4, 2, 2, 4>(p, stream);
+            else launch_bf16<64, 64, 4, 4, 2, 4>(p, stream);
         } else if (dp == 128) {
-            if (plan.variant == 0) launch_bf16<128, 1, 2, 4>(p, grid, stream);
-            else if (plan.variant == 1) launch_bf16<128, 2, 2, 2>(p, grid, stream);
-            else launch_bf16<128, 4, 2, 2>(p, grid, stream);
+            if (wgs32 <= 256) launch_bf16<128, 128, 8, 1, 2, 8>(p, stream);
+            else if (p.M > 32 && wgs64 <= 256) launch_bf16<128, 128, 8, 2, 2, 8>(p, stream);
+            else if (p.M <= 32) launch_bf16<128, 128, 4, 1, 2, 4>(p, stream);
+            else if (p.M <= 64 || wgs64 < 768) launch_bf16<128, 128, 4, 2, 2, 2>(p, stream);
+            else launch_bf16<128, 128, 4, 4, 2, 2>(p, stream);
         } else {
-            if (plan.variant == 1) launch_bf16<256, 2, 1, 2>(p, grid, stream);
-            else launch_bf16<256, 4, 1, 1>(p, grid, stream);
+            if (wgs32 <= 64) launch_bf16<256, 64, 8, 2, 1, 4>(p, stream);
+            else if (wgs32 <= 128) launch_bf16<256, 128, 8, 2, 1, 4>(p, stream);
+            else if (wgs32 <= 256) launch_bf16<256, 256, 8, 2, 1, 4>(p, stream);
+            else if (p.M <= 32) launch_bf16<256, 256, 4, 2, 1, 2>(p, stream);
+            else launch_bf16<256, 256, 4, 4, 1, 1>(p, stream);
         }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("tree_attn launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
-    if (plan.n_chunks_max > 1) {
-        const int rows = 256 / (p.d / 4);
-        launch_kernel(K_ATTN_COMBINE, tree_attn_bf16_combine_kernel, dim3((unsigned)p.H_kv * ((p.M + rows - 1) / rows), 1, p.B), dim3(256), stream, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) { set_error("tree_attn_combine launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
-    }
     return MCSD_OK;
 }
 

@@ -90,6 +90,10 @@ def test_attn_workspace_and_descriptor_errors(lib):
     assert M.mcsd_attn_workspace_bytes(good_attn_desc()) % 256 == 0
     assert M.mcsd_attn_workspace_bytes(good_attn_desc()) > 0
     assert M.mcsd_attn_workspace_bytes(good_attn_desc(dtype=M.DTYPE_FP32, d=64)) == 0
+    # shapes outside the d = 128 kernel bring no workspace and touch none, however long the cache
+    for d in (8, 64, 96, 256):
+        for kw in (dict(L_stride=16384, B=1), dict(L_stride=2000, B=8), dict(L_stride=0, B=300)):
+            assert M.mcsd_attn_workspace_bytes(good_attn_desc(d=d, **kw)) == 0, (d, kw)
     bufs = M.AttnBufs(C.sizeof(M.AttnBufs), 4096, 4096, 4096, 4096, 4096, 4096, 4096, 4096, 4096, 1 << 40)
     cases = [(dict(N=0), -4), (dict(N=129), -4), (dict(H_q=5), -2), (dict(B=0), -2), (dict(d=130), -3),
              (dict(d=512), -3), (dict(dtype=7), -3), (dict(scale=float("nan")), -2), (dict(L_stride=-1), -2)]

@@ -1,6 +1,6 @@
 """Tree attention with fp32 storage or a head dimension other than 128 against the CPU oracle: head
 dimensions around the paddings (64, 128, 256), row counts around the row tiles, prefixes around the
-16- and 32-key tiles and long enough to be split; the paged cache and a call without a workspace
+16- and 32-key tiles and long enough for many steps; the paged cache and a call without a workspace
 give the same attention."""
 import numpy as np
 import pytest
@@ -42,10 +42,60 @@ def test_against_oracle(dtype, d, B, H_q, H_kv, kconfig, prefix):
     M.mcsd_tree_attn_paged(paged_call.args, paged)
     torch.cuda.synchronize()
     assert torch.equal(paged_call.out, call.out)
-    # without a workspace the keys are not split: the same attention, summed in another order
+    # without a workspace the same attention
     t = call.tensors
     whole = torch.zeros_like(t["out"])
     M.mcsd_tree_attn(M.attn_args(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_len"], t["k_tree"], t["v_tree"], t["parent"],
                                  whole, ai.scale))
     torch.cuda.synchronize()
     assert_attn_close(whole.to(torch.float32).cpu().numpy().astype(np.float64), ref, dtype, "no workspace")
+
+
+@pytest.mark.parametrize("dtype,d,H_q,H_kv,prefix", [("bf16", 64, 32, 8, (200, 2000)), ("bf16", 96, 4, 2, (1500, 1500)), ("bf16", 256, 2, 1, (900, 1100)),
+                                                     ("fp32", 128, 4, 4, (700, 700))])
+def test_no_workspace_is_used_and_the_bits_depend_on_the_inputs_alone(dtype, d, H_q, H_kv, prefix):
+    """A workspace that comes along is not written, of whatever size and alignment; the result has the same
+    bits with it, without it, from the entry point that brings none, and from two streams at once that
+    were handed the same pointer."""
+    w = W.Workload(name="t", index=71, B=2, H_q=H_q, H_kv=H_kv, d=d, dtype=dtype, prefix=prefix, kconfig=(4, 2, 2), V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(d), L_stride=prefix[1] + 500)
+    t = D.make_attn_call(ai).tensors
+    ws = torch.full((64 << 20,), 77, dtype=torch.uint8, device="cuda:0")
+    results = []
+    def args(workspace=None):
+        results.append(torch.zeros_like(t["out"]))
+        return M.attn_args(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_len"], t["k_tree"], t["v_tree"], t["parent"],
+                           results[-1], ai.scale, workspace)
+    for workspace in (None, ws, ws[:1000], ws[64:]):
+        M.mcsd_tree_attn(args(workspace))
+    M.mcsd_tree_attn_static(args())
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    for _ in range(4):
+        for s in streams:
+            a = args(ws)
+            s.wait_stream(torch.cuda.current_stream())
+            M.mcsd_tree_attn(a, stream=s)
+    torch.cuda.synchronize()
+    for r in results[1:]:
+        assert torch.equal(r.view(torch.int16), results[0].view(torch.int16))
+    assert (ws == 77).all()
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale,
+                      O.FP32 if dtype == "fp32" else O.BF16, n_threads=16)
+    assert_attn_close(results[0].to(torch.float32).cpu().numpy().astype(np.float64), ref, dtype, "no workspace")
+
+
+# many units, so that every instantiation is met (the cases above are the small launches)
+@pytest.mark.parametrize("d,B,H_kv,G,kconfig", [
+    (64, 16, 10, 2, (4, 2, 2)), (64, 13, 20, 1, (2, 2)), (64, 15, 10, 4, (4, 2, 2)), (64, 20, 20, 2, (4, 2, 2)), (40, 16, 32, 4, (4, 2, 2)),
+    (72, 16, 10, 2, (4, 2, 2)), (128 - 8, 13, 20, 1, (2, 2)), (96, 15, 20, 2, (4, 2, 2)), (96, 12, 32, 4, (4, 2, 2)),
+    (136, 2, 3, 1, (2, 2)), (200, 10, 10, 1, (2, 2)), (136, 10, 10, 1, (2, 2)), (256, 20, 10, 1, (2, 2)), (248, 13, 20, 1, (2, 2)), (256, 13, 10, 2, (4, 2, 2))])
+def test_every_split_of_the_rows_and_columns(d, B, H_kv, G, kconfig):
+    w = W.Workload(name="t", index=72, B=B, H_q=H_kv * G, H_kv=H_kv, d=d, dtype="bf16", prefix=(0, 70), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(d + B), L_stride=300)
+    call = D.make_attn_call(ai)
+    M.mcsd_tree_attn(call.args)
+    torch.cuda.synchronize()
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
+    assert_attn_close(call.out_numpy(), ref, "bf16", f"d={d} units={B * H_kv} rows={ai.N * G}")
