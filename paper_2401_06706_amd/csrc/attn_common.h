@@ -29,6 +29,7 @@ struct AttnParams {
     int root_row;         // 1: row 0 of the tree block is the root, N counts it
     int R;                // rows per (b, g) in the partial buffers
     int split_bias;       // see split_tiles
+    int even_units, even_n; // units of the launch and 256 / units where one workgroup per CU is wanted, or 0 (see split_tiles)
     int rank_pairs;       // hand the (sequence, segment) pairs out longest first
     int *chunk_of_launch; // workspace word with the chunk_tiles of this launch, or nullptr: chunk_tiles holds
     float scale_log2;     // scale * log2(e)
@@ -98,10 +99,16 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16)
 // The T key tiles of a sequence are cut into n segments of seg tiles (the last one possibly
 // shorter): n = (T + bias) / chunk_tiles, at least 1.  With bias = chunk_tiles / 2 that is
 // T / chunk_tiles rounded to nearest, so a sequence a little longer than a multiple of
-// chunk_tiles does not pay a partial for a sliver; seg < 1.5 chunk_tiles.
-__device__ __forceinline__ void split_tiles(int T, int chunk_tiles, int bias, int *n, int *seg)
+// chunk_tiles does not pay a partial for a sliver; seg < 1.5 chunk_tiles.  A launch of 257..447
+// workgroups leaves the CUs that hold two of them behind: where even_units says so, a sequence whose
+// segments would make it one gets as many as make one workgroup per CU.
+__device__ __forceinline__ void split_tiles(int T, int chunk_tiles, int bias, int even_units, int even_n, int *n, int *seg)
 {
-    const int nn = max(1, (T + bias) / chunk_tiles);
+    int nn = max(1, (T + bias) / chunk_tiles);
+    if (even_units) {
+        const int wgs = nn * even_units;
+        if (wgs > 256 && wgs < 448) nn = even_n;
+    }
     *n = nn;
     *seg = (T + nn - 1) / nn;
 }

@@ -91,6 +91,7 @@ struct AttnPlan {
     int tiles_tree;       // 32-key tiles needed for N tree keys
     int chunk_tiles;      // 32-key tiles per workgroup
     int n_chunks_max;     // grid extent along the key axis
+    int even_units;       // 0, or the units of a launch whose segments are made one per CU by the real lengths (see split_tiles)
     bool chunk_on_device; // the segments are lengthened on the device by the real sequence lengths
     size_t partial_stride_rows; // rows per (b, g) in the partial buffers = n_row_tiles * row_tile
     size_t ws_bytes;

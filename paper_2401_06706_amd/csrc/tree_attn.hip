@@ -203,7 +203,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
                 if (!lens_known) Lb = max(0, min(p.prefix_len[tid / p.n_chunks_max], p.L_stride));
                 const int Tb = (Lb + KT - 1) / KT + p.tiles_tree;
                 int nb, segb;
-                split_tiles(Tb, chunk_tiles, split_bias, &nb, &segb);
+                split_tiles(Tb, chunk_tiles, split_bias, p.even_units, p.even_n, &nb, &segb);
                 my_len = max(0, min(segb, Tb - (tid % p.n_chunks_max) * segb));
                 s_pair_len[tid] = my_len;
                 if (tid % p.n_chunks_max == 0) s_seq_L[tid / p.n_chunks_max] = Lb;
@@ -227,7 +227,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         }
         total_tiles = (L + KT - 1) / KT + p.tiles_tree;
         int n_seg, seg;
-        split_tiles(total_tiles, chunk_tiles, split_bias, &n_seg, &seg);
+        split_tiles(total_tiles, chunk_tiles, split_bias, p.even_units, p.even_n, &n_seg, &seg);
         t_begin = chunk * seg;
         if (t_begin >= total_tiles) return;
         t_end = min(total_tiles, t_begin + seg);
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnParams p, in
     const int chunk_tiles = p.chunk_of_launch ? chunk_of_launch : p.chunk_tiles;
     const int total_tiles = (L + KT - 1) / KT + p.tiles_tree;
     int n_chunks, seg;
-    split_tiles(total_tiles, chunk_tiles, chunk_tiles / 2, &n_chunks, &seg);
+    split_tiles(total_tiles, chunk_tiles, chunk_tiles / 2, p.even_units, p.even_n, &n_chunks, &seg);
     n_chunks = (total_tiles + seg - 1) / seg;      // segments that are not empty
     if (n_chunks <= 1) return;      // the attention kernel wrote the output itself
     const int d4 = threadIdx.x & 31;        // 16-byte piece of the row
@@ -938,19 +938,20 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
         if (fine < least) fine = least;
         if (fine < chunk) chunk = fine;
     }
-    // One launch of 257..447 workgroups leaves the CUs that hold two of them behind: such a plan is
-    // lengthened to one workgroup per CU (one sequence of 8000 keys, 32 heads: 320 workgroups 36.7 us,
-    // 256 workgroups 32.0 us).
-    const long wgs = units * ((total_max + chunk / 2) / chunk);
-    if (pl.variant < 2 && forced_target <= 0 && wgs > 256 && wgs < 448 && units <= 128) {
-        const long n = 256 / units;
-        chunk = ((total_max + n - 1) / n + key_streams - 1) / key_streams * key_streams;
-    }
     const int forced = g_force_chunk_tiles.load();
+    // (see split_tiles.  By the real lengths, on the device: one sequence, 32 heads, a cache of 8192 rows,
+    // 8192 / 5000 / 4000 / 2000 / 1000 keys: segments of 24 tiles 39.4 / 21.2 / 19.7 / 16.3 / 18.6 us, lengthened by
+    // the capacity 28.0 / 21.9 / 20.1 / 18.1 / 17.6, here 28.6 / 20.2 / 19.0 / 15.3 / 17.5; 56 rows, 16 heads, a cache of
+    // 16384: 16384 / 6000 keys 69.0 / 29.8, 41.8 / 19.4, 41.7 / 19.6; two sequences of 8000 keys, 16 heads 40.0, 26.9, 27.6)
+    pl.even_units = pl.variant < 2 && forced_target <= 0 && forced <= 0 && units <= 128 ? (int)units : 0;
     if (forced > 0) chunk = forced;
     if (chunk > total_max) chunk = total_max;
     pl.chunk_tiles = (int)chunk;
     pl.n_chunks_max = (int)((total_max + chunk - 1) / chunk);
+    if (pl.even_units) {        // (no shorter sequence has more segments then; workgroups without one would disturb the spread over the CUs)
+        const long wgs = units * ((total_max + chunk / 2) / chunk);
+        if (wgs > 256 && wgs < 448) pl.n_chunks_max = (int)(256 / units);
+    }
     pl.partial_stride_rows = (size_t)pl.n_row_tiles * pl.row_tile;
     if (pl.n_chunks_max > 1) {
         size_t elems = (size_t)d.B * d.H_kv * pl.n_chunks_max * pl.partial_stride_rows * (size_t)(d.d + 2);
@@ -995,6 +996,8 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
     p.n_row_tiles = plan.n_row_tiles; p.chunk_tiles = plan.chunk_tiles; p.n_chunks_max = plan.n_chunks_max;
     p.tiles_tree = plan.tiles_tree; p.R = (int)plan.partial_stride_rows;
     p.split_bias = plan.chunk_tiles / 2;
+    p.even_units = plan.even_units;
+    p.even_n = plan.even_units ? 256 / plan.even_units : 0;
     p.rank_pairs = d.B * plan.n_chunks_max <= 256 && plan.n_chunks_max > 1 &&
                    (long)d.H_kv * plan.n_row_tiles * plan.n_chunks_max * d.B > 512;
     if (plan.ws_bytes > 0) {

@@ -341,3 +341,21 @@ def test_short_segments_of_small_launches(B, H_q, H_kv, kconfig, prefix, L_strid
     M.mcsd_tree_attn_paged(paged_call.args, paged)
     torch.cuda.synchronize()
     assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,L_stride", [(1, 32, 32, (4, 2, 2), 8200), (2, 16, 16, (4, 2, 2), 8200), (1, 32, 16, (4, 2, 2), 12000), (3, 8, 8, (2, 2), 30000)])
+def test_one_workgroup_per_unit_by_the_real_lengths(B, H_q, H_kv, kconfig, L_stride):
+    """Up to 64 rows per KV head and a cache that would be cut into 257..447 segments, or more when it is
+    full: the sequences get as many as suit their lengths, which may differ within the launch."""
+    for lo, hi in ((0, 40), (900, 1100), (0, 5000), (L_stride - 200, L_stride)):
+        w = wl(H_q=H_q, H_kv=H_kv, kconfig=kconfig, prefix=(lo, hi), B=B)
+        ai = W.gen_attn_inputs(w, np.random.default_rng(B + hi), L_stride=L_stride)
+        check_full(ai, f"one per CU {lo}..{hi} of {L_stride}")
+        if hi > 5000:
+            continue
+        tree = D.make_attn_call(ai)
+        M.mcsd_tree_attn(tree.args)
+        paged_call, paged, _ = D.make_paged_attn_call(tree, ai, 64, seed=B)
+        M.mcsd_tree_attn_paged(paged_call.args, paged)
+        torch.cuda.synchronize()
+        assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
