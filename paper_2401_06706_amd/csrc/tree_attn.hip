@@ -63,8 +63,8 @@ __device__ __forceinline__ int segment_tiles(const AttnParams &p, int lane, int 
     };
     const int units = p.H_kv * p.n_row_tiles;
     const long work = (long)sum(T) * units;
-    const int slots = work > 512 * 128 ? 1024 : (work < 512 * 12 ? 256 : 512);
-    int chunk = max(p.chunk_tiles, (int)((work + slots - 1) / slots));
+    const int slots_log2 = work > 512 * 128 ? 10 : (work < 512 * 12 ? 8 : 9), slots = 1 << slots_log2;
+    int chunk = max(p.chunk_tiles, (int)((work + slots - 1) >> slots_log2));
     if (slots == 1024 && chunk == p.chunk_tiles) return chunk;      // the caches are as full as the host assumed
 #pragma unroll 1
     for (int i = 0; i < 8; ++i) {
@@ -178,7 +178,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
     int b, g, rt, t_begin, t_end, total_tiles, L;
     int chunk_tiles = p.chunk_tiles, split_bias = p.split_bias, len_of_lane = 0;
     const bool lens_known = COOP && p.chunk_of_launch;
-    if (lens_known) {
+    if (__builtin_expect(lens_known, 0)) {      // (out of the way of the launches without it)
         chunk_tiles = segment_tiles(p, lane, &len_of_lane);
         split_bias = chunk_tiles / 2;
         if (tid == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0) *p.chunk_of_launch = chunk_tiles;       // for the merge
@@ -196,14 +196,40 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         rt = blockIdx.y % p.n_row_tiles;
         int chunk = blockIdx.y / p.n_row_tiles;
         const int n_pairs = p.B * p.n_chunks_max;
-        if (p.rank_pairs) {
+        int upto = 0, live = 0;             // segments of the sequences up to number `lane`; of all
+        if (__builtin_expect(lens_known, 0)) {
+            if (lane < p.B) {
+                const int Tl = (len_of_lane + KT - 1) / KT + p.tiles_tree;
+                int nl, segl;
+                split_tiles(Tl, chunk_tiles, split_bias, 0, 0, &nl, &segl);
+                upto = (Tl + segl - 1) / segl;
+            }
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);      // running sum: inside the rows of 16
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);
+            upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);
+            live = __builtin_amdgcn_readlane(upto, 63);
+        }
+        if (__builtin_expect(lens_known && live * p.H_kv * p.n_row_tiles <= 512, 0)) {
+            // All start at once: their order does not matter, but those without a segment come last (among
+            // the others they would leave some CUs with two).  Without the ranking, cache of 16384 rows,
+            // GQA 32/8, 28 nodes, 16384 / 8000 / 2000 / 500 keys 28.6 / 23.2 / 19.3 / 19.3 -> 26.4 / 20.7 / 16.7 / 16.7 us
+            // (1024 workgroups by capacity: 92 / 52 / 26 / 18); four sequences of 400 keys 22.4 -> 19.3 (20.5).
+            const int pair = blockIdx.z * p.n_chunks_max + chunk;
+            if (pair >= live) return;
+            b = __ffsll((long long)__ballot(upto > pair)) - 1;
+            chunk = pair - (b > 0 ? __builtin_amdgcn_readlane(upto, b - 1) : 0);
+            L = __builtin_amdgcn_readlane(len_of_lane, b);
+        } else if (p.rank_pairs) {
             int my_len = 0;
             int Lb = lens_known ? __shfl(len_of_lane, tid / p.n_chunks_max) : 0;
             if (tid < n_pairs) {
                 if (!lens_known) Lb = max(0, min(p.prefix_len[tid / p.n_chunks_max], p.L_stride));
                 const int Tb = (Lb + KT - 1) / KT + p.tiles_tree;
                 int nb, segb;
-                split_tiles(Tb, chunk_tiles, split_bias, p.even_units, p.even_n, &nb, &segb);
+                split_tiles(Tb, chunk_tiles, split_bias, COOP ? 0 : p.even_units, p.even_n, &nb, &segb);
                 my_len = max(0, min(segb, Tb - (tid % p.n_chunks_max) * segb));
                 s_pair_len[tid] = my_len;
                 if (tid % p.n_chunks_max == 0) s_seq_L[tid / p.n_chunks_max] = Lb;
@@ -227,7 +253,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         }
         total_tiles = (L + KT - 1) / KT + p.tiles_tree;
         int n_seg, seg;
-        split_tiles(total_tiles, chunk_tiles, split_bias, p.even_units, p.even_n, &n_seg, &seg);
+        split_tiles(total_tiles, chunk_tiles, split_bias, COOP ? 0 : p.even_units, p.even_n, &n_seg, &seg);
         t_begin = chunk * seg;
         if (t_begin >= total_tiles) return;
         t_end = min(total_tiles, t_begin + seg);
