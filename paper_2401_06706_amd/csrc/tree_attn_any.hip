@@ -80,8 +80,8 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 // first tiles -> epilogue, a step of 64 KB takes 1.2 to 1.5 us.  Measured (d 64, 8 sequences of
 // 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
 // reading the cache again, 1262 us; the keys split over 512 workgroups of four waves, partials in
-// the caller's workspace and a merge launch, 21.0 us; this kernel 19.7 us.  That split is faster only
-// for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 115, 4720 on the
+// the caller's workspace and a merge launch, 21.0 us; this kernel 19.5 us.  That split is faster only
+// for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 112, 4720 on the
 // vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
 // never asked for.
 template <int DP, int DS, int NW, int RH, int MT, int TS>

@@ -209,7 +209,8 @@ __global__ __launch_bounds__(64 * COMMIT_WAVES) void kv_commit_kernel(CommitPara
         }
         int g = lane / vec_per_row, c4 = lane % vec_per_row;
         for (int e0 = 0; e0 < n_vec; e0 += 128) {
-            // two pieces of K and of V requested before the first is stored
+            // Two pieces of K and of V per pass.  (The compiler keeps them in LDS, 64 KB of it, and waits for
+            // the first pair before it requests the second; the figures at the launch are those of this form.)
             uint4 k[2], v[2];
             size_t dst[2];
 #pragma unroll
