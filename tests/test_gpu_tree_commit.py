@@ -372,7 +372,7 @@ def test_kv_commit_with_root_row_matches_oracle(dtype, n_layers, B, H_kv, d, kco
     ("bf16", 9, 8, 128, 4),         # and a layer more
     ("bf16", 3, 7, 200, 3),         # 25 pieces per row, a remainder in every pass
     ("fp32", 2, 2, 512, 2),         # rows of more than 64 pieces
-    ("fp32", 1, 2, 4, 64), ("fp32", 1, 2, 4, 65)])      # the longest path that one launch takes, and one longer
+    ("fp32", 1, 2, 4, 64), ("fp32", 1, 2, 4, 65)])      # the row lengths of the longest path for one launch, and one longer
 def test_kv_commit_in_one_launch_and_in_two(dtype, n_layers, H_kv, d, gamma):
     rng = np.random.default_rng(d + gamma)
     B, Ls, kconfig = 4, 96, (2,) + (1,) * (min(gamma, 16) - 1)
@@ -414,3 +414,49 @@ def test_kv_commit_with_a_count_outside_the_path(root_row, n_layers):
         assert new_L[1] == 5 and fl.tolist() == [0, 64, 0] and nxt[1] == out_tok[1, 0]
         for got, want in ((k[:, ::2], ref[0][:, ::2]), (v[:, ::2], ref[1][:, ::2]), (new_L[::2], ref[2][::2]), (nxt[::2], ref[3][::2])):
             np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("root_row,gamma", [(False, 64), (False, 65), (False, 128), (True, 63), (True, 64), (True, 127)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_kv_commit_of_the_longest_paths(root_row, gamma, paged):
+    """Paths of as many rows as one launch takes (64, the root among them), one more, and the most there
+    are: every lane of the wavefront that looks at them has a row, or has two.  Contiguous and paged."""
+    rng = np.random.default_rng(gamma)
+    B, H_kv, d, N, Ls = 3, 2, 4, 127, 256
+    n_acc = np.array([gamma, gamma - 1, 0], np.int32)
+    L = np.array([3, Ls - gamma - int(root_row), 17], np.int32)             # sequence 1 fits with a row to spare
+    f32 = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    kp, vp = f32(1, B, H_kv, Ls, d), f32(1, B, H_kv, Ls, d)
+    kt, vt = f32(1, B, H_kv, N + int(root_row), d), f32(1, B, H_kv, N + int(root_row), d)
+    paths = rng.integers(0, N, (B, gamma)).astype(np.int32)
+    out_tok = rng.integers(0, 32000, (B, gamma + 1)).astype(np.int32)
+    for broken in (False, True):
+        if broken:                          # an entry outside the tree late in the path ends the copy there
+            paths[0, gamma - 1] = N
+        want = n_acc.copy()
+        want[0] -= int(broken)
+        ref = O.kv_commit(kp, vp, kt, vt, want, paths, out_tok, L, root_row=root_row)
+        if not paged:
+            got_k, got_v, got_L, nxt, fl = run_commit(kp, vp, kt, vt, n_acc, paths, out_tok, L, "fp32", root_row)
+        else:
+            page, per = 32, Ls // 32
+            table = rng.permutation(B * per).reshape(B, per).astype(np.int32)
+            def pool(a):
+                out = np.empty((1, B * per, H_kv, page, d), np.float32)
+                for b in range(B):
+                    for i in range(per):
+                        out[0, table[b, i]] = a[0, b, :, i * page:(i + 1) * page]
+                return torch.from_numpy(out).to(DEV)
+            t_k, t_v, t_L = pool(kp), pool(vp), dev_i32(L)
+            t_nxt, t_fl = (torch.full((B,), -9, dtype=torch.int32, device=DEV) for _ in range(2))
+            args, paged_kv = M.paged_commit_args(t_k, t_v, dev_i32(table), torch.from_numpy(kt).to(DEV), torch.from_numpy(vt).to(DEV),
+                                                 dev_i32(n_acc), dev_i32(paths), dev_i32(out_tok), t_L, t_nxt, t_fl, Ls, root_row=root_row)
+            M.mcsd_kv_commit_paged(args, paged_kv)
+            torch.cuda.synchronize()
+            got_k, got_v = (O.gather_pages(t.cpu().numpy()[0], table, Ls)[None] for t in (t_k, t_v))
+            got_L, nxt, fl = t_L.cpu().numpy(), t_nxt.cpu().numpy(), t_fl.cpu().numpy()
+        np.testing.assert_array_equal(got_k, ref[0])
+        np.testing.assert_array_equal(got_v, ref[1])
+        np.testing.assert_array_equal(got_L, ref[2])
+        np.testing.assert_array_equal(nxt, out_tok[np.arange(B), n_acc])
+        assert fl.tolist() == [64 if broken else 0, 0, 0]
