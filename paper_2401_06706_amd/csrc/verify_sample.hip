@@ -525,8 +525,8 @@ void verify_rows_kernel(VerifyParams p)
                     if (remove && my_tok == tok) { my_q = 0.0; my_q32 = 0.f; }
                     if (uniform(removes && (vanished || (valid && ratio >= 1.0)))) {
                         // Put back, the row holds beta e_q for tokens that had left q and have p = 0.  And the
-                        // token of this round leaves q with some of its p left, or all (so does one that
-                        // only a uniform above 1 rejects): no later round may lower that.
+                        // token just rejected leaves q with some of its p left, or all (so does one that
+                        // only a uniform above 1 rejects): no later rejection may lower that.
 #pragma unroll 1
                         for (int n = vanished ? 0 : i; n <= i; ++n) {
                             const int x = __builtin_amdgcn_readfirstlane(s_tok[n]);
