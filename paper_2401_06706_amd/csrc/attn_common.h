@@ -144,6 +144,48 @@ __device__ __forceinline__ void build_ancestor_masks(const int32_t *parent, int 
     }
 }
 
+// Workgroups start in the order z, y, x.  The (sequence, segment) pairs are handed out longest first (the
+// short last segments of the sequences fill the end of the launch instead of a mostly idle last round
+// of workgroups): pair number `slot` in dispatch order takes the pair of rank `slot` by length.  Done when
+// the pairs fit one workgroup's threads and the launch does not fit the chip at once (two workgroups
+// per CU start together anyway; the ranking is 1.4 us ahead of the first request).
+template <int NT>
+struct PairRanks { int len[NT], of_rank[NT], seq_L[NT]; };
+
+template <int NT, typename LenOf>
+__device__ __forceinline__ void longest_first(const AttnParams &p, PairRanks<NT> &s, int tid, int slot, int chunk_tiles, int split_bias,
+                                              int even_units, LenOf len_of, int *b, int *chunk, int *L)
+{
+    const int n_pairs = p.B * p.n_chunks_max;
+    const int seq = min(tid / p.n_chunks_max, p.B - 1), Lb = len_of(seq);      // (by all lanes: len_of may exchange between them)
+    int my_len = 0;
+    if (tid < n_pairs) {
+        const int Tb = (Lb + KT - 1) / KT + p.tiles_tree;
+        int nb, segb;
+        split_tiles(Tb, chunk_tiles, split_bias, even_units, p.even_n, &nb, &segb);
+        my_len = max(0, min(segb, Tb - (tid % p.n_chunks_max) * segb));
+        s.len[tid] = my_len;
+        if (tid % p.n_chunks_max == 0) s.seq_L[seq] = Lb;
+    }
+    __syncthreads();
+    if (tid < n_pairs) {
+        int rank = 0;
+        for (int j = 0; j < n_pairs; ++j) {
+            const int other = s.len[j];
+            rank += (other > my_len || (other == my_len && j < tid)) ? 1 : 0;
+        }
+        s.of_rank[rank] = tid;
+    }
+    __syncthreads();
+    const int pair = s.of_rank[slot];
+    *b = __builtin_amdgcn_readfirstlane(pair / p.n_chunks_max);       // read from LDS: make it scalar again
+    *chunk = __builtin_amdgcn_readfirstlane(pair % p.n_chunks_max);
+    *L = __builtin_amdgcn_readfirstlane(s.seq_L[*b]);      // already loaded and clamped: no second trip to memory
+}
+
+// bf16, d = 128, more than 64 rows per KV head (tree_attn_shared.hip)
+void launch_attn_shared(const AttnParams &p, dim3 grid, hipStream_t stream, const WalkParams &w);
+
 // fp32 storage and head dimensions other than 128 (tree_attn_any.hip): one launch, no workspace
 int32_t launch_attn_any(const AttnParams &p, hipStream_t stream);
 

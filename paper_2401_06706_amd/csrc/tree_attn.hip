@@ -13,8 +13,8 @@
 //   segment   = a run of consecutive key tiles of a unit, processed by one workgroup
 //               (4 waves): wave (rh, ks) owns 32 rows and every KS-th tile of the run and
 //               runs an independent online softmax with no workgroup barrier in the loop
-//               (32- and 64-row tiles), or four waves of 32 rows walk one key stream together
-//               and share every tile through LDS (128-row tiles, more than 64 rows per KV head).
+//               (32- and 64-row tiles); more than 64 rows per KV head run the kernel of
+//               tree_attn_shared.hip, whose four waves share every tile of one key stream.
 //   The T tiles of a unit are cut into round(T / chunk_tiles) equal segments (at least one):
 //   grid (KV head, segment x row tile, sequence).  The (sequence, segment) pairs are handed
 //   out longest first.  A segment that covers its whole unit writes the output rows itself;
@@ -34,47 +34,6 @@
 namespace mcsd {
 namespace {
 
-// Tiles per segment from the lengths the sequences really have.  The host's plan knows the capacity
-// of the cache only; the compute units hold 512 workgroups at a time, and a launch a little above a
-// multiple of that runs a nearly empty last round.  The segments are made so long that the launch
-// just fits one round; two where a workgroup would walk more than 128 tiles (older and younger
-// workgroups of a unit then even out), one workgroup per CU below 12 tiles (half the partials).
-// Measured, attention and merge, against 1024 workgroups by capacity: one sequence of 16000 keys, GQA
-// 64/8, 84 nodes: 68 against 83 us; 8 x 1000..3000 keys, 28 nodes: 44 against 52 us; one sequence of
-// 8000 keys, 28 nodes: 25 against 39 us.  Every wavefront works it out from the lengths of up to 64 sequences.
-// (*len: the length of sequence number `lane`)
-__device__ __forceinline__ int segment_tiles(const AttnParams &p, int lane, int *len)
-{
-    int T = 0;
-    *len = 0;
-    if (lane < p.B) {
-        *len = max(0, min(p.prefix_len[lane], p.L_stride));
-        T = (*len + KT - 1) / KT + p.tiles_tree;
-    }
-    // sum over the wavefront without a trip through LDS: inside the rows of 16 lanes, then across them
-    auto sum = [](int v) {
-        v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);      // lanes 1 apart
-        v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false);      // 2 apart
-        v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);     // mirror of 8
-        v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);     // mirror of 16
-        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // rows 0, 2 into 1, 3
-        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // and into 2, 3
-        return __builtin_amdgcn_readlane(v, 63);
-    };
-    const int units = p.H_kv * p.n_row_tiles;
-    const long work = (long)sum(T) * units;
-    const int slots_log2 = work > 512 * 128 ? 10 : (work < 512 * 12 ? 8 : 9), slots = 1 << slots_log2;
-    int chunk = max(p.chunk_tiles, (int)((work + slots - 1) >> slots_log2));
-    if (slots == 1024 && chunk == p.chunk_tiles) return chunk;      // the caches are as full as the host assumed
-#pragma unroll 1
-    for (int i = 0; i < 8; ++i) {
-        const int n = lane < p.B ? max(1, (T + chunk / 2) / chunk) : 0;
-        if (sum(n) * units <= slots) break;
-        chunk += (chunk + 15) / 16;
-    }
-    return chunk;
-}
-
 // --------------------------------------------------------------------- MFMA path
 // RH = row groups per workgroup, KS = key streams per workgroup.  Wave (rh, ks) owns query rows
 // [32 rh, 32 (rh+1)) of the workgroup's row tile and the key tiles t_begin + ks, + KS, ... of the
@@ -90,20 +49,10 @@ __device__ __forceinline__ int segment_tiles(const AttnParams &p, int lane, int 
 //   V  global -> registers (a lane reads 8 key rows x 16 contiguous bytes, neighbouring
 //      lanes neighbouring bytes; one tile ahead), in-lane 8x8 transpose of the 16-bit
 //      elements, registers -> the same LDS area -> operand (exchange inside 16-lane groups).
-//
-// COOP (one key stream, several row groups): the waves of the workgroup share every K/V tile.
-// Each wave loads a quarter of the tile and stores it to a double-buffered LDS tile that all
-// waves read their operands from after one workgroup barrier per tile; K in the operand order
-// above, V in its natural order (row pitch 288 bytes) and read with the transposing LDS load,
-// which hands a lane the four keys of one d column that the PV operand needs.  Per wave and
-// tile that is a quarter of the global loads and LDS stores of the private scheme and no
-// in-register transpose, which matters where the matrix cores are the limit (many query rows
-// per KV head).
-template <int RH, int KS, bool PAGED, bool COOP = false>
+template <int RH, int KS, bool PAGED>
 __global__ __launch_bounds__(RH * KS * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
 {
-    static_assert(!COOP || (KS == 1 && RH == 4), "the shared-tile scheme splits a tile over four waves of one key stream");
     // A row of workgroups appended to the grid along y carries the walk of a verification that ran
     // before this launch on the same stream (one wavefront per sequence; the row has H_kv B workgroups
     // of four, for as many sequences as the verification has), when the caller asked for that: a step whose attention needs no merge launch then has
@@ -132,7 +81,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
     __shared__ int s_parent[MCSD_MAX_NODES];
     __shared__ float s_m[KS][ROWS], s_l[KS][ROWS];
     __shared__ float s_mstar[ROWS], s_linv[ROWS];
-    __shared__ int s_pair_len[NT], s_pair_of_rank[NT], s_seq_L[NT];
+    __shared__ PairRanks<NT> s_rank;
 
     // LDS positions (in 16-byte granules inside this wave's area).
     //   K granule (row r, granule c) is the operand of lane (c & 3, r & 15) for (sub = r >> 4, kk = c >> 2):
@@ -157,103 +106,26 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
     //   V load s (0..7): row (s < 4 ? 0 : 16) + 4 lj + (s & 3), granule lc
     const uint32_t k_lane_off = lane * 16;
     const uint32_t v_lane_off = lj * 1024 + lc * 16;
-    // COOP: wave w loads K rows and V rows 8 w .. 8 w + 7 (load j = 0, 1: row 8 w + 4 j + lj, granule lc).
-    //   A buffer is 2048 words of K (operand order) followed by 32 V rows of 72 words.
-    constexpr int COOP_BUF_WORDS = 2048 + KT * 72;
-    static_assert(!COOP || 2 * COOP_BUF_WORDS <= NW * AREA_WORDS, "the two tile buffers live in the epilogue areas");
-    uint32_t coop_kst[2], coop_vst[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int i = 2 * wave + j;                 // K load index of the private scheme
-        coop_kst[j] = 4 * ((lc >> 2) * 64 + (lc & 3) * 16 + ((4 * (i & 3) + lj) ^ lc) + (i >> 2) * 256);
-        coop_vst[j] = 2048 + (4 * i + lj) * 72 + lc * 4;
-    }
-    //   transposing read for (sub, nt): the 16 lanes of a group point at keys 16 sub + 4 lj + (lc >> 2),
-    //   d columns 16 nt + 4 (lc & 3) .. + 3; lane lc receives column 16 nt + lc of keys 16 sub + 4 lj + 0..3
-    const uint32_t coop_vld = 2048 + (4 * lj + (lc >> 2)) * 72 + (lc & 3) * 2;     // + sub 16 x 72 + nt 8 words
     const float c2 = p.scale_log2;      // >= 0 (checked by the host)
     const uint16_t *qb = static_cast<const uint16_t *>(p.q);
 
     // ---- this workgroup's segment: unit (b, g, rt), tiles [t_begin, t_end) of total_tiles
     int b, g, rt, t_begin, t_end, total_tiles, L;
-    int chunk_tiles = p.chunk_tiles, split_bias = p.split_bias, len_of_lane = 0;
-    const bool lens_known = COOP && p.chunk_of_launch;
-    if (__builtin_expect(lens_known, 0)) {      // (out of the way of the launches without it)
-        chunk_tiles = segment_tiles(p, lane, &len_of_lane);
-        split_bias = chunk_tiles / 2;
-        if (tid == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0) *p.chunk_of_launch = chunk_tiles;       // for the merge
-    }
     bool direct;
     size_t part_row;                    // first row of this segment's partial in the workspace
     {
-        // Workgroups start in the order z, y, x.  The (sequence, chunk) pairs are handed out
-        // longest first (the short last chunks of the sequences fill the end of the launch
-        // instead of a mostly idle last wave of workgroups): pair number r in dispatch order
-        // takes the pair of rank r by length.  Done when the pairs fit one workgroup's threads and the
-        // launch does not fit the chip at once (two workgroups per CU start together anyway; the
-        // ranking is 1.4 us ahead of the first request).
+        // (the ranking, which waits for every length, only where the launch does not fit the chip at once)
         g = blockIdx.x; b = blockIdx.z;
         rt = blockIdx.y % p.n_row_tiles;
         int chunk = blockIdx.y / p.n_row_tiles;
-        const int n_pairs = p.B * p.n_chunks_max;
-        int upto = 0, live = 0;             // segments of the sequences up to number `lane`; of all
-        if (__builtin_expect(lens_known, 0)) {
-            if (lane < p.B) {
-                const int Tl = (len_of_lane + KT - 1) / KT + p.tiles_tree;
-                int nl, segl;
-                split_tiles(Tl, chunk_tiles, split_bias, 0, 0, &nl, &segl);
-                upto = (Tl + segl - 1) / segl;
-            }
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);      // running sum: inside the rows of 16
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);
-            upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);
-            live = __builtin_amdgcn_readlane(upto, 63);
-        }
-        if (__builtin_expect(lens_known && live * p.H_kv * p.n_row_tiles <= 512, 0)) {
-            // All start at once: their order does not matter, but those without a segment come last (among
-            // the others they would leave some CUs with two).  Without the ranking, cache of 16384 rows,
-            // GQA 32/8, 28 nodes, 16384 / 8000 / 2000 / 500 keys 28.6 / 23.2 / 19.3 / 19.3 -> 26.4 / 20.7 / 16.7 / 16.7 us
-            // (1024 workgroups by capacity: 92 / 52 / 26 / 18); four sequences of 400 keys 22.4 -> 19.3 (20.5).
-            const int pair = blockIdx.z * p.n_chunks_max + chunk;
-            if (pair >= live) return;
-            b = __ffsll((long long)__ballot(upto > pair)) - 1;
-            chunk = pair - (b > 0 ? __builtin_amdgcn_readlane(upto, b - 1) : 0);
-            L = __builtin_amdgcn_readlane(len_of_lane, b);
-        } else if (p.rank_pairs) {
-            int my_len = 0;
-            int Lb = lens_known ? __shfl(len_of_lane, tid / p.n_chunks_max) : 0;
-            if (tid < n_pairs) {
-                if (!lens_known) Lb = max(0, min(p.prefix_len[tid / p.n_chunks_max], p.L_stride));
-                const int Tb = (Lb + KT - 1) / KT + p.tiles_tree;
-                int nb, segb;
-                split_tiles(Tb, chunk_tiles, split_bias, COOP ? 0 : p.even_units, p.even_n, &nb, &segb);
-                my_len = max(0, min(segb, Tb - (tid % p.n_chunks_max) * segb));
-                s_pair_len[tid] = my_len;
-                if (tid % p.n_chunks_max == 0) s_seq_L[tid / p.n_chunks_max] = Lb;
-            }
-            __syncthreads();
-            if (tid < n_pairs) {
-                int rank = 0;
-                for (int j = 0; j < n_pairs; ++j) {
-                    const int lj2 = s_pair_len[j];
-                    rank += (lj2 > my_len || (lj2 == my_len && j < tid)) ? 1 : 0;
-                }
-                s_pair_of_rank[rank] = tid;
-            }
-            __syncthreads();
-            const int pair = s_pair_of_rank[blockIdx.z * p.n_chunks_max + chunk];
-            b = __builtin_amdgcn_readfirstlane(pair / p.n_chunks_max);       // read from LDS: make it scalar again
-            chunk = __builtin_amdgcn_readfirstlane(pair % p.n_chunks_max);
-            L = __builtin_amdgcn_readfirstlane(s_seq_L[b]);      // already loaded and clamped: no second trip to memory
-        } else {
-            L = lens_known ? __builtin_amdgcn_readlane(len_of_lane, b) : max(0, min(p.prefix_len[b], p.L_stride));
-        }
+        if (p.rank_pairs)
+            longest_first(p, s_rank, tid, (int)(blockIdx.z * p.n_chunks_max) + chunk, p.chunk_tiles, p.split_bias, p.even_units,
+                          [&](int seq) { return max(0, min(p.prefix_len[seq], p.L_stride)); }, &b, &chunk, &L);
+        else
+            L = max(0, min(p.prefix_len[b], p.L_stride));
         total_tiles = (L + KT - 1) / KT + p.tiles_tree;
         int n_seg, seg;
-        split_tiles(total_tiles, chunk_tiles, split_bias, COOP ? 0 : p.even_units, p.even_n, &n_seg, &seg);
+        split_tiles(total_tiles, p.chunk_tiles, p.split_bias, p.even_units, p.even_n, &n_seg, &seg);
         t_begin = chunk * seg;
         if (t_begin >= total_tiles) return;
         t_end = min(total_tiles, t_begin + seg);
@@ -354,58 +226,9 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
                 vcur[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, v_lane_off + ((s < 4) ? 0 : 4096) + (s & 3) * 256, r.off, 0);
         };
 
-        // Paged cache, COOP: the block-table entry of a tile is read one step before the tile is
-        // requested, ahead of the workgroup barrier.  Scalar loads share the LDS counter and
-        // return out of order, so using one right after issuing it would drain every LDS read in
-        // flight; at the barrier that wait is made anyway.  The page and the row inside it of the
-        // tile that is looked up next advance by one tile per step (no division in the loop).
-        int ahead_page = 0, ahead_row = 0;          // of the tile whose entry is read next
-        int blk_ahead = -1, row_ahead = 0;          // entry and row-in-page read last
-        auto table_lookup_next = [&](int tt) {      // tt = index of that tile
-            row_ahead = ahead_row;
-            blk_ahead = (PAGED && tt < tilesP && tt < t_end) ? (int)block_table_c[(size_t)b * p.max_pages + ahead_page] : -1;
-            ahead_row += KT;
-            if (ahead_row >= p.page_size) { ahead_row = 0; ++ahead_page; }
-        };
-        // COOP: this wave's quarter of both tiles (two K and two V requests)
-        auto load_kv_coop = [&](const TileRef &r, const int st) {
-            __amdgpu_buffer_rsrc_t rk = r.tree ? rs_ktre : rs_kpre;
-            __amdgpu_buffer_rsrc_t rv = r.tree ? rs_vtre : rs_vpre;
-            if (PAGED && r.paged) {
-                rk = make_rsrc(static_cast<const char *>(p.k_prefix) + r.page_off, (uint32_t)r.nvalid * (D * 2));
-                rv = make_rsrc(static_cast<const char *>(p.v_prefix) + r.page_off, (uint32_t)r.nvalid * (D * 2));
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                kraw[2 * st + j] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane_off + (2 * wave + j) * 1024, r.off, 0);
-                vcur[2 * st + j] = __builtin_amdgcn_raw_buffer_load_b128(rv, k_lane_off + (2 * wave + j) * 1024, r.off, 0);
-            }
-        };
-
         int t = t_begin + ks;
-        // (read before the first K/V requests, as inside the loop: the wait at the loop top is the
-        // longer of the two paths into it)
-        if (COOP && PAGED) {
-            ahead_page = ((t + 3) * KT) / p.page_size;
-            ahead_row = ((t + 3) * KT) % p.page_size;
-            table_lookup_next(t + 3);
-        }
-        if (COOP) {
-            // the first tile goes to its LDS buffer here, every later one inside the step before it;
-            // requests run two to three tiles ahead of their use
-            load_kv_coop(tile_ref(t), 0);
-            load_kv_coop(tile_ref(t + 1), 1);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                *reinterpret_cast<u32x4 *>(s_big + coop_kst[j]) = kraw[j];
-                *reinterpret_cast<u32x4 *>(s_big + coop_vst[j]) = vcur[j];
-            }
-            load_kv_coop(tile_ref(t + 2), 0);
-        } else {
-            load_k(tile_ref(t));
-            load_v(tile_ref(t));
-        }
-        const bool wave_active = !COOP || row0 + WROWS * rh < p.M;     // a wave whose rows all lie past M only helps to load
+        load_k(tile_ref(t));
+        load_v(tile_ref(t));
         // the masks are needed from the first tree tile on; built while the first loads are in flight
         if (t_end > tilesP) {
             build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
@@ -420,154 +243,19 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
             r.off = t * TILE_BYTES; r.nvalid = KT; r.tree = false; r.tt = 0; r.page_off = 0; r.paged = false;
             return r;
         };
-        auto tile_step = [&](const int t, auto stage, auto plain) __attribute__((always_inline)) {
-            constexpr int ST = decltype(stage)::value;      // COOP: register stage and LDS buffer of this tile
+        auto tile_step = [&](const int t, auto plain) __attribute__((always_inline)) {
             constexpr bool PLAIN = decltype(plain)::value;
             const TileRef cur = PLAIN ? plain_ref(t) : tile_ref(t);
             // Both K and V run one tile ahead of their use: K(t) goes from its load registers to LDS
             // (operand order) and K(t + KS) is requested into the same registers; V(t + KS) is
             // requested further down, as soon as V(t) has left its registers.
-            if (COOP) {
-                // Tile t is in buffer t & 1 once every wave has passed this barrier; tile t + 1 goes
-                // from its registers to the other buffer while the matrix cores work on QK, and
-                // tile t + 3 is requested into the registers that frees.  The other buffer is free:
-                // it held tile t - 1, whose last read precedes every wave's arrival here.  One
-                // barrier per tile, and no wave waits for memory or for its LDS stores at it.
-                const uint32_t *cb = s_big + ST * COOP_BUF_WORDS;
-                uint32_t *nb = s_big + (ST ^ 1) * COOP_BUF_WORDS;
-                const int blk_next = blk_ahead, row_next = row_ahead;
-                if (PAGED) table_lookup_next(t + 4);
-                __syncthreads();
-                typedef short v4i16 __attribute__((ext_vector_type(4)));
-                typedef v4i16 __attribute__((address_space(3))) *lds_v4i16_ptr;
-                f32x4 sacc[2][MT];
-                if (wave_active) {
-                    bf16x8 kop[4][2];
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) {
-                        kop[kk][0] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(cb + 4 * kld_pos[kk]));
-                        kop[kk][1] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(cb + 4 * (kld_pos[kk] + 256)));
-                    }
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        sacc[0][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                        sacc[1][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            sacc[0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[kk][0], qreg[mt][kk], sacc[0][mt], 0, 0, 0);
-                            sacc[1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[kk][1], qreg[mt][kk], sacc[1][mt], 0, 0, 0);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    *reinterpret_cast<u32x4 *>(nb + coop_kst[j]) = kraw[2 * (ST ^ 1) + j];
-                    *reinterpret_cast<u32x4 *>(nb + coop_vst[j]) = vcur[2 * (ST ^ 1) + j];
-                }
-                load_kv_coop(PLAIN && !PAGED ? plain_ref(t + 3) : tile_ref_blk(t + 3, blk_next, row_next), ST ^ 1);
-                if (!wave_active) return;
-                // V^T operands by transposing LDS reads, requested now: they arrive during the first softmax
-                bf16x8 vop[8];
-#pragma unroll
-                for (int nt = 0; nt < 8; ++nt) {
-                    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(cb + coop_vld + nt * 8));
-                    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(cb + coop_vld + 16 * 72 + nt * 8));
-                    vop[nt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                }
-                const bool masked = !PLAIN && (cur.nvalid < KT || cur.tree);
-                uint32_t vis[MT];
-                float lmax[MT];
-                bool raise = false;
-                settle_scores(sacc[0][0], sacc[0][1], sacc[1][0], sacc[1][1]);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    vis[mt] = 0xffffffffu;
-                    if (masked) {
-                        const int node_m = min(row0 + WROWS * rh + 16 * mt + lc, p.M - 1) / p.G;
-                        if (cur.tree) vis[mt] = s_anc[node_m][cur.tt];
-                        if (cur.nvalid < KT) vis[mt] &= (1u << cur.nvalid) - 1u;
-#pragma unroll
-                        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (!((vis[mt] >> (16 * sub + 4 * lj + i)) & 1u)) sacc[sub][mt][i] = -INFINITY;
-                    }
-                    // online softmax with a lazily raised running max (scaled, base-2 domain)
-                    const float mr = max_of_scores(sacc[0][mt], sacc[1][mt]);
-                    lmax[mt] = (mr == -INFINITY) ? -INFINITY : mr * c2;
-                    raise |= lmax[mt] > m_used[mt] + RESCALE_GAP;
-                }
-                // one test for both row tiles: everything from here to the end of the step is one
-                // straight run, in which the scheduler can place the vector work of one row tile
-                // between the matrix instructions of the other
-                if (__any(raise)) {
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        float rm = lmax[mt];
-                        rm = fmaxf(rm, __shfl_xor(rm, 16));
-                        rm = fmaxf(rm, __shfl_xor(rm, 32));
-                        const float m_new = fmaxf(m_used[mt], rm);
-                        const float alpha = fast_exp2(m_used[mt] - m_new);
-                        m_used[mt] = m_new;
-                        l_part[mt] *= alpha;
-#pragma unroll
-                        for (int nt = 0; nt < 8; ++nt) oacc[nt][mt] *= alpha;
-                    }
-                }
-                // weights of one row tile: p = 2^(s c2 - m), masked keys 0; returns the lane's share of the row sum
-                auto weights = [&](const int mt, bf16x8 &pop) __attribute__((always_inline)) {
-                    float pv[8];
-#pragma unroll
-                    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) pv[4 * sub + i] = fast_exp2(fmaf(sacc[sub][mt][i], c2, -m_used[mt]));
-                    if (masked) {
-                        // also covers scale == 0, where a masked score can not be told apart by its value
-#pragma unroll
-                        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (!((vis[mt] >> (16 * sub + 4 * lj + i)) & 1u)) pv[4 * sub + i] = 0.f;
-                    }
-                    const u32x4 pk = {pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]), pack_bf16(pv[4], pv[5]), pack_bf16(pv[6], pv[7])};
-                    pop = __builtin_bit_cast(bf16x8, pk);
-                    return ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
-                };
-                // A wave issues in order, and vector instructions placed behind a matrix instruction
-                // run while the matrix pipe works on it.  So: the weights of the first row tile; then
-                // its eight PV matrix instructions, each followed by a share of the second row tile's
-                // weights; then the second row tile's PV.  (O^T[d][row] += sum_key V[key][d] P[row][key])
-                static_assert(MT == 2, "the schedule below is written for two row tiles per wave");
-                bf16x8 pop0, pop1;
-                const float sum0 = weights(0, pop0);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int nt = 0; nt < 8; ++nt)
-                    oacc[nt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[nt], pop0, oacc[nt][0], 0, 0, 0);
-                const float sum1 = weights(1, pop1);
-                l_part[0] += sum0;
-                if (!masked) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x402, 4, 0);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int nt = 0; nt < 8; ++nt)
-                    oacc[nt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[nt], pop1, oacc[nt][1], 0, 0, 0);
-                l_part[1] += sum1;
-                return;
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    *reinterpret_cast<u32x4 *>(area + 4 * (kst_pos[i & 3] + (i >> 2) * 256)) = kraw[i];
-                load_k(PLAIN && !PAGED ? plain_ref(t + KS) : tile_ref(t + KS));
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
+            for (int i = 0; i < 8; ++i)
+                *reinterpret_cast<u32x4 *>(area + 4 * (kst_pos[i & 3] + (i >> 2) * 256)) = kraw[i];
+            load_k(PLAIN && !PAGED ? plain_ref(t + KS) : tile_ref(t + KS));
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
             // S^T[key][row] = sum_d K[key][d] Q[row][d]   (raw, the softmax scale is applied in the exponent)
             f32x4 sacc[2][MT];
@@ -693,36 +381,11 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
         };
-        if (COOP) {
-            // Tiles alternate between the two register stages / LDS buffers.  The pair loop has no
-            // branch around its second half: with one, the wait for a stage's data at the top of
-            // the loop would have to cover the path on which no younger loads are in flight, that
-            // is, wait for everything.  An odd last tile is handled after the loop.
-            // The bulk of a long contiguous prefix goes through the plain step: while t + 4 is
-            // still a whole prefix tile of this segment, so are t, t + 1 and the two tiles requested
-            // during the pair.
-            {
-                const int t_plain = min(t_end, L / KT);
-                // (the loop, 4.5 KB, starts on an instruction-cache line: 213.7 us against 216.1 us for the
-                // long-prompt GQA batch where it happened not to)
-                asm volatile(".p2align 6");
-                for (; t + 4 < t_plain; t += 2) {
-                    tile_step(t, std::integral_constant<int, 0>(), std::true_type());
-                    tile_step(t + 1, std::integral_constant<int, 1>(), std::true_type());
-                }
-            }
-            for (; t + 1 < t_end; t += 2) {
-                tile_step(t, std::integral_constant<int, 0>(), std::false_type());
-                tile_step(t + 1, std::integral_constant<int, 1>(), std::false_type());
-            }
-            if (t < t_end) tile_step(t, std::integral_constant<int, 0>(), std::false_type());
-        } else {
-            {
-                const int t_plain = min(t_end, L / KT);
-                for (; t + KS < t_plain; t += KS) tile_step(t, std::integral_constant<int, 0>(), std::true_type());
-            }
-            for (; t < t_end; t += KS) tile_step(t, std::integral_constant<int, 0>(), std::false_type());
+        {
+            const int t_plain = min(t_end, L / KT);
+            for (; t + KS < t_plain; t += KS) tile_step(t, std::true_type());
         }
+        for (; t < t_end; t += KS) tile_step(t, std::false_type());
 
         // ---- epilogue: merge the key streams.  (m, l) per row through LDS; O in two halves of d:
         // every wave stores its rescaled half as float4 rows [row][68] in its own area, then all
@@ -1045,11 +708,11 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         if (paged) {
             if (plan.variant == 0) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<1, 4, true>, grid, dim3(256), stream, p, mw);
             else if (plan.variant == 1) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<2, 2, true>, grid, dim3(256), stream, p, mw);
-            else launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<4, 1, true, true>, grid, dim3(256), stream, p, mw);
+            else launch_attn_shared(p, grid, stream, mw);
         } else {
             if (plan.variant == 0) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<1, 4, false>, grid, dim3(256), stream, p, mw);
             else if (plan.variant == 1) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<2, 2, false>, grid, dim3(256), stream, p, mw);
-            else launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<4, 1, false, true>, grid, dim3(256), stream, p, mw);
+            else launch_attn_shared(p, grid, stream, mw);
         }
         e = hipGetLastError();
         if (e != hipSuccess) { set_error("tree_attn_mfma launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
