@@ -139,6 +139,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         // Q operand, held in registers: lane (lj, lc) has Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. +7].
         // Lanes past the last row repeat it (their results are not written): nothing looks at the
         // values here, so that the first K/V requests go out right behind these loads.
+        const int my_parent = t_end > tilesP ? parent_of_thread(p, b) : -1;
         bf16x8 qreg[MT][4];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -231,7 +232,7 @@ void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
         load_v(tile_ref(t));
         // the masks are needed from the first tree tile on; built while the first loads are in flight
         if (t_end > tilesP) {
-            build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+            build_ancestor_masks(p, my_parent, s_anc, s_parent);
             __syncthreads();
         }
         // PLAIN (a promise of the caller): tile t and the tile requested during this step are whole

@@ -112,48 +112,71 @@ void tree_attn_bf16_kernel(AttnParams p)
     const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
     const int row0 = blockIdx.x / p.H_kv * ROWS, d0 = blockIdx.y * DS;
 
-    const int L = max(0, min(p.prefix_len[b], p.L_stride));
-    const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
+    const int len = p.prefix_len[b];
+    const int my_parent = parent_of_thread(p, b);
     const uint32_t row_bytes = (uint32_t)p.d * 2u;
 
-    // load i of a thread: granule tid + NT i of the step's TS x 32 rows, row-major
-    uint32_t k_off[NL], v_off[NV];
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int gid = tid + NT * i, r = (gid / GR) % KT, c = gid % GR;
-        k_off[i] = (8 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int gid = tid + NT * i, r = (gid / GV) % KT, c = gid % GV;
-        v_off[i] = (d0 + 8 * c < p.d) ? (uint32_t)r * row_bytes + 2u * d0 + 16u * c : OFF_NOWHERE;
-    }
+    // Load i of a thread: granule tid + NT i of the step's TS x 32 rows, row-major, that is column granule c of
+    // row r0 + i (NT / GR).  Columns past d are requested beyond every extent.
+    static_assert(NT % GR == 0 && NT % GV == 0 && (NT / GR % KT == 0 || KT % (NT / GR) == 0) && (NT / GV % KT == 0 || KT % (NT / GV) == 0), "rows of a load");
+    const uint32_t k_col = 8 * (tid % GR) < p.d ? 16u * (tid % GR) : OFF_NOWHERE;
+    const uint32_t v_col = d0 + 8 * (tid % GV) < p.d ? 2u * d0 + 16u * (tid % GV) : OFF_NOWHERE;
+    const uint32_t k_off = k_col == OFF_NOWHERE ? k_col : k_col + tid / GR * row_bytes, k_off_tile = k_col == OFF_NOWHERE ? k_col : k_col + tid / GR % KT * row_bytes;
+    const uint32_t v_off = v_col == OFF_NOWHERE ? v_col : v_col + tid / GV * row_bytes, v_off_tile = v_col == OFF_NOWHERE ? v_col : v_col + tid / GV % KT * row_bytes;
     u32x4 kraw[NL], vraw[NV];
-    auto request = [&](int t0) __attribute__((always_inline)) {
-        auto source = [&](int granule) __attribute__((always_inline)) {       // one tile per wave and load
-            return tile_source<KT>(p, b, g, L, tiles_prefix, t0 + granule / KT, t_end, row_bytes);
-        };
-        if constexpr (DS == DP) {
+    // A step of prefix tiles of a contiguous cache: one resource over the sequence's rows (those past the
+    // last one read as zero), scalar offsets.
+    const size_t kv_head = (size_t)b * p.H_kv + g, slab = kv_head * (size_t)p.L_stride * row_bytes;
+    auto request_prefix = [&](int t0, int rows) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rk = make_rsrc(static_cast<const char *>(p.k_prefix) + slab, (uint32_t)rows * row_bytes);
+        const __amdgpu_buffer_rsrc_t rv = make_rsrc(static_cast<const char *>(p.v_prefix) + slab, (uint32_t)rows * row_bytes);
+        const uint32_t at = (uint32_t)t0 * (KT * row_bytes);
 #pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const TileSrc s = source((wave * 64 + NT * i) / GR);
-                kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), k_off[i], 0, 0);
-                vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), v_off[i], 0, 0);
-            }
-        } else {
+        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off, at + i * (NT / GR) * row_bytes, 0);
 #pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const TileSrc s = source((wave * 64 + NT * i) / GR);
-                kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.kb, s.bytes), k_off[i], 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const TileSrc s = source((wave * 64 + NT * i) / GV);
-                vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(s.vb, s.bytes), v_off[i], 0, 0);
-            }
-        }
+        for (int i = 0; i < NV; ++i) vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off, at + i * (NT / GV) * row_bytes, 0);
     };
-    request(0);
+    // The first step's tiles are asked for before the length is there, as if the cache were full: all rows
+    // of the slab may be read, and a sequence shorter than a step requests its own again below.
+    const bool contiguous = !p.block_table;
+    const bool ahead = contiguous && p.L_stride >= TS * KT;
+    if (ahead) request_prefix(0, p.L_stride);
+
+    const int L = max(0, min(len, p.L_stride));
+    const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
+    // The other steps (a paged cache, the end of the prefix, the tree).  Lane j works out where tile j of the step lies;
+    // a wave's share of a load lies in one tile.  The block-table entries of a step are read one step
+    // before it.  Tiles at or past t_end are empty, which keeps every request unconditional.
+    int blk = 0;
+    auto look_up = [&](int t0) __attribute__((always_inline)) {
+        const int t = t0 + (lane & (TS - 1));
+        if (!contiguous && t < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + (unsigned)(t * KT) / (unsigned)p.page_size];
+    };
+    auto request_any = [&](int t0) __attribute__((always_inline)) {
+        const int t = t0 + (lane & (TS - 1)), key = t * KT, node = key - tiles_prefix * KT;
+        const bool tree = t >= tiles_prefix;
+        size_t row = kv_head * (size_t)p.L_stride + (size_t)key;
+        if (!contiguous)        // (an entry outside the pool never leaves it)
+            row = ((size_t)min(max(blk, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (unsigned)key % (unsigned)p.page_size;
+        if (tree) row = kv_head * (size_t)p.N + (size_t)node;
+        const int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
+        const size_t at = t >= t_end ? 0 : row * row_bytes;
+        const int lo = (int)(uint32_t)at, hi = (int)(uint32_t)(at >> 32);
+        auto tile = [&](const void *prefix, const void *tree_block, int row_of_step) __attribute__((always_inline)) {
+            const int j = row_of_step / KT;
+            const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
+            return make_rsrc(static_cast<const char *>(t0 + j >= tiles_prefix ? tree_block : prefix) + off, (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes);
+        };
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, (wave * 64 + NT * i) / GR), k_off_tile, i * (NT / GR) % KT * row_bytes, 0);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, (wave * 64 + NT * i) / GV), v_off_tile, i * (NT / GV) % KT * row_bytes, 0);
+    };
+    look_up(0);
+    if (!ahead || L < TS * KT) request_any(0);
+    look_up(TS);
 
     // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
     bf16x8 qreg[MT][NKK];
@@ -169,7 +192,7 @@ void tree_attn_bf16_kernel(AttnParams p)
             qreg[mt][kk] = __builtin_bit_cast(bf16x8, v);
         }
     }
-    build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+    build_ancestor_masks(p, my_parent, s_anc, s_parent);
 
     f32x4 oacc[NNT][MT];
     float m_used[MT], l_part[MT];
@@ -185,7 +208,10 @@ void tree_attn_bf16_kernel(AttnParams p)
     typedef short v4i16 __attribute__((ext_vector_type(4)));
     typedef v4i16 __attribute__((address_space(3))) *lds_v4i16_ptr;
 
-    for (int t0 = 0; t0 < t_end; t0 += TS) {
+    // PLAIN (a promise of the caller): the TS tiles of this step are whole prefix tiles, and those of the next
+    // one prefix tiles, of a contiguous cache.
+    auto step = [&](const int t0, auto plain) __attribute__((always_inline)) {
+        constexpr bool PLAIN = decltype(plain)::value;
         __syncthreads();                    // the last step's operands (and the masks) have been read (written)
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
@@ -197,12 +223,14 @@ void tree_attn_bf16_kernel(AttnParams p)
             const int gid = tid + NT * i, c = gid % GV, row = gid / GV;
             *reinterpret_cast<u32x4 *>(s_big + row / KT * STREAM_WORDS + KT * PK + row % KT * PV + 4 * c) = vraw[i];
         }
-        request(t0 + TS);
+        if (PLAIN) request_prefix(t0 + TS, L);
+        else { request_any(t0 + TS); look_up(t0 + 2 * TS); }
         __syncthreads();
-        if (!wave_active) continue;
+        if (!wave_active) return;
+#pragma unroll 1
         for (int ts = ks; ts < TS; ts += KS) {
             const int t = t0 + ts;
-            if (t >= t_end) break;
+            if (!PLAIN && t >= t_end) break;
             const uint32_t *kt = s_big + ts * STREAM_WORDS, *vt = kt + KT * PK;
             f32x4 sacc[2][MT];
 #pragma unroll
@@ -218,8 +246,8 @@ void tree_attn_bf16_kernel(AttnParams p)
                 }
             }
             // lane (lj, lc): row 16 mt + lc, keys 16 sub + 4 lj + i
-            const bool tree = t >= tiles_prefix;
-            const int nvalid = tree ? KT : min(KT, L - t * KT);          // (a tree tile's mask ends with the tree)
+            const bool tree = !PLAIN && t >= tiles_prefix;
+            const int nvalid = PLAIN || tree ? KT : min(KT, L - t * KT);          // (a tree tile's mask ends with the tree)
             // (whole prefix tiles, nearly all of them, pay nothing for the masks)
             const bool masked = tree || nvalid < KT;
             uint32_t vis[MT];
@@ -298,7 +326,11 @@ void tree_attn_bf16_kernel(AttnParams p)
                 }
             }
         }
-    }
+    };
+    int t0 = 0;
+    if (contiguous)
+        for (; (t0 + TS) * KT <= L && t0 + 2 * TS <= tiles_prefix; t0 += TS) step(t0, std::true_type());
+    for (; t0 < t_end; t0 += TS) step(t0, std::false_type());
 
     // ---- epilogue: merge the key streams in LDS, then write whole rows
 #pragma unroll
@@ -378,6 +410,7 @@ void tree_attn_f32_kernel(AttnParams p)
     const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
     const int row0 = blockIdx.x / p.H_kv * ROWS, d0 = blockIdx.y * DS;
 
+    const int my_parent = parent_of_thread(p, b);
     const int L = max(0, min(p.prefix_len[b], p.L_stride));
     const int tiles_prefix = (L + KW - 1) / KW, t_end = tiles_prefix + (p.N + KW - 1) / KW;
     const uint32_t row_bytes = (uint32_t)p.d * 4u;
@@ -424,7 +457,7 @@ void tree_attn_f32_kernel(AttnParams p)
             if (r < p.M && 16 * kk + 4 * lj < p.d) qreg[kk] = *reinterpret_cast<const f32x4 *>(src + 16 * kk + 4 * lj);
         }
     }
-    build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+    build_ancestor_masks(p, my_parent, s_anc, s_parent);
     __syncthreads();
 
     f32x4 oacc[NB][4];

@@ -166,6 +166,7 @@ void tree_attn_shared_kernel(AttnParams p, WalkParams w)
     // (their results are not written): nothing looks at the values here, so that the first K/V requests
     // go out right behind these loads.
     const int my_row = min(row0 + l32, p.M - 1), my_node = my_row / p.G;
+    const int my_parent = t_end > tilesP ? parent_of_thread(p, b) : -1;
     bf16x8 qreg[8];
     {
         const uint16_t *src = static_cast<const uint16_t *>(p.q) + (((size_t)b * p.N + my_node) * p.H_q + (size_t)g * p.G + my_row % p.G) * D + 8 * h;
@@ -285,7 +286,7 @@ void tree_attn_shared_kernel(AttnParams p, WalkParams w)
     const bool wave_active = row0 < p.M;        // a wave whose rows all lie past M only helps to load
     // the masks are needed from the first tree tile on; built while the first loads are in flight
     if (t_end > tilesP) {
-        build_ancestor_masks(p.parent + (p.parent_per_seq ? (size_t)b * (p.N - p.root_row) : 0), p.N, p.root_row, s_anc, s_parent);
+        build_ancestor_masks(p, my_parent, s_anc, s_parent);
         __syncthreads();
     }
     // PLAIN (a promise of the caller): tile t and the tile requested during this step are whole
