@@ -71,16 +71,19 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 
 // Workgroup of NW waves, one unit (sequence, KV head, row tile) with all of its keys, DS of the output
 // columns.  Wave (rh, ks) owns 16 MT query rows and every KS-th tile; the TS tiles of a step are loaded
-// by all threads together, one step ahead in registers, and go through LDS in their natural order
+// one step ahead into registers, by all threads together or, where every wave has a tile to itself, by
+// that wave without a barrier in the loop, and go through LDS in their natural order
 // with row pitches that keep all accesses free of bank conflicts (K: 4 words, V: 8 words past a
 // multiple of 32).  V is read back with the transposing LDS load.  The streams meet in LDS at the
 // end: no memory besides the arguments, so that calls on several streams share nothing, and the
 // bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any.)
-// Bound by latency, not bandwidth, at the sizes it meets: about 8 us are the chain prefix length ->
-// first tiles -> epilogue, a step of 64 KB takes 1.2 to 1.5 us.  Measured (d 64, 8 sequences of
+// Bound by latency, not bandwidth, at the sizes it meets: about 7 us are the chain first tiles -> masks ->
+// epilogue with the launch, a step of 64 KB takes 0.9 us.  Measured (d 64, 8 sequences of
 // 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
 // reading the cache again, 1262 us; the keys split over 512 workgroups of four waves, partials in
-// the caller's workspace and a merge launch, 21.0 us; this kernel 19.5 us.  That split is faster only
+// the caller's workspace and a merge launch, 21.0 us; this kernel with the place of every tile worked out
+// by every wave 19.4 us, with one resource for the prefix 18.4, and with tiles of their own instead of
+// steps in lockstep 14.6 (two steps ahead in registers, in lockstep: 20.1).  That split is faster only
 // for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 112, 4720 on the
 // vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
 // never asked for.
@@ -116,13 +119,18 @@ void tree_attn_bf16_kernel(AttnParams p)
     const int my_parent = parent_of_thread(p, b);
     const uint32_t row_bytes = (uint32_t)p.d * 2u;
 
-    // Load i of a thread: granule tid + NT i of the step's TS x 32 rows, row-major, that is column granule c of
-    // row r0 + i (NT / GR).  Columns past d are requested beyond every extent.
-    static_assert(NT % GR == 0 && NT % GV == 0 && (NT / GR % KT == 0 || KT % (NT / GR) == 0) && (NT / GV % KT == 0 || KT % (NT / GV) == 0), "rows of a load");
-    const uint32_t k_col = 8 * (tid % GR) < p.d ? 16u * (tid % GR) : OFF_NOWHERE;
-    const uint32_t v_col = d0 + 8 * (tid % GV) < p.d ? 2u * d0 + 16u * (tid % GV) : OFF_NOWHERE;
-    const uint32_t k_off = k_col == OFF_NOWHERE ? k_col : k_col + tid / GR * row_bytes, k_off_tile = k_col == OFF_NOWHERE ? k_col : k_col + tid / GR % KT * row_bytes;
-    const uint32_t v_off = v_col == OFF_NOWHERE ? v_col : v_col + tid / GV * row_bytes, v_off_tile = v_col == OFF_NOWHERE ? v_col : v_col + tid / GV % KT * row_bytes;
+    // OWN: every wavefront has a tile of the step to itself (32 rows: one row group), which it loads itself, without
+    // a barrier in the loop.  Load i of a thread: granule gid + GS i of the TS x 32 rows of the step, or of the
+    // wavefront's tile, row-major, that is column granule c of row r0 + i GS / GR.  Columns past d are
+    // requested beyond every extent.
+    constexpr bool OWN = RH == 1 && TS == KS;
+    constexpr int GS = OWN ? 64 : NT;
+    static_assert((GS / GR % KT == 0 || KT % (GS / GR) == 0) && (GS / GV % KT == 0 || KT % (GS / GV) == 0), "a wave's share of a load lies in one tile");
+    const int gid = OWN ? lane : tid, my_tile = OWN ? ks : 0;
+    const uint32_t k_col = 8 * (gid % GR) < p.d ? 16u * (gid % GR) : OFF_NOWHERE;
+    const uint32_t v_col = d0 + 8 * (gid % GV) < p.d ? 2u * d0 + 16u * (gid % GV) : OFF_NOWHERE;
+    const uint32_t k_off = k_col == OFF_NOWHERE ? k_col : k_col + gid / GR * row_bytes, k_off_tile = k_col == OFF_NOWHERE ? k_col : k_col + gid / GR % KT * row_bytes;
+    const uint32_t v_off = v_col == OFF_NOWHERE ? v_col : v_col + gid / GV * row_bytes, v_off_tile = v_col == OFF_NOWHERE ? v_col : v_col + gid / GV % KT * row_bytes;
     u32x4 kraw[NL], vraw[NV];
     // A step of prefix tiles of a contiguous cache: one resource over the sequence's rows (those past the
     // last one read as zero), scalar offsets.
@@ -130,11 +138,11 @@ void tree_attn_bf16_kernel(AttnParams p)
     auto request_prefix = [&](int t0, int rows) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t rk = make_rsrc(static_cast<const char *>(p.k_prefix) + slab, (uint32_t)rows * row_bytes);
         const __amdgpu_buffer_rsrc_t rv = make_rsrc(static_cast<const char *>(p.v_prefix) + slab, (uint32_t)rows * row_bytes);
-        const uint32_t at = (uint32_t)t0 * (KT * row_bytes);
+        const uint32_t at = (uint32_t)(t0 + my_tile) * (KT * row_bytes);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off, at + i * (NT / GR) * row_bytes, 0);
+        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off, at + i * (GS / GR) * row_bytes, 0);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off, at + i * (NT / GV) * row_bytes, 0);
+        for (int i = 0; i < NV; ++i) vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off, at + i * (GS / GV) * row_bytes, 0);
     };
     // The first step's tiles are asked for before the length is there, as if the cache were full: all rows
     // of the slab may be read, and a sequence shorter than a step requests its own again below.
@@ -162,17 +170,16 @@ void tree_attn_bf16_kernel(AttnParams p)
         const int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
         const size_t at = t >= t_end ? 0 : row * row_bytes;
         const int lo = (int)(uint32_t)at, hi = (int)(uint32_t)(at >> 32);
-        auto tile = [&](const void *prefix, const void *tree_block, int row_of_step) __attribute__((always_inline)) {
-            const int j = row_of_step / KT;
+        auto tile = [&](const void *prefix, const void *tree_block, int j) __attribute__((always_inline)) {
             const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
             return make_rsrc(static_cast<const char *>(t0 + j >= tiles_prefix ? tree_block : prefix) + off, (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes);
         };
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, (wave * 64 + NT * i) / GR), k_off_tile, i * (NT / GR) % KT * row_bytes, 0);
+            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, OWN ? ks : (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, (wave * 64 + NT * i) / GV), v_off_tile, i * (NT / GV) % KT * row_bytes, 0);
+            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, OWN ? ks : (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
     };
     look_up(0);
     if (!ahead || L < TS * KT) request_any(0);
@@ -212,20 +219,26 @@ void tree_attn_bf16_kernel(AttnParams p)
     // one prefix tiles, of a contiguous cache.
     auto step = [&](const int t0, auto plain) __attribute__((always_inline)) {
         constexpr bool PLAIN = decltype(plain)::value;
-        __syncthreads();                    // the last step's operands (and the masks) have been read (written)
+        if (!OWN) __syncthreads();          // the last step's operands have been read
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int gid = tid + NT * i, c = gid % GR, row = gid / GR;
-            *reinterpret_cast<u32x4 *>(s_big + row / KT * STREAM_WORDS + row % KT * PK + 4 * c) = kraw[i];
+            const int row = (gid + GS * i) / GR;
+            *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + row % KT * PK + 4 * (gid % GR)) = kraw[i];
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int gid = tid + NT * i, c = gid % GV, row = gid / GV;
-            *reinterpret_cast<u32x4 *>(s_big + row / KT * STREAM_WORDS + KT * PK + row % KT * PV + 4 * c) = vraw[i];
+            const int row = (gid + GS * i) / GV;
+            *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + KT * PK + row % KT * PV + 4 * (gid % GV)) = vraw[i];
         }
         if (PLAIN) request_prefix(t0 + TS, L);
         else { request_any(t0 + TS); look_up(t0 + 2 * TS); }
-        __syncthreads();
+        if (OWN) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+            __syncthreads();
+        }
         if (!wave_active) return;
 #pragma unroll 1
         for (int ts = ks; ts < TS; ts += KS) {
@@ -326,7 +339,12 @@ void tree_attn_bf16_kernel(AttnParams p)
                 }
             }
         }
+        if (OWN) {                          // the operands have been read before the next tile is stored
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
     };
+    if (OWN) __syncthreads();               // the masks are there (the other form passes a barrier before it reads them)
     int t0 = 0;
     if (contiguous)
         for (; (t0 + TS) * KT <= L && t0 + 2 * TS <= tiles_prefix; t0 += TS) step(t0, std::true_type());
