@@ -57,7 +57,14 @@ __device__ __forceinline__ TileSrc tile_source(const AttnParams &p, int b, int g
     return s;
 }
 
-constexpr uint32_t OFF_NOWHERE = 0x7fffffffu;       // beyond every tile's extent: reads as zero
+constexpr uint32_t OFF_NOWHERE = 0x7fffffffu;       // beyond every extent: reads as zero
+
+// The prefix rows of a (sequence, KV head) are read through one buffer resource: a contiguous cache, whose offsets stay
+// far from 32 bits.
+__device__ __forceinline__ bool one_resource(const AttnParams &p, uint32_t row_bytes)
+{
+    return !p.block_table && (uint64_t)p.L_stride * row_bytes <= 0x40000000u;
+}
 
 // ------------------------------------------------------------------------------ bf16
 // A weight p >= 0 as hi + lo, both bf16: hi is p cut to bf16, taken one step lower where that cut
@@ -146,7 +153,7 @@ void tree_attn_bf16_kernel(AttnParams p)
     };
     // The first step's tiles are asked for before the length is there, as if the cache were full: all rows
     // of the slab may be read, and a sequence shorter than a step requests its own again below.
-    const bool contiguous = !p.block_table;
+    const bool contiguous = one_resource(p, row_bytes);
     const bool ahead = contiguous && p.L_stride >= TS * KT;
     if (ahead) request_prefix(0, p.L_stride);
 
@@ -158,13 +165,13 @@ void tree_attn_bf16_kernel(AttnParams p)
     int blk = 0;
     auto look_up = [&](int t0) __attribute__((always_inline)) {
         const int t = t0 + (lane & (TS - 1));
-        if (!contiguous && t < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + (unsigned)(t * KT) / (unsigned)p.page_size];
+        if (p.block_table && t < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + (unsigned)(t * KT) / (unsigned)p.page_size];
     };
     auto request_any = [&](int t0) __attribute__((always_inline)) {
         const int t = t0 + (lane & (TS - 1)), key = t * KT, node = key - tiles_prefix * KT;
         const bool tree = t >= tiles_prefix;
         size_t row = kv_head * (size_t)p.L_stride + (size_t)key;
-        if (!contiguous)        // (an entry outside the pool never leaves it)
+        if (p.block_table)      // (an entry outside the pool never leaves it)
             row = ((size_t)min(max(blk, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (unsigned)key % (unsigned)p.page_size;
         if (tree) row = kv_head * (size_t)p.N + (size_t)node;
         const int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
@@ -399,23 +406,25 @@ void tree_attn_bf16_kernel(AttnParams p)
 // fp32 multiplies on the matrix cores.  A workgroup of 8 waves owns 16 query rows of a KV head and
 // DS output columns; every wave walks every 8th tile of 16 keys with its own online softmax and
 // the streams are merged at the end (no workspace, no barrier in the loop).  Bound by the fp32
-// matrix rate at one workgroup per CU (48 instructions of 32 cycles per wave and tile, two waves per
-// SIMD): 2 sequences of 301 and 1000 tokens, 16 heads of 128, 28 nodes: 326 us with one workgroup
-// per (node, head) on the vector units, 19.9 us here; relative error against 64 bits 5.2e-7 then,
-// 3.0e-7 now.
+// matrix rate at one workgroup per CU (d 128, slices of 32 columns: 40 instructions of 32 cycles per wave
+// and tile, two waves per SIMD, 9 us for 1000 keys): 2 sequences of 301 and 1000 tokens, 16 heads of
+// 128, 28 nodes: 326 us with one workgroup per (node, head) on the vector units, 19.7 us with slices of 64
+// columns, 17.5 us here; relative error against 64 bits 5.2e-7 on the vector units, 2.9e-7 since.
 //   S^T: the contraction index is d; step (kk, j) of lane (lj, lc) takes d = 16 kk + 4 lj + j, so
 //        that both operands are 16-byte pieces (K from LDS, Q in registers).
 //   O^T: step i takes key 4 lj + i, the key whose weight the lane holds; row index lc of the matrix
 //        (blk, e) is column 64 blk + 4 lc + e, so that V comes straight from memory in 16-byte
-//        pieces, 256 contiguous bytes per key.
+//        lane, 64 E contiguous bytes per key (E = 4, or 2 for slices of 32 columns).
 template <int DP, int DS>
 __global__ __launch_bounds__(512, 2)
 void tree_attn_f32_kernel(AttnParams p)
 {
     constexpr int KW = 16, KS = 8, ROWS = 16;
     constexpr int GR = DP / 4, NL = KW * GR / 64;        // 16-byte granules per row; K loads per lane and tile
+    constexpr int E = DS >= 64 ? 4 : DS / 16, NB = DS / (16 * E);        // columns of V per lane and load, loads per row
     constexpr int PK = DP + 4, PO = DS + 4;              // row pitches in words
-    constexpr int NKK = DP / 16, NB = DS / 64;
+    constexpr int NKK = DP / 16;
+    typedef float fE __attribute__((ext_vector_type(E)));
 
     __shared__ __attribute__((aligned(16))) float s_big[KS][KW * PK];
     __shared__ uint32_t s_anc[MCSD_MAX_NODES][4];
@@ -428,41 +437,51 @@ void tree_attn_f32_kernel(AttnParams p)
     const int g = blockIdx.x % p.H_kv, b = blockIdx.z;
     const int row0 = blockIdx.x / p.H_kv * ROWS, d0 = blockIdx.y * DS;
 
+    const int len = p.prefix_len[b];
     const int my_parent = parent_of_thread(p, b);
-    const int L = max(0, min(p.prefix_len[b], p.L_stride));
-    const int tiles_prefix = (L + KW - 1) / KW, t_end = tiles_prefix + (p.N + KW - 1) / KW;
     const uint32_t row_bytes = (uint32_t)p.d * 4u;
 
-    uint32_t k_off[NL], v_off[NB];
-    uint32_t k_pos[NL];
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int gid = lane + 64 * i, r = gid / GR, c = gid % GR;
-        k_off[i] = (4 * c < p.d) ? (uint32_t)r * row_bytes + 16u * c : OFF_NOWHERE;
-        k_pos[i] = r * PK + 4 * c;
-    }
+    // K load i: granule lane + 64 i of the tile, row-major; V load (n, i): row 4 lj + i, columns d0 + 16 E n + E lc ..
+    const uint32_t k_off = 4 * (lane % GR) < p.d ? lane / GR * row_bytes + 16u * (lane % GR) : OFF_NOWHERE;
+    const uint32_t k_pos = lane / GR * PK + 4 * (lane % GR);             // + i (64 / GR) PK
+    uint32_t v_off[NB];
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        const int col = d0 + 64 * n + 4 * lc;
-        v_off[n] = (col < p.d) ? (uint32_t)(4 * lj) * row_bytes + 4u * col : OFF_NOWHERE - 4096u;     // (plus up to three rows)
+        const int col = d0 + 16 * E * n + E * lc;
+        v_off[n] = col < p.d ? (uint32_t)(4 * lj) * row_bytes + 4u * col : OFF_NOWHERE;
     }
-    u32x4 kraw[NL], vraw[NB][4];
-    auto request_k = [&](const TileSrc &s) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(s.kb, s.bytes);
+    u32x4 kraw[NL];
+    fE vraw[NB][4];
+    auto request_k = [&](const __amdgpu_buffer_rsrc_t &rs, uint32_t at) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_off[i], 0, 0);
+        for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_off, at + i * (64 / GR) * row_bytes, 0);
     };
-    auto request_v = [&](const TileSrc &s) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(s.vb, s.bytes);
+    auto request_v = [&](const __amdgpu_buffer_rsrc_t &rs, uint32_t at) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NB; ++n)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vraw[n][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, v_off[n] + i * row_bytes, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (E == 4) vraw[n][i] = __builtin_bit_cast(fE, __builtin_amdgcn_raw_buffer_load_b128(rs, v_off[n], at + i * row_bytes, 0));
+                else vraw[n][i] = __builtin_bit_cast(fE, __builtin_amdgcn_raw_buffer_load_b64(rs, v_off[n], at + i * row_bytes, 0));
+            }
     };
-    {
+    // The prefix of a contiguous cache: one resource, scalar offsets.  The first tiles are asked for before the
+    // length is there, as if the cache were full (all rows of the slab may be read); a wave whose first
+    // tile is not a whole one of the prefix asks again.
+    const size_t slab = ((size_t)b * p.H_kv + g) * (size_t)p.L_stride * row_bytes;
+    const bool contiguous = one_resource(p, row_bytes), ahead = contiguous && p.L_stride >= KS * KW;
+    if (ahead) {
+        request_k(make_rsrc(static_cast<const char *>(p.k_prefix) + slab, (uint32_t)p.L_stride * row_bytes), ks * KW * row_bytes);
+        request_v(make_rsrc(static_cast<const char *>(p.v_prefix) + slab, (uint32_t)p.L_stride * row_bytes), ks * KW * row_bytes);
+    }
+    const int L = max(0, min(len, p.L_stride));
+    const int tiles_prefix = (L + KW - 1) / KW, t_end = tiles_prefix + (p.N + KW - 1) / KW;
+    const __amdgpu_buffer_rsrc_t rs_k = make_rsrc(static_cast<const char *>(p.k_prefix) + slab, contiguous ? (uint32_t)L * row_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t rs_v = make_rsrc(static_cast<const char *>(p.v_prefix) + slab, contiguous ? (uint32_t)L * row_bytes : 0u);
+    if (!ahead || (ks + 1) * KW > L) {
         const TileSrc s = tile_source<KW>(p, b, g, L, tiles_prefix, ks, t_end, row_bytes);
-        request_k(s);
-        request_v(s);
+        request_k(make_rsrc(s.kb, s.bytes), 0);
+        request_v(make_rsrc(s.vb, s.bytes), 0);
     }
 
     f32x4 qreg[NKK];
@@ -478,21 +497,26 @@ void tree_attn_f32_kernel(AttnParams p)
     build_ancestor_masks(p, my_parent, s_anc, s_parent);
     __syncthreads();
 
-    f32x4 oacc[NB][4];
+    f32x4 oacc[NB][E];
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) oacc[n][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < E; ++e) oacc[n][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
     float m_used = M_INIT, l_part = 0.f;
     const float c2 = p.scale_log2;
     const int node_m = min(row0 + lc, p.M - 1) / p.G;
     float *area = s_big[ks];
 
-    for (int t = ks; t < t_end; t += KS) {
-        const TileSrc next = tile_source<KW>(p, b, g, L, tiles_prefix, t + KS, t_end, row_bytes);
+    // PLAIN (a promise of the caller): tile t is a whole prefix tile, and t + KS a prefix tile, of a contiguous cache.
+    auto step = [&](const int t, auto plain) __attribute__((always_inline)) {
+        constexpr bool PLAIN = decltype(plain)::value;
+        TileSrc next = {};
+        if (!PLAIN) next = tile_source<KW>(p, b, g, L, tiles_prefix, t + KS, t_end, row_bytes);
+        const uint32_t at = (uint32_t)(t + KS) * (KW * row_bytes);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4 *>(area + k_pos[i]) = kraw[i];
-        request_k(next);
+        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4 *>(area + k_pos + i * (64 / GR) * PK) = kraw[i];
+        if (PLAIN) request_k(rs_k, at);
+        else request_k(make_rsrc(next.kb, next.bytes), 0);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -510,16 +534,19 @@ void tree_attn_f32_kernel(AttnParams p)
         }
         f32x4 sc = s0 + s1;
         // lane (lj, lc): row lc, keys 4 lj + i
-        const bool tree = t >= tiles_prefix;
-        const int key0 = (t - tiles_prefix) * KW;                    // of a tree tile
-        const int nvalid = tree ? KW : min(KW, L - t * KW);
-        uint32_t vis = tree ? s_anc[node_m][key0 >> 5] >> (key0 & 31) : 0xffffffffu;
-        if (nvalid < KW) vis = (1u << nvalid) - 1u;
-        vis >>= 4 * lj;
+        uint32_t vis = 0xfu;
+        if (!PLAIN) {
+            const bool tree = t >= tiles_prefix;
+            const int key0 = (t - tiles_prefix) * KW;                    // of a tree tile
+            const int nvalid = tree ? KW : min(KW, L - t * KW);
+            vis = tree ? s_anc[node_m][key0 >> 5] >> (key0 & 31) : 0xffffffffu;
+            if (nvalid < KW) vis = (1u << nvalid) - 1u;
+            vis >>= 4 * lj;
+        }
         float mr = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (!((vis >> i) & 1u)) sc[i] = -INFINITY;
+            if (!PLAIN && !((vis >> i) & 1u)) sc[i] = -INFINITY;
             mr = fmaxf(mr, sc[i]);
         }
         const float lmax = (mr == -INFINITY) ? -INFINITY : mr * c2;
@@ -534,13 +561,13 @@ void tree_attn_f32_kernel(AttnParams p)
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) oacc[n][e] *= alpha;
+                for (int e = 0; e < E; ++e) oacc[n][e] *= alpha;
         }
         float pw[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             pw[i] = fast_exp2(fmaf(sc[i], c2, -m_used));
-            if (!((vis >> i) & 1u)) pw[i] = 0.f;
+            if (!PLAIN && !((vis >> i) & 1u)) pw[i] = 0.f;
         }
         l_part += (pw[0] + pw[1]) + (pw[2] + pw[3]);
 #pragma unroll
@@ -548,33 +575,33 @@ void tree_attn_f32_kernel(AttnParams p)
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    oacc[n][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vraw[n][i][e]), pw[i], oacc[n][e], 0, 0, 0);
-        request_v(next);
+                for (int e = 0; e < E; ++e)
+                    oacc[n][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vraw[n][i][e], pw[i], oacc[n][e], 0, 0, 0);
+        if (PLAIN) request_v(rs_v, at);
+        else request_v(make_rsrc(next.vb, next.bytes), 0);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // the K operands are read before the next tile is stored
         __builtin_amdgcn_wave_barrier();
-    }
+    };
+    int t = ks;
+    if (contiguous && DP <= 128)            // (d = 256, 1000 keys: the general form is 2 to 4 % faster, 30.9 against 32.4 us)
+        for (; (t + 1) * KW <= L && t + KS < tiles_prefix; t += KS) step(t, std::true_type());
+    for (; t < t_end; t += KS) step(t, std::false_type());
 
-    // ---- epilogue: merge the eight streams
+    // ---- epilogue: merge the eight streams, each brought to the largest of the maxima, behind one barrier
     float lt = l_part;
     lt += __shfl_xor(lt, 16);
     lt += __shfl_xor(lt, 32);
     if (lj == 0) { s_m[ks][lc] = m_used; s_l[ks][lc] = lt; }
-    __syncthreads();
-    {
-        float ms = s_m[0][lc];
+    // oacc[n][e][i] is row lc, column 16 E n + E (4 lj + i) + e
 #pragma unroll
-        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][lc]);
-        const float fsc = exp2f(m_used - ms);
-        // oacc[n][e][i] is row lc, column 64 n + 16 lj + 4 i + e
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
-        for (int n = 0; n < NB; ++n)
+        for (int i = 0; i < 4; ++i) {
+            fE v;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const f32x4 v = {oacc[n][0][i] * fsc, oacc[n][1][i] * fsc, oacc[n][2][i] * fsc, oacc[n][3][i] * fsc};
-                *reinterpret_cast<f32x4 *>(area + lc * PO + 64 * n + 16 * lj + 4 * i) = v;
-            }
-    }
+            for (int e = 0; e < E; ++e) v[e] = oacc[n][e][i];
+            *reinterpret_cast<fE *>(area + lc * PO + 16 * E * n + E * (4 * lj + i)) = v;
+        }
     __syncthreads();
     const int rows_valid = min(ROWS, p.M - row0);
     for (int idx = tid; idx < ROWS * (DS / 4); idx += 512) {
@@ -586,8 +613,9 @@ void tree_attn_f32_kernel(AttnParams p)
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k2 = 0; k2 < KS; ++k2) {
-            ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
-            acc += *reinterpret_cast<const f32x4 *>(s_big[k2] + r * PO + 4 * c);
+            const float f = exp2f(s_m[k2][r] - ms);
+            ls += f * s_l[k2][r];
+            acc += f * *reinterpret_cast<const f32x4 *>(s_big[k2] + r * PO + 4 * c);
         }
         const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
         float *ob = static_cast<float *>(p.out) + (((size_t)b * p.N + node) * p.H_q + (size_t)g * p.G + hh) * (size_t)p.d + d0 + 4 * c;
@@ -616,13 +644,17 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
     if (p.B > 65535) { set_error("attn: B %d > 65535", p.B); return MCSD_E_UNSUPPORTED; }
     const int dp = p.d <= 64 ? 64 : (p.d <= 128 ? 128 : 256);
     if (p.dtype == MCSD_DTYPE_FP32) {
-        // Few units: the output columns are split over workgroups as well (every slice scores the
-        // keys again, which is half of the work).  The line is where the slices stop fitting the 256
-        // CUs side by side; beyond it the repeated scores are all that a slice adds.
-        const bool slices = (long)p.B * p.H_kv * ((p.M + 15) / 16) < 128;
-        if (dp == 64) launch_f32<64, 64>(p, stream);
-        else if (dp == 128) { if (slices) launch_f32<128, 64>(p, stream); else launch_f32<128, 128>(p, stream); }
-        else { if (slices) launch_f32<256, 64>(p, stream); else launch_f32<256, 128>(p, stream); }
+        // Few units: the output columns are split over workgroups as well (every slice scores the keys again):
+        // slices of 32 columns while those fit one per CU, of 64 while the units would leave half of the
+        // CUs idle.  us at 200 / 1000 keys, slices of 32, of 64 columns:
+        //   d 64   16 units of 16 rows  6.6/12.3  7.1/14.3     64 units  6.9/12.6  7.4/14.6     96 units  7.0/12.7  7.5/14.6
+        //   d 128  16                   8.5/17.4  8.9/19.6     64        9.1/20.2  9.4/21.1     96       13.6/32.2  9.5/22.4
+        //   d 256  16                  13.1/28.9 13.6/32.4     64       25.0/59.4 14.4/35.6     96       36.4/87.2 26.0/65.2
+        const long units16 = (long)p.B * p.H_kv * ((p.M + 15) / 16);
+        const bool narrow = units16 * (dp / 32) <= 256, slices = units16 < 128;
+        if (dp == 64) { if (narrow) launch_f32<64, 32>(p, stream); else launch_f32<64, 64>(p, stream); }
+        else if (dp == 128) { if (narrow) launch_f32<128, 32>(p, stream); else if (slices) launch_f32<128, 64>(p, stream); else launch_f32<128, 128>(p, stream); }
+        else { if (narrow) launch_f32<256, 32>(p, stream); else if (slices) launch_f32<256, 64>(p, stream); else launch_f32<256, 128>(p, stream); }
     } else {
         // Rows of a KV head per workgroup and wavefronts.  While the launch fits one workgroup per CU, few
         // rows by eight wavefronts: the walk over the keys is the time, and the key tiles that several
