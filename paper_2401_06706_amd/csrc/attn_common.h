@@ -195,6 +195,9 @@ __device__ __forceinline__ void longest_first(const AttnParams &p, PairRanks<NT>
 // bf16, d = 128, more than 64 rows per KV head (tree_attn_shared.hip)
 void launch_attn_shared(const AttnParams &p, dim3 grid, hipStream_t stream, const WalkParams &w);
 
+// bf16, d = 128, all keys of a unit in one workgroup and `columns` (32, 64, 128) of the output (tree_attn_any.hip)
+int32_t launch_attn_sliced(const AttnParams &p, int columns, hipStream_t stream, const WalkParams *tail_walk);
+
 // fp32 storage and head dimensions other than 128 (tree_attn_any.hip): one launch, no workspace
 int32_t launch_attn_any(const AttnParams &p, hipStream_t stream);
 

@@ -82,10 +82,11 @@ __device__ __forceinline__ void walk_sequence(const WalkParams &w, int b)
 
 // ---- tree attention -------------------------------------------------------
 struct AttnPlan {
-    bool use_mfma;        // bf16, d == 128: tree_attn.hip; otherwise tree_attn_any.hip (nothing below but rows_per_kv is used)
+    bool use_mfma;        // bf16, d == 128: what follows; otherwise tree_attn_any.hip (nothing below but rows_per_kv is used)
     int rows_per_kv;      // M = N * (H_q / H_kv) query rows that share one KV head
     int row_tile;         // query rows per workgroup (32 or 64) for the MFMA kernel
     int variant;          // which instantiation of the MFMA kernel
+    int slice_columns;    // 0, or: no segments, workgroups of 32 rows, all keys and this many output columns (tree_attn_any.hip)
     int n_row_tiles;
     int tiles_prefix_max; // 32-key tiles needed for L_stride prefix keys
     int tiles_tree;       // 32-key tiles needed for N tree keys

@@ -1,5 +1,6 @@
 // Tree attention (Sec. 3.3 of the paper) for the storage types and head dimensions that the
-// d = 128 bf16 kernel does not take, on the matrix cores of gfx950.
+// d = 128 bf16 kernels do not take, and for the launches of theirs that leave the chip half idle, on the
+// matrix cores of gfx950.
 //
 //   tree_attn_bf16_kernel  bf16 storage, d a multiple of 8 up to 256 (padded to 64, 128 or 256)
 //   tree_attn_f32_kernel   fp32 storage, d a multiple of 4 up to 256 (same paddings)
@@ -94,10 +95,17 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 // for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 112, 4720 on the
 // vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
 // never asked for.
+// A row of workgroups appended to the grid along y carries the walk of a verification that ran before this launch
+// on the same stream (see tree_attn_mfma_kernel).
 template <int DP, int DS, int NW, int RH, int MT, int TS>
 __global__ __launch_bounds__(64 * NW, 2)
-void tree_attn_bf16_kernel(AttnParams p)
+void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 {
+    if ((int)blockIdx.y * DS >= p.d) {
+        const int first = (int)(blockIdx.z * gridDim.x + blockIdx.x) * NW + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        for (int wb = first; wb < w.B; wb += (int)(gridDim.z * gridDim.x) * NW) walk_sequence(w, wb);
+        return;
+    }
     constexpr int KS = NW / RH, NT = 64 * NW;
     static_assert(TS % KS == 0, "every key stream takes the same number of tiles of a step");
     constexpr int WROWS = 16 * MT, ROWS = WROWS * RH;
@@ -161,20 +169,31 @@ void tree_attn_bf16_kernel(AttnParams p)
     const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
     // The other steps (a paged cache, the end of the prefix, the tree).  Lane j works out where tile j of the step lies;
     // a wave's share of a load lies in one tile.  The block-table entries of a step are read one step
-    // before it.  Tiles at or past t_end are empty, which keeps every request unconditional.
-    int blk = 0;
-    auto look_up = [&](int t0) __attribute__((always_inline)) {
-        const int t = t0 + (lane & (TS - 1));
-        if (p.block_table && t < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + (unsigned)(t * KT) / (unsigned)p.page_size];
+    // before it, and page and row advance from step to step without a division.  Tiles at or past t_end
+    // are empty, which keeps every request unconditional.
+    int blk = 0, blk_row = 0;           // of this lane's tile in the step that is requested next
+    int page = 0, page_row = 0, page_step = 0, row_step = 0;
+    if (p.block_table) {
+        const unsigned key = (lane & (TS - 1)) * KT, size = p.page_size;
+        page = key / size; page_row = key % size;
+        page_step = TS * KT / size; row_step = TS * KT % size;
+    }
+    auto look_up = [&](int t0) __attribute__((always_inline)) {        // (t0 = 0, TS, 2 TS, ...)
+        if (!p.block_table) return;
+        if (t0 + (lane & (TS - 1)) < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + page];
+        blk_row = page_row;
+        page += page_step; page_row += row_step;
+        if (page_row >= p.page_size) { page_row -= p.page_size; ++page; }
     };
     auto request_any = [&](int t0) __attribute__((always_inline)) {
         const int t = t0 + (lane & (TS - 1)), key = t * KT, node = key - tiles_prefix * KT;
         const bool tree = t >= tiles_prefix;
         size_t row = kv_head * (size_t)p.L_stride + (size_t)key;
         if (p.block_table)      // (an entry outside the pool never leaves it)
-            row = ((size_t)min(max(blk, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (unsigned)key % (unsigned)p.page_size;
+            row = ((size_t)min(max(blk, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (size_t)blk_row;
         if (tree) row = kv_head * (size_t)p.N + (size_t)node;
-        const int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
+        int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
+        if (DP == 128 && p.d == 128 && !tree && (unsigned)blk >= (unsigned)p.n_pages && p.block_table) rows = 0;       // (d = 128: such a tile reads as zero keys)
         const size_t at = t >= t_end ? 0 : row * row_bytes;
         const int lo = (int)(uint32_t)at, hi = (int)(uint32_t)(at >> 32);
         auto tile = [&](const void *prefix, const void *tree_block, int j) __attribute__((always_inline)) {
@@ -189,7 +208,7 @@ void tree_attn_bf16_kernel(AttnParams p)
             vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, OWN ? ks : (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
     };
     look_up(0);
-    if (!ahead || L < TS * KT) request_any(0);
+    if (!ahead || (OWN ? (ks + 1) * KT > L : L < TS * KT)) request_any(0);
     look_up(TS);
 
     // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
@@ -413,8 +432,8 @@ void tree_attn_bf16_kernel(AttnParams p)
 //   S^T: the contraction index is d; step (kk, j) of lane (lj, lc) takes d = 16 kk + 4 lj + j, so
 //        that both operands are 16-byte pieces (K from LDS, Q in registers).
 //   O^T: step i takes key 4 lj + i, the key whose weight the lane holds; row index lc of the matrix
-//        (blk, e) is column 64 blk + 4 lc + e, so that V comes straight from memory in 16-byte
-//        lane, 64 E contiguous bytes per key (E = 4, or 2 for slices of 32 columns).
+//        (blk, e) is column 16 E blk + E lc + e (E = 4, or 2 for slices of 32 columns), so that V comes
+//        straight from memory, E words per lane.
 template <int DP, int DS>
 __global__ __launch_bounds__(512, 2)
 void tree_attn_f32_kernel(AttnParams p)
@@ -625,10 +644,13 @@ void tree_attn_f32_kernel(AttnParams p)
 }
 
 template <int DP, int DS, int NW, int RH, int MT, int TS>
-void launch_bf16(const AttnParams &p, hipStream_t stream)
+void launch_bf16(const AttnParams &p, hipStream_t stream, const WalkParams *tail_walk = nullptr)
 {
     constexpr int ROWS = 16 * MT * RH;
-    launch_kernel(K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS>, dim3((unsigned)p.H_kv * ((p.M + ROWS - 1) / ROWS), (p.d + DS - 1) / DS, p.B), dim3(64 * NW), stream, p);
+    WalkParams w = {};
+    if (tail_walk) w = *tail_walk;
+    const dim3 grid((unsigned)p.H_kv * ((p.M + ROWS - 1) / ROWS), (p.d + DS - 1) / DS + (tail_walk ? 1 : 0), p.B);
+    launch_kernel(p.d == 128 ? K_ATTN_MFMA : K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS>, grid, dim3(64 * NW), stream, p, w);
 }
 
 template <int DP, int DS>
@@ -638,6 +660,16 @@ void launch_f32(const AttnParams &p, hipStream_t stream)
 }
 
 }  // namespace
+
+int32_t launch_attn_sliced(const AttnParams &p, int columns, hipStream_t stream, const WalkParams *tail_walk)
+{
+    if (columns == 32) launch_bf16<128, 32, 8, 1, 2, 8>(p, stream, tail_walk);
+    else if (columns == 64) launch_bf16<128, 64, 8, 1, 2, 8>(p, stream, tail_walk);
+    else launch_bf16<128, 128, 8, 1, 2, 8>(p, stream, tail_walk);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("tree_attn launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
+    return MCSD_OK;
+}
 
 int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
 {
