@@ -85,13 +85,14 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 // multiple of 32).  V is read back with the transposing LDS load.  The streams meet in LDS at the
 // end: no memory besides the arguments, so that calls on several streams share nothing, and the
 // bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any.)
-// Bound by latency, not bandwidth, at the sizes it meets: about 7 us are the chain first tiles -> masks ->
-// epilogue with the launch, a step of 64 KB takes 0.9 us.  Measured (d 64, 8 sequences of
+// Bound by what one CU takes in, about 72 bytes a ns (two steps ahead in registers, with or without lockstep, only
+// makes the first ones come later), behind 5 to 6 us of launch, first tiles, masks and epilogue.  Measured (d 64, 8 sequences of
 // 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
 // reading the cache again, 1262 us; the keys split over 512 workgroups of four waves, partials in
 // the caller's workspace and a merge launch, 21.0 us; this kernel with the place of every tile worked out
 // by every wave 19.4 us, with one resource for the prefix 18.4, and with tiles of their own instead of
-// steps in lockstep 14.6 (two steps ahead in registers, in lockstep: 20.1).  That split is faster only
+// steps in lockstep 14.6.  (One lane per tile for a wave's own tile, all waves through all steps and three
+// barriers behind them: 9 sequences of 111 keys 8.0 against 7.1 us, paged, 4 x 1000 keys, GQA 32/8 13.1 against 11.4.)  That split is faster only
 // for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 112, 4720 on the
 // vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
 // never asked for.
@@ -159,56 +160,60 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 #pragma unroll
         for (int i = 0; i < NV; ++i) vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off, at + i * (GS / GV) * row_bytes, 0);
     };
-    // The first step's tiles are asked for before the length is there, as if the cache were full: all rows
-    // of the slab may be read, and a sequence shorter than a step requests its own again below.
-    const bool contiguous = one_resource(p, row_bytes);
-    const bool ahead = contiguous && p.L_stride >= TS * KT;
+    // The first tiles are asked for before the length is there, as if the cache were full: all rows of the slab
+    // may be read, and what turns out not to be (whole) prefix tiles is requested again below.
+    constexpr int REACH = OWN ? 1 : TS;         // tiles of a step that one request covers, the first at t0 + my_tile
+    const bool contiguous = one_resource(p, row_bytes), ahead = contiguous && p.L_stride >= (my_tile + REACH) * KT;
     if (ahead) request_prefix(0, p.L_stride);
 
     const int L = max(0, min(len, p.L_stride));
     const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
-    // The other steps (a paged cache, the end of the prefix, the tree).  Lane j works out where tile j of the step lies;
-    // a wave's share of a load lies in one tile.  The block-table entries of a step are read one step
-    // before it, and page and row advance from step to step without a division.  Tiles at or past t_end
-    // are empty, which keeps every request unconditional.
+    // The other steps (a paged cache, the end of the prefix, the tree).  Lane j works out where tile j of the step lies
+    // (all lanes the tile of their wavefront); a wave's share of a load lies in one tile.  The block-table
+    // entries of a step are read one step before it, and page and row advance from step to step without a
+    // division.  Tiles at or past t_end are empty, which keeps every request unconditional.
+    const int lane_tile = OWN ? ks : lane & (TS - 1);
     int blk = 0, blk_row = 0;           // of this lane's tile in the step that is requested next
     int page = 0, page_row = 0, page_step = 0, row_step = 0;
     if (p.block_table) {
-        const unsigned key = (lane & (TS - 1)) * KT, size = p.page_size;
+        const unsigned key = lane_tile * KT, size = p.page_size;
         page = key / size; page_row = key % size;
         page_step = TS * KT / size; row_step = TS * KT % size;
     }
     auto look_up = [&](int t0) __attribute__((always_inline)) {        // (t0 = 0, TS, 2 TS, ...)
         if (!p.block_table) return;
-        if (t0 + (lane & (TS - 1)) < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + page];
+        if (t0 + lane_tile < tiles_prefix) blk = p.block_table[(size_t)b * p.max_pages + page];
         blk_row = page_row;
         page += page_step; page_row += row_step;
         if (page_row >= p.page_size) { page_row -= p.page_size; ++page; }
     };
     auto request_any = [&](int t0) __attribute__((always_inline)) {
-        const int t = t0 + (lane & (TS - 1)), key = t * KT, node = key - tiles_prefix * KT;
+        const int t = t0 + lane_tile, key = t * KT, node = key - tiles_prefix * KT;
+        if (OWN && t >= t_end) return;          // (there is no such step)
+        const int entry = OWN ? __builtin_amdgcn_readfirstlane(blk) : blk;
         const bool tree = t >= tiles_prefix;
         size_t row = kv_head * (size_t)p.L_stride + (size_t)key;
         if (p.block_table)      // (an entry outside the pool never leaves it)
-            row = ((size_t)min(max(blk, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (size_t)blk_row;
+            row = ((size_t)min(max(entry, 0), p.n_pages - 1) * p.H_kv + g) * (size_t)p.page_size + (size_t)blk_row;
         if (tree) row = kv_head * (size_t)p.N + (size_t)node;
         int rows = t >= t_end ? 0 : min(KT, (tree ? p.N - node : L - key));
-        if (DP == 128 && p.d == 128 && !tree && (unsigned)blk >= (unsigned)p.n_pages && p.block_table) rows = 0;       // (d = 128: such a tile reads as zero keys)
+        if (DP == 128 && p.d == 128 && !tree && (unsigned)entry >= (unsigned)p.n_pages && p.block_table) rows = 0;       // (d = 128: such a tile reads as zero keys)
         const size_t at = t >= t_end ? 0 : row * row_bytes;
         const int lo = (int)(uint32_t)at, hi = (int)(uint32_t)(at >> 32);
         auto tile = [&](const void *prefix, const void *tree_block, int j) __attribute__((always_inline)) {
+            if constexpr (OWN) return make_rsrc(static_cast<const char *>(tree ? tree_block : prefix) + at, (uint32_t)rows * row_bytes);
             const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
             return make_rsrc(static_cast<const char *>(t0 + j >= tiles_prefix ? tree_block : prefix) + off, (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes);
         };
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, OWN ? ks : (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
+            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, OWN ? 0 : (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, OWN ? ks : (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
+            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, OWN ? 0 : (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
     };
     look_up(0);
-    if (!ahead || (OWN ? (ks + 1) * KT > L : L < TS * KT)) request_any(0);
+    if (!ahead || (my_tile + REACH) * KT > L) request_any(0);
     look_up(TS);
 
     // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
@@ -241,8 +246,8 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     typedef short v4i16 __attribute__((ext_vector_type(4)));
     typedef v4i16 __attribute__((address_space(3))) *lds_v4i16_ptr;
 
-    // PLAIN (a promise of the caller): the TS tiles of this step are whole prefix tiles, and those of the next
-    // one prefix tiles, of a contiguous cache.
+    // PLAIN (a promise of the caller): the tiles of this step (OWN: of this wavefront) are whole prefix tiles, and those
+    // of the next one prefix tiles, of a contiguous cache.
     auto step = [&](const int t0, auto plain) __attribute__((always_inline)) {
         constexpr bool PLAIN = decltype(plain)::value;
         if (!OWN) __syncthreads();          // the last step's operands have been read
@@ -269,7 +274,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 #pragma unroll 1
         for (int ts = ks; ts < TS; ts += KS) {
             const int t = t0 + ts;
-            if (!PLAIN && t >= t_end) break;
+            if (!PLAIN && !OWN && t >= t_end) break;
             const uint32_t *kt = s_big + ts * STREAM_WORDS, *vt = kt + KT * PK;
             f32x4 sacc[2][MT];
 #pragma unroll
@@ -373,10 +378,13 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     if (OWN) __syncthreads();               // the masks are there (the other form passes a barrier before it reads them)
     int t0 = 0;
     if (contiguous)
-        for (; (t0 + TS) * KT <= L && t0 + 2 * TS <= tiles_prefix; t0 += TS) step(t0, std::true_type());
-    for (; t0 < t_end; t0 += TS) step(t0, std::false_type());
+        for (; (t0 + my_tile + REACH) * KT <= L && t0 + TS + my_tile + REACH <= tiles_prefix; t0 += TS) step(t0, std::true_type());
+    for (; t0 + my_tile < t_end; t0 += TS) step(t0, std::false_type());
 
-    // ---- epilogue: merge the key streams in LDS, then write whole rows
+    // ---- epilogue: every wave leaves its (m, l) per row and its O in LDS (OWN: in the area of its tiles); behind
+    // a barrier the key streams are added up, each brought to the largest of the maxima, and whole rows written
+    constexpr int AREA = OWN ? STREAM_WORDS : ROWS * PO;         // words of a key stream
+    static_assert(AREA >= ROWS * PO && KS * AREA <= LDS_WORDS, "the outputs fit");
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         float lt = l_part[mt];
@@ -384,35 +392,27 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
         lt += __shfl_xor(lt, 32);
         if (lj == 0) { s_m[ks][WROWS * rh + 16 * mt + lc] = m_used[mt]; s_l[ks][WROWS * rh + 16 * mt + lc] = lt; }
     }
-    __syncthreads();                        // (also: every wave is done with the tiles)
+    if (!OWN) __syncthreads();              // every wave is done with the tiles
     float *area = reinterpret_cast<float *>(s_big);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int r = WROWS * rh + 16 * mt + lc;
-        float ms = s_m[0][r];
-#pragma unroll
-        for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
-        const float fsc = exp2f(m_used[mt] - ms);
-#pragma unroll
-        for (int nt = 0; nt < NNT; ++nt) oacc[nt][mt] *= fsc;
-    }
 #pragma unroll
     for (int nt = 0; nt < NNT; ++nt)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            *reinterpret_cast<f32x4 *>(area + (ks * ROWS + WROWS * rh + 16 * mt + lc) * PO + 16 * nt + 4 * lj) = oacc[nt][mt];
+            *reinterpret_cast<f32x4 *>(area + ks * AREA + (WROWS * rh + 16 * mt + lc) * PO + 16 * nt + 4 * lj) = oacc[nt][mt];
     __syncthreads();
     const int rows_valid = min(ROWS, p.M - row0), d4n = min(DS, p.d - d0) / 4;
-    for (int idx = tid; idx < rows_valid * d4n; idx += NT) {
-        const int r = idx / d4n, d4 = idx % d4n;
+    for (int idx = tid; idx < ROWS * (DS / 4); idx += NT) {
+        const int r = idx / (DS / 4), d4 = idx % (DS / 4);
+        if (r >= rows_valid || d4 >= d4n) continue;
         float ms = s_m[0][r], ls = 0.f;
 #pragma unroll
         for (int k2 = 1; k2 < KS; ++k2) ms = fmaxf(ms, s_m[k2][r]);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k2 = 0; k2 < KS; ++k2) {
-            ls += exp2f(s_m[k2][r] - ms) * s_l[k2][r];
-            acc += *reinterpret_cast<const f32x4 *>(area + (k2 * ROWS + r) * PO + 4 * d4);
+            const float f = fast_exp2(s_m[k2][r] - ms);
+            ls += f * s_l[k2][r];
+            acc += f * *reinterpret_cast<const f32x4 *>(area + k2 * AREA + r * PO + 4 * d4);
         }
         const float inv = 1.0f / ls;
         const int gr = row0 + r, node = gr / p.G, hh = gr % p.G;
