@@ -662,24 +662,25 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     // in about 72 bytes a ns here whatever is in flight, so the fewer bytes each has to read the better: slices of
     // 32, 64 or 128 columns, as many as fit one workgroup per CU.  The lines are where segments or, with up to
     // 32 rows, the kernel above with its four waves get ahead (that one splits from 36 tiles on).
-    // us before / this, at 200, 500, 1000, 1500, 2000 keys:
-    //   28 rows,  32 KV heads (32 columns)     7.5/8.5  10.4/10.2  16.8/12.5  12.5/15.7  14.5/19.2
-    //   28 rows, 128 KV heads (64)             8.2/10.1 12.5/13.4  20.8/19.1  25.7/24.1
-    //   28 rows, 256 KV heads (128)            9.9/13.3 17.6/20.9  34.8/31.1
-    //   56 rows,  16 KV heads (32)            11.1/9.1  13.6/10.2  12.8/12.4  15.5/14.7  14.6/17.0
-    //   56 rows,  40 KV heads (64)            11.3/10.3 13.9/11.6  14.1/14.2  17.2/18.1  19.7/23.2
-    //   60 rows, 128 KV heads (128)           12.0/13.2 18.8/16.7  24.4/22.9  33.9/28.8  45.0/34.6
-    //   112 rows,  8 KV heads (32)            14.0/8.2  11.8/10.0  12.5/12.5  15.0/14.1  13.7/16.6
-    //   112 rows, 32 KV heads (64)            14.6/9.3  13.5/11.6  15.0/14.2  18.3/16.1  23.6/20.0
-    //   112 rows, 64 KV heads (128)           14.9/11.5 15.9/14.6  23.6/19.5  27.5/23.9  26.5/27.8
-    //   672 rows,  8 KV heads (128)           13.9/12.0 15.0/14.1  19.5/17.7  22.4/21.0  21.7/24.4
-    // (since then 0.4 to 1.3 us less in the right-hand columns)
+    // us without / with this, at 200, 500, 1000, 1500, 2000 keys (*: measured with two terms per weight and three
+    // barriers in the epilogue, 5 to 12 % slower than now):
+    //   28 rows,  32 KV heads (32 columns)     7.5/8.5* 10.4/9.1  16.8/11.0  12.5/15.7* 14.5/19.2*
+    //   28 rows, 128 KV heads (64)             8.2/10.1* 12.5/13.4* 20.8/17.4 25.6/22.7
+    //   28 rows, 256 KV heads (128)            9.9/13.3* 17.6/20.9* 34.8/28.7 (700: 21.2/22.9)
+    //   56 rows,  16 KV heads (32)            11.1/9.1* 13.6/10.2* 12.8/12.4* 15.5/14.7* 14.6/17.0*
+    //   56 rows,  40 KV heads (64)            11.3/8.9  13.9/10.2  14.1/12.3  17.1/16.4  19.7/23.2*
+    //   60 rows, 128 KV heads (128)           12.0/13.2* 18.8/16.7* 24.4/20.3 33.9/28.8* 44.7/31.7
+    //   112 rows,  8 KV heads (32)            14.0/7.6  11.8/10.0* 12.5/11.0  15.0/14.1* 13.7/16.6*
+    //   112 rows, 32 KV heads (64)            14.6/8.5  13.5/11.6* 15.0/12.3  18.3/14.4  23.5/18.7 (3000: 27.0/25.5)
+    //   112 rows, 64 KV heads (128)           14.9/10.0 15.9/14.6* 23.6/17.3  27.5/21.8  26.5/27.8*
+    //   672 rows,  8 KV heads (128)           13.9/10.2 15.0/14.1* 19.5/14.9  22.4/17.6  21.7/24.4*
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
-        long least = 1, most = 54;
-        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (wgs32 <= 128 ? 22 : 25); most = 35; }
-        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 14; most = wgs32 > 64 && wgs32 <= 128 ? 35 : 50; }
+        const bool some = wgs32 > 64 && wgs32 <= 128;
+        long least = 1, most = some ? 96 : 54;
+        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some ? 50 : 35; }
+        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 14; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {
             pl.slice_columns = wgs32 <= 64 ? 32 : (wgs32 <= 128 ? 64 : 128);
             pl.n_chunks_max = 1;

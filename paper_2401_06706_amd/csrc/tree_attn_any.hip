@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 // with row pitches that keep all accesses free of bank conflicts (K: 4 words, V: 8 words past a
 // multiple of 32).  V is read back with the transposing LDS load.  The streams meet in LDS at the
 // end: no memory besides the arguments, so that calls on several streams share nothing, and the
-// bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any.)
+// bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any and, for d = 128, make_attn_plan.)
 // Bound by what one CU takes in, about 72 bytes a ns (two steps ahead in registers, with or without lockstep, only
 // makes the first ones come later), behind 5 to 6 us of launch, first tiles, masks and epilogue.  Measured (d 64, 8 sequences of
 // 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
@@ -98,7 +98,10 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
 // never asked for.
 // A row of workgroups appended to the grid along y carries the walk of a verification that ran before this launch
 // on the same stream (see tree_attn_mfma_kernel).
-template <int DP, int DS, int NW, int RH, int MT, int TS>
+//
+// TERMS: bf16 terms per weight.  Two for d != 128; one for d = 128, as in the other kernels for it (a step of
+// two terms has twice the PV matrix instructions and a third more vector instructions).
+template <int DP, int DS, int NW, int RH, int MT, int TS, int TERMS>
 __global__ __launch_bounds__(64 * NW, 2)
 void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 {
@@ -333,7 +336,6 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 float pv[8];
-                uint32_t hi[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int sub = e >> 2, i = e & 3;
@@ -345,17 +347,23 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
                     for (int e = 0; e < 8; ++e)
                         if (!((vis[mt] >> (16 * (e >> 2) + (e & 3))) & 1u)) pv[e] = 0.f;
                 }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) hi[e] = weight_hi_bits(pv[e]);
                 l_part[mt] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
                 u32x4 ph, plw;
+                if constexpr (TERMS == 1) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    ph[j] = __builtin_amdgcn_perm(hi[2 * j + 1], hi[2 * j], 0x07060302u);
-                    plw[j] = pack_bf16(pv[2 * j] - __uint_as_float(hi[2 * j]), pv[2 * j + 1] - __uint_as_float(hi[2 * j + 1]));
+                    for (int j = 0; j < 4; ++j) ph[j] = pack_bf16(pv[2 * j], pv[2 * j + 1]);
+                } else {
+                    uint32_t hi[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) hi[e] = weight_hi_bits(pv[e]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        ph[j] = __builtin_amdgcn_perm(hi[2 * j + 1], hi[2 * j], 0x07060302u);
+                        plw[j] = pack_bf16(pv[2 * j] - __uint_as_float(hi[2 * j]), pv[2 * j + 1] - __uint_as_float(hi[2 * j + 1]));
+                    }
+                    plo[mt] = __builtin_bit_cast(bf16x8, plw);
                 }
                 phi[mt] = __builtin_bit_cast(bf16x8, ph);
-                plo[mt] = __builtin_bit_cast(bf16x8, plw);
             }
             const uint32_t *vl = vt + (4 * lj + (lc >> 2)) * PV + (lc & 3) * 2;
 #pragma unroll
@@ -366,7 +374,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, phi[mt], oacc[nt][mt], 0, 0, 0);
-                    oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, plo[mt], oacc[nt][mt], 0, 0, 0);
+                    if constexpr (TERMS == 2) oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, plo[mt], oacc[nt][mt], 0, 0, 0);
                 }
             }
         }
@@ -643,14 +651,14 @@ void tree_attn_f32_kernel(AttnParams p)
     }
 }
 
-template <int DP, int DS, int NW, int RH, int MT, int TS>
+template <int DP, int DS, int NW, int RH, int MT, int TS, int TERMS = 2>
 void launch_bf16(const AttnParams &p, hipStream_t stream, const WalkParams *tail_walk = nullptr)
 {
     constexpr int ROWS = 16 * MT * RH;
     WalkParams w = {};
     if (tail_walk) w = *tail_walk;
     const dim3 grid((unsigned)p.H_kv * ((p.M + ROWS - 1) / ROWS), (p.d + DS - 1) / DS + (tail_walk ? 1 : 0), p.B);
-    launch_kernel(p.d == 128 ? K_ATTN_MFMA : K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS>, grid, dim3(64 * NW), stream, p, w);
+    launch_kernel(p.d == 128 ? K_ATTN_MFMA : K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS, TERMS>, grid, dim3(64 * NW), stream, p, w);
 }
 
 template <int DP, int DS>
@@ -663,9 +671,9 @@ void launch_f32(const AttnParams &p, hipStream_t stream)
 
 int32_t launch_attn_sliced(const AttnParams &p, int columns, hipStream_t stream, const WalkParams *tail_walk)
 {
-    if (columns == 32) launch_bf16<128, 32, 8, 1, 2, 8>(p, stream, tail_walk);
-    else if (columns == 64) launch_bf16<128, 64, 8, 1, 2, 8>(p, stream, tail_walk);
-    else launch_bf16<128, 128, 8, 1, 2, 8>(p, stream, tail_walk);
+    if (columns == 32) launch_bf16<128, 32, 8, 1, 2, 8, 1>(p, stream, tail_walk);
+    else if (columns == 64) launch_bf16<128, 64, 8, 1, 2, 8, 1>(p, stream, tail_walk);
+    else launch_bf16<128, 128, 8, 1, 2, 8, 1>(p, stream, tail_walk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("tree_attn launch failed: %s", hipGetErrorString(e)); return MCSD_E_HIP; }
     return MCSD_OK;
@@ -690,8 +698,11 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
     } else {
         // Rows of a KV head per workgroup and wavefronts.  While the launch fits one workgroup per CU, few
         // rows by eight wavefronts: the walk over the keys is the time, and the key tiles that several
-        // workgroups read come out of L2.  Beyond, four wavefronts (two workgroups per CU) and the
-        // more rows the more workgroups there are, so that a tile is read for more of them.
+        // workgroups read come out of L2; and slices of the output columns as long as those fit, too, since
+        // what counts is the bytes a CU has to read (1000 keys, 28 rows, 8 heads, d 96: 14.9 us whole, 10.9
+        // in slices of 32; 1500 keys, d 64 12.1 and 10.7).  Beyond, four wavefronts (two workgroups per CU) and the
+        // more rows the more workgroups there are, so that a tile is read for more of them.  (The figures for
+        // 8 x 32 rows are of the form in lockstep, which took a quarter longer.)
         // d 64, us at 200 / 1500 keys, 32 rows x 8 wavefronts, 64 x 8, 32 x 4, 64 x 4, 128 x 4:
         //   64 units of 112 rows   (256, 128 workgroups of 32, 64 rows)  7.8/17.4  8.6/22  8.1/20  9.3/28  12/42
         //   256 units of 28        (256)                                 8.2/20.6  8.1/22  8.3/21  8.8/28  11/40
@@ -707,13 +718,16 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
         // 73/273 46/174 33/145 26/142.
         const long units = (long)p.B * p.H_kv, wgs32 = units * ((p.M + 31) / 32), wgs64 = units * ((p.M + 63) / 64);
         if (dp == 64) {
-            if (wgs32 <= 256) launch_bf16<64, 64, 8, 1, 2, 8>(p, stream);
+            if (wgs32 <= 128 && p.d > 32) launch_bf16<64, 32, 8, 1, 2, 8>(p, stream);
+            else if (wgs32 <= 256) launch_bf16<64, 64, 8, 1, 2, 8>(p, stream);
             else if (p.M > 32 && wgs64 <= 256) launch_bf16<64, 64, 8, 2, 2, 8>(p, stream);
             else if (p.M <= 32 || wgs32 <= 768) launch_bf16<64, 64, 4, 1, 2, 4>(p, stream);
             else if (p.M <= 64 || wgs64 < 1024) launch_bf16<64, 64, 4, 2, 2, 4>(p, stream);
             else launch_bf16<64, 64, 4, 4, 2, 4>(p, stream);
         } else if (dp == 128) {
-            if (wgs32 <= 256) launch_bf16<128, 128, 8, 1, 2, 8>(p, stream);
+            if (wgs32 * ((p.d + 31) / 32) <= 256) launch_bf16<128, 32, 8, 1, 2, 8>(p, stream);
+            else if (wgs32 <= 128) launch_bf16<128, 64, 8, 1, 2, 8>(p, stream);
+            else if (wgs32 <= 256) launch_bf16<128, 128, 8, 1, 2, 8>(p, stream);
             else if (p.M > 32 && wgs64 <= 256) launch_bf16<128, 128, 8, 2, 2, 8>(p, stream);
             else if (p.M <= 32) launch_bf16<128, 128, 4, 1, 2, 4>(p, stream);
             else if (p.M <= 64 || wgs64 < 768) launch_bf16<128, 128, 4, 2, 2, 2>(p, stream);
