@@ -1,0 +1,59 @@
+"""Tree attention where requests go out ahead of the sequence length, and where the output columns are
+sliced over workgroups: the rows of the cache past a sequence's length hold NaN, lengths lie around the
+tiles and steps (16, 32, 128, 256 keys) and are shorter than the capacity, head dimensions end inside a slice."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mcsd_oracle as O
+from paper_2401_06706_amd import binding as M
+from paper_2401_06706_amd import device as D
+from paper_2401_06706_amd import workloads as W
+from tests.parity import assert_attn_close
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = (0, 1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 255, 256, 257, 300)
+
+
+def run(dtype, d, H_q, H_kv, kconfig, lengths, capacity):
+    w = W.Workload(name="t", index=72, B=len(lengths), H_q=H_q, H_kv=H_kv, d=d, dtype=dtype, prefix=(max(lengths), max(lengths)),
+                   kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(d + H_q + capacity), L_stride=capacity)
+    ai.prefix_len[:] = lengths
+    print(f"[slices] {dtype} d={d} H={H_q}/{H_kv} N={ai.N} L={list(lengths)} capacity={capacity}", flush=True)
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale,
+                      O.FP32 if dtype == "fp32" else O.BF16, n_threads=16)
+    call = D.make_attn_call(ai)
+    for b, n in enumerate(lengths):
+        call.tensors["k_prefix"][b, :, n:] = float("nan")
+        call.tensors["v_prefix"][b, :, n:] = float("nan")
+    M.mcsd_tree_attn(call.args)
+    torch.cuda.synchronize()
+    assert_attn_close(call.out_numpy(), ref, dtype, f"{dtype} d={d}")
+    # through pages: the same tiles, hence the same bits
+    paged_call, paged, _ = D.make_paged_attn_call(call, ai, 96, seed=d)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert torch.equal(paged_call.out, call.out)
+
+
+# bf16 at d = 128: 28 rows whole (capacity below the slices' range) and sliced, 56, 112 and 224 rows sliced,
+# 112 rows in segments (capacity beyond it); the other head dimensions and fp32, whose last slice is ragged
+@pytest.mark.parametrize("dtype,d,H_q,H_kv,kconfig,capacity", [
+    ("bf16", 128, 2, 2, (4, 2, 2), 300), ("bf16", 128, 2, 2, (4, 2, 2), 640), ("bf16", 128, 8, 8, (4, 2, 2), 1000),
+    ("bf16", 128, 2, 2, (8, 2, 1, 1), 301), ("bf16", 128, 4, 1, (4, 2, 2), 300), ("bf16", 128, 8, 1, (4, 2, 2), 1504),
+    ("bf16", 128, 32, 8, (4, 2, 2), 320), ("bf16", 128, 16, 4, (4, 2, 2), 300), ("bf16", 128, 4, 1, (4, 2, 2), 4000), ("bf16", 64, 4, 2, (4, 2, 2), 300),
+    ("bf16", 40, 2, 2, (4, 2, 2), 300), ("bf16", 24, 2, 2, (2, 2), 300), ("bf16", 96, 2, 2, (4, 2, 2), 301), ("bf16", 72, 8, 8, (4, 2, 2), 300),
+    ("bf16", 120, 16, 16, (2, 2), 300), ("bf16", 200, 2, 2, (4, 2, 2), 300), ("fp32", 64, 2, 2, (4, 2, 2), 300), ("fp32", 36, 2, 2, (2, 2), 300),
+    ("fp32", 128, 1, 1, (4, 2, 2), 303), ("fp32", 128, 16, 16, (4, 2, 2), 300), ("fp32", 100, 1, 1, (2, 2), 300), ("fp32", 228, 1, 1, (2, 2), 300),
+])
+def test_rows_past_the_length_are_not_used(dtype, d, H_q, H_kv, kconfig, capacity):
+    for i in range(0, len(LENGTHS), 5):
+        run(dtype, d, H_q, H_kv, kconfig, LENGTHS[i:i + 5], capacity)
+
+
+def test_a_capacity_below_the_first_tiles():
+    for dtype, d in (("bf16", 128), ("bf16", 64), ("fp32", 128)):
+        for capacity in (1, 31, 96, 128):
+            run(dtype, d, 2, 2, (4, 2, 2), (0, capacity // 2, capacity), capacity)
