@@ -30,6 +30,7 @@ struct AttnParams {
     int R;                // rows per (b, g) in the partial buffers
     int split_bias;       // see split_tiles
     int even_units, even_n; // units of the launch and 256 / units where one workgroup per CU is wanted, or 0 (see split_tiles)
+    int first_ahead;      // ask for the first tiles ahead of the length (see first_tiles_ahead)
     int rank_pairs;       // hand the (sequence, segment) pairs out longest first
     int *chunk_of_launch; // workspace word with the chunk_tiles of this launch, or nullptr: chunk_tiles holds
     float scale_log2;     // scale * log2(e)
@@ -40,6 +41,23 @@ struct AttnParams {
     int page_size, n_pages, max_pages;
 };
 
+
+// Whether the workgroups of a launch ask for their first tiles before the length is there, as if the (contiguous)
+// cache were full: it saves a trip to memory, but a short prefix in a larger cache then comes behind tiles that
+// nothing needs.  Up to 8 MiB of them in all, `tiles` per (sequence, KV head), that costs less than it saves.
+// us with / without at 20, 100 and 300 keys of a cache of 300:
+//   d 128, 28 rows,  64 KV heads, 4 tiles (4 MiB)   7.2/7.2  7.5/8.3  8.9/9.9
+//                   128 (8)                         7.9/7.3  8.1/8.9  9.6/10.2
+//                   256 (16)                        9.8/7.7  9.9/9.3  12.1/11.8
+//                   512 (32)                        13.6/10.2 13.6/13.1 18.4/18.6
+//   d 128, 60 rows, 256, 2 tiles (8)                11.3/10.7 11.5/12.0 14.6/15.1
+//   d 64,  28 rows, 128, 8 tiles (8)                6.8/5.7  7.0/6.4  7.5/8.0
+//                   256 (16)                        9.3/6.3  9.5/7.8  9.7/10.0
+//   d 96,  28 rows, 128, 8 tiles (12)               9.0/6.9  9.3/7.8  9.6/9.9
+inline bool first_tiles_ahead(const AttnParams &p, int tiles, uint32_t row_bytes)
+{
+    return (uint64_t)p.B * p.H_kv * (2u * KT * tiles) * row_bytes <= (8u << 20);
+}
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {

@@ -50,7 +50,7 @@ namespace {
 //      lanes neighbouring bytes; one tile ahead), in-lane 8x8 transpose of the 16-bit
 //      elements, registers -> the same LDS area -> operand (exchange inside 16-lane groups).
 //
-// WHOLE (contiguous cache, no sequence is split, room for KS tiles): a workgroup owns all keys of its unit, so
+// WHOLE (contiguous cache, no sequence is split, room for KS tiles, few units: first_tiles_ahead): a workgroup owns all keys of its unit, so
 // that the first tiles lie at the start of the slab whatever the length is: they are asked for
 // as soon as the arguments are there, as if the cache were full (all rows of the slab may be read), and a wave
 // whose first tile is not a whole one of the prefix asks again.  That takes the length's trip to memory and some
@@ -739,7 +739,8 @@ int32_t launch_tree_attn(const mcsd_attn_desc &d, const mcsd_attn_bufs &b, const
         int walk_rows = 0;
         if (tail_walk && plan.n_chunks_max == 1) { mw = *tail_walk; walk_rows = 1; }
         const dim3 grid(d.H_kv, plan.n_chunks_max * plan.n_row_tiles + walk_rows, d.B);
-        const bool whole = plan.n_chunks_max == 1 && d.L_stride >= KT * (4 >> plan.variant);      // (see tree_attn_mfma_kernel)
+        const int streams = 4 >> plan.variant;
+        const bool whole = plan.n_chunks_max == 1 && d.L_stride >= KT * streams && first_tiles_ahead(p, streams, 256);      // (see tree_attn_mfma_kernel)
         if (plan.variant == 2) launch_attn_shared(p, grid, stream, mw);
         else if (paged) {
             if (plan.variant == 0) launch_kernel(K_ATTN_MFMA, tree_attn_mfma_kernel<1, 4, true, false>, grid, dim3(256), stream, p, mw);

@@ -62,7 +62,7 @@ constexpr uint32_t OFF_NOWHERE = 0x7fffffffu;       // beyond every extent: read
 
 // The prefix rows of a (sequence, KV head) are read through one buffer resource: a contiguous cache, whose offsets stay
 // far from 32 bits.
-__device__ __forceinline__ bool one_resource(const AttnParams &p, uint32_t row_bytes)
+__host__ __device__ __forceinline__ bool one_resource(const AttnParams &p, uint32_t row_bytes)
 {
     return !p.block_table && (uint64_t)p.L_stride * row_bytes <= 0x40000000u;
 }
@@ -164,10 +164,14 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 #pragma unroll
         for (int i = 0; i < NV; ++i) vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off, at + i * (GS / GV) * row_bytes, 0);
     };
-    // The first tiles are asked for before the length is there, as if the cache were full: all rows of the slab
-    // may be read, and what turns out not to be (whole) prefix tiles is requested again below.
+    // OWN: the first tiles are asked for before the length is there, as if the cache were full, where they are few
+    // (first_tiles_ahead): all rows of the slab may be read, and what turns out not to be a (whole) prefix tile is
+    // requested again below.  Not in lockstep, where a wave loads parts of all tiles of the step: with that request 16
+    // sequences of 100 keys in a cache of 600, GQA 32/8, d 96 take 13.2 us, without it 11.5, and no size is faster
+    // with it (the kernel is shorter by a copy of the requests, which counts for launches of a step or two: 64
+    // sequences of 32 keys, d 64 11.5 and 10.3 us, 8 of 300, d 256 16.9 and 16.8).
     constexpr int REACH = OWN ? 1 : TS;         // tiles of a step that one request covers, the first at t0 + my_tile
-    const bool contiguous = one_resource(p, row_bytes), ahead = contiguous && p.L_stride >= (my_tile + REACH) * KT;
+    const bool contiguous = one_resource(p, row_bytes), ahead = OWN && p.first_ahead && p.L_stride >= (my_tile + REACH) * KT;
     if (ahead) request_prefix(0, p.L_stride);
 
     const int L = max(0, min(len, p.L_stride));
@@ -511,20 +515,16 @@ void tree_attn_f32_kernel(AttnParams p)
                 else vraw[n][i] = __builtin_bit_cast(fE, __builtin_amdgcn_raw_buffer_load_b64(rs, v_off[n], at + i * row_bytes, 0));
             }
     };
-    // The prefix of a contiguous cache: one resource, scalar offsets.  The first tiles are asked for before the
-    // length is there, as if the cache were full (all rows of the slab may be read); a wave whose first
-    // tile is not a whole one of the prefix asks again.
+    // The prefix of a contiguous cache: one resource, scalar offsets.  (The first tiles ahead of the length, as in the
+    // bf16 kernel: 20, 60, 100, 300 keys in a cache of 300, 32 heads of 128 7.2, 7.7, 8.3, 11.1 us, here 6.6, 7.3,
+    // 8.0, 11.0; 128 heads 10.3, 11.0, 11.8, 15.8 and 7.6, 9.6, 11.2, 15.6.)
     const size_t slab = ((size_t)b * p.H_kv + g) * (size_t)p.L_stride * row_bytes;
-    const bool contiguous = one_resource(p, row_bytes), ahead = contiguous && p.L_stride >= KS * KW;
-    if (ahead) {
-        request_k(make_rsrc(static_cast<const char *>(p.k_prefix) + slab, (uint32_t)p.L_stride * row_bytes), ks * KW * row_bytes);
-        request_v(make_rsrc(static_cast<const char *>(p.v_prefix) + slab, (uint32_t)p.L_stride * row_bytes), ks * KW * row_bytes);
-    }
+    const bool contiguous = one_resource(p, row_bytes);
     const int L = max(0, min(len, p.L_stride));
     const int tiles_prefix = (L + KW - 1) / KW, t_end = tiles_prefix + (p.N + KW - 1) / KW;
     const __amdgpu_buffer_rsrc_t rs_k = make_rsrc(static_cast<const char *>(p.k_prefix) + slab, contiguous ? (uint32_t)L * row_bytes : 0u);
     const __amdgpu_buffer_rsrc_t rs_v = make_rsrc(static_cast<const char *>(p.v_prefix) + slab, contiguous ? (uint32_t)L * row_bytes : 0u);
-    if (!ahead || (ks + 1) * KW > L) {
+    {
         const TileSrc s = tile_source<KW>(p, b, g, L, tiles_prefix, ks, t_end, row_bytes);
         request_k(make_rsrc(s.kb, s.bytes), 0);
         request_v(make_rsrc(s.vb, s.bytes), 0);
@@ -676,8 +676,10 @@ void launch_bf16(const AttnParams &p, hipStream_t stream, const WalkParams *tail
     constexpr int ROWS = 16 * MT * RH;
     WalkParams w = {};
     if (tail_walk) w = *tail_walk;
+    AttnParams q = p;
+    q.first_ahead = one_resource(p, 2u * p.d) && first_tiles_ahead(p, TS, 2u * p.d);
     const dim3 grid((unsigned)p.H_kv * ((p.M + ROWS - 1) / ROWS), (p.d + DS - 1) / DS + (tail_walk ? 1 : 0), p.B);
-    launch_kernel(p.d == 128 ? K_ATTN_MFMA : K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS, TERMS>, grid, dim3(64 * NW), stream, p, w);
+    launch_kernel(p.d == 128 ? K_ATTN_MFMA : K_ATTN_GENERIC, tree_attn_bf16_kernel<DP, DS, NW, RH, MT, TS, TERMS>, grid, dim3(64 * NW), stream, q, w);
 }
 
 template <int DP, int DS>

@@ -57,3 +57,29 @@ def test_a_capacity_below_the_first_tiles():
     for dtype, d in (("bf16", 128), ("bf16", 64), ("fp32", 128)):
         for capacity in (1, 31, 96, 128):
             run(dtype, d, 2, 2, (4, 2, 2), (0, capacity // 2, capacity), capacity)
+
+
+# The first tiles are asked for ahead of the lengths while they are 8 MiB or less in all: 4 sequences of these shapes
+# are (at the line, where they lie on it), 16 are not.  Both forms walk the same tiles in the same order.
+@pytest.mark.parametrize("kconfig,capacity,few", [((4, 2, 2), 300, 4), ((4, 2, 2, 1, 1), 300, 8)])
+def test_first_tiles_ahead_of_the_lengths_or_not(kconfig, capacity, few):
+    lengths = (20, 0, 1, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 257, 299, 300)
+    w = W.Workload(name="t", index=74, B=16, H_q=32, H_kv=32, d=128, dtype="bf16", prefix=(300, 300), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(few), L_stride=capacity)
+    ai.prefix_len[:] = lengths
+    call = D.make_attn_call(ai)
+    t = call.tensors
+    for b, n in enumerate(lengths):
+        t["k_prefix"][b, :, n:] = float("nan")
+        t["v_prefix"][b, :, n:] = float("nan")
+    M.mcsd_tree_attn(call.args)
+    outs = []
+    for b in range(0, 16, few):
+        part = {k: t[k][b:b + few] for k in ("q", "k_prefix", "v_prefix", "prefix_len", "k_tree", "v_tree")}
+        outs.append(torch.zeros_like(part["q"]))
+        M.mcsd_tree_attn(M.attn_args(part["q"], part["k_prefix"], part["v_prefix"], part["prefix_len"], part["k_tree"], part["v_tree"],
+                                     t["parent"], outs[-1], ai.scale, t["workspace"]))
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat(outs).view(torch.int16), call.out.view(torch.int16))
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
+    assert_attn_close(call.out_numpy(), ref, "bf16", f"{kconfig} capacity={capacity}")
