@@ -197,7 +197,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     };
     auto request_any = [&](int t0) __attribute__((always_inline)) {
         constexpr bool SAME = !OWN && NT / GR <= KT && NT / GV <= KT;       // load i lies in the same tile for all waves
-        if (SAME && (TS <= 2 || contiguous)) {
+        if (SAME && TS <= 2) {
             // a few tiles by scalar arithmetic (32 x 64 keys, GQA 32/8, d 96, two tiles a step: 12.3 us, 13.0 the other way)
             TileSrc src[TS];
 #pragma unroll
@@ -231,6 +231,27 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
             const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
             return make_rsrc(static_cast<const char *>(t0 + j >= tiles_prefix ? tree_block : prefix) + off, (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes);
         };
+        if constexpr (SAME) {
+            // tile by tile, K and V behind each other: the places of all four or eight tiles at once are more than the
+            // scalar registers hold (51 and 63 of them spilled).  us with scalar arithmetic and all places at once / here,
+            // GQA 32/8: 16 x 100 keys, d 96 12.4/11.3, through pages 12.7/11.5; 32 x 64, d 64 10.1/8.7, 10.3/8.8; 8 x 500,
+            // d 256 22.6/22.0, 25.5/22.4
+#pragma unroll
+            for (int j = 0; j < TS; ++j) {
+                const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
+                const uint32_t bytes = (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes;
+                const bool of_tree = t0 + j >= tiles_prefix;
+                const __amdgpu_buffer_rsrc_t rk = make_rsrc(static_cast<const char *>(of_tree ? p.k_tree : p.k_prefix) + off, bytes);
+                const __amdgpu_buffer_rsrc_t rv = make_rsrc(static_cast<const char *>(of_tree ? p.v_tree : p.v_prefix) + off, bytes);
+#pragma unroll
+                for (int i = NL / TS * j; i < NL / TS * (j + 1); ++i)
+                    kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
+#pragma unroll
+                for (int i = NV / TS * j; i < NV / TS * (j + 1); ++i)
+                    vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NL; ++i)
             kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, OWN ? 0 : (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);

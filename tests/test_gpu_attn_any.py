@@ -87,10 +87,13 @@ def test_no_workspace_is_used_and_the_bits_depend_on_the_inputs_alone(dtype, d, 
 
 
 # many units, so that every instantiation is met (the cases above are the small launches)
-@pytest.mark.parametrize("d,B,H_kv,G,kconfig", [
+SPLITS = [
     (64, 16, 10, 2, (4, 2, 2)), (64, 13, 20, 1, (2, 2)), (64, 15, 10, 4, (4, 2, 2)), (64, 20, 20, 2, (4, 2, 2)), (40, 16, 32, 4, (4, 2, 2)),
     (72, 16, 10, 2, (4, 2, 2)), (128 - 8, 13, 20, 1, (2, 2)), (96, 15, 20, 2, (4, 2, 2)), (96, 12, 32, 4, (4, 2, 2)),
-    (136, 2, 3, 1, (2, 2)), (200, 10, 10, 1, (2, 2)), (136, 10, 10, 1, (2, 2)), (256, 20, 10, 1, (2, 2)), (248, 13, 20, 1, (2, 2)), (256, 13, 10, 2, (4, 2, 2))])
+    (136, 2, 3, 1, (2, 2)), (200, 10, 10, 1, (2, 2)), (136, 10, 10, 1, (2, 2)), (256, 20, 10, 1, (2, 2)), (248, 13, 20, 1, (2, 2)), (256, 13, 10, 2, (4, 2, 2))]
+
+
+@pytest.mark.parametrize("d,B,H_kv,G,kconfig", SPLITS)
 def test_every_split_of_the_rows_and_columns(d, B, H_kv, G, kconfig):
     w = W.Workload(name="t", index=72, B=B, H_q=H_kv * G, H_kv=H_kv, d=d, dtype="bf16", prefix=(0, 70), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
     ai = W.gen_attn_inputs(w, np.random.default_rng(d + B), L_stride=300)
@@ -99,3 +102,32 @@ def test_every_split_of_the_rows_and_columns(d, B, H_kv, G, kconfig):
     torch.cuda.synchronize()
     ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
     assert_attn_close(call.out_numpy(), ref, "bf16", f"d={d} units={B * H_kv} rows={ai.N * G}")
+
+
+@pytest.mark.parametrize("d,B,H_kv,G,kconfig", SPLITS)
+def test_every_split_over_several_steps(d, B, H_kv, G, kconfig):
+    """The same launches with lengths of up to three steps of the widest form (eight tiles of 32 keys), around its
+    ends, in a cache with spare rows that hold NaN; through pages, which have no straight-line step, the same
+    bits.  The oracle on every length, 1500 rows in all."""
+    lengths = (600, 0, 70, 255, 256, 257, 300, 512, 513, 530)
+    w = W.Workload(name="t", index=73, B=B, H_q=H_kv * G, H_kv=H_kv, d=d, dtype="bf16", prefix=(0, 600), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
+    rng = np.random.default_rng(d + B)
+    ai = W.gen_attn_inputs(w, rng, L_stride=640)
+    ai.prefix_len[:] = [lengths[b % len(lengths)] for b in range(B)]
+    call = D.make_attn_call(ai)
+    for b in range(B):
+        call.tensors["k_prefix"][b, :, int(ai.prefix_len[b]):] = float("nan")
+        call.tensors["v_prefix"][b, :, int(ai.prefix_len[b]):] = float("nan")
+    M.mcsd_tree_attn(call.args)
+    torch.cuda.synchronize()
+    n = 1500
+    sel = np.stack([np.arange(n) % B, rng.integers(0, ai.N, n), rng.integers(0, ai.H_q, n)], 1).astype(np.int32)
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, sel=sel, n_threads=16)
+    got = call.out_numpy()
+    assert np.isfinite(got).all()
+    assert_attn_close(got[sel[:, 0], sel[:, 1], sel[:, 2]], ref, "bf16", f"d={d} units={B * H_kv} rows={ai.N * G}")
+    for page in (32, 96):
+        paged_call, paged, _ = D.make_paged_attn_call(call, ai, page, seed=d)
+        M.mcsd_tree_attn_paged(paged_call.args, paged)
+        torch.cuda.synchronize()
+        assert torch.equal(paged_call.out, call.out)
