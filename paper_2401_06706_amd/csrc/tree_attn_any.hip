@@ -706,7 +706,7 @@ void launch_bf16(const AttnParams &p, hipStream_t stream, const WalkParams *tail
 template <int DP, int DS>
 void launch_f32(const AttnParams &p, hipStream_t stream)
 {
-    launch_kernel(K_ATTN_GENERIC, tree_attn_f32_kernel<DP, DS>, dim3((unsigned)p.H_kv * ((p.M + 15) / 16), DP / DS, p.B), dim3(512), stream, p);
+    launch_kernel(K_ATTN_GENERIC, tree_attn_f32_kernel<DP, DS>, dim3((unsigned)p.H_kv * ((p.M + 15) / 16), (p.d + DS - 1) / DS, p.B), dim3(512), stream, p);
 }
 
 }  // namespace
