@@ -150,7 +150,8 @@ typedef struct {
 } mcsd_attn_bufs;
 
 /* Bytes of scratch mcsd_tree_attn needs for this descriptor (0 on a bad descriptor).  0 for fp32
- * storage and for d != 128: such calls neither read nor write a workspace. */
+ * storage and for d != 128: such calls neither read nor write a workspace.  The figure depends on
+ * the sizes alone: some calls that have to bring a workspace do not use it. */
 size_t mcsd_attn_workspace_bytes(const mcsd_attn_desc *desc);
 int32_t mcsd_tree_attn(const mcsd_attn_desc *desc, const mcsd_attn_bufs *bufs, void *stream);
 
@@ -174,7 +175,9 @@ int32_t mcsd_tree_attn_static(const mcsd_attn_desc *desc, const mcsd_attn_bufs *
  * attention kernel for all later calls of this process (0 = automatic for each value).
  * variant 1, 2, 3 = the 32-row x 4-key-stream, 64-row x 2-key-stream and shared-tile kernels;
  * chunk_tiles = 32-key tiles per segment; target_items = workgroups aimed at when the segment
- * length is derived.  The workspace size depends on the plan: query mcsd_attn_workspace_bytes
+ * length is derived.  Any value but 0 also keeps calls from the kernel that gives a workgroup all
+ * keys and a slice of the output columns (small launches, caches of middling capacity), which the
+ * automatic plan takes ahead of those three.  The workspace size depends on the plan: query mcsd_attn_workspace_bytes
  * after changing it.  MCSD_E_SHAPE for values out of range. */
 int32_t mcsd_attn_plan_override(int32_t variant, int32_t chunk_tiles, int32_t target_items);
 

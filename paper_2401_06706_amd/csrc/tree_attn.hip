@@ -660,27 +660,36 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     // Launches that leave CUs idle and caches of middling capacity: no segments and no merge, but all keys of 32
     // rows and a slice of the output columns per workgroup of eight waves (tree_attn_bf16_kernel).  A CU takes
     // in about 72 bytes a ns here whatever is in flight, so the fewer bytes each has to read the better: slices of
-    // 32, 64 or 128 columns, as many as fit one workgroup per CU.  The lines are where segments or, with up to
-    // 32 rows, the kernel above with its four waves get ahead (that one splits from 36 tiles on).
-    // us without / with this, at 200, 500, 1000, 1500, 2000 keys (*: measured with two terms per weight and three
-    // barriers in the epilogue, 5 to 12 % slower than now):
-    //   28 rows,  32 KV heads (32 columns)     7.5/8.5* 10.4/9.1  16.8/11.0  12.5/15.7* 14.5/19.2*
-    //   28 rows, 128 KV heads (64)             8.2/10.1* 12.5/13.4* 20.8/17.4 25.6/22.7
-    //   28 rows, 256 KV heads (128)            9.9/13.3* 17.6/20.9* 34.8/28.7 (700: 21.2/22.9)
-    //   56 rows,  16 KV heads (32)            11.1/9.1* 13.6/10.2* 12.8/12.4* 15.5/14.7* 14.6/17.0*
-    //   56 rows,  40 KV heads (64)            11.3/8.9  13.9/10.2  14.1/12.3  17.1/16.4  19.7/23.2*
-    //   60 rows, 128 KV heads (128)           12.0/13.2* 18.8/16.7* 24.4/20.3 33.9/28.8* 44.7/31.7
-    //   112 rows,  8 KV heads (32)            14.0/7.6  11.8/10.0* 12.5/11.0  15.0/14.1* 13.7/16.6*
-    //   112 rows, 32 KV heads (64)            14.6/8.5  13.5/11.6* 15.0/12.3  18.3/14.4  23.5/18.7 (3000: 27.0/25.5)
-    //   112 rows, 64 KV heads (128)           14.9/10.0 15.9/14.6* 23.6/17.3  27.5/21.8  26.5/27.8*
-    //   672 rows,  8 KV heads (128)           13.9/10.2 15.0/14.1* 19.5/14.9  22.4/17.6  21.7/24.4*
+    // 32, 64 or 128 columns, as many as fit one workgroup per CU.  The host knows the capacity only, and the lines
+    // go by it: with spare rows a launch keeps segments and merge however short the sequences are.  They are where
+    // segments or, with up to 32 rows, the kernel above with its four waves get ahead (that one splits from 36 tiles on).
+    // us without / with this, at 200, 500, 1000, 1500, 2000 keys, caches and sequences full:
+    //   28 rows,  32 KV heads (32 columns)     7.3/7.1  10.6/9.4  17.1/11.6 12.6/13.7 14.3/15.8
+    //   28 rows, 128 KV heads (64)             8.5/9.3  11.6/11.4 18.3/15.9 23.6/21.1 31.2/28.5
+    //   28 rows, 256 KV heads (128)            9.8/12.0 15.8/16.8 35.4/28.7 44.1/38.8 58.9/50.0
+    //   56 rows,  16 KV heads (32)            11.1/7.7  13.3/8.7  13.1/11.2 15.8/13.6 14.9/15.9
+    //   56 rows,  40 KV heads (64)            11.4/8.4  14.3/10.4 14.4/12.9 16.4/15.3 19.3/17.6
+    //   56 rows, 128 KV heads, GQA 2 (128)    10.7/10.9 18.6/13.4 (30: 7.9/8.4, 300: 12.4/11.5) 31.2/23.9 47.4/31.3
+    //   60 rows, 128 KV heads (128)           12.3/11.6 17.8/13.8 22.5/18.2 33.6/25.9 45.3/32.5
+    //   112 rows,  8 KV heads (32)            13.6/7.3  11.5/8.5  12.6/10.5 15.5/12.9 14.3/14.8
+    //   112 rows, 32 KV heads (64)            14.1/8.3  13.8/10.3 15.3/12.9 18.0/15.5 21.0/17.5 (3000: 26.1/22.4)
+    //   112 rows, 64 KV heads (128)           14.8/10.2 16.1/12.8 21.0/15.9 25.6/19.0 25.3/22.1
+    //   672 rows,  8 KV heads (128)           14.5/10.0 15.5/11.7 20.2/14.7 23.2/18.0 23.3/21.6
+    // One sequence full and the others of 100 keys: the long one has its slices' CUs only, where segments
+    // take those of the short ones as well.  At 1500, 2000, 2500 keys (1600, 2000, 2400 where marked *):
+    //   28 rows, 4 x 32 KV heads  15.4/15.6 17.5/17.6 19.3/19.8     8 x 32  17.3/20.1 19.1/23.6 19.9/30.4
+    //   60 rows, 4 x 32           18.2/18.5 20.0/21.5 22.7/24.1
+    //   112 rows, 4 x 8           15.8/14.5 18.1/17.0 18.4/19.0     3 x 8*  15.3/14.5 15.4/16.7 15.5/18.0
+    //   224 rows, 2 x 8           16.5/14.2 17.4/17.3 17.6/19.5     8 x 4*  16.4/17.8 16.5/20.3 16.8/21.9
+    // The upper lines are where that loss is no larger yet than the gain of full sequences (3 x 8 of 112 rows, full:
+    // 16.2/15.1 19.8/17.3 20.1/18.6; at 3000 keys 22.0/21.6, and 18.7/21.2 with one full).
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
         const bool some = wgs32 > 64 && wgs32 <= 128;
-        long least = 1, most = some ? 96 : 54;
+        long least = 1, most = some ? 66 : 54;
         if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some ? 50 : 35; }
-        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 14; most = wgs32 <= 128 ? 50 : 66; }
+        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {
             pl.slice_columns = wgs32 <= 64 ? 32 : (wgs32 <= 128 ? 64 : 128);
             pl.n_chunks_max = 1;

@@ -83,3 +83,36 @@ def test_first_tiles_ahead_of_the_lengths_or_not(kconfig, capacity, few):
     assert torch.equal(torch.cat(outs).view(torch.int16), call.out.view(torch.int16))
     ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
     assert_attn_close(call.out_numpy(), ref, "bf16", f"{kconfig} capacity={capacity}")
+
+
+def writes_partials(call, run):
+    """Whether the call `run` leaves something in its workspace: segments and a merge do, slices do not."""
+    call.tensors["workspace"].fill_(77)
+    run()
+    torch.cuda.synchronize()
+    return not bool((call.tensors["workspace"] == 77).all())
+
+
+# Both sides of the lines between slices and segments, one sequence full and the others short (capacities in
+# tiles of 32 keys, one or two of the tree: 65 + 1 and 66 + 1, 49 + 1 ..., 9 + 1 and 8 + 2 beside the whole kernel)
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,capacity,slices", [
+    (4, 32, 8, (4, 2, 2), 2080, True), (4, 32, 8, (4, 2, 2), 2081, False), (2, 64, 8, (4, 2, 2), 2080, True), (3, 32, 8, (4, 2, 2), 2112, False),
+    (8, 32, 8, (4, 2, 2), 1696, True), (8, 32, 8, (4, 2, 2), 1697, False), (4, 32, 32, (4, 2, 2, 1, 1), 2048, True),
+    (4, 32, 32, (4, 2, 2, 1, 1), 2049, False), (1, 32, 32, (4, 2, 2, 1, 1), 1536, True), (1, 32, 32, (4, 2, 2, 1, 1), 1537, False)])
+def test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slices):
+    w = W.Workload(name="t", index=76, B=B, H_q=H_q, H_kv=H_kv, d=128, dtype="bf16", prefix=(capacity, capacity), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(capacity))
+    ai.prefix_len[1:] = 100
+    call = D.make_attn_call(ai)
+    for b in range(1, B):
+        call.tensors["k_prefix"][b, :, 100:] = float("nan")
+        call.tensors["v_prefix"][b, :, 100:] = float("nan")
+    assert writes_partials(call, lambda: M.mcsd_tree_attn(call.args)) != slices
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
+    assert_attn_close(call.out_numpy(), ref, "bf16", f"{B} x {H_q}/{H_kv} capacity={capacity}")
+
+
+# (whole below ten tiles, slices from there on; both without partials)
+@pytest.mark.parametrize("capacity", [224, 225, 256, 257, 383])
+def test_the_lower_line_of_the_slices(capacity):
+    run("bf16", 128, 64, 64, (4, 2, 2, 1, 1), (capacity, capacity - 33, 31), capacity)
