@@ -343,6 +343,26 @@ def test_short_segments_of_small_launches(B, H_q, H_kv, kconfig, prefix, L_strid
     assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
 
 
+# (the 32-row kernel with segments again, the 64-row kernel and shared tiles where the launch is not in slices of the
+# output columns: capacities beyond those, or more than 256 workgroups of 32 rows)
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,prefix,L_stride", [
+    (1, 32, 8, (2, 2), (2000, 2000), 2000), (1, 32, 32, (4, 2, 2, 1, 1), (2000, 2000), 2000), (2, 64, 8, (2, 2), (30, 2000), 2000),
+    (1, 32, 32, (4, 2, 2, 1, 1), (700, 900), 1700), (9, 32, 8, (4, 2, 2), (30, 300), 300), (9, 32, 8, (4, 2, 2), (500, 500), 500)])
+def test_short_segments_and_their_merge(B, H_q, H_kv, kconfig, prefix, L_stride):
+    """Segments of two or three tiles per key stream with a merge behind them, which the workspace shows: against the
+    oracle, contiguous and paged."""
+    ai = W.gen_attn_inputs(wl(H_q=H_q, H_kv=H_kv, kconfig=kconfig, prefix=prefix, B=B), np.random.default_rng(B + H_q + H_kv), L_stride=L_stride)
+    call = D.make_attn_call(ai)
+    call.tensors["workspace"].fill_(77)
+    M.mcsd_tree_attn(call.args)
+    paged_call, paged, _ = D.make_paged_attn_call(call, ai, 64, seed=B)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert not bool((call.tensors["workspace"] == 77).all())
+    assert_attn_close(call.out_numpy(), oracle_rows(ai), "bf16", f"short segments {prefix} of {L_stride}")
+    assert torch.equal(call.out.view(torch.int16), paged_call.out.view(torch.int16))
+
+
 @pytest.mark.parametrize("B,H_q,H_kv,kconfig,L_stride", [(1, 32, 32, (4, 2, 2), 8200), (2, 16, 16, (4, 2, 2), 8200), (1, 32, 16, (4, 2, 2), 12000), (3, 8, 8, (2, 2), 30000)])
 def test_one_workgroup_per_unit_by_the_real_lengths(B, H_q, H_kv, kconfig, L_stride):
     """Up to 64 rows per KV head and a cache that would be cut into 257..447 segments, or more when it is

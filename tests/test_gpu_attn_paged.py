@@ -51,13 +51,14 @@ def test_paged_batched_ragged_against_oracle_on_gathered_cache():
     assert_attn_close(paged_call.out_numpy(), ref, "bf16", "paged")
 
 
+@pytest.mark.parametrize("capacity", [1536, 3072])
 @pytest.mark.parametrize("page_size", [32, 96, 256])
-def test_paged_many_rows_per_kv_head_against_oracle(page_size):
-    """224 query rows per KV head (the kernel whose waves share each K/V tile and look the block
-    table up one step ahead), ragged prefixes, pages of one tile, three tiles (not a power of two)
-    and eight tiles; several segments per sequence and one."""
+def test_paged_many_rows_per_kv_head_against_oracle(page_size, capacity):
+    """224 query rows per KV head (in a cache of 1536 rows slices of the output columns, of 3072 the kernel whose
+    waves share each K/V tile and look the block table up one step ahead), ragged prefixes, pages of one tile,
+    three tiles (not a power of two) and eight tiles; several segments per sequence and one."""
     w = W.WORKLOADS["c4"].with_(B=3, H_q=16, H_kv=2, kconfig=(4, 2, 2), prefix=(5, 1500))
-    ai = W.gen_attn_inputs(w, np.random.default_rng(page_size), L_stride=1536)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(page_size), L_stride=capacity)
     tree, paged_call, table = run_both(ai, page_size, seed=page_size)
     assert torch.equal(tree.out.view(torch.int16), paged_call.out.view(torch.int16))
     kpool = paged_call.tensors["k_pool"].view(torch.int16).cpu().numpy().view(np.uint16)

@@ -116,3 +116,43 @@ def test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slic
 @pytest.mark.parametrize("capacity", [224, 225, 256, 257, 383])
 def test_the_lower_line_of_the_slices(capacity):
     run("bf16", 128, 64, 64, (4, 2, 2, 1, 1), (capacity, capacity - 33, 31), capacity)
+
+
+@pytest.mark.parametrize("H_q,H_kv,bad", [(4, 4, {1: -5, 9: 2 ** 30}), (4, 4, {0: 2 ** 30, 20: -1}), (8, 2, {4: -(2 ** 31), 12: 2 ** 31 - 1}), (4, 4, {25: -5, 26: 2 ** 30})])
+def test_table_entries_outside_the_pool_read_as_zero_keys(H_q, H_kv, bad):
+    """Pages of 32 rows of one sequence of 600 keys in a cache of 864, in slices: page j is tile j, the first
+    step of a workgroup is tiles 0 .. 7.  Entries of used pages outside the pool read as zero keys, those of pages past the
+    length (the last case) as nothing."""
+    w = W.Workload(name="t", index=75, B=1, H_q=H_q, H_kv=H_kv, d=128, dtype="bf16", prefix=(600, 600), kconfig=(4, 2, 2), V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(H_q), L_stride=864)
+    tree = D.make_attn_call(ai)
+    paged_call, paged, table = D.make_paged_attn_call(tree, ai, 32)
+    entries = table.astype(np.int64)
+    for j, e in bad.items():
+        entries[0, j] = e
+        ai.k_prefix[0, :, 32 * j:32 * j + 32] = 0
+        ai.v_prefix[0, :, 32 * j:32 * j + 32] = 0
+    paged_call.tensors["block_table"].copy_(torch.from_numpy(entries.astype(np.int32)))
+    assert not writes_partials(paged_call, lambda: M.mcsd_tree_attn_paged(paged_call.args, paged))
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=4)
+    assert_attn_close(paged_call.out_numpy(), ref, "bf16", f"{bad}")
+
+
+@pytest.mark.parametrize("H_q,H_kv,capacity", [(32, 32, 512), (8, 1, 1500), (32, 8, 1000)])
+def test_slices_give_the_same_bits_on_every_run(H_q, H_kv, capacity):
+    """Scores that grow along the prefix raise the running maxima again and again (as in the test of the whole and
+    segmented kernels): a result read before it has landed would move the raises around."""
+    w = W.Workload(name="t", index=77, B=2, H_q=H_q, H_kv=H_kv, d=128, dtype="bf16", prefix=(capacity, capacity), kconfig=(4, 2, 2), V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(H_q))
+    ramp = np.linspace(0.2, 3.0, capacity, dtype=np.float32)[None, None, :, None]
+    ai.k_prefix = W.f32_to_bf16_bits(W.bf16_bits_to_f32(ai.k_prefix) * ramp)
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
+    call = D.make_attn_call(ai)
+    assert not writes_partials(call, lambda: M.mcsd_tree_attn(call.args))
+    first = call.out.clone()
+    assert_attn_close(call.out_numpy(), ref, "bf16", f"ramp {H_q}/{H_kv}")
+    for rep in range(4):
+        call.out.fill_(3.0)
+        M.mcsd_tree_attn(call.args)
+        torch.cuda.synchronize()
+        assert torch.equal(call.out.view(torch.int16), first.view(torch.int16)), rep

@@ -12,12 +12,16 @@ from tests.parity import assert_attn_close, compare_verify, run_oracle
 pytestmark = pytest.mark.gpu
 
 
-def test_verify_step_matches_separate_calls_and_oracle():
-    w = W.WORKLOADS["c4"].with_(B=4, H_q=8, H_kv=8, prefix=(100, 700), V=8192, n_greedy=2)
+# (the walk rides on the only launch of the attention, slices of the output columns, or on the merge of its segments)
+@pytest.mark.parametrize("longest,merged", [(700, False), (2500, True)])
+def test_verify_step_matches_separate_calls_and_oracle(longest, merged):
+    w = W.WORKLOADS["c4"].with_(B=4, H_q=8, H_kv=8, prefix=(100, longest), V=8192, n_greedy=2)
     ai, vi = W.gen_attn_inputs(w), W.gen_verify_inputs(w)
     a1, v1 = D.make_attn_call(ai), D.make_verify_call(vi, want_residual=True)
+    a1.tensors["workspace"].fill_(77)
     M.mcsd_verify_step(a1.args, v1.args)
     torch.cuda.synchronize()
+    assert bool((a1.tensors["workspace"] == 77).all()) != merged
     a2, v2 = D.make_attn_call(ai), D.make_verify_call(vi, want_residual=True)
     M.mcsd_tree_attn(a2.args)
     M.mcsd_verify_sample(v2.args)
