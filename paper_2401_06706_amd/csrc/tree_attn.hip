@@ -40,7 +40,7 @@ namespace {
 // segment.  Waves of one key stream read the same K/V tiles (the second read is served by the
 // L1/L2 caches).
 //
-// Data movement per 32-key tile and wave (8 KB of K, 8 KB of V, one 8.5 KB LDS area):
+// Data movement per 32-key tile and wave (8 KB of K, 8 KB of V, one 16.9 KB LDS area):
 //   K  global -> registers with fully contiguous 1 KB loads (issued one tile ahead),
 //      registers -> LDS in MFMA-operand order (16-byte granules, XOR-swizzled so that
 //      both the stores and the operand loads are bank-conflict free), LDS -> operand.
@@ -54,8 +54,8 @@ namespace {
 // that the first tiles lie at the start of the slab whatever the length is: they are asked for
 // as soon as the arguments are there, as if the cache were full (all rows of the slab may be read), and a wave
 // whose first tile is not a whole one of the prefix asks again.  That takes the length's trip to memory and some
-// 300 instructions out of the chain; with it, and one barrier instead of five behind the loop, one sequence of 512
-// keys and 32 heads 11.7 -> 10.2 us.
+// 300 instructions out of the chain; with it, and one barrier instead of five behind the loop, one sequence of 300
+// keys and 32 heads 10.0 -> 8.4 us (9.2 without the requests ahead).
 template <int RH, int KS, bool PAGED, bool WHOLE>
 __global__ __launch_bounds__(RH * KS * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_mfma_kernel(AttnParams p, WalkParams w)
@@ -620,8 +620,8 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     // A split plan that leaves CUs idle: with the merge launch paid anyway, segments of 3 tiles per key
     // stream (2 with four streams) as long as all fit one per CU; on shared tiles only up to the eight
     // that the merge takes in one trip.  With the merge, segments of 6 tiles per stream / these: 60 rows,
-    // 32 KV heads, 1000 keys 15.9 / 13.8 us; 48 rows, 2 x 8 KV heads, 1000 keys 15.6 / 12.4; 24 rows, 8 KV
-    // heads, 2000 keys 14.3 / 12.6; 112 rows, 8 KV heads, 500 keys 14.7 / 13.1, but 2000 keys 15.4 / 16.0.
+    // 32 KV heads, 2000 keys 19.3 / 16.0 us; 48 rows, 2 x 8 KV heads, 2000 keys 16.0 / 12.9; 24 rows, 8 KV heads,
+    // 2000 keys 13.1 / 11.4; 112 rows, 9 x 8 KV heads, 300 keys 15.0 / 14.6, but 500 keys 16.1 / 18.3.
     if (forced_target <= 0 && (total_max + chunk / 2) / chunk > 1) {
         long fine = (total_max * units + 255) / 256;
         if (pl.variant == 2 && fine < (total_max + 7) / 8) fine = (total_max + 7) / 8;

@@ -7,8 +7,8 @@
 //
 // In both, a lane of S^T = K Q^T holds scores of one query row, which is the B operand layout of
 // O^T += V^T P^T: the weights never leave their lane.  The fp32 kernel multiplies in fp32
-// (v_mfma_f32_16x16x4_f32); the bf16 kernel feeds PV with two bf16 terms per weight, which hold it to
-// 2^-17 (see weight_hi_bits).
+// (v_mfma_f32_16x16x4_f32); the bf16 kernel feeds PV with two bf16 terms per weight where d != 128, which hold
+// it to 2^-17 (see weight_hi_bits), and with one at d = 128, as the other kernels for it.
 #include <type_traits>
 
 #include "attn_common.h"
@@ -480,7 +480,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
 // matrix rate at one workgroup per CU (d 128, slices of 32 columns: 40 instructions of 32 cycles per wave
 // and tile, two waves per SIMD, 9 us for 1000 keys): 2 sequences of 301 and 1000 tokens, 16 heads of
 // 128, 28 nodes: 326 us with one workgroup per (node, head) on the vector units, 19.7 us with slices of 64
-// columns, 17.5 us here; relative error against 64 bits 5.2e-7 on the vector units, 2.9e-7 since.
+// columns, 17.7 us here; relative error against 64 bits 5.2e-7 on the vector units, 2.9e-7 since.
 //   S^T: the contraction index is d; step (kk, j) of lane (lj, lc) takes d = 16 kk + 4 lj + j, so
 //        that both operands are 16-byte pieces (K from LDS, Q in registers).
 //   O^T: step i takes key 4 lj + i, the key whose weight the lane holds; row index lc of the matrix
