@@ -115,7 +115,7 @@ def test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slic
 # (whole below ten tiles, slices from there on; both without partials)
 @pytest.mark.parametrize("capacity", [224, 225, 256, 257, 383])
 def test_the_lower_line_of_the_slices(capacity):
-    run("bf16", 128, 64, 64, (4, 2, 2, 1, 1), (capacity, capacity - 33, 31), capacity)
+    run("bf16", 128, 32, 32, (4, 2, 2, 1, 1), (capacity, capacity - 33, 31), capacity)
 
 
 @pytest.mark.parametrize("H_q,H_kv,bad", [(4, 4, {1: -5, 9: 2 ** 30}), (4, 4, {0: 2 ** 30, 20: -1}), (8, 2, {4: -(2 ** 31), 12: 2 ** 31 - 1}), (4, 4, {25: -5, 26: 2 ** 30})])
