@@ -681,13 +681,15 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     //   60 rows, 4 x 32           18.2/18.5 20.0/21.5 22.7/24.1
     //   112 rows, 4 x 8           15.8/14.5 18.1/17.0 18.4/19.0     3 x 8*  15.3/14.5 15.4/16.7 15.5/18.0
     //   224 rows, 2 x 8           16.5/14.2 17.4/17.3 17.6/19.5     8 x 4*  16.4/17.8 16.5/20.3 16.8/21.9
-    // The upper lines are where that loss is no larger yet than the gain of full sequences (3 x 8 of 112 rows, full:
-    // 16.2/15.1 19.8/17.3 20.1/18.6; at 3000 keys 22.0/21.6, and 18.7/21.2 with one full).
+    // The upper lines are where that loss is no larger yet than the gain of full sequences.  These figures are of inputs
+    // that the memory-side cache holds; from memory, 2000 keys, full and one full: 112 rows, 4 x 8 24.2/20.0 and
+    // 19.2/18.6, 3 x 8 20.6/19.4 and 16.3/18.8 (1500: 17.8/16.4, 16.3/15.6), 60 rows, 4 x 32 47.9/33.4 and 22.4/26.8,
+    // 2 x 32 24.3/22.8 and 21.6/21.4, but 56 rows, 40 heads 20.0/21.7 (1500: 17.8/18.0; warm 17.9/17.3 and 16.5/15.5).
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
         const bool some = wgs32 > 64 && wgs32 <= 128;
-        long least = 1, most = some ? 66 : 54;
+        long least = 1, most = some && wgs32 > 96 ? 66 : 54;
         if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some ? 50 : 35; }
         else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {

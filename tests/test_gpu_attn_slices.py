@@ -94,11 +94,12 @@ def writes_partials(call, run):
 
 
 # Both sides of the lines between slices and segments, one sequence full and the others short (capacities in
-# tiles of 32 keys, one or two of the tree: 65 + 1 and 66 + 1, 49 + 1 ..., 9 + 1 and 8 + 2 beside the whole kernel)
+# tiles of 32 keys, one or two of the tree: 65 + 1 and 66 + 1, 53 + 1 and 54 + 1, 48 + 2 and 49 + 2, ...)
 @pytest.mark.parametrize("B,H_q,H_kv,kconfig,capacity,slices", [
-    (4, 32, 8, (4, 2, 2), 2080, True), (4, 32, 8, (4, 2, 2), 2081, False), (2, 64, 8, (4, 2, 2), 2080, True), (3, 32, 8, (4, 2, 2), 2112, False),
+    (4, 32, 8, (4, 2, 2), 2080, True), (4, 32, 8, (4, 2, 2), 2081, False), (2, 64, 8, (4, 2, 2), 2080, True), (3, 32, 8, (4, 2, 2), 1696, True), (3, 32, 8, (4, 2, 2), 1697, False),
     (8, 32, 8, (4, 2, 2), 1696, True), (8, 32, 8, (4, 2, 2), 1697, False), (4, 32, 32, (4, 2, 2, 1, 1), 2048, True),
-    (4, 32, 32, (4, 2, 2, 1, 1), 2049, False), (1, 32, 32, (4, 2, 2, 1, 1), 1536, True), (1, 32, 32, (4, 2, 2, 1, 1), 1537, False)])
+    (4, 32, 32, (4, 2, 2, 1, 1), 2049, False), (2, 32, 32, (4, 2, 2, 1, 1), 1536, True), (2, 32, 32, (4, 2, 2, 1, 1), 1537, False),
+    (1, 32, 32, (4, 2, 2, 1, 1), 1536, True), (1, 32, 32, (4, 2, 2, 1, 1), 1537, False)])
 def test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slices):
     w = W.Workload(name="t", index=76, B=B, H_q=H_q, H_kv=H_kv, d=128, dtype="bf16", prefix=(capacity, capacity), kconfig=kconfig, V=8, sigma_q=1.0, variant=0)
     ai = W.gen_attn_inputs(w, np.random.default_rng(capacity))
