@@ -79,6 +79,43 @@ __device__ __forceinline__ double wave_sum(double v)    // valid in lane 63
     return v;
 }
 
+// The same sum in every lane.  The last two steps exchange whole rows of 16 lanes and the two halves of the
+// wavefront (v_permlane16_swap, v_permlane32_swap on two copies leave one side in the first, the other in
+// the second): one instruction per word, and both partners add the same two numbers.
+__device__ __forceinline__ double add_rows(double v)
+{
+    const long long x = __double_as_longlong(v);
+    const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double(((long long)h[0] << 32) | l[0]) + __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+
+__device__ __forceinline__ double add_halves(double v)
+{
+    const long long x = __double_as_longlong(v);
+    const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __longlong_as_double(((long long)h[0] << 32) | l[0]) + __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double mov_dpp_d(double v)    // (every lane has a source)
+{
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(x >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+__device__ __forceinline__ double wave_sum_all(double v)
+{
+    v += mov_dpp_d<DPP_QUAD_1032>(v);
+    v += mov_dpp_d<DPP_QUAD_2301>(v);
+    v += mov_dpp_d<DPP_ROW_HALF_MIRROR>(v);
+    v += mov_dpp_d<DPP_ROW_MIRROR>(v);
+    return add_halves(add_rows(v));
+}
+
 // Inclusive running sum over the lanes of the wavefront: shifts inside the rows of 16 lanes
 // (a lane without a source adds zero), then the totals of the rows before it.
 __device__ __forceinline__ double wave_scan_inclusive(double v)
@@ -111,11 +148,11 @@ __device__ __forceinline__ double row_totals_scattered(double (&x)[ITEMS], int l
             for (int j = 0; j < N / 2; ++j) {
                 const double mine = keep_hi ? x[j + N / 2] : x[j];
                 const double give = keep_hi ? x[j] : x[j + N / 2];
-                x[j] = mine + dpp_d<CTRL, 0xf>(0.0, give);
+                x[j] = mine + mov_dpp_d<CTRL>(give);
             }
             if (keep_hi) which += N / 2;
         } else {
-            x[0] += dpp_d<CTRL, 0xf>(0.0, x[0]);
+            x[0] += mov_dpp_d<CTRL>(x[0]);
         }
     };
     // Widest exchange first: the row mirror (lane i <-> 15 - i) flips bit 3, and every later

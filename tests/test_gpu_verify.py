@@ -412,3 +412,35 @@ def test_residual_that_vanishes_after_removals(V, B, variant):
     tested = ~np.isnan(orc.ratio)
     np.testing.assert_array_equal(~np.isnan(gpu["ratio"]), tested)
     assert np.abs(gpu["ratio"] - orc.ratio)[tested].max() <= 1e-6
+
+
+@pytest.mark.parametrize("B", [1, 4], ids=["few-rows", "many-rows"])
+@pytest.mark.parametrize("V", [5, 300, 4096, 8190, 16384, 16641, 20003, 32000, 32768, 50001, 65536])
+def test_endpoints_at_the_edges_of_what_a_wavefront_holds(V, B):
+    """129 rows per sequence, each with its mass on a token and its neighbours: the first and last ones of the
+    256-token pieces and of the wavefronts' shares, and of the row.  All weights are exact in fp32, so the
+    endpoint of a uniform in the middle of the token's interval is that token."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(128,), variant=W.WITH_REPLACEMENT)
+    rng = np.random.default_rng(V)
+    vi = W.gen_verify_inputs(w, rng, draw_candidates_on_host=False)
+    pieces = (V + 255) // 256
+    edges = sorted({min(max(e + d, 0), V - 1) for n in (1, 4, 8) for s in range(n + 1)
+                    for e in (256 * (s * pieces // n), 256 * s * n, 1024 * (s * pieces // n // 4)) for d in (-1, 0, 1)} | {0, V - 1, V // 2})
+    vi.cand_tok[:] = 0
+    vi.u_accept[:] = np.float32(0.999)
+    vi.u_endpoint[:] = np.float32(0.5)
+    vi.target_logits[:] = -np.inf
+    vi.draft_logits[:] = 0.0
+    want = np.zeros((B, 129), np.int64)
+    for b in range(B):
+        for r in range(129):
+            x = want[b, r] = edges[(r + 37 * b) % len(edges)]
+            n = [t for t in (x - 1, x, x + 1) if 0 <= t < V]
+            vi.target_logits[b, r, n] = 1.25
+            vi.u_endpoint[b, r] = (n.index(x) + 0.5) / len(n)
+    vi.target_logits[:, 0, :V - 1] = -np.inf        # the root: token 0 is its only candidate, 128 times, and is rejected
+    vi.target_logits[:, 0, V - 1] = 1.25
+    want[:, 0] = V - 1
+    gpu, orc, _ = check(vi, f"edges V={V} B={B}", want_residual=V <= 20003)
+    np.testing.assert_array_equal(orc.endpoint, want)
+    np.testing.assert_array_equal(gpu["endpoint"], want)
