@@ -77,21 +77,28 @@ __device__ __forceinline__ uint32_t weight_hi_bits(float p)
     return __builtin_elementwise_sub_sat(__float_as_uint(p), 1u) & 0xffff0000u;
 }
 
+// 16 bytes per lane from memory into LDS, lane after lane from `to` on (the same in all lanes).  Zeros from beyond the resource.
+__device__ __forceinline__ void load_into_lds(__amdgpu_buffer_rsrc_t rs, uint32_t *to, uint32_t lane_offset, uint32_t offset)
+{
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)to, 16, lane_offset, offset, 0, 0);
+}
+
 // Workgroup of NW waves, one unit (sequence, KV head, row tile) with all of its keys, DS of the output
 // columns.  Wave (rh, ks) owns 16 MT query rows and every KS-th tile; the TS tiles of a step are loaded
 // one step ahead into registers, by all threads together or, where every wave has a tile to itself, by
-// that wave without a barrier in the loop, and go through LDS in their natural order
-// with row pitches that keep all accesses free of bank conflicts (K: 4 words, V: 8 words past a
-// multiple of 32).  V is read back with the transposing LDS load.  The streams meet in LDS at the
+// that wave without a barrier in the loop.  Those of all threads go through LDS in their natural order
+// with row pitches against bank conflicts (K: 4 words, V: 8 words past a multiple of 32); a wave's own go straight
+// into LDS (see OWN).  V is read back with the transposing LDS load.  The streams meet in LDS at the
 // end: no memory besides the arguments, so that calls on several streams share nothing, and the
 // bits of a result depend on the arguments alone.  (Which instantiation: launch_attn_any and, for d = 128, make_attn_plan.)
-// Bound by what one CU takes in, about 72 bytes a ns (two steps ahead in registers, with or without lockstep, only
-// makes the first ones come later), behind 5 to 6 us of launch, first tiles, masks and epilogue.  Measured (d 64, 8 sequences of
+// Bound, a wave with its own tiles, by the instructions of two waves per SIMD and by LDS, behind 6 to 7 us of launch, first tiles,
+// masks and epilogue: with all tiles read from L1 a launch takes as long, without exponentials 0.6 us less of 13.  Measured (d 64, 8 sequences of
 // 200..2000 tokens, GQA 32/8, 28 nodes): one workgroup per (node, head) on the vector units, every one
 // reading the cache again, 1262 us; the keys split over 512 workgroups of four waves, partials in
 // the caller's workspace and a merge launch, 21.0 us; this kernel with the place of every tile worked out
 // by every wave 19.4 us, with one resource for the prefix 18.4, and with tiles of their own instead of
-// steps in lockstep 14.6.  (One lane per tile for a wave's own tile, all waves through all steps and three
+// steps in lockstep 14.6; with tiles that go straight into LDS 13.4.  (One lane per tile for a wave's own tile, all waves through all steps and three
 // barriers behind them: 9 sequences of 111 keys 8.0 against 7.1 us, paged, 4 x 1000 keys, GQA 32/8 13.1 against 11.4.)  That split is faster only
 // for long prompts on few heads (one sequence of 16000 keys and 8 KV heads: 33 us, here 112, 4720 on the
 // vector units; d 256, 2 heads, 1500 keys: 21, 34, 421), and it needs a workspace that these shapes
@@ -117,8 +124,11 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     constexpr int NL = TS * KT * GR / NT, NV = TS * KT * GV / NT;        // K and V loads per thread and step
     static_assert(KT * GV % 64 == 0 && NV > 0, "a wave's share of a load lies in one tile");
     constexpr int PK = DP / 2 + 4, PV = DS / 2 + 8;      // row pitches in words
-    constexpr int STREAM_WORDS = KT * (PK + PV);
     constexpr int PO = DS + 4;                           // row pitch of the epilogue's fp32 area
+    constexpr bool OWN = RH == 1 && TS == KS;
+    constexpr int V_AT = OWN ? KT * DP / 2 : KT * PK;    // where V lies behind K
+    constexpr int TILE_WORDS = OWN ? KT * (DP + DS) / 2 : KT * (PK + PV);
+    constexpr int STREAM_WORDS = OWN && TILE_WORDS < ROWS * PO ? ROWS * PO : TILE_WORDS;        // (OWN: a wavefront's outputs take the place of its tile)
     constexpr int LDS_WORDS = TS * STREAM_WORDS > KS * ROWS * PO ? TS * STREAM_WORDS : KS * ROWS * PO;
     constexpr int NKK = DP / 32, NNT = DS / 16;
 
@@ -142,11 +152,35 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     // a barrier in the loop.  Load i of a thread: granule gid + GS i of the TS x 32 rows of the step, or of the
     // wavefront's tile, row-major, that is column granule c of row r0 + i GS / GR.  Columns past d are
     // requested beyond every extent.
-    constexpr bool OWN = RH == 1 && TS == KS;
+    // The tiles behind the first go from memory straight into LDS, 16 bytes per lane at consecutive places: the stores of
+    // them through registers were what bounded a step (576 KB of ds_write_b128, 32 rows, 1500 keys, d 128 in slices of 64:
+    // 3.8 of the 7.5 us of all steps with the loads, as much without them; GQA 32/8, 4 x 100..1500 keys 14.2 -> 12.7 us,
+    // d 64, 8 x 200..2000 14.7 -> 13.4, d 96, 4 x 200..1500 14.7 -> 13.1, 28 rows, 512 keys, 32 heads 8.95 -> 8.7; one tile per wave,
+    // 8 x 30..64 keys, d 96 7.2 -> 7.4).  Those places are the rows without
+    // a gap, so a lane takes the granule of its row that keeps the reads free of bank conflicts: K granule c of row r lies
+    // at place c ^ f(r), V in pairs of granules, pair n of row r at place n ^ h(r) (16 consecutive rows of an operand,
+    // and the 8 of a transposing read, then meet all banks once).
     constexpr int GS = OWN ? 64 : NT;
     static_assert(OWN || TS > 2 || (NT / GR <= KT && NT / GV <= KT), "without block-table entries ahead");
     static_assert((GS / GR % KT == 0 || KT % (GS / GR) == 0) && (GS / GV % KT == 0 || KT % (GS / GV) == 0), "a wave's share of a load lies in one tile");
     const int gid = OWN ? lane : tid, my_tile = OWN ? ks : 0;
+    constexpr int KR = 64 / GR, VR = 64 / GV;            // OWN: rows per load
+    constexpr int KVAR = OWN ? 16 / KR : 1, VVAR = OWN && VR < 8 ? 8 / VR : 1;  // loads after which the places repeat
+    static_assert(!OWN || (DP <= 128 && NL % KVAR == 0 && NV % VVAR == 0), "places");
+    auto place_k = [](int r) __attribute__((always_inline)) { return DP == 128 ? r & 15 : (r >> 1) & 7; };
+    auto place_v = [](int r) __attribute__((always_inline)) { return DS == 128 ? r & 7 : (DS == 64 ? (r >> 1) & 3 : (r >> 2) & 1); };
+    uint32_t ko[KVAR], vo[VVAR];
+#pragma unroll
+    for (int i = 0; i < KVAR; ++i) {
+        const int c = lane % GR ^ place_k(KR * i + lane / GR);
+        ko[i] = 8 * c < p.d ? lane / GR * row_bytes + 16u * c : OFF_NOWHERE;
+    }
+#pragma unroll
+    for (int i = 0; i < VVAR; ++i) {
+        const int c = lane % GV ^ (2 * place_v(VR * i + lane / GV));
+        vo[i] = d0 + 8 * c < p.d ? lane / GV * row_bytes + 2u * d0 + 16u * c : OFF_NOWHERE;
+    }
+    uint32_t *const own_tile = s_big + (OWN ? ks : 0) * STREAM_WORDS;
     const uint32_t k_col = 8 * (gid % GR) < p.d ? 16u * (gid % GR) : OFF_NOWHERE;
     const uint32_t v_col = d0 + 8 * (gid % GV) < p.d ? 2u * d0 + 16u * (gid % GV) : OFF_NOWHERE;
     const uint32_t k_off = k_col == OFF_NOWHERE ? k_col : k_col + gid / GR * row_bytes, k_off_tile = k_col == OFF_NOWHERE ? k_col : k_col + gid / GR % KT * row_bytes;
@@ -155,10 +189,27 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     // A step of prefix tiles of a contiguous cache: one resource over the sequence's rows (those past the
     // last one read as zero), scalar offsets.
     const size_t kv_head = (size_t)b * p.H_kv + g, slab = kv_head * (size_t)p.L_stride * row_bytes;
-    auto request_prefix = [&](int t0, int rows) __attribute__((always_inline)) {
+    // OWN: a tile that starts `at` bytes into the resources, into registers or (dma) into its place in LDS
+    auto request_own = [&](__amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv, uint32_t at, auto dma) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            if constexpr (decltype(dma)::value) load_into_lds(rk, own_tile + 256 * i, ko[i % KVAR], at + i * KR * row_bytes);
+            else kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, ko[i % KVAR], at + i * KR * row_bytes, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if constexpr (decltype(dma)::value) load_into_lds(rv, own_tile + V_AT + 256 * i, vo[i % VVAR], at + i * VR * row_bytes);
+            else vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, vo[i % VVAR], at + i * VR * row_bytes, 0);
+        }
+    };
+    auto request_prefix = [&](int t0, int rows, auto dma) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t rk = make_rsrc(static_cast<const char *>(p.k_prefix) + slab, (uint32_t)rows * row_bytes);
         const __amdgpu_buffer_rsrc_t rv = make_rsrc(static_cast<const char *>(p.v_prefix) + slab, (uint32_t)rows * row_bytes);
         const uint32_t at = (uint32_t)(t0 + my_tile) * (KT * row_bytes);
+        if constexpr (OWN) {
+            request_own(rk, rv, at, dma);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NL; ++i) kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off, at + i * (GS / GR) * row_bytes, 0);
 #pragma unroll
@@ -172,7 +223,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     // sequences of 32 keys, d 64 11.5 and 10.3 us, 8 of 300, d 256 16.9 and 16.8).
     constexpr int REACH = OWN ? 1 : TS;         // tiles of a step that one request covers, the first at t0 + my_tile
     const bool contiguous = one_resource(p, row_bytes), ahead = OWN && p.first_ahead && p.L_stride >= (my_tile + REACH) * KT;
-    if (ahead) request_prefix(0, p.L_stride);
+    if (ahead) request_prefix(0, p.L_stride, std::false_type());
 
     const int L = max(0, min(len, p.L_stride));
     const int tiles_prefix = (L + KT - 1) / KT, t_end = tiles_prefix + (p.N + KT - 1) / KT;
@@ -195,7 +246,7 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
         page += page_step; page_row += row_step;
         if (page_row >= p.page_size) { page_row -= p.page_size; ++page; }
     };
-    auto request_any = [&](int t0) __attribute__((always_inline)) {
+    auto request_any = [&](int t0, auto dma) __attribute__((always_inline)) {
         constexpr bool SAME = !OWN && NT / GR <= KT && NT / GV <= KT;       // load i lies in the same tile for all waves
         if (SAME && TS <= 2) {
             // a few tiles by scalar arithmetic (32 x 64 keys, GQA 32/8, d 96, two tiles a step: 12.3 us, 13.0 the other way)
@@ -231,6 +282,10 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
             const size_t off = (uint32_t)__builtin_amdgcn_readlane(lo, j) | (size_t)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32;
             return make_rsrc(static_cast<const char *>(t0 + j >= tiles_prefix ? tree_block : prefix) + off, (uint32_t)__builtin_amdgcn_readlane(rows, j) * row_bytes);
         };
+        if constexpr (OWN) {
+            request_own(tile(p.k_prefix, p.k_tree, 0), tile(p.v_prefix, p.v_tree, 0), 0, dma);
+            return;
+        }
         if constexpr (SAME) {
             // tile by tile, K and V behind each other: the places of all four or eight tiles at once are more than the
             // scalar registers hold (51 and 63 of them spilled).  us with scalar arithmetic and all places at once / here,
@@ -254,13 +309,13 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
         }
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, OWN ? 0 : (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
+            kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.k_prefix, p.k_tree, (wave * 64 + NT * i) / GR / KT), k_off_tile, i * (GS / GR) % KT * row_bytes, 0);
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, OWN ? 0 : (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
+            vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(tile(p.v_prefix, p.v_tree, (wave * 64 + NT * i) / GV / KT), v_off_tile, i * (GS / GV) % KT * row_bytes, 0);
     };
     look_up(0);
-    if (!ahead || (my_tile + REACH) * KT > L) request_any(0);
+    if (!ahead || (my_tile + REACH) * KT > L) request_any(0, std::false_type());
     look_up(TS);
 
     // Q operand: lane (lj, lc) holds Q[row0 + WROWS rh + 16 mt + lc][32 kk + 8 lj .. + 7]
@@ -297,24 +352,50 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     // of the next one prefix tiles, of a contiguous cache.
     auto step = [&](const int t0, auto plain) __attribute__((always_inline)) {
         constexpr bool PLAIN = decltype(plain)::value;
-        if (!OWN) __syncthreads();          // the last step's operands have been read
+        bf16x8 kop[OWN ? 2 * NKK : 1], vops[OWN ? NNT : 1];
+        // Ahead of the scores in slices of 32 columns, behind their matrix instructions in wider ones (28 rows, 512 keys, 32 heads, slices of
+        // 32: 8.7 us and 9.1; GQA 32/8, 4 x 100..1500 keys, slices of 64: 12.8 and 12.7; d 64, 8 x 200..2000: 13.6 and 13.4).
+        auto v_and_next = [&]() __attribute__((always_inline)) {
+            const uint32_t *vl = own_tile + V_AT + (4 * lj + (lc >> 2)) * (DS / 2) + (lc & 3) * 2;
+            const int at_v = place_v(4 * lj + (lc >> 2));
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int row = (gid + GS * i) / GR;
-            *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + row % KT * PK + 4 * (gid % GR)) = kraw[i];
-        }
+            for (int nt = 0; nt < (OWN ? NNT : 0); ++nt) {
+                const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + (nt ^ at_v) * 8));
+                const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + 16 * (DS / 2) + (nt ^ at_v) * 8));
+                vops[nt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+            if (PLAIN || t0 + TS + my_tile < t_end) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (all operands have left)
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (PLAIN) request_prefix(t0 + TS, L, std::true_type());
+                else { request_any(t0 + TS, std::true_type()); look_up(t0 + 2 * TS); }
+            }
+        };
+        if constexpr (OWN) {
+            // The operands leave LDS for registers at once, and the next tile takes their place while this one is computed.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const uint32_t *kt = own_tile + lc * (DP / 2);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int row = (gid + GS * i) / GV;
-            *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + KT * PK + row % KT * PV + 4 * (gid % GV)) = vraw[i];
-        }
-        if (PLAIN) request_prefix(t0 + TS, L);
-        else if (t0 + TS < t_end) { request_any(t0 + TS); look_up(t0 + 2 * TS); }
-        if (OWN) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int kk = 0; kk < NKK; ++kk) {
+                const int c = 4 * ((4 * kk + lj) ^ place_k(lc));
+                kop[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + c));
+                kop[NKK + kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + 16 * (DP / 2) + c));
+            }
+            if constexpr (DS < 64) v_and_next();
         } else {
+            __syncthreads();                // the last step's operands have been read
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const int row = (gid + GS * i) / GR;
+                *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + row % KT * PK + 4 * (gid % GR)) = kraw[i];
+            }
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int row = (gid + GS * i) / GV;
+                *reinterpret_cast<u32x4 *>(s_big + (my_tile + row / KT) * STREAM_WORDS + V_AT + row % KT * PV + 4 * (gid % GV)) = vraw[i];
+            }
+            if (PLAIN) request_prefix(t0 + TS, L, std::false_type());
+            else if (t0 + TS < t_end) { request_any(t0 + TS, std::false_type()); look_up(t0 + 2 * TS); }
             __syncthreads();
         }
         if (!wave_active) return;
@@ -322,20 +403,21 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
         for (int ts = ks; ts < TS; ts += KS) {
             const int t = t0 + ts;
             if (!PLAIN && !OWN && t >= t_end) break;
-            const uint32_t *kt = s_big + ts * STREAM_WORDS, *vt = kt + KT * PK;
+            const uint32_t *kt = s_big + ts * STREAM_WORDS, *vt = kt + V_AT;
             f32x4 sacc[2][MT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) { sacc[0][mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; sacc[1][mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk) {
-                const bf16x8 k0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + lc * PK + 16 * kk + 4 * lj));
-                const bf16x8 k1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + (16 + lc) * PK + 16 * kk + 4 * lj));
+                const bf16x8 k0 = OWN ? kop[OWN ? kk : 0] : __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + lc * PK + 16 * kk + 4 * lj));
+                const bf16x8 k1 = OWN ? kop[OWN ? NKK + kk : 0] : __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kt + (16 + lc) * PK + 16 * kk + 4 * lj));
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     sacc[0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qreg[mt][kk], sacc[0][mt], 0, 0, 0);
                     sacc[1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qreg[mt][kk], sacc[1][mt], 0, 0, 0);
                 }
             }
+            if constexpr (OWN && DS >= 64) v_and_next();
             // lane (lj, lc): row 16 mt + lc, keys 16 sub + 4 lj + i
             const bool tree = !PLAIN && t >= tiles_prefix;
             const int nvalid = PLAIN || tree ? KT : min(KT, L - t * KT);          // (a tree tile's mask ends with the tree)
@@ -412,9 +494,14 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
             const uint32_t *vl = vt + (4 * lj + (lc >> 2)) * PV + (lc & 3) * 2;
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt) {
-                const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + nt * 8));
-                const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + 16 * PV + nt * 8));
-                const bf16x8 vop = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                bf16x8 vop;
+                if constexpr (OWN) {
+                    vop = vops[nt];
+                } else {
+                    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + nt * 8));
+                    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vl + 16 * PV + nt * 8));
+                    vop = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     oacc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, phi[mt], oacc[nt][mt], 0, 0, 0);
@@ -422,12 +509,17 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
                 }
             }
         }
-        if (OWN) {                          // the operands have been read before the next tile is stored
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
     };
-    if (OWN) __syncthreads();               // the masks are there (the other form passes a barrier before it reads them)
+    if (OWN) {
+        __syncthreads();                    // the masks are there (the other form passes a barrier before it reads them)
+        // the first tile, through registers (it may have been asked for twice)
+        if (my_tile < t_end) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4 *>(own_tile + 256 * i + 4 * lane) = kraw[i];
+#pragma unroll
+            for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4 *>(own_tile + V_AT + 256 * i + 4 * lane) = vraw[i];
+        }
+    }
     int t0 = 0;
     if (contiguous)
         for (; (t0 + my_tile + REACH) * KT <= L && t0 + TS + my_tile + REACH <= tiles_prefix; t0 += TS) step(t0, std::true_type());

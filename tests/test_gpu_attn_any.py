@@ -131,3 +131,23 @@ def test_every_split_over_several_steps(d, B, H_kv, G, kconfig):
         M.mcsd_tree_attn_paged(paged_call.args, paged)
         torch.cuda.synchronize()
         assert torch.equal(paged_call.out, call.out)
+
+
+@pytest.mark.parametrize("d", [8, 40, 64, 72, 88, 96, 104, 120, 128])
+@pytest.mark.parametrize("H_kv,G", [(2, 1), (64, 4)], ids=["slices", "whole"])
+def test_tiles_behind_the_first(d, H_kv, G):
+    """Lengths around the steps of eight tiles, where a wavefront has one tile, or one more that comes while the first
+    is computed: whole ones, ragged ones and the tree's; columns that end inside an operand. Contiguous and through pages."""
+    lengths = np.array([257] if H_kv > 2 else [225, 255, 256, 257, 300, 511, 513, 780], np.int32)
+    w = W.Workload(name="t", index=73, B=len(lengths), H_q=H_kv * G, H_kv=H_kv, d=d, dtype="bf16", prefix=(800, 800), kconfig=(4, 2, 2), V=8, sigma_q=1.0, variant=0)
+    ai = W.gen_attn_inputs(w, np.random.default_rng(d + H_kv), L_stride=803)
+    ai.prefix_len[:] = lengths
+    ref = O.tree_attn(ai.q, ai.k_prefix, ai.v_prefix, ai.prefix_len, ai.k_tree, ai.v_tree, ai.parent, ai.scale, O.BF16, n_threads=16)
+    call = D.make_attn_call(ai)
+    M.mcsd_tree_attn(call.args)
+    torch.cuda.synchronize()
+    assert_attn_close(call.out_numpy(), ref, "bf16", f"d={d}")
+    paged_call, paged, _ = D.make_paged_attn_call(call, ai, 32, seed=d)
+    M.mcsd_tree_attn_paged(paged_call.args, paged)
+    torch.cuda.synchronize()
+    assert torch.equal(paged_call.out, call.out)
