@@ -155,8 +155,8 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     // The tiles behind the first go from memory straight into LDS, 16 bytes per lane at consecutive places: the stores of
     // them through registers were what bounded a step (576 KB of ds_write_b128, 32 rows, 1500 keys, d 128 in slices of 64:
     // 3.8 of the 7.5 us of all steps with the loads, as much without them; GQA 32/8, 4 x 100..1500 keys 14.2 -> 12.7 us,
-    // d 64, 8 x 200..2000 14.7 -> 13.4, d 96, 4 x 200..1500 14.7 -> 13.1, 28 rows, 512 keys, 32 heads 8.95 -> 8.7; one tile per wave,
-    // 8 x 30..64 keys, d 96 7.2 -> 7.4).  Those places are the rows without
+    // d 64, 8 x 200..2000 14.7 -> 13.4, d 96, 4 x 200..1500 14.7 -> 13.1, 28 rows, 512 keys, 32 heads 8.95 -> 8.7; launches of
+    // one tile per wave as before).  Those places are the rows without
     // a gap, so a lane takes the granule of its row that keeps the reads free of bank conflicts: K granule c of row r lies
     // at place c ^ f(r), V in pairs of granules, pair n of row r at place n ^ h(r) (16 consecutive rows of an operand,
     // and the 8 of a transposing read, then meet all banks once).
@@ -191,15 +191,21 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     const size_t kv_head = (size_t)b * p.H_kv + g, slab = kv_head * (size_t)p.L_stride * row_bytes;
     // OWN: a tile that starts `at` bytes into the resources, into registers or (dma) into its place in LDS
     auto request_own = [&](__amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv, uint32_t at, auto dma) __attribute__((always_inline)) {
+        // (places and offsets counted up as they are needed: kept ready for all loads they do not fit the scalar registers)
+        int word = (int)(own_tile - s_big);
+        uint32_t k_at = at, v_at = at;
+        if constexpr (decltype(dma)::value) asm volatile("" : "+s"(word));
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            if constexpr (decltype(dma)::value) load_into_lds(rk, own_tile + 256 * i, ko[i % KVAR], at + i * KR * row_bytes);
-            else kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, ko[i % KVAR], at + i * KR * row_bytes, 0);
+        for (int i = 0; i < NL; ++i, k_at += KR * row_bytes) {
+            if constexpr (decltype(dma)::value) load_into_lds(rk, s_big + word + 256 * i, ko[i % KVAR], k_at);
+            else kraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, ko[i % KVAR], k_at, 0);
+            if constexpr (decltype(dma)::value) asm volatile("" : "+s"(k_at));
         }
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if constexpr (decltype(dma)::value) load_into_lds(rv, own_tile + V_AT + 256 * i, vo[i % VVAR], at + i * VR * row_bytes);
-            else vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, vo[i % VVAR], at + i * VR * row_bytes, 0);
+        for (int i = 0; i < NV; ++i, v_at += VR * row_bytes) {
+            if constexpr (decltype(dma)::value) load_into_lds(rv, s_big + word + V_AT + 256 * i, vo[i % VVAR], v_at);
+            else vraw[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, vo[i % VVAR], v_at, 0);
+            if constexpr (decltype(dma)::value) asm volatile("" : "+s"(v_at));
         }
     };
     auto request_prefix = [&](int t0, int rows, auto dma) __attribute__((always_inline)) {
