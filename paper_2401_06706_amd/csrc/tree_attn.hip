@@ -658,8 +658,8 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
         pl.ws_bytes = 0;
     }
     // Launches that leave CUs idle and caches of middling capacity: no segments and no merge, but all keys of 32
-    // rows and a slice of the output columns per workgroup of eight waves (tree_attn_bf16_kernel).  A CU takes
-    // in about 72 bytes a ns here whatever is in flight, so the fewer bytes each has to read the better: slices of
+    // rows and a slice of the output columns per workgroup of eight waves (tree_attn_bf16_kernel).  What
+    // a wave does in its step is the time here, so the fewer columns it has the better: slices of
     // 32, 64 or 128 columns, as many as fit one workgroup per CU.  The host knows the capacity only, and the lines
     // go by it: with spare rows a launch keeps segments and merge however short the sequences are.  They are where
     // segments or, with up to 32 rows, the kernel above with its four waves get ahead (that one splits from 36 tiles on).
@@ -685,12 +685,18 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     // that the memory-side cache holds; from memory, 2000 keys, full and one full: 112 rows, 4 x 8 24.2/20.0 and
     // 19.2/18.6, 3 x 8 20.6/19.4 and 16.3/18.8 (1500: 17.8/16.4, 16.3/15.6), 60 rows, 4 x 32 47.9/33.4 and 22.4/26.8,
     // 2 x 32 24.3/22.8 and 21.6/21.4, but 56 rows, 40 heads 20.0/21.7 (1500: 17.8/18.0; warm 17.9/17.3 and 16.5/15.5).
+    // 28 rows (4 and 24 alike) by more than 160 workgroups, since the tiles go straight into LDS (tree_attn_any.hip), from memory, without / with
+    // this: full; lengths spread evenly from an eighth on; one full and the others of 100 keys:
+    //   6 x 32 heads   1110 keys  30.3/25.2 25.9/21.9 17.9/17.3   1560  39.1/32.4 27.2/26.9 17.8/19.2   2000  49.2/39.5 35.0/32.6 16.2/20.6
+    //   8 x 32                    36.2/30.9 27.6/23.0 17.8/16.7         47.0/40.4 35.6/31.1 19.7/18.9         58.8/50.4 39.2/37.2 19.9/22.2
+    //   11 x 16                   29.5/24.6 27.3/21.1 15.8/14.6         38.3/30.4 26.6/26.0 17.8/17.3
+    //   5 x 32 (160)  1500  34.7/28.1 22.7/25.6 17.8/19.7
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
         const bool some = wgs32 > 64 && wgs32 <= 128;
         long least = 1, most = some && wgs32 > 96 ? 66 : 54;
-        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some ? 50 : 35; }
+        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some || wgs32 > 160 ? 50 : 35; }
         else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {
             pl.slice_columns = wgs32 <= 64 ? 32 : (wgs32 <= 128 ? 64 : 128);

@@ -113,6 +113,14 @@ def test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slic
     assert_attn_close(call.out_numpy(), ref, "bf16", f"{B} x {H_q}/{H_kv} capacity={capacity}")
 
 
+# The same for up to 32 rows per KV head: 49 + 1 tiles above 160 workgroups, 34 + 1 from 129 up to there
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig,capacity,slices", [
+    (8, 32, 32, (4, 2, 2), 1568, True), (8, 32, 32, (4, 2, 2), 1569, False), (23, 28, 7, (2, 2), 1567, True), (23, 28, 7, (2, 2), 1600, False),
+    (5, 32, 32, (4, 2, 2), 1088, True), (5, 32, 32, (4, 2, 2), 1089, False)])
+def test_lines_of_up_to_32_rows(B, H_q, H_kv, kconfig, capacity, slices):
+    test_lines_between_slices_and_segments(B, H_q, H_kv, kconfig, capacity, slices)
+
+
 # (whole below ten tiles, slices from there on; both without partials)
 @pytest.mark.parametrize("capacity", [224, 225, 256, 257, 383])
 def test_the_lower_line_of_the_slices(capacity):
