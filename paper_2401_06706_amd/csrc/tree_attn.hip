@@ -691,13 +691,21 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     //   8 x 32                    36.2/30.9 27.6/23.0 17.8/16.7         47.0/40.4 35.6/31.1 19.7/18.9         58.8/50.4 39.2/37.2 19.9/22.2
     //   11 x 16                   29.5/24.6 27.3/21.1 15.8/14.6         38.3/30.4 26.6/26.0 17.8/17.3
     //   5 x 32 (160)  1500  34.7/28.1 22.7/25.6 17.8/19.7
+    // The lower lines, the kernel above whole / this, at 32, 96, 150, 180, 210, 240, 350 keys, all full (lengths spread: alike or better):
+    //   28 rows,  32 KV heads (32)   7.6/7.1 7.7/7.1 7.8/7.6 7.6/7.6 7.6/7.7 8.5/8.1 9.5/8.8     (7 and 8 tiles go twice round its four waves)
+    //   28 rows,   8 KV heads (32)   6.8/6.2 7.3/6.8 7.6/7.6 7.4/7.6 7.4/7.6 8.4/7.9 8.5/7.9
+    //   28 rows,  96 KV heads (64)   30: 7.7/7.7, 60: 7.8/8.1, 200: 8.5/9.2, 400: 11.3/11.0, 550: 12.7/12.0
+    //   28 rows, 192 KV heads (128)  30: 8.0/9.5, 60: 8.3/10.1, 200: 9.5/11.7, 550: 14.9/16.6, 700: 16.8/18.5
+    //   60 rows (nodes), 128 KV heads (128)  10.2/9.8 10.7/10.8 12.0/11.1 12.1/11.4 13.0/11.8
+    //   56 rows (nodes),  80 KV heads (128)   9.6/9.0 10.1/10.0 11.6/10.8 11.5/10.9 12.3/11.2
+    //   56 rows, 28 nodes, 128 KV heads (128) 8.7/9.4  9.4/10.6 10.2/10.5 11.3/11.0 11.3/11.1 12.2/11.6    (one tile of the tree, not two)
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
         const bool some = wgs32 > 64 && wgs32 <= 128;
         long least = 1, most = some && wgs32 > 96 ? 66 : 54;
-        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? 14 : (some ? 22 : 25); most = some || wgs32 > 160 ? 50 : 35; }
-        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
+        if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? (total_max <= 6 ? 1 : 9) : (some ? 22 : 25); most = some || wgs32 > 160 ? 50 : 35; }
+        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 || d.N > 32 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {
             pl.slice_columns = wgs32 <= 64 ? 32 : (wgs32 <= 128 ? 64 : 128);
             pl.n_chunks_max = 1;

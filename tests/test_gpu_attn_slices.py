@@ -127,6 +127,14 @@ def test_the_lower_line_of_the_slices(capacity):
     run("bf16", 128, 32, 32, (4, 2, 2, 1, 1), (capacity, capacity - 33, 31), capacity)
 
 
+# (28 rows: slices up to six tiles and from nine on, whole between; 60 rows of 60 nodes and 56 of 28 by more than 128 workgroups)
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig", [(2, 4, 4, (4, 2, 2)), (5, 16, 16, (4, 2, 2, 1, 1)), (17, 16, 8, (4, 2, 2))])
+@pytest.mark.parametrize("capacity", [1, 33, 160, 161, 224, 225, 256, 257])
+def test_the_lower_lines_for_few_rows(B, H_q, H_kv, kconfig, capacity):
+    lengths = tuple(max(0, capacity - 37 * b) for b in range(B))
+    run("bf16", 128, H_q, H_kv, kconfig, lengths, capacity)
+
+
 @pytest.mark.parametrize("H_q,H_kv,bad", [(4, 4, {1: -5, 9: 2 ** 30}), (4, 4, {0: 2 ** 30, 20: -1}), (8, 2, {4: -(2 ** 31), 12: 2 ** 31 - 1}), (4, 4, {25: -5, 26: 2 ** 30})])
 def test_table_entries_outside_the_pool_read_as_zero_keys(H_q, H_kv, bad):
     """Pages of 32 rows of one sequence of 600 keys in a cache of 864, in slices: page j is tile j, the first
