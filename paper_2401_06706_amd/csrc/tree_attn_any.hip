@@ -839,7 +839,7 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
         // Rows of a KV head per workgroup and wavefronts.  While the launch fits one workgroup per CU, few
         // rows by eight wavefronts: the walk over the keys is the time, and the key tiles that several
         // workgroups read come out of L2; and slices of the output columns as long as those fit, too, since
-        // what counts is the bytes a CU has to read (1000 keys, 28 rows, 8 heads, d 96: 14.9 us whole, 10.9
+        // what counts is what a wavefront does in its step (1000 keys, 28 rows, 8 heads, d 96: 14.9 us whole, 10.9
         // in slices of 32; 1500 keys, d 64 12.1 and 10.7).  Beyond, four wavefronts (two workgroups per CU) and the
         // more rows the more workgroups there are, so that a tile is read for more of them.  (The figures for
         // 8 x 32 rows are of the form in lockstep, which took a quarter longer.)
@@ -856,11 +856,20 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
         // d 256, eight wavefronts and 32 rows, slices of 64, 128, 256 columns, four wavefronts: 64 units 11/35
         // 12/41 13/41 15/51; 128 units 20/73 13/46 15/55 15/58; 192 units 29/103 23/86 16/61 16/62; 512 units
         // 73/273 46/174 33/145 26/142.
+        // 257 to 512 workgroups of 32 rows, more than 32 rows, since a wavefront's own tiles go straight into LDS: 64 rows x 8 in
+        // lockstep, eight tiles a step / 32 x 4, two workgroups per CU, with caches of 256, 320, 600, 1000 keys, all full; lengths
+        // spread evenly from an eighth on; all of a quarter (the host knows the capacity only):
+        //   d 64, 8 x 32 units of 56 rows  11.7/10.7 11.3/9.7 8.0/8.3   11.8/10.9 11.4/10.0 8.0/8.7   15.3/13.4 14.1/11.9 9.2/9.5   20.9/17.8 19.4/14.2
+        //         9 x 8 of 112             10.4/10.1 10.5/9.6 7.7/7.6   10.4/10.1 10.5/9.5 7.8/8.0    12.9/12.2 12.8/10.8 8.4/8.8   17.9/15.1 17.7/13.2
+        //   d 96, 8 x 32 of 56             16.3/14.2 15.1/12.1 10.8/10.1 17.2/14.8 15.6/12.8 10.9/10.7 22.0/18.5 19.8/15.3 12.5/12.0 34.0/27.8 28.8/19.6
+        //         9 x 8 of 112             14.6/12.9 14.3/12.0 10.1/9.6  15.1/13.1 14.3/11.9 10.1/10.2 18.8/16.3 17.8/13.9 11.3/11.1 27.0/21.2 25.0/17.6
+        // Below (200 keys: 9.8/10.0 9.1/9.7 8.0/8.6 and 13.5/13.2 12.2/12.0, 9 x 8 8.5/9.1 and 11.7/12.0) one step of the lockstep has all tiles.
+        const int tiles = (p.L_stride + 31) / 32 + (p.N + 31) / 32;
         const long units = (long)p.B * p.H_kv, wgs32 = units * ((p.M + 31) / 32), wgs64 = units * ((p.M + 63) / 64);
         if (dp == 64) {
             if (wgs32 <= 128 && p.d > 32) launch_bf16<64, 32, 8, 1, 2, 8>(p, stream);
             else if (wgs32 <= 256) launch_bf16<64, 64, 8, 1, 2, 8>(p, stream);
-            else if (p.M > 32 && wgs64 <= 256) launch_bf16<64, 64, 8, 2, 2, 8>(p, stream);
+            else if (p.M > 32 && wgs64 <= 256 && tiles <= 16) launch_bf16<64, 64, 8, 2, 2, 8>(p, stream);
             else if (p.M <= 32 || wgs32 <= 768) launch_bf16<64, 64, 4, 1, 2, 4>(p, stream);
             else if (p.M <= 64 || wgs64 < 1024) launch_bf16<64, 64, 4, 2, 2, 4>(p, stream);
             else launch_bf16<64, 64, 4, 4, 2, 4>(p, stream);
@@ -868,8 +877,8 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
             if (wgs32 * ((p.d + 31) / 32) <= 256) launch_bf16<128, 32, 8, 1, 2, 8>(p, stream);
             else if (wgs32 <= 128) launch_bf16<128, 64, 8, 1, 2, 8>(p, stream);
             else if (wgs32 <= 256) launch_bf16<128, 128, 8, 1, 2, 8>(p, stream);
-            else if (p.M > 32 && wgs64 <= 256) launch_bf16<128, 128, 8, 2, 2, 8>(p, stream);
-            else if (p.M <= 32) launch_bf16<128, 128, 4, 1, 2, 4>(p, stream);
+            else if (p.M > 32 && wgs64 <= 256 && tiles <= 8) launch_bf16<128, 128, 8, 2, 2, 8>(p, stream);
+            else if (wgs32 <= 512 || p.M <= 32) launch_bf16<128, 128, 4, 1, 2, 4>(p, stream);
             else if (p.M <= 64 || wgs64 < 768) launch_bf16<128, 128, 4, 2, 2, 2>(p, stream);
             else launch_bf16<128, 128, 4, 4, 2, 2>(p, stream);
         } else {

@@ -288,7 +288,7 @@ struct Share {
 //
 // Bound: HBM in a batch (16 sequences of 61 rows of 32000, 8 of them argmax: 171 MB in 33 us), the vector units of one CU
 // for a single sequence (29 rows, 512 threads, a row with four rejections): the target row there 1.5 us and the draft row 3.8
-// (a CU takes in 72 bytes a ns), all exponentials and sums 6.4, 1.4 per rejection, 0.9 of which is the pass (two products, a
+// (256 KB through one CU, from memory), all exponentials and sums 6.4, 1.4 per rejection, 0.9 of which is the pass (two products, a
 // conversion and an fp64 addition per token, at the full rate of a SIMD), 1.2 the endpoint.  With the residual in the row, the
 // ratio and beta divided behind the barrier, and piece totals of the whole row for the endpoint it was 1.7 per rejection and
 // 2.3 for the endpoint.  A call with its walk: c2's 29 rows 18.6 -> 17.3 us, 6 x 29 rows of 50001 32.8 -> 28.3 (its items

@@ -135,6 +135,14 @@ def test_the_lower_lines_for_few_rows(B, H_q, H_kv, kconfig, capacity):
     run("bf16", 128, H_q, H_kv, kconfig, lengths, capacity)
 
 
+# (257 to 512 workgroups of 32 rows: 64 rows in lockstep up to 16 tiles at d <= 64 and eight beyond, then 32 rows with tiles of their own)
+@pytest.mark.parametrize("d,capacity", [(64, 480), (64, 481), (40, 700), (96, 224), (96, 225), (72, 300), (120, 520)])
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig", [(9, 32, 8, (4, 2, 2)), (13, 20, 10, (4, 2, 2)), (6, 80, 16, (2, 2, 2))])
+def test_more_than_one_workgroup_of_32_rows_per_cu(d, capacity, B, H_q, H_kv, kconfig):
+    lengths = tuple(max(0, capacity - 41 * b) for b in range(B))
+    run("bf16", d, H_q, H_kv, kconfig, lengths, capacity)
+
+
 @pytest.mark.parametrize("H_q,H_kv,bad", [(4, 4, {1: -5, 9: 2 ** 30}), (4, 4, {0: 2 ** 30, 20: -1}), (8, 2, {4: -(2 ** 31), 12: 2 ** 31 - 1}), (4, 4, {25: -5, 26: 2 ** 30})])
 def test_table_entries_outside_the_pool_read_as_zero_keys(H_q, H_kv, bad):
     """Pages of 32 rows of one sequence of 600 keys in a cache of 864, in slices: page j is tile j, the first
