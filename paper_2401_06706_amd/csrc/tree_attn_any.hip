@@ -171,12 +171,12 @@ void tree_attn_bf16_kernel(AttnParams p, WalkParams w)
     auto place_v = [](int r) __attribute__((always_inline)) { return DS == 128 ? r & 7 : (DS == 64 ? (r >> 1) & 3 : (r >> 2) & 1); };
     uint32_t ko[KVAR], vo[VVAR];
 #pragma unroll
-    for (int i = 0; i < KVAR; ++i) {
+    for (int i = 0; i < (OWN ? KVAR : 0); ++i) {
         const int c = lane % GR ^ place_k(KR * i + lane / GR);
         ko[i] = 8 * c < p.d ? lane / GR * row_bytes + 16u * c : OFF_NOWHERE;
     }
 #pragma unroll
-    for (int i = 0; i < VVAR; ++i) {
+    for (int i = 0; i < (OWN ? VVAR : 0); ++i) {
         const int c = lane % GV ^ (2 * place_v(VR * i + lane / GV));
         vo[i] = d0 + 8 * c < p.d ? lane / GV * row_bytes + 2u * d0 + 16u * c : OFF_NOWHERE;
     }
