@@ -517,7 +517,7 @@ void verify_rows_kernel(VerifyParams p)
                 }
             }
             mq = row_top(mq, 1);
-            double partq = 0.0;
+            double partq[4] = {0.0, 0.0, 0.0, 0.0};     // (by fourths as well: equal rows have equal sums)
 #pragma unroll
             for (int g = 0; g < ITEMS; g += G) {
                 if (g > 0 && g >= own.items) continue;
@@ -525,16 +525,16 @@ void verify_rows_kernel(VerifyParams p)
                 for (int j = g; j < g + G; ++j) {
                     if (j < RQ) {
                         eq[j < RQ ? j : 0] = exp_weights(eq[j < RQ ? j : 0], mq, c2);
-                        partq += sum4(eq[j < RQ ? j : 0]);
+                        partq[j / GI] += sum4(eq[j < RQ ? j : 0]);
                     } else if (j < own.items) {
                         const float4 e = exp_weights(s_q[(j - RQ) * VT + t], mq, c2);
                         s_q[(j - RQ) * VT + t] = e;
-                        partq += sum4(e);
+                        partq[j / GI] += sum4(e);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            leave_sum(partq, 1, 0);
+            leave_sum((partq[0] + partq[1]) + (partq[2] + partq[3]), 1, 0);
             leave_weights();
         }
         leave_sum((part[0] + part[1]) + (part[2] + part[3]), 0, 0);
@@ -618,13 +618,16 @@ void verify_rows_kernel(VerifyParams p)
                     // rejected: the residual with C + A / Z_q, in fp64 but for the two products per token.  (The token that
                     // leaves q keeps its e_q in the row: its residual is 0 now and stays 0 whatever is subtracted later.)
                     const double A_of = A, C_of = C, a_of = my_a;
-                    C += A * rz;
+                    // A / Z_q: the product with 1 / Z_q, and what is missing there (so that it is 1 for equal sums)
+                    double beta = A * rz;
+                    beta = rz > 0.0 ? fma(fma(-beta, Zq, A), rz, beta) : 0.0;
+                    C += beta;
                     Ch = (float)C;
                     Cl = (float)(C - (double)Ch);
                     sum_residual();
                     slot ^= 1;
                     leave_sum((part[0] + part[1]) + (part[2] + part[3]), 0, slot);
-                    my_a = fmax(0.0, my_a - A * rz * my_q);
+                    my_a = fmax(0.0, my_a - beta * my_q);
                     const bool gone = removes && ((good >> l) & 1ull), at_one = (__ballot(sure) >> l) & 1ull;
                     const int tok = __builtin_amdgcn_readlane(my_tok, l);
                     const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_q32), l));

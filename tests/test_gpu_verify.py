@@ -444,3 +444,22 @@ def test_endpoints_at_the_edges_of_what_a_wavefront_holds(V, B):
     gpu, orc, _ = check(vi, f"edges V={V} B={B}", want_residual=V <= 20003)
     np.testing.assert_array_equal(orc.endpoint, want)
     np.testing.assert_array_equal(gpu["endpoint"], want)
+
+
+@pytest.mark.parametrize("variant", [W.WITH_REPLACEMENT, W.WITHOUT_REPLACEMENT], ids=["wr", "wor"])
+@pytest.mark.parametrize("V,B", [(700, 24), (2001, 24), (8190, 24), (16383, 24), (20003, 24), (32000, 128), (32766, 128), (50001, 12), (65536, 12)])
+def test_equal_rows_leave_nothing_at_the_first_rejection(V, B, variant):
+    """p == q of many different weights and a candidate that is none: the sums of both rows are the same number and their ratio is
+    exactly 1, so that nothing is left of p in any sequence (flagged; p stays as it was), whatever the last bits are."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(3,), variant=variant)
+    vi = W.gen_verify_inputs(w, np.random.default_rng(V), temperature=[0.7 if b % 3 else 1.0 for b in range(B)])
+    vi.draft_logits[:, 0] = vi.target_logits[:, 0]
+    vi.cand_tok[:, 0] = -1
+    vi.cand_tok[::2, 1:] = V
+    print(f"[verify] equal rows: V={V} B={B} variant={variant}", flush=True)
+    gpu = run_gpu(vi, want_residual=True)
+    assert (gpu["flags"][:, 0] & M.FLAG_ZERO_RESIDUAL).all() and (gpu["flags"][:, 0] & M.FLAG_BAD_TOKEN).all()
+    assert (gpu["acc_child"][:, 0] == np.arange(B) % 2 * 2 - 1).all() and (gpu["ratio"][1::2, 1] == 1.0).all()
+    z = vi.target_logits[:, 0].astype(np.float64) / vi.temperature[:, None]
+    p = np.exp(z - z.max(axis=1, keepdims=True))
+    assert np.abs(gpu["residual_out"][:, 0] - p / p.sum(axis=1, keepdims=True)).max() <= 1e-6
