@@ -32,6 +32,7 @@ namespace {
 using namespace vocab;
 
 constexpr float LOG2E_F = 1.44269504088896340736f;
+constexpr int MAX_BASES = 16;      // a row is written anew when 2^-16 of its sum is left: of 1 down to the smallest float ten times
 
 struct VerifyParams {
     int B, N, V, P, variant, gamma_max, per_seq, ranked;
@@ -283,8 +284,12 @@ struct Share {
 // computes: the two row pairs of 32000 tokens are 512 KB, as much as all registers of the unit.
 //
 // The residual of round n is max(0, e_p - C e_q) with C the sum of the betas so far (what is once zero
-// stays zero), so that the target row never changes: a pass reads, clamps and adds up, and a rejection
-// that would leave nothing is undone by keeping the old C.
+// stays zero), so that the target row need not change: a pass reads, clamps and adds up, and a rejection
+// that would leave nothing is undone by keeping the old C.  C has 48 bits, as two floats, so what is
+// left of a row may not become small beside what was subtracted: at 2^-16 the row is written anew, C begins
+// at 0 again, and the candidates' tracks begin from the betas (which nothing but these seldom cases reads).
+// Without that 2^-53 of p was nothing; with it, and with the quotient corrected, 29 rows of 32000 take
+// 16.2 us where they took 15.9 (four rejections each, from memory), 16 x 61 rows as long as before.
 //
 // Bound: HBM in a batch (16 sequences of 61 rows of 32000, 8 of them argmax: 171 MB in 33 us), the vector units of one CU
 // for a single sequence (29 rows, 512 threads, a row with four rejections): the target row there 1.5 us and the draft row 3.8
@@ -310,7 +315,8 @@ void verify_rows_kernel(VerifyParams p)
     __shared__ int s_besti[NWAVES];
     __shared__ int s_best;
     __shared__ int s_gone_tok[MCSD_MAX_NODES], s_kept_tok[MCSD_MAX_NODES];
-    __shared__ double s_gone_C[MCSD_MAX_NODES];         // C behind their rejection
+    __shared__ double s_beta[MCSD_MAX_NODES];           // of the rejections; s_gone_tok: the token that left q by each, or -1
+    __shared__ float s_base[MAX_BASES][2];              // C of the rows that were written anew
     __shared__ float s_kept[MCSD_MAX_NODES], s_kept_w[MCSD_MAX_NODES][2];       // what they keep; e_p and e_q
     __shared__ double s_cand[2][64];                    // e_p and e_q of the candidates of 64 nodes
 
@@ -327,8 +333,11 @@ void verify_rows_kernel(VerifyParams p)
 
     // Requested ahead of the rows (memory answers in order), by every wavefront for itself: the parents and
     // the candidates; lane = node here, and 64 + lane.
+    auto node_words = [&](const void *x) __attribute__((always_inline)) {      // 32 bits per node of the sequence
+        return __builtin_amdgcn_make_buffer_rsrc((char *)x + 4 * nodes, 0, N * 4, 0x00020000);
+    };
     const __amdgpu_buffer_rsrc_t rs_parent = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(p.parent) + (p.per_seq ? nodes : 0), 0, N * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_tok = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(p.cand_tok) + nodes, 0, N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_tok = node_words(p.cand_tok);
     const int pa0 = __builtin_amdgcn_raw_buffer_load_b32(rs_parent, lane * 4, 0, 0), pa1 = __builtin_amdgcn_raw_buffer_load_b32(rs_parent, lane * 4, 256, 0);
     const int tok0 = __builtin_amdgcn_raw_buffer_load_b32(rs_tok, lane * 4, 0, 0), tok1 = __builtin_amdgcn_raw_buffer_load_b32(rs_tok, lane * 4, 256, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -573,29 +582,52 @@ void verify_rows_kernel(VerifyParams p)
             // Every wavefront follows the candidates of 64 nodes in fp64, a lane each, so that all of them take the
             // same decisions without a barrier; a round costs the one of its sum.
             double C = 0.0;
-            float z_low = (float)Zq * 0x1p-16f;
-            int n_gone = 0;                         // tokens that have left q
+            float z_low = (float)Zq * 0x1p-16f, a_low = (float)A * 0x1p-16f;
+            int n_bases = 0, n_left = 0;
             const bool removes = p.variant == MCSD_WITHOUT_REPLACEMENT;
             unsigned long long left = base ? kids.m1 : kids.m0;
-            bool acc;
-            for (;;) {
-                // of the lane's candidate: the residual and e_q in fp64, and e_q with the rounding of the vector passes
-                double my_a = s_cand[0][lane], my_q = s_cand[1][lane];
-                float my_q32 = __builtin_amdgcn_exp2f((my_zq - mq) * c2);
-                if (base && kids.m0) {
-                    // candidates of the nodes from 64 on, after the rejections of all before them
-                    double cut = C;
-                    bool gone = false;
+            bool acc, low = false;
+            auto split_C = [&](double c) __attribute__((always_inline)) {
+                Ch = (float)c;
+                Cl = (float)(c - (double)Ch);
+            };
+            // The rejections of some lanes, in their order behind the n_left that were left so far: how many they are then
+            // (every wavefront writes the same, for itself).
+            auto leave_rejections = [&](unsigned long long lanes, double my_beta) __attribute__((always_inline)) {
+                if ((lanes >> lane) & 1ull) {
+                    const int n = n_left + __builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
+                    s_beta[n] = my_beta;
+                    s_gone_tok[n] = removes && valid ? my_tok : -1;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                return n_left + __popcll(lanes);
+            };
+            // the residual that the row has of a token
+            auto in_row = [&](float e_p, float e_q) __attribute__((always_inline)) {
 #pragma unroll 1
-                    for (int n = 0; n < n_gone; ++n)
-                        if (!gone && s_gone_tok[n] == my_tok) { gone = true; cut = s_gone_C[n]; }
-                    my_a = fmax(0.0, my_a - cut * my_q);
-                    if (gone) { my_q = 0.0; my_q32 = 0.f; }
+                for (int n = 0; n < n_bases; ++n) e_p = __builtin_amdgcn_fmed3f(fmaf(-s_base[n][1], e_q, fmaf(-s_base[n][0], e_q, e_p)), 0.f, 1.f);
+                return residual_of(e_p, e_q);
+            };
+            for (;;) {
+                // of the lane's candidate: the residual and e_q in fp64
+                double my_a = s_cand[0][lane], my_q = s_cand[1][lane];
+#pragma unroll 1
+                for (int n = 0; n < n_left; ++n) {
+                    my_a = fmax(0.0, my_a - s_beta[n] * my_q);
+                    if (s_gone_tok[n] == my_tok) my_q = 0.0;
                 }
                 // What a decision needs besides A is computed while the sum is on its way.  x = a(x) Z_q / e_q(x): the
                 // ratio is min(1, x / A), and u <= x / A is u A <= x.
-                double x = my_a * (Zq / my_q), rz = (Zq > 0.0) ? 1.0 / Zq : 0.0;    // (nothing left in q: the residual is p itself)
-                double of_x = 0.0, of_A = 1.0;      // the ratio that the lane's candidate was tested at: min(1, of_x / of_A)
+                double x, rz;
+                auto with_q = [&]() __attribute__((always_inline)) {
+                    x = my_a * (Zq / my_q);
+                    rz = (Zq > 0.0) ? 1.0 / Zq : 0.0;       // (nothing left in q: the residual is p itself)
+                };
+                with_q();
+                double of_x = 0.0, of_A = 0.0;      // the ratio that the lane's candidate was tested at: min(1, of_x / of_A)
+                double my_beta = 0.0;               // of its rejection
                 const unsigned long long all = left, good = __ballot(valid);
                 unsigned long long no_q = 0ull;     // of those tested, the candidates that q did not have
                 for (;;) {
@@ -608,8 +640,8 @@ void verify_rows_kernel(VerifyParams p)
                     acc = (__ballot(yes) >> l) & 1ull;
                     no_q |= __ballot(!has_q) & (1ull << l);
                     if (lane == l) {
-                        of_x = sure ? 1.0 : (has_q ? x : 0.0);
-                        of_A = sure || !has_q ? 1.0 : A;
+                        of_x = sure ? INFINITY : (has_q ? x : 0.0);
+                        of_A = A;
                     }
                     if (acc) {
                         accepted = base + l;
@@ -617,58 +649,54 @@ void verify_rows_kernel(VerifyParams p)
                     }
                     // rejected: the residual with C + A / Z_q, in fp64 but for the two products per token.  (The token that
                     // leaves q keeps its e_q in the row: its residual is 0 now and stays 0 whatever is subtracted later.)
-                    const double A_of = A, C_of = C, a_of = my_a;
                     // A / Z_q: the product with 1 / Z_q, and what is missing there (so that it is 1 for equal sums)
                     double beta = A * rz;
                     beta = rz > 0.0 ? fma(fma(-beta, Zq, A), rz, beta) : 0.0;
-                    C += beta;
-                    Ch = (float)C;
-                    Cl = (float)(C - (double)Ch);
+                    if (lane == l) my_beta = beta;
+                    split_C(C + beta);
                     sum_residual();
                     slot ^= 1;
                     leave_sum((part[0] + part[1]) + (part[2] + part[3]), 0, slot);
                     my_a = fmax(0.0, my_a - beta * my_q);
                     const bool gone = removes && ((good >> l) & 1ull), at_one = (__ballot(sure) >> l) & 1ull;
                     const int tok = __builtin_amdgcn_readlane(my_tok, l);
-                    const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_q32), l));
                     if (gone) {
-                        // Z_q loses exactly the fp32 weight that its sum contained
-                        Zq -= (double)w;
-                        rz = (Zq > 0.0) ? 1.0 / Zq : 0.0;
-                        if (my_tok == tok) { my_q = 0.0; my_q32 = 0.f; }
+                        // Z_q loses exactly the fp32 weight that its sum contained (nothing where the token had left before)
+                        const float w = __builtin_amdgcn_exp2f((__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_zq), l)) - mq) * c2);
+                        Zq -= (__ballot(has_q) >> l) & 1ull ? (double)w : 0.0;
+                        if (my_tok == tok) my_q = 0.0;
                     }
-                    x = my_a * (Zq / my_q);
+                    with_q();
                     __syncthreads();
                     A = read_total(0, slot);
 #pragma unroll 1
                     for (int n = 0; n < n_kept; ++n)        // in the place of what the row has of them
-                        A += (double)s_kept[n] - (double)residual_of(s_kept_w[n][0], s_kept_w[n][1]);
-                    stale = uniform(!(A > 0.0));
+                        A += (double)s_kept[n] - (double)in_row(s_kept_w[n][0], s_kept_w[n][1]);
+                    low = uniform(!(A > (double)a_low));
+                    stale = low && uniform(!(A > 0.0));
                     if (stale) {
                         // max(0, p - q) vanished everywhere, which a rejection excludes in exact arithmetic
                         // (it needs p = q) and rounding or a bad candidate can produce: p stays as it was.
-                        C = C_of;
-                        Ch = (float)C;
-                        Cl = (float)(C - (double)Ch);
-                        A = A_of;
-                        my_a = a_of;
-                        x = my_a * (Zq / my_q);
+                        // (The candidates' tracks begin anew from the list of rejections, ahead of this loop.)
+                        split_C(C);
+                        A = readlane_d(of_A, l);
+                        if (lane == l) my_beta = 0.0;
                         fl |= (uint32_t)MCSD_FLAG_ZERO_RESIDUAL;
+                    } else {
+                        C += beta;
                     }
                     if (gone) {
-                        // (every wavefront writes the same, for itself)
-                        if (lane == 0) { s_gone_tok[n_gone] = tok; s_gone_C[n_gone] = C; }
-                        ++n_gone;
                         if (stale || at_one) {
                             // This token leaves q with some of its p left, or all (so does one that only a uniform above 1
                             // rejects): no later rejection may lower that.
                             bool known = false;
 #pragma unroll 1
                             for (int n = 0; n < n_kept; ++n) known |= s_kept_tok[n] == tok;
-                            const float e_p = __builtin_amdgcn_exp2f((__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_zp), l)) - mp) * c2);
+                            const float zp = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_resource(zp_row, V), tok * 4, 0, 0));
+                            const float e_p = __builtin_amdgcn_exp2f((zp - mp) * c2);
                             const float e_q = __builtin_amdgcn_exp2f((__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_zq), l)) - mq) * c2);
                             if (uniform(!known)) {
-                                if (lane == 0) { s_kept_tok[n_kept] = tok; s_kept[n_kept] = residual_of(e_p, e_q); s_kept_w[n_kept][0] = e_p; s_kept_w[n_kept][1] = e_q; }
+                                if (lane == 0) { s_kept_tok[n_kept] = tok; s_kept[n_kept] = in_row(e_p, e_q); s_kept_w[n_kept][0] = e_p; s_kept_w[n_kept][1] = e_q; }
                                 ++n_kept;
                             }
                         }
@@ -677,45 +705,63 @@ void verify_rows_kernel(VerifyParams p)
                             // again without the removed tokens, from memory (rare; a pass over the
                             // resident row here would cost every row registers)
                             const __amdgpu_buffer_rsrc_t rs = row_resource(zq_row, V);
+                            const int n_rejected = leave_rejections(all & ~left, my_beta);
                             double partq = 0.0;
 #pragma unroll 1
                             for (int e0 = t; e0 < V; e0 += VT) {
                                 const float e = __builtin_amdgcn_exp2f((__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, e0 * 4, 0, 0)) - mq) * c2);
                                 bool in = true;
 #pragma unroll 1
-                                for (int n = 0; n < n_gone; ++n) in &= s_gone_tok[n] != e0;
+                                for (int n = 0; n < n_rejected; ++n) in &= s_gone_tok[n] != e0;
                                 if (in) partq += (double)e;
                             }
                             leave_sum(partq, 1, slot);
                             __syncthreads();
                             Zq = read_total(1, slot);
                             z_low = (float)Zq * 0x1p-16f;
-                            rz = (Zq > 0.0) ? 1.0 / Zq : 0.0;
-                            x = my_a * (Zq / my_q);
+                            with_q();
                         }
                     }
-                    if (!left) break;
+                    if (!left || low) break;
                 }
                 // their ratios (NaN: not tested) and flags
                 const VerifyParams *late = arguments();
                 const unsigned long long tested = all & ~left;
                 const bool was = (tested >> lane) & 1ull;
-                const double r = valid ? of_x / of_A : 0.0;
+                const double r = valid && of_x != 0.0 ? fmin(1.0, of_x / of_A) : 0.0;
                 if (late->ratio && wave == 0 && ((all >> lane) & 1ull)) late->ratio[nodes + base + lane] = was ? (float)r : NaN;
                 if (__ballot(was && fabs((double)my_u - r) < (double)late->eps)) fl |= (uint32_t)MCSD_FLAG_NEAR_TIE_ACCEPT;
                 if (tested & ~good) fl |= (uint32_t)MCSD_FLAG_BAD_TOKEN;
                 if (no_q & good) fl |= (uint32_t)MCSD_FLAG_ZERO_DRAFT_PROB;
-                if (base || !kids.m1) break;
                 if (acc) {
-                    if (late->ratio && wave == 0 && ((kids.m1 >> lane) & 1ull)) late->ratio[nodes + 64 + lane] = NaN;
+                    if (!base && late->ratio && wave == 0 && ((kids.m1 >> lane) & 1ull)) late->ratio[nodes + 64 + lane] = NaN;
                     break;
                 }
+                if (!left && (base || !kids.m1)) break;
+                n_left = leave_rejections(tested, my_beta);
+                if (low && !stale && n_bases < MAX_BASES) {
+                    // What is left is small beside what C e_q takes from e_p: C, of 48 bits as two floats, would lose it, and
+                    // in the end nothing would be left.  The residual in the place of e_p, and C from 0 on, so that the error
+                    // of C is 2^-33 of what is left at most.  (Seldom: with candidates drawn from q one row in 2^16.)
+                    asm volatile("" : "+v"(tq), "+v"(Ch));
+#pragma unroll
+                    for (int j = 0; j < ITEMS; ++j) {
+                        a[j] = residual(j, draft_item(j));
+                        asm volatile("" : "+v"(a[j].x), "+v"(a[j].y), "+v"(a[j].z), "+v"(a[j].w), "+v"(tq));    // (item by item: LDS reads ahead do not fit the registers)
+                    }
+                    if (lane == 0) { s_base[n_bases][0] = Ch; s_base[n_bases][1] = Cl; }
+                    ++n_bases;
+                    C = 0.0;
+                    Ch = Cl = 0.f;
+                    a_low = (float)A * 0x1p-16f;
+                }
+                if (left) continue;
                 base = 64;
                 left = kids.m1;
-                my_tok = __builtin_amdgcn_raw_buffer_load_b32(rs_tok, lane * 4, 256, 0);
+                my_tok = __builtin_amdgcn_raw_buffer_load_b32(node_words(late->cand_tok), lane * 4, 256, 0);
                 valid = f1 && my_tok >= 0 && my_tok < V;
                 const int at1 = valid ? my_tok * 4 : V * 4;
-                my_u = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_u, lane * 4, 256, 0));
+                my_u = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(node_words(late->u_accept), lane * 4, 256, 0));
                 my_zp = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_resource(zp_row, V), at1, 0, 0));
                 my_zq = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_resource(zq_row, V), at1, 0, 0));
                 leave_weights();                    // (no reader of the first is left behind the barriers of the rounds)
@@ -723,6 +769,7 @@ void verify_rows_kernel(VerifyParams p)
             }
             if (n_kept && (accepted < 0 || p.residual_out)) {
                 // the residual as it is, with the tokens that keep theirs
+                __syncthreads();                    // the last of them is known
                 asm volatile("" : "+v"(tq), "+v"(Ch));
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j) a[j] = residual(j, draft_item(j));
@@ -853,7 +900,8 @@ void verify_rows_kernel(VerifyParams p)
         if (owner && naive && k > 0) {
             // multi-candidate naive sampling (the comparison rule of the ablation, Sec. 4.5): the
             // token just drawn from p is kept; a candidate equal to it is accepted, the first such
-            const int tok0 = __builtin_amdgcn_raw_buffer_load_b32(rs_tok, lane * 4, 0, 0), tok1 = __builtin_amdgcn_raw_buffer_load_b32(rs_tok, lane * 4, 256, 0);
+            const __amdgpu_buffer_rsrc_t rs = node_words(out->cand_tok);
+            const int tok0 = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0), tok1 = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 256, 0);
             const unsigned long long m0 = __ballot(f0 && tok0 == endpoint && tok0 >= 0 && tok0 < V);
             const unsigned long long m1 = __ballot(f1 && tok1 == endpoint && tok1 >= 0 && tok1 < V);
             if (__ballot((f0 && (tok0 < 0 || tok0 >= V)) || (f1 && (tok1 < 0 || tok1 >= V)))) fl |= (uint32_t)MCSD_FLAG_BAD_TOKEN;

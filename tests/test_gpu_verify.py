@@ -1,4 +1,6 @@
 """GPU parity of mcsd_verify_sample (through the C ABI) against the CPU oracle."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 import torch
@@ -463,3 +465,68 @@ def test_equal_rows_leave_nothing_at_the_first_rejection(V, B, variant):
     z = vi.target_logits[:, 0].astype(np.float64) / vi.temperature[:, None]
     p = np.exp(z - z.max(axis=1, keepdims=True))
     assert np.abs(gpu["residual_out"][:, 0] - p / p.sum(axis=1, keepdims=True)).max() <= 1e-6
+
+
+def exact_row(p, q, cands, us, removes, V):
+    """Algorithms 1 and 2 on a few tokens in rationals; an id that is none is rejected and stays what it is.  Returns the
+    accepted candidate or None, the ratios tested and p."""
+    p, q, ratios = dict(p), dict(q), []
+    for i, (x, u) in enumerate(zip(cands, us)):
+        known = 0 <= x < V
+        a, e = (p.get(x, 0) / sum(p.values()), q.get(x, 0) / sum(q.values())) if known else (0, 1)
+        ratios.append(min(Fraction(1), a / e) if e else Fraction(int(a > 0)))
+        if ratios[-1] > 0 and u <= ratios[-1]:
+            return i, ratios, p
+        s, z = sum(p.values()), sum(q.values())
+        p = {y: max(Fraction(0), w / s - q.get(y, 0) / z) for y, w in p.items()}
+        assert sum(p.values()) > 0
+        if removes and known:
+            q[x] = Fraction(0)
+    return None, ratios, p
+
+
+@pytest.mark.parametrize("variant", [W.WITH_REPLACEMENT, W.WITHOUT_REPLACEMENT], ids=["wr", "wor"])
+@pytest.mark.parametrize("V,B", [(5, 8), (3000, 8), (8190, 8), (16383, 8), (20003, 4), (32000, 8), (32766, 8), (50001, 4), (65536, 4)])
+def test_residuals_far_below_what_was_subtracted(V, B, variant):
+    """Rows that lose half or more of what is left in each of 66 rounds, by a token that p does not have or by ids that are none:
+    down to 2^-66 of p there is something left, no round may find that nothing is.  Weights of 0 and 1, whose rounds are exact in
+    fp32 and fp64 (sequence 3 of four: 0.7 and 0.3, one token left).  Sequences 1 and 2: behind 63 rounds token y0 leaves q by a
+    uniform above 1 and keeps its 2^-64; the next round leaves y1 a third of that, a ratio of 3/4 in the 66th, which is
+    accepted or not."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(66,), variant=variant)
+    removes = variant == W.WITHOUT_REPLACEMENT
+    rng = np.random.default_rng(V + B)
+    vi = W.gen_verify_inputs(w, rng, temperature=[1.0] * B, draw_candidates_on_host=False)
+    vi.target_logits[:, 0] = vi.draft_logits[:, 0] = -np.inf
+    vi.u_accept[:] = np.float32(0.875)
+    vi.u_endpoint[:, 0] = np.float32(0.4375)
+    want = []
+    for b in range(B):
+        y0, y1, z0, z1 = (int(x) for x in rng.permutation(V)[:4])
+        if b >= 4:
+            y0, z0 = (V - 1, z0 if z0 != V - 1 else y0) if y1 != V - 1 and z1 != V - 1 else (y0, z0)
+        if b % 4 in (1, 2):
+            p, q = {y0: Fraction(1), y1: Fraction(1)}, {x: Fraction(1) for x in (y0, y1, z0, z1)}
+            vi.cand_tok[b] = [-1, V][b % 2]
+            vi.cand_tok[b, 63], vi.cand_tok[b, 65] = y0, y1
+            vi.u_accept[b, 63] = 1.5
+            vi.u_accept[b, 65] = [0, 0.5, 0.875][b % 4]
+        else:
+            p, q = {y0: Fraction(1)}, {y0: Fraction(1), z0: Fraction(1)} if b % 4 == 0 else {y0: Fraction(7, 3), z0: Fraction(1)}
+            vi.cand_tok[b] = -1 if removes else z0
+        for logits, weights in ((vi.target_logits, p), (vi.draft_logits, q)):
+            for x, v in weights.items():
+                logits[b, 0, x] = np.log(float(v))
+        want.append(exact_row(p, q, vi.cand_tok[b].tolist(), [Fraction(float(u)) for u in vi.u_accept[b]], removes, V))
+    print(f"[verify] far below: V={V} B={B} variant={variant}", flush=True)
+    gpu = run_gpu(vi, want_residual=True)
+    assert not (gpu["flags"][:, 0] & (M.FLAG_ZERO_RESIDUAL | M.FLAG_NONFINITE | M.FLAG_ZERO_DRAFT_PROB)).any()
+    for b, (accepted, ratios, p) in enumerate(want):
+        left = np.zeros(V)
+        for x, v in p.items():
+            left[x] = float(v / sum(p.values()))
+        assert gpu["acc_child"][b, 0] == (-1 if accepted is None else accepted), b
+        assert gpu["endpoint"][b, 0] == (int(np.nonzero(np.cumsum(left) > 0.4375)[0][0]) if accepted is None else -1), b
+        assert np.abs(gpu["ratio"][b, :len(ratios)] - np.array([float(r) for r in ratios])).max() <= 1e-6, b
+        assert np.isnan(gpu["ratio"][b, len(ratios):]).all(), b
+        assert np.abs(gpu["residual_out"][b, 0] - left).max() <= 1e-6, b
