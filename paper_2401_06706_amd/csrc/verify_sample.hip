@@ -577,6 +577,7 @@ void verify_rows_kernel(VerifyParams p)
         int slot = 0;                               // where the totals of the residual's wavefronts are
         bool stale = false;                         // they, and part, are not those of the residual as it is now
         int accepted = -1;
+        bool rejected = false;
         int n_kept = 0;                             // tokens that have left q and keep a residual that C does not lower (see below)
         if (rounds) {
             // Every wavefront follows the candidates of 64 nodes in fp64, a lane each, so that all of them take the
@@ -653,6 +654,7 @@ void verify_rows_kernel(VerifyParams p)
                     double beta = A * rz;
                     beta = rz > 0.0 ? fma(fma(-beta, Zq, A), rz, beta) : 0.0;
                     if (lane == l) my_beta = beta;
+                    rejected = true;
                     split_C(C + beta);
                     sum_residual();
                     slot ^= 1;
@@ -924,7 +926,8 @@ void verify_rows_kernel(VerifyParams p)
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
                 if (j >= own.items) continue;
-                const float4 r = residual(j, draft_item(j));
+                // (nothing rejected: the weights as they are, a NaN among them too, which the clamp makes 0)
+                const float4 r = rejected ? residual(j, draft_item(j)) : a[j];
                 const int off = own.token(j, lane) * 4;
                 if (ALIGNED) {
                     const u32x4 v = {__float_as_uint(r.x * inv), __float_as_uint(r.y * inv), __float_as_uint(r.z * inv), __float_as_uint(r.w * inv)};

@@ -530,3 +530,37 @@ def test_residuals_far_below_what_was_subtracted(V, B, variant):
         assert np.abs(gpu["ratio"][b, :len(ratios)] - np.array([float(r) for r in ratios])).max() <= 1e-6, b
         assert np.isnan(gpu["ratio"][b, len(ratios):]).all(), b
         assert np.abs(gpu["residual_out"][b, 0] - left).max() <= 1e-6, b
+
+
+@pytest.mark.parametrize("variant", [W.WITH_REPLACEMENT, W.WITHOUT_REPLACEMENT, W.NAIVE], ids=["wr", "wor", "naive"])
+@pytest.mark.parametrize("V,B", [(700, 2), (4097, 2), (16383, 2), (20003, 2), (32000, 60), (32766, 60), (50001, 2), (65536, 2)])
+def test_rows_that_nothing_was_rejected_in_are_written_as_they_are(V, B, variant):
+    """A NaN logit of a target row (root: its first candidate goes at ratio 1; a leaf) is in the row that is written out, with
+    zeros beside it: the row has no sum.  A NaN in the draft row of a root whose first candidate is accepted leaves p whole.  All
+    flagged."""
+    w = W.WORKLOADS["c2"].with_(V=V, B=B, kconfig=(7,), variant=variant)
+    vi = W.gen_verify_inputs(w, np.random.default_rng(V))
+    at = (V - 1, V // 2)
+    vi.target_logits[::2, 0, at[0]] = np.nan
+    vi.target_logits[:, 3, at[1]] = np.nan
+    vi.draft_logits[1::2, 0, at[1]] = np.nan
+    vi.cand_tok[vi.cand_tok == at[0]] = 0
+    vi.u_accept[:] = 0.5
+    print(f"[verify] as they are: V={V} B={B} variant={variant}", flush=True)
+    gpu = run_gpu(vi, want_residual=True)
+    naive = variant == W.NAIVE
+    bad = np.zeros((B, 8), bool)
+    bad[::2, 0] = bad[:, 3] = True
+    if not naive:
+        bad[1::2, 0] = True
+        assert (gpu["acc_child"][:, 0] == 0).all() and (gpu["ratio"][:, 0] == 1.0).all()
+    np.testing.assert_array_equal((gpu["flags"] & M.FLAG_NONFINITE) != 0, bad)
+    out = gpu["residual_out"]
+    for b in range(B):
+        for r in range(8):
+            z = vi.target_logits[b, r].astype(np.float64)
+            if np.isnan(z).any():
+                assert np.isnan(out[b, r, at[0 if r == 0 else 1]]) and np.nansum(np.abs(out[b, r])) == 0 and np.isnan(out[b, r]).sum() == 1, (b, r)
+            else:
+                p = np.exp(z - z.max())
+                assert np.abs(out[b, r] - p / p.sum()).max() <= 1e-6, (b, r)
