@@ -699,13 +699,19 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     //   60 rows (nodes), 128 KV heads (128)  10.2/9.8 10.7/10.8 12.0/11.1 12.1/11.4 13.0/11.8
     //   56 rows (nodes),  80 KV heads (128)   9.6/9.0 10.1/10.0 11.6/10.8 11.5/10.9 12.3/11.2
     //   56 rows, 28 nodes, 128 KV heads (128) 8.7/9.4  9.4/10.6 10.2/10.5 11.3/11.0 11.3/11.1 12.2/11.6    (one tile of the tree, not two)
+    // Trees of more than 32 rows with the root's, one query head per KV head, from memory, at 30, 96, 160, 224 keys and with sequences of 60 keys in a cache of 224: the
+    // kernel above does more for every node of the tree, so from about 50 rows on it is behind.
+    //   33 rows, 128 KV heads   9.4/9.4  9.5/10.2 10.3/10.6 11.2/11.5  9.3/9.9     80 KV heads   9.3/9.2 9.1/9.6 10.1/10.1 11.0/10.8  9.0/9.4
+    //   48                      9.9/9.8  9.7/10.2 10.6/10.6 11.7/11.6  9.6/10.1                  9.7/9.4 9.5/9.8 10.4/10.1 11.3/10.7  9.5/9.7
+    //   56                     10.2/9.8  9.9/10.3 10.8/10.6 12.1/11.9  9.9/10.1                 10.1/9.4 9.7/9.7 10.6/10.1 11.5/10.7  9.7/9.7
+    //   64                     10.6/10.0 10.2/10.5 11.2/10.8 12.0/11.5 10.3/10.3                10.5/9.7 10.0/9.9 10.9/10.2 11.8/10.8 10.1/9.8
     // (The workspace that a split plan of these sizes asks for stays asked for.)
     const long wgs32 = (long)d.B * d.H_kv * ((pl.rows_per_kv + 31) / 32);
     if (wgs32 <= 256 && g_force_variant.load() == 0 && forced <= 0 && forced_target <= 0) {
         const bool some = wgs32 > 64 && wgs32 <= 128;
         long least = 1, most = some && wgs32 > 96 ? 66 : 54;
         if (pl.rows_per_kv <= 32) { least = wgs32 <= 64 ? (total_max <= 6 ? 1 : 9) : (some ? 22 : 25); most = some || wgs32 > 160 ? 50 : 35; }
-        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 || d.N > 32 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
+        else if (pl.rows_per_kv <= 64) { least = wgs32 <= 128 || n_rows_tree > 50 ? 1 : 10; most = wgs32 <= 128 ? 50 : 66; }
         if (total_max >= least && total_max <= most) {
             pl.slice_columns = wgs32 <= 64 ? 32 : (wgs32 <= 128 ? 64 : 128);
             pl.n_chunks_max = 1;

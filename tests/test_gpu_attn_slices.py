@@ -181,3 +181,39 @@ def test_slices_give_the_same_bits_on_every_run(H_q, H_kv, capacity):
         M.mcsd_tree_attn(call.args)
         torch.cuda.synchronize()
         assert torch.equal(call.out.view(torch.int16), first.view(torch.int16)), rep
+
+
+# (the lines of make_attn_plan between whole and sliced launches without partials: one row per node and more than 128 workgroups of
+# 32 rows, slices below ten tiles from 51 rows of the tree on, the root's among them; 28 rows, slices up to six tiles and from nine on)
+@pytest.mark.parametrize("B,H,nodes,root,capacity,sliced", [
+    (3, 32, 33, False, 96, False), (3, 32, 40, False, 31, False), (5, 16, 50, False, 96, False), (5, 16, 51, False, 96, True), (3, 32, 32, True, 96, False),
+    (3, 32, 49, True, 96, False), (3, 32, 50, True, 96, True), (4, 32, 63, True, 1, True), (3, 32, 33, False, 256, True), (2, 16, 33, False, 96, True),
+    (2, 16, 28, False, 160, True), (2, 16, 28, False, 161, False), (2, 16, 28, False, 224, False), (2, 16, 28, False, 225, True)])
+def test_which_kernel_runs(B, H, nodes, root, capacity, sliced):
+    """Seen by the bits: the plan override never slices, and the slices add up their keys in another order."""
+    rng = np.random.default_rng(nodes + capacity)
+    n, lengths = nodes + root, [max(1, capacity - 3 * b) for b in range(B)]
+    bf16 = lambda *shape: W.f32_to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+    q, k, v, kt, vt = bf16(B, n, H, 128), bf16(B, H, capacity, 128), bf16(B, H, capacity, 128), bf16(B, H, n, 128), bf16(B, H, n, 128)
+    parent = np.array([-1] + [i // 2 for i in range(nodes - 1)], np.int32)
+    dev = [torch.from_numpy(x.view(np.int16)).cuda().view(torch.bfloat16) for x in (q, k, v, kt, vt)]
+    out = []
+    for variant in (0, 2 if n > 32 else 1):
+        o = torch.full_like(dev[0], 3.0)
+        args = M.attn_args(dev[0], dev[1], dev[2], torch.tensor(lengths, dtype=torch.int32, device="cuda"), dev[3], dev[4], torch.from_numpy(parent).cuda(), o, 128 ** -0.5,
+                           workspace=torch.empty(1 << 26, dtype=torch.uint8, device="cuda"))
+        print(f"[which] B={B} H={H} nodes={nodes} root={root} capacity={capacity} variant={variant}", flush=True)
+        M.mcsd_attn_plan_override(variant=variant)
+        try:
+            M.mcsd_tree_attn(args)
+            torch.cuda.synchronize()
+        finally:
+            M.mcsd_attn_plan_override()
+        out.append(o)
+    assert torch.equal(out[0], out[1]) != sliced
+    full = np.concatenate([[-1], parent + 1]).astype(np.int32) if root else parent
+    sel = np.stack([np.arange(600) % B, rng.integers(0, n, 600), rng.integers(0, H, 600)], 1).astype(np.int32)
+    ref = O.tree_attn(q, k, v, np.array(lengths, np.int32), kt, vt, full, 128 ** -0.5, O.BF16, sel=sel, n_threads=16)
+    for o in out:
+        got = o.float().cpu().numpy()
+        assert_attn_close(got[sel[:, 0], sel[:, 1], sel[:, 2]], ref, "bf16", f"{nodes}")
