@@ -691,6 +691,10 @@ bool make_attn_plan(const mcsd_attn_desc &d, AttnPlan *plan)
     //   8 x 32                    36.2/30.9 27.6/23.0 17.8/16.7         47.0/40.4 35.6/31.1 19.7/18.9         58.8/50.4 39.2/37.2 19.9/22.2
     //   11 x 16                   29.5/24.6 27.3/21.1 15.8/14.6         38.3/30.4 26.6/26.0 17.8/17.3
     //   5 x 32 (160)  1500  34.7/28.1 22.7/25.6 17.8/19.7
+    // Measured again between, 1250 and 1400 keys, with all of a quarter and all of 60 keys besides:
+    //   6 x 32  34.2/29.1 26.5/24.0 19.3/19.3 16.4/12.2 11.9/9.8    36.2/31.7 26.2/26.2 19.3/20.6 17.5/12.7 12.0/9.8
+    //   7 x 32  37.2/32.1 29.5/25.7 17.7/18.6 16.7/12.9 12.2/10.1   39.5/36.0 29.2/28.6 19.0/20.5 17.5/13.4 12.2/10.1
+    // One full sequence among short ones pays up to 1.09 there for 0.73 to 0.91 of the others.
     // The lower lines, the kernel above whole / this, at 32, 96, 150, 180, 210, 240, 350 keys, all full (lengths spread: alike or better):
     //   28 rows,  32 KV heads (32)   7.6/7.1 7.7/7.1 7.8/7.6 7.6/7.6 7.6/7.7 8.5/8.1 9.5/8.8     (7 and 8 tiles go twice round its four waves)
     //   28 rows,   8 KV heads (32)   6.8/6.2 7.3/6.8 7.6/7.6 7.4/7.6 7.4/7.6 8.4/7.9 8.5/7.9

@@ -864,6 +864,16 @@ int32_t launch_attn_any(const AttnParams &p, hipStream_t stream)
         //   d 96, 8 x 32 of 56             16.3/14.2 15.1/12.1 10.8/10.1 17.2/14.8 15.6/12.8 10.9/10.7 22.0/18.5 19.8/15.3 12.5/12.0 34.0/27.8 28.8/19.6
         //         9 x 8 of 112             14.6/12.9 14.3/12.0 10.1/9.6  15.1/13.1 14.3/11.9 10.1/10.2 18.8/16.3 17.8/13.9 11.3/11.1 27.0/21.2 25.0/17.6
         // Below (200 keys: 9.8/10.0 9.1/9.7 8.0/8.6 and 13.5/13.2 12.2/12.0, 9 x 8 8.5/9.1 and 11.7/12.0) one step of the lockstep has all tiles.
+        // So it has for short sequences in a larger cache, which therefore lose at d <= 64: all of 60 keys, caches of 512 to 2000, 7.8/8.3 (72 units
+        // of 112 rows) to 8.4/9.1 (256 of 56), all of 128 of 512 8.8/9.5 to 9.5/10.2, while one full among sequences of 100 gains 13.0/10.4 to 27.3/19.0.
+        // d 96 with more than 256 workgroups of 64 rows (65 to 96, 129 to 160 rows), four wavefronts of 64 rows, two tiles a step / this; caches of
+        // 60, 200, 400, 1000 keys, full; spread; all of 60 keys in a cache of 1000:
+        //   130 units of 70 rows   11.4/11.6 16.2/14.2 21.0/17.5 35.7/30.8   10.8/10.6 14.6/14.0 17.8/15.5 28.4/22.6   11.1/12.7
+        //   140 of 70              13.0/11.7 17.6/14.5 23.0/17.9 38.5/32.3   12.5/10.7 16.2/14.3 19.7/15.6 30.5/23.5   12.6/12.8
+        //   170 of 94              13.4/12.6 18.1/15.3 23.6/20.3 39.8/38.1   12.9/11.8 16.5/15.3 20.5/17.0 32.4/26.8   13.0/13.9
+        //    88 of 132             11.0/10.9 15.9/13.1 20.3/15.4 35.0/24.9   10.4/10.0 14.1/12.8 17.4/14.1 27.9/20.8   10.8/11.1
+        //   100 of 160             13.3/11.9 18.0/14.8 23.2/18.0 38.1/31.7   12.7/11.0 16.5/14.7 20.1/15.8 31.4/23.6   12.9/13.0
+        // (with few more than 256 workgroups of 64 rows one has a CU to itself mostly, and short sequences lose most: 1.15 there.)
         const int tiles = (p.L_stride + 31) / 32 + (p.N + 31) / 32;
         const long units = (long)p.B * p.H_kv, wgs32 = units * ((p.M + 31) / 32), wgs64 = units * ((p.M + 63) / 64);
         if (dp == 64) {

@@ -217,3 +217,11 @@ def test_which_kernel_runs(B, H, nodes, root, capacity, sliced):
     for o in out:
         got = o.float().cpu().numpy()
         assert_attn_close(got[sel[:, 0], sel[:, 1], sel[:, 2]], ref, "bf16", f"{nodes}")
+
+
+# (65 to 96 and 129 to 160 rows by more than 256 workgroups of 64 rows and up to 512 of 32: 32 rows with tiles of their own at any capacity)
+@pytest.mark.parametrize("d,capacity", [(96, 60), (72, 225), (120, 300)])
+@pytest.mark.parametrize("B,H_q,H_kv,kconfig", [(13, 20, 10, (5, 2, 2)), (17, 20, 10, (5, 2, 2)), (10, 50, 10, (4, 2, 2))])
+def test_more_than_one_workgroup_of_64_rows_per_cu(d, capacity, B, H_q, H_kv, kconfig):
+    lengths = tuple(max(0, capacity - 19 * b) for b in range(B))
+    run("bf16", d, H_q, H_kv, kconfig, lengths, capacity)
