@@ -3,19 +3,20 @@
 //
 // One workgroup owns one row of the tree (the root or a node).  Both logit rows of the node are read
 // from HBM exactly once with 128-bit loads and stay on the compute unit, in registers and (the larger
-// vocabularies) partly in LDS, for all k sequential accept/reject rounds; every round is one
-// elementwise pass over the resident data plus one block reduction.
+// vocabularies) partly in LDS, for all k sequential accept/reject rounds; every round reads the
+// resident data once and adds up.
 //
 // Algorithm 2's removal of a rejected token from q needs no pass: that token's residual is already
 // 0 and stays 0 whatever is subtracted from it later, so only Z_q changes, by exactly the fp32 weight
-// of the token.  (A residual that vanished is put back without the removed tokens.)
+// of the token.  (A residual that vanished stays what it was; a token that leaves q with some of its p left keeps that in a list.)
 //
-// Instead of renormalising after each rejection the kernels carry an
+// Instead of renormalising after each rejection the kernels have an
 // unnormalised residual a(x) and its sum A (p-hat = a / A), and the unnormalised
 // draft weights e_q(x) with the running mass Z_q of the tokens not yet removed
 // (q-bar = e_q / Z_q).  Algorithm 1/2's update p := max(0, p - q) / sum(...) then
-// reads a := max(0, a - (A / Z_q) e_q), A := sum a, and the normaliser the paper
-// divides by (the probability of the rejection, Appendix A) is A_new / A_old.
+// reads a := max(0, a - beta e_q) with beta = A / Z_q, A := sum a, and the normaliser the paper
+// divides by (the probability of the rejection, Appendix A) is A_new / A_old.  What is once zero stays zero, so
+// a is max(0, e_p - C e_q) with C the sum of the betas: no row is rewritten, but for the seldom one of which little is left.
 //
 // The handful of numbers that decide an accept test - a(x), e_q(x) at the k
 // candidate tokens - are tracked separately in fp64 by one lane per candidate, in every wavefront,
@@ -289,7 +290,7 @@ struct Share {
 // left of a row may not become small beside what was subtracted: at 2^-16 the row is written anew, C begins
 // at 0 again, and the candidates' tracks begin from the betas (which nothing but these seldom cases reads).
 // Without that 2^-53 of p was nothing; with it, and with the quotient corrected, 29 rows of 32000 take
-// 16.2 us where they took 15.9 (four rejections each, from memory), 16 x 61 rows as long as before.
+// 16.2 us where they took 15.9 (candidates mostly rejected, from memory), 16 x 61 rows as long as before.
 //
 // Bound: HBM in a batch (16 sequences of 61 rows of 32000, 8 of them argmax: 171 MB in 33 us), the vector units of one CU
 // for a single sequence (29 rows, 512 threads, a row with four rejections): the target row there 1.5 us and the draft row 3.8
@@ -553,7 +554,9 @@ void verify_rows_kernel(VerifyParams p)
         if (uniform((bool)(!((A > 0.0) & (A < INFINITY)) | (rounds & !((Zq > 0.0) & (Zq < INFINITY)))))) fl |= (uint32_t)MCSD_FLAG_NONFINITE;
 
         float Ch = 0.f, Cl = 0.f;                   // C as a two-term float, so that no common rounding of it biases the sums
-        // the residual of a token and of item j; 0 <= e_p <= 1, so that the maximum with 0 is the clamp of the second product
+        // The residual of a token and of item j; 0 <= e_p <= 1, so that the maximum with 0 is the clamp of the second product.
+        // Items past the share may hold -inf as they were padded (the passes skip them by groups), and C e_q + e_p is NaN
+        // there: v_med3_f32 gives the least of the other two for a NaN, 0, and so does the clamp bit it may become.
         auto residual_of = [&](float e_p, float e_q) __attribute__((always_inline)) {
             return __builtin_amdgcn_fmed3f(fmaf(-Cl, e_q, fmaf(-Ch, e_q, e_p)), 0.f, 1.f);
         };
@@ -991,12 +994,16 @@ int32_t launch_verify(const mcsd_verify_desc &d, const mcsd_verify_bufs &b, hipS
     // Threads and the split between registers and LDS by the size of the row pair: up to 16384 tokens
     // everything in registers, several workgroups per compute unit; up to 32768 two per unit with 18 of
     // 32 items of the draft row in LDS; beyond, one per unit with the same split.  Measured for 16 x 61
-    // rows of 32000: 33.5 us; 512 threads with 9 of 16 items in LDS (128 registers, 16 spilled) 38.3 us;
-    // 1024 threads, all in registers, one workgroup per unit 42.5 us.
+    // rows of 32000 when a rejection still rewrote the row: 33.5 us; 512 threads with 9 of 16 items in LDS (128
+    // registers, 16 spilled) 38.3 us; 1024 threads, all in registers, one workgroup per unit 42.5 us.
+    // (Registers put aside in memory now, per thread: 5 of the 128 where four wavefronts share a SIMD, 8 of the 256 of two per unit,
+    // 4 beyond 32768.  None of them within a pass.)
     // With few rows nothing else loads beside a row, and two wavefronts per SIMD fill each other's waits:
-    // 512 threads, both rows in registers, one workgroup per unit.  Rows of 32000, a call with its walk,
-    // two workgroups per unit / this: 29 rows 19.1 / 16.8 us, 116 24.7 / 21.8, 261 26.8 / 23.8, 340 31.3 / 27.6,
-    // 348 32.4 / 28.7, 464 36.6 / 37.1, 976 36.4 / 42.6 (1024 threads: 18.8, 24.4, 26.8, 29.2, 31.1, 38.7, 45.4).
+    // 512 threads, both rows in registers, one workgroup per unit.  A call with its walk, trees of 4x2x2 whose candidates
+    // are mostly rejected, from memory, two workgroups per unit / this: rows of 32000, 29 of them 20.4 / 16.1 us, 116 21.8 / 17.4, 261 27.2 / 21.9,
+    // 348 28.0 / 26.9, 406 34.9 / 30.1, 435 35.5 / 32.1, 464 34.8 / 30.2, 522 36.1 / 36.0, 580 38.4 / 37.5, 976 (16 x 61) 48.7 / 52.6 (half of them argmax 36.0 / 39.5);
+    // rows of 20000, 29 16.3 / 14.7, 261 21.5 / 20.1, 348 25.8 / 26.7, 435 26.5 / 27.3, 493 24.3 / 26.7, 580 28.8 / 32.8, 976 40.4 / 49.3.
+    // One line between their crossings, at about 300 rows and 550.
     // Two per unit read the row in order (Share), the others dealt: that instance is the one bound by HBM.
     const long rows = (long)d.B * (1 + d.N);
     if (d.V <= 4096) launch_rows<4, 256, 0, 4, true>(p, stream);
