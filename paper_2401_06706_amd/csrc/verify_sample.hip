@@ -289,8 +289,8 @@ struct Share {
 // that would leave nothing is undone by keeping the old C.  C has 48 bits, as two floats, so what is
 // left of a row may not become small beside what was subtracted: at 2^-16 the row is written anew, C begins
 // at 0 again, and the candidates' tracks begin from the betas (which nothing but these seldom cases reads).
-// Without that 2^-53 of p was nothing; with it, and with the quotient corrected, 29 rows of 32000 take
-// 16.2 us where they took 15.9 (candidates mostly rejected, from memory), 16 x 61 rows as long as before.
+// Without that 2^-53 of p was nothing; with it, and with the exact quotient, 29 rows of 32000 take
+// 15.8 us where they took 15.6 (candidates mostly rejected, from memory), 4 x 17 of 50001 with 16 rejections 59.5 and 57.8, 16 x 61 as before.
 //
 // Bound: HBM in a batch (16 sequences of 61 rows of 32000, 8 of them argmax: 171 MB in 33 us), the vector units of one CU
 // for a single sequence (29 rows, 512 threads, a row with four rejections): the target row there 1.5 us and the draft row 3.8
@@ -624,10 +624,15 @@ void verify_rows_kernel(VerifyParams p)
                 }
                 // What a decision needs besides A is computed while the sum is on its way.  x = a(x) Z_q / e_q(x): the
                 // ratio is min(1, x / A), and u <= x / A is u A <= x.
-                double x, rz;
+                // (LQ: x and 1 / Z_q at the end of a round, nothing across the pass, which leaves no registers; else the quotient stays until Z_q changes)
+                double x = 0.0, rz = 0.0, zr = 0.0;
                 auto with_q = [&]() __attribute__((always_inline)) {
-                    x = my_a * (Zq / my_q);
-                    rz = (Zq > 0.0) ? 1.0 / Zq : 0.0;       // (nothing left in q: the residual is p itself)
+                    if (LQ) {
+                        x = my_a * (Zq / my_q);
+                        rz = Zq > 0.0 ? 1.0 / Zq : 0.0;
+                    } else {
+                        zr = Zq / my_q;
+                    }
                 };
                 with_q();
                 double of_x = 0.0, of_A = 0.0;      // the ratio that the lane's candidate was tested at: min(1, of_x / of_A)
@@ -637,6 +642,7 @@ void verify_rows_kernel(VerifyParams p)
                 for (;;) {
                     const int l = __ffsll((long long)left) - 1;
                     left &= left - 1ull;
+                    if (!LQ) x = my_a * zr;
                     const bool has_q = my_q > 0.0, sure = (has_q & !(x < A)) | (!has_q & (my_a > 0.0));     // a ratio of one
                     // (a token of probability zero - a duplicate of a rejected one, Sec. 3.2 - is never
                     // accepted, also not by a uniform of exactly 0 from outside the open interval)
@@ -653,9 +659,11 @@ void verify_rows_kernel(VerifyParams p)
                     }
                     // rejected: the residual with C + A / Z_q, in fp64 but for the two products per token.  (The token that
                     // leaves q keeps its e_q in the row: its residual is 0 now and stays 0 whatever is subtracted later.)
-                    // A / Z_q: the product with 1 / Z_q, and what is missing there (so that it is 1 for equal sums)
-                    double beta = A * rz;
-                    beta = rz > 0.0 ? fma(fma(-beta, Zq, A), rz, beta) : 0.0;
+                    // A / Z_q, exactly 1 for equal sums; with 1 / Z_q at hand, their product and what is missing there.
+                    // (Nothing left in q: the residual is p itself.)
+                    double beta = LQ ? A * rz : A / Zq;
+                    if (LQ) beta = fma(fma(-beta, Zq, A), rz, beta);
+                    beta = Zq > 0.0 ? beta : 0.0;
                     if (lane == l) my_beta = beta;
                     rejected = true;
                     split_C(C + beta);
@@ -670,8 +678,9 @@ void verify_rows_kernel(VerifyParams p)
                         const float w = __builtin_amdgcn_exp2f((__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_zq), l)) - mq) * c2);
                         Zq -= (__ballot(has_q) >> l) & 1ull ? (double)w : 0.0;
                         if (my_tok == tok) my_q = 0.0;
+                        if (!LQ) with_q();
                     }
-                    with_q();
+                    if (LQ) with_q();
                     __syncthreads();
                     A = read_total(0, slot);
 #pragma unroll 1
