@@ -378,8 +378,12 @@ void verify_rows_kernel(VerifyParams p)
     __builtin_amdgcn_sched_barrier(0);
     // (ahead of the passes over the row: a branch per item inside them costs more than the items skipped in them save)
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
+    for (int j = 0; j < ITEMS; ++j) {
         if (!own.whole(j)) own.settle(j, lane, a[j], tail_p);
+        // (One register per value on both ways; without this the compiler copies two of each four, and puts 8 registers aside for it
+        // instead of 4: 16 x 61 rows of 32000 48.1 us, 47.3 with it.  Not where it is the other way round: 8 items, odd lengths two to a CU.)
+        if (ITEMS >= 16 && (ALIGNED || WGS == 1)) asm("" : "+v"(a[j].x), "+v"(a[j].y), "+v"(a[j].z), "+v"(a[j].w));
+    }
     if (T == 0.f) {
         // argmax sampling: lowest id on ties.  Ascending token order: a strict comparison keeps the
         // first of equal values; elements are named by their number in the thread (an inline constant).
@@ -624,10 +628,12 @@ void verify_rows_kernel(VerifyParams p)
                 }
                 // What a decision needs besides A is computed while the sum is on its way.  x = a(x) Z_q / e_q(x): the
                 // ratio is min(1, x / A), and u <= x / A is u A <= x.
-                // (LQ: x and 1 / Z_q at the end of a round, nothing across the pass, which leaves no registers; else the quotient stays until Z_q changes)
+                // Two per CU with LDS: x and 1 / Z_q at the end of a round, nothing across the pass, which leaves no registers
+                // (16 x 61 rows of 32000 the other way 49.2 us, 48.1 this). Else the quotient stays until Z_q changes.
+                constexpr bool LATE = LQ > 0 && WGS > 1;
                 double x = 0.0, rz = 0.0, zr = 0.0;
                 auto with_q = [&]() __attribute__((always_inline)) {
-                    if (LQ) {
+                    if (LATE) {
                         x = my_a * (Zq / my_q);
                         rz = Zq > 0.0 ? 1.0 / Zq : 0.0;
                     } else {
@@ -642,7 +648,7 @@ void verify_rows_kernel(VerifyParams p)
                 for (;;) {
                     const int l = __ffsll((long long)left) - 1;
                     left &= left - 1ull;
-                    if (!LQ) x = my_a * zr;
+                    if (!LATE) x = my_a * zr;
                     const bool has_q = my_q > 0.0, sure = (has_q & !(x < A)) | (!has_q & (my_a > 0.0));     // a ratio of one
                     // (a token of probability zero - a duplicate of a rejected one, Sec. 3.2 - is never
                     // accepted, also not by a uniform of exactly 0 from outside the open interval)
@@ -661,8 +667,8 @@ void verify_rows_kernel(VerifyParams p)
                     // leaves q keeps its e_q in the row: its residual is 0 now and stays 0 whatever is subtracted later.)
                     // A / Z_q, exactly 1 for equal sums; with 1 / Z_q at hand, their product and what is missing there.
                     // (Nothing left in q: the residual is p itself.)
-                    double beta = LQ ? A * rz : A / Zq;
-                    if (LQ) beta = fma(fma(-beta, Zq, A), rz, beta);
+                    double beta = LATE ? A * rz : A / Zq;
+                    if (LATE) beta = fma(fma(-beta, Zq, A), rz, beta);
                     beta = Zq > 0.0 ? beta : 0.0;
                     if (lane == l) my_beta = beta;
                     rejected = true;
@@ -678,9 +684,9 @@ void verify_rows_kernel(VerifyParams p)
                         const float w = __builtin_amdgcn_exp2f((__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_zq), l)) - mq) * c2);
                         Zq -= (__ballot(has_q) >> l) & 1ull ? (double)w : 0.0;
                         if (my_tok == tok) my_q = 0.0;
-                        if (!LQ) with_q();
+                        if (!LATE) with_q();
                     }
-                    if (LQ) with_q();
+                    if (LATE) with_q();
                     __syncthreads();
                     A = read_total(0, slot);
 #pragma unroll 1
@@ -1005,8 +1011,8 @@ int32_t launch_verify(const mcsd_verify_desc &d, const mcsd_verify_bufs &b, hipS
     // 32 items of the draft row in LDS; beyond, one per unit with the same split.  Measured for 16 x 61
     // rows of 32000 when a rejection still rewrote the row: 33.5 us; 512 threads with 9 of 16 items in LDS (128
     // registers, 16 spilled) 38.3 us; 1024 threads, all in registers, one workgroup per unit 42.5 us.
-    // (Registers put aside in memory now, per thread: 5 of the 128 where four wavefronts share a SIMD, 8 of the 256 of two per unit,
-    // 4 beyond 32768.  None of them within a pass.)
+    // (Registers put aside in memory, per thread: 4 or 5 of the 128 where four wavefronts share a SIMD, 4 of the 256 of two per unit, 8 where
+    // V is no multiple of four, 2 beyond 32768.)
     // With few rows nothing else loads beside a row, and two wavefronts per SIMD fill each other's waits:
     // 512 threads, both rows in registers, one workgroup per unit.  A call with its walk, trees of 4x2x2 whose candidates
     // are mostly rejected, from memory, two workgroups per unit / this: rows of 32000, 29 of them 20.4 / 16.1 us, 116 21.8 / 17.4, 261 27.2 / 21.9,
